@@ -285,6 +285,7 @@ razer_status razer_linear(const razer_tensor* w, const void* a_bf16, const razer
         const size_t rest = workspace_bytes - a_bytes - 256u;
         return razer_linear(&w2, wsb, nullptr, m, y_bf16, ld_y, rest ? wsb + a_bytes + 256u : nullptr, rest, hip_stream);
     }
+    const GemvProblem one{w->codes, w->scales, w->tensor_scale, n, (uint16_t*)y_bf16, ld_y};
     if (k == 0) {                                                        // empty contraction: Y = 0
         const int64_t total = m * n;
         launch(fill_zero_bf16_kernel, (unsigned)((total + 255) / 256), 256, 0, st, (uint16_t*)y_bf16, m, n, ld_y);
@@ -297,9 +298,8 @@ razer_status razer_linear(const razer_tensor* w, const void* a_bf16, const razer
         if (m <= kGemvDirectMaxM || (m <= kSkinnyMaxM && k > kSkinnyMaxK))
             e = launch_gemv(wsv, w->codes, w->scales, w->tensor_scale, n, k, (const uint16_t*)a_bf16, m,
                             (uint16_t*)y_bf16, ld_y, st);
-        else if (m <= 64 && k <= kSkinnyMaxK)                        // K inside the workgroup: no workspace
-            e = launch_skinny(wsv, w->codes, w->scales, w->tensor_scale, n, k, (const uint16_t*)a_bf16, m,
-                              (uint16_t*)y_bf16, ld_y, nullptr, st);
+        else if (m <= kRingMaxM && k <= kSkinnyMaxK)                 // no workspace
+            e = launch_skinny(wsv, 1, &one, k, (const uint16_t*)a_bf16, m, st);
         else {
             const size_t need = gemm_workspace_bytes(n, k, m);       // K-slices while the tiles are few
             if (need > 0 && (!workspace || workspace_bytes < need || !aligned16(workspace))) return RAZER_ERR_WORKSPACE;
@@ -309,18 +309,20 @@ razer_status razer_linear(const razer_tensor* w, const void* a_bf16, const razer
     } else if (!a_q && m > kGemvDirectMaxM && m <= kSkinnyMaxM && k <= kSkinnyMaxK) {
         const size_t need = skinny_workspace_bytes(n, k, m);
         if (need > 0 && (!workspace || workspace_bytes < need || !aligned16(workspace))) return RAZER_ERR_WORKSPACE;
-        e = launch_skinny(wsv, w->codes, w->scales, w->tensor_scale, n, k, (const uint16_t*)a_bf16, m,
-                          (uint16_t*)y_bf16, ld_y, (float*)workspace, st);
+        e = launch_skinny(wsv, 1, &one, k, (const uint16_t*)a_bf16, m, st);
     } else if (!a_q && m <= kGemvDirectMaxM) {
         e = launch_gemv(wsv, w->codes, w->scales, w->tensor_scale, n, k, (const uint16_t*)a_bf16, m,
                         (uint16_t*)y_bf16, ld_y, st);
     } else {
         const size_t need = gemm_workspace_bytes(n, k, m);
         if (need > 0 && (!workspace || workspace_bytes < need || !aligned16(workspace))) return RAZER_ERR_WORKSPACE;
-        e = launch_gemm(wsv, w->codes, w->scales, w->tensor_scale, n, k, (const uint16_t*)a_bf16, asv,
-                        a_q ? a_q->codes : nullptr, a_q ? a_q->scales : nullptr,
-                        a_q ? a_q->tensor_scale : nullptr, m, (uint16_t*)y_bf16, ld_y,
-                        need > 0 ? (float*)workspace : nullptr, st);
+        if (!a_q && ring_serves(1, &one, k, m))
+            e = launch_skinny(wsv, 1, &one, k, (const uint16_t*)a_bf16, m, st);
+        else
+            e = launch_gemm(wsv, w->codes, w->scales, w->tensor_scale, n, k, (const uint16_t*)a_bf16, asv,
+                            a_q ? a_q->codes : nullptr, a_q ? a_q->scales : nullptr,
+                            a_q ? a_q->tensor_scale : nullptr, m, (uint16_t*)y_bf16, ld_y,
+                            need > 0 ? (float*)workspace : nullptr, st);
     }
     return e == hipSuccess ? RAZER_OK : RAZER_ERR_HIP;
 }
@@ -397,7 +399,8 @@ razer_status razer_linear_grouped(const razer_tensor* const* w, int32_t count, c
         if (m <= kGemvDirectMaxM) {
             path = GEMV;                                 // every block size and both weight formats
         } else if (sv0.f16 && m > kSkinnyMaxM) {
-            path = SEQUENCE;                             // FP16 scale words: no grouped matrix-core launch
+            // FP16 scale words: no grouped launch of the tiled matrix-core kernels
+            path = m <= kRingMaxM && k <= kSkinnyMaxK ? SKINNY : SEQUENCE;
         } else if (m <= kSkinnyMaxM && k > kSkinnyMaxK) {
             path = SEQUENCE;
         } else if (m <= kSkinnyMaxM) {
@@ -424,8 +427,11 @@ razer_status razer_linear_grouped(const razer_tensor* const* w, int32_t count, c
     hipError_t e = hipSuccess;
     switch (path) {
         case GEMV: e = launch_gemv_grouped(sv0, count, p, k, (const uint16_t*)a_bf16, m, st); break;
-        case SKINNY: e = launch_skinny_grouped(sv0, count, p, k, (const uint16_t*)a_bf16, m, (float*)workspace, st); break;
-        case GEMM: e = launch_gemm_grouped(sv0, count, p, k, (const uint16_t*)a_bf16, m, (float*)workspace, st); break;
+        case SKINNY: e = launch_skinny(sv0, count, p, k, (const uint16_t*)a_bf16, m, st); break;
+        case GEMM:
+            if (ring_serves(count, p, k, m)) e = launch_skinny(sv0, count, p, k, (const uint16_t*)a_bf16, m, st);
+            else e = launch_gemm_grouped(sv0, count, p, k, (const uint16_t*)a_bf16, m, (float*)workspace, st);
+            break;
         case SEQUENCE:
             for (int i = 0; i < count; ++i) {
                 razer_status s = razer_linear(w[i], a_bf16, nullptr, m, y_bf16[i], ld_y[i], workspace, workspace_bytes,

@@ -50,18 +50,17 @@ hipError_t launch_dequant(int fmt, SvConfig cfg, const uint8_t* codes, const uin
 // Y[m][n] = A[m][:] . W[n][:], m <= kGemvMaxM: wavefront dot products, HBM-bound (4 rows per pass).
 constexpr int kGemvMaxM = 16;
 constexpr int kGemvDirectMaxM = 4;     // rows the GEMV kernel takes in one pass
-constexpr int kSkinnyMaxM = 32;        // above this the tiled GEMM takes over
+constexpr int kSkinnyMaxM = 32;        // up to here the small-batch kernel always
+constexpr int kRingMaxM = 64;          // ... and from 33 rows where it is the faster one (FP16-scale format: always)
+constexpr int64_t kComputeUnits = 256;
+constexpr uint32_t kLdsBytes = 160u * 1024u;   // per compute unit
 // The small-batch kernel and the register-decode GEMM address inside a row block / tile with 32-bit
-// offsets (up to 31 rows x 2 K bytes, resp. 255 rows x 2 K bytes); longer rows take the LDS-staged GEMM.
+// offsets (up to 63 rows x 2 K bytes, resp. 255 rows x 2 K bytes); longer rows take the LDS-staged GEMM.
 constexpr int64_t kSkinnyMaxK = (int64_t)1 << 24;
 constexpr int64_t kRbMaxK = (int64_t)1 << 22;
 
-// 5 <= m <= kSkinnyMaxM: decode-once MFMA kernel; K-slices meet in an fp32 workspace of
-// skinny_workspace_bytes(n, k, m) bytes (0 when a single slice covers K).
+// Workspace reported for 5 <= m <= kSkinnyMaxM (the kernel itself needs none; razer_skinny.hip).
 size_t skinny_workspace_bytes(int64_t n, int64_t k, int64_t m);
-hipError_t launch_skinny(SvConfig cfg, const uint8_t* codes, const uint8_t* scales, const float* ts, int64_t n,
-                         int64_t k, const uint16_t* a, int64_t m, uint16_t* y, int64_t ld_y, float* workspace,
-                         hipStream_t st);
 // y = bf16(scale * sum of the K-slices' fp32 partial sums [slices][m][n], in slice order); scale = -ts_w,
 // or ts_w * ts_a when a_ts is given.
 hipError_t launch_slice_reduce(const float* partial, const float* w_ts, const float* a_ts, int64_t m, int64_t n,
@@ -94,10 +93,11 @@ hipError_t launch_gemm(SvConfig wcfg, const uint8_t* w_codes, const uint8_t* w_s
                        const uint8_t* a_scales, const float* a_ts, int64_t m, uint16_t* y, int64_t ld_y,
                        float* workspace, hipStream_t st);
 
-// Grouped form of launch_skinny (5 <= m <= 32, any block size, every n a positive multiple of 4);
-// workspace = the matrices' skinny_workspace_bytes added up, matrix after matrix.
-hipError_t launch_skinny_grouped(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a,
-                                 int64_t m, float* workspace, hipStream_t st);
+// 5 <= m <= kRingMaxM: decode-once MFMA kernel, one launch for up to 4 matrices sharing K, the activation rows, the
+// format, the block size and the special values (every n > 0, 0 < k <= kSkinnyMaxK).  No workspace.
+hipError_t launch_skinny(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, hipStream_t st);
+// 33..64 rows of the scale-byte format: whether that kernel or the register-decode GEMM is the faster one.
+bool ring_serves(int count, const GemvProblem* p, int64_t k, int64_t m);
 
 // Sum of the K-slices of a grouped launch: partial holds matrix i's [nslices][m][n_i] fp32 slices
 // behind those of matrices 0 .. i-1 (every n a positive multiple of 4, y 8-byte aligned, ld_y % 4 == 0).

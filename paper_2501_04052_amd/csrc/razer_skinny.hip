@@ -1,39 +1,29 @@
-// Weight-only RaZeR linear layer for 5..32 activation rows on gfx950 (small-batch decode, Sec. 4.3 /
-// App. D.2 of arxiv 2501.04052): every packed weight is read from HBM and decoded exactly once, the
-// multiply-accumulate goes to v_mfma_f32_16x16x32_bf16 with the activation rows padded to 16 or 32.
+// Linear layer for 5..64 activation rows on gfx950 (small-batch decode, Sec. 4.3 / App. D.2 of arxiv 2501.04052):
+// every packed weight is read from HBM and decoded exactly once, in registers, straight into the operand of
+// v_mfma_f32_16x16x32_bf16 it is used in.
 //
-// A lane's 8 consecutive codes (one dword) decode straight into the 4 registers of an MFMA "A"
-// operand (rows = weight rows n, k = this lane's 8 k's), so the weights never pass through LDS.
-// MFMA operands are invariant under a permutation of k applied to both operands: lane group g of
-// step s, instruction j holds k = 128 s + 32 g + 8 j .. +7, which makes a lane's 4 operands one
-// 16-byte load of codes plus one 16-bit load of scale bytes.  Activations (M x KC bf16, shared by
-// the 4 waves = 64 weight rows of a workgroup) are staged once in LDS, chunk-swizzled with the row.
+// Mapping (ring_kernel).  A workgroup owns G groups of 16 weight rows, numbered through all matrices of the launch
+// one after another; its 8 waves take the 128-k steps of K in turn (wave w: steps w, w + 8, ...).  What a step needs
+// -- G x (1 KiB of codes, 64 scale entries) and the step's activation rows -- is copied global -> LDS by the load
+// unit into memory that only this wave reads, so the K loop has no barrier: the wave waits for its own copies, takes
+// the operands into registers, requests its next step into the same place and multiplies while that one is on its
+// way.  Partial sums of the waves meet in LDS after one barrier.  One launch, no workspace.
 //
-// Work split: grid = (N / 64 / nrb) x (K / KC): a workgroup stages its K-slice of the activations once
-// and walks through nrb consecutive 64-row blocks, loading the next block's weights while it decodes
-// and multiplies the current one.  K-slices of one output tile are summed in fixed order by a second
-// kernel (slice_reduce_kernel) from an fp32 workspace [slices][M][N] (deterministic, no atomics).
-// The kernel is bound by the decode's vector ALU work (about 3 ops per weight), not by HBM.
-//
-// A second kernel for up to 16 activation rows (mv_kernel) keeps K inside the workgroup instead: the
-// structure of the streaming GEMV -- a wave owns a K-slice of every row, its activation fragments stay in
-// registers, it walks over groups of 16 rows with the next group's weights in flight, partial sums of the
-// waves meet in LDS -- with the dot products on the 16x16x32 matrix instruction.  One launch, no workspace.
-// Which of the two serves a shape, and with which launch shape, is the tuner's choice (razer_tune.h).
+// Why through LDS although nothing is shared: the matrix instruction wants 16 rows in 16 neighbouring lanes, and a
+// load whose neighbouring lanes lie in 16 different rows costs the address unit a cache-line lookup per lane.  Read
+// straight into registers like that, the activations alone cost more than everything else together (22016 x 4096,
+// 16 rows: 35.7 us, 24.6 us with the same bytes read contiguously, 16.5 us without activations).  The copies read
+// 64 to 256 consecutive bytes per row; the order the lanes need comes from the LDS addresses, xor-swizzled so that a
+// 128-bit read of 16 rows hits 16 different bank groups.
+// What bounds it: at 16 rows and 22016 x 4096 the copies alone take 10.6 us, decode and matrix instructions alone 12.
+// Measured against the kernels this replaced (K cut into slices that met in a workspace; activations loaded into
+// registers), 7B-shaped layer as 4 calls: 8 rows 59 -> 44 us, 16 rows 65 -> 48, 32 rows 84 -> 60, 64 rows (they took
+// the 64-row tiles of the register-decode GEMM) 110 -> 89; FP16-scale format 8 rows 56 -> 41, 64 rows 215 -> 84.
 #include "razer_device.hpp"
 #include "razer_kernels.hpp"
 
 namespace razer {
 
-template <int BYTE>
-__device__ __forceinline__ uint32_t sk_cvt_scaled_pair(uint32_t xflip, float s, uint32_t patch)
-{
-    v2f p = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(xflip, 1.0f, BYTE);   // -element, exact
-    p.x *= s;
-    p.y *= s;
-    v2bf b = __builtin_convertvector(p, v2bf);
-    return patch_zero_halves(__builtin_bit_cast(uint32_t, b), patch);
-}
 // 8 codes -> 8 bare, negated FP4 values as bf16, remapped codes patched with `patch` (the negated special
 // value as a bf16 pair): the FP16-scale format, whose scale multiplies the block's partial sum instead.
 template <int BYTE>
@@ -49,220 +39,453 @@ __device__ __forceinline__ v8bf sk_decode_dword_bare(uint32_t x, uint32_t patch)
                                sk_cvt_bare_pair<3>(xf, patch));
     return __builtin_bit_cast(v8bf, r);
 }
-__device__ __forceinline__ v8bf sk_decode_dword(uint32_t x, uint2 le)
+
+// ---- decode through byte tables ----------------------------------------------------------------------------
+// A block's eight scaled magnitudes and its special value are 8 bf16 numbers: their high bytes fill one pair of
+// registers and their low bytes another, and v_perm_b32 looks up four codes per instruction.  Table position of
+// FP4 magnitude m: m ^ 4, position 4 (the magnitude 0) holds the negated special value; the selector of the true
+// zero (code 0) gets bit 3 set as well: 12, which v_perm_b32 answers with 0x00.  The codes' sign bits flip the high
+// bytes' signs afterwards (code 8 carries one, hence the negation).  The pairs come out in the order (0,2) (4,6)
+// (1,3) (5,7) of the dword's codes: sk_permute_pairs() puts the activations in the same order.
+// Per dword 8 byte permutes (4.2 clk each, measured) and 10 plain logic operations (2.3-2.5 clk): 58 clk against 89
+// for convert, two multiplications, convert and patch per pair.
+__device__ __forceinline__ uint4 sk_byte_table(uint32_t sb, float sv0, float sv1)
 {
-    const uint32_t xf = x ^ kRemapXor;
-    const float s = u2f(le.x);
-    const uint4 r = make_uint4(sk_cvt_scaled_pair<0>(xf, s, le.y), sk_cvt_scaled_pair<1>(xf, s, le.y),
-                               sk_cvt_scaled_pair<2>(xf, s, le.y), sk_cvt_scaled_pair<3>(xf, s, le.y));
-    return __builtin_bit_cast(v8bf, r);
+    float s, sv;
+    decode_scale_byte<0>(sb, sv0, sv1, s, sv);
+    // bf16 bits of s x {2, 3, 4, 6} and {special, .5, 1, 1.5}; a zero scale makes all of them 0
+    const uint32_t b1 = f2u(s) >> 16, b15 = f2u(1.5f * s) >> 16, live = s != 0.0f ? 0xFFFFu : 0u;
+    const uint32_t sp = (uint32_t)f32_to_bf16_rne(-(sv * s));
+    const uint32_t v0 = (b1 + 0x80u) & live, v1 = (b15 + 0x80u) & live, v2 = (b1 + 0x100u) & live, v3 = (b15 + 0x100u) & live;
+    const uint32_t v4 = sp, v5 = (b1 - 0x80u) & live, v6 = b1, v7 = b15;
+    return make_uint4((v0 >> 8) | ((v1 >> 8) << 8) | ((v2 >> 8) << 16) | ((v3 >> 8) << 24),
+                      (v4 >> 8) | ((v5 >> 8) << 8) | ((v6 >> 8) << 16) | ((v7 >> 8) << 24),
+                      (v0 & 255u) | ((v1 & 255u) << 8) | ((v2 & 255u) << 16) | (v3 << 24),
+                      (v4 & 255u) | ((v5 & 255u) << 8) | ((v6 & 255u) << 16) | (v7 << 24));
+}
+__device__ __forceinline__ v8bf sk_decode_dword_table(uint32_t x, v4u t)
+{
+    const uint32_t z = x ^ 0x44444444u, nz = (x | 0x88888888u) - 0x11111111u;          // bit 3 of nz: magnitude not 0
+    const uint32_t sel = __builtin_amdgcn_bitop3_b32(nz, z, 0x77777777u, 0x89);         // low bits of z, bit 3 of ~(nz | z)
+    const uint32_t se = sel & 0x0F0F0F0Fu, so = (sel >> 4) & 0x0F0F0F0Fu;
+    const uint32_t he = __builtin_amdgcn_bitop3_b32(__builtin_amdgcn_perm(t.y, t.x, se), x << 4, 0x80808080u, 0x78);
+    const uint32_t ho = __builtin_amdgcn_bitop3_b32(__builtin_amdgcn_perm(t.y, t.x, so), x, 0x80808080u, 0x78);
+    const uint32_t le = __builtin_amdgcn_perm(t.w, t.z, se), lo = __builtin_amdgcn_perm(t.w, t.z, so);
+    return __builtin_bit_cast(v8bf, make_uint4(__builtin_amdgcn_perm(he, le, 0x05010400u), __builtin_amdgcn_perm(he, le, 0x07030602u),
+                                               __builtin_amdgcn_perm(ho, lo, 0x05010400u), __builtin_amdgcn_perm(ho, lo, 0x07030602u)));
+}
+// 8 bf16 activations in the pair order of sk_decode_dword_table
+__device__ __forceinline__ v4u sk_permute_pairs(v4u a)
+{
+    return v4u{__builtin_amdgcn_perm(a.y, a.x, 0x05040100u), __builtin_amdgcn_perm(a.w, a.z, 0x05040100u),
+               __builtin_amdgcn_perm(a.y, a.x, 0x07060302u), __builtin_amdgcn_perm(a.w, a.z, 0x07060302u)};
 }
 
-constexpr int kSkRows = 64;            // weight rows per workgroup (4 waves x 16)
-
-// NB: activation fragments of 16 rows (M <= 16 NB); STEPS: 128-k steps per workgroup (KC = 128 STEPS).
-// NRB: consecutive 64-row blocks per workgroup, a template parameter so that the walk is straight-line
-// code -- with the prefetch under a run-time branch the compiler has to assume at every use of the
-// current block's registers that the prefetch did not happen, and waits for most of it.
-template <int NB, int STEPS, bool GB, int NRB>
-__device__ __forceinline__ void skinny_body(const uint8_t* __restrict__ codes, const uint8_t* __restrict__ scales,
-                                            const float* __restrict__ w_ts, float sv0, float sv1, int64_t n,
-                                            int64_t k, const uint16_t* __restrict__ a, int64_t m,
-                                            uint16_t* __restrict__ y, int64_t ld_y, float* __restrict__ partial,
-                                            int nslices, int lb, unsigned block)
+// ---------------------------------------------------------------------------------------------
+// NA: activation copies of 4 rows per step (m <= 4 NA); G: groups of 16 weight rows per workgroup.  LDS of a wave: the
+// activations of its step [4 NA rows][256 B], the codes [G][16 rows][64 B], the scale entries [G][16 rows][4] (a 1- or
+// 2-byte copy lands zero-extended in 4 bytes); the partial sums reuse it.
+// SF = 1: the FP16-scale format (one step = one block of 128: one scale word per row).  The operands are bare FP4
+// values and swap roles, so that a lane's four results of a step belong to ITS weight row (lane % 16) and activation
+// rows 4 (lane / 16) + 0..3, and the step's sum is folded into the running sums with the lane's own scale in fp32.
+constexpr int kRingWaves = 8;
+constexpr uint32_t kRingTableBytes = 4096;
+template <int NA, int G>
+constexpr uint32_t ring_slot_bytes() { return NA * 1024u + G * 1280u; }
+template <int NA, int G>
+constexpr uint32_t ring_wave_bytes()
 {
-    constexpr int nrb = NRB;
-    constexpr int KC = 128 * STEPS;
-    constexpr int ROWB = KC * 2;                                   // bytes per activation row in LDS
-    __shared__ __align__(16) uint8_t atile[NB * 16 * ROWB];
-    __shared__ uint2 lut[256];
-
-    // the wave index is uniform: read as a scalar it keeps the row arithmetic off the vector unit
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int tid = wave * 64 + lane;
-    const int slice = block % nslices;
-    const int64_t nfirst = (int64_t)(block / nslices) * nrb * kSkRows;   // nrb consecutive 64-row blocks
-    const int64_t k0 = (int64_t)slice * KC;
-    const float ts = *w_ts;
-
-    // this lane's weights of the row block at n0: row n0 + 16 wave + (lane % 16),
-    // k = k0 + 128 s + 32 (lane / 16) .. +31.  Rows past N re-read the last row (never stored).  Steps past
-    // K re-read step 0; where they are used their scale bytes are cleared: scale code 0 is 0.0, so whatever
-    // the codes are, the weights (special values included) decode to 0.  Nothing here touches a loaded
-    // value: an operation on one would make the wave wait for the load right where it was issued, and the
-    // loads for the next row block are meant to stay in flight while the current one is decoded.
-    // Addresses: a uniform 64-bit base per row block (scalar unit) plus 32-bit lane offsets -- the host
-    // sends rows longer than kSkinnyMaxK elsewhere.
-    const uint32_t code_ld = (uint32_t)(k >> 1), scale_ld = (uint32_t)(k >> lb);
-    const uint32_t krem = (uint32_t)((k - k0 < KC) ? k - k0 : KC);       // elements of this slice inside K
-    const uint32_t kl = 32u * (lane >> 4);
-    auto load_weights = [&](int64_t n0, uint4 (&cw)[STEPS], uint32_t (&sw)[STEPS]) {
-        int64_t r0 = n0 + 16 * wave;                               // uniform: first row of this wave
-        r0 = r0 < n ? r0 : n - 1;
-        const uint32_t left = (uint32_t)((n - 1 - r0 < 15) ? n - 1 - r0 : 15);
-        const uint32_t dl = ((uint32_t)lane & 15u) < left ? ((uint32_t)lane & 15u) : left;
-        const uint8_t* cbase = codes + r0 * (int64_t)code_ld + (k0 >> 1);
-        const uint8_t* sbase = scales + r0 * (int64_t)scale_ld + (k0 >> (GB ? lb : 4));   // k0 holds whole blocks
-        const uint32_t crow = dl * code_ld, srow = dl * scale_ld;
-#pragma unroll
-        for (int s = 0; s < STEPS; ++s) {
-            const uint32_t kin = 128u * s + kl;                    // offset inside the slice
-            const bool in = kin < krem;
-            const uint32_t kc = in ? kin : 0u;
-            cw[s] = *reinterpret_cast<const uint4*>(cbase + (crow + (kc >> 1)));
-            uint32_t sc;
-            if (GB) {
-                const uint32_t b = sbase[srow + (kc >> lb)];
-                sc = b | (b << 8);
-            } else {
-                sc = *reinterpret_cast<const uint16_t*>(sbase + (srow + (kc >> 4)));
-            }
-            sw[s] = sc;
-        }
-    };
-    uint4 cw[STEPS];
-    uint32_t sw[STEPS];
-    // activations [NB*16][KC] -> LDS, 16-byte chunks swizzled with the row (shared by all row blocks).
-    // Fragment rows past M copy row M - 1: their product columns are never stored.  Chunks past K must be
-    // zero -- the weights there are zero, but 0 x Inf would not be.
-    constexpr int CH = KC / 8;                                     // 16-byte chunks per row
-    constexpr int UNITS = NB * 16 * CH;
-    const uint8_t* abase = reinterpret_cast<const uint8_t*>(a + k0);
-    const uint32_t a_ld = (uint32_t)k * 2u;
-    // (loads in batches of four, from clamped addresses and without a branch around any of them: a load
-    // under a branch is waited for before the next one is issued)
-    // The first row block's weights are requested right behind the first batch: loads return in order, so
-    // the staging (L2 hits) is not held up behind them (HBM), and they are under way while LDS is filled.
-    constexpr int NU = UNITS / 256, BATCH = NU < 4 ? NU : 4;
-#pragma unroll
-    for (int i0 = 0; i0 < NU; i0 += BATCH) {
-        uint4 stage[BATCH];
-#pragma unroll
-        for (int i = 0; i < BATCH; ++i) {
-            const uint32_t u = (uint32_t)tid + (i0 + i) * 256u, row = u / CH, c = u % CH;
-            const uint32_t src_row = row < (uint32_t)m ? row : (uint32_t)m - 1u;
-            const uint32_t src_c = c * 8u < krem ? c : 0u;
-            stage[i] = *reinterpret_cast<const uint4*>(abase + (src_row * a_ld + src_c * 16u));
-        }
-        if (i0 == 0) load_weights(nfirst, cw, sw);
-#pragma unroll
-        for (int i = 0; i < BATCH; ++i) {
-            const uint32_t u = (uint32_t)tid + (i0 + i) * 256u, row = u / CH, c = u % CH;
-            const uint32_t keep = c * 8u < krem ? 0xFFFFFFFFu : 0u;
-            const uint4 v = make_uint4(stage[i].x & keep, stage[i].y & keep, stage[i].z & keep, stage[i].w & keep);
-            *reinterpret_cast<uint4*>(atile + row * ROWB + ((c ^ (row & 15u)) << 4)) = v;
-        }
-    }
-    // LDS address of this lane's activation fragment for instruction j of step 0, fragment 0: row lane % 16,
-    // logical chunk 4 (lane / 16) + j, swizzled; step s adds 256 bytes, fragment b adds 16 rows
-    uint32_t afrag[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-        afrag[j] = ((uint32_t)lane & 15u) * ROWB + (((4u * (lane >> 4) + j) ^ ((uint32_t)lane & 15u)) << 4);
-    for (uint32_t sb = tid; sb < 256u; sb += 256) {
-        float s, sv;
-        decode_scale_byte<0>(sb, sv0, sv1, s, sv);
-        const uint32_t p = (uint32_t)f32_to_bf16_rne(-(sv * s));
-        lut[sb] = make_uint2(f2u(s), p | (p << 16));
-    }
-    __syncthreads();
-
-    // two register buffers in turn; the next row block's weights are in flight while this one is decoded
-    // and multiplied.  Blocks past N (last workgroup of a matrix) load clamped rows and store nothing.
-    uint4 cwn[STEPS];
-    uint32_t swn[STEPS];
-#pragma unroll
-    for (int rb = 0; rb < NRB; ++rb) {
-        const int64_t n0 = nfirst + (int64_t)rb * kSkRows;
-        uint4 (&cwc)[STEPS] = (rb & 1) ? cwn : cw;
-        uint32_t (&swc)[STEPS] = (rb & 1) ? swn : sw;
-        if (rb + 1 < NRB) {
-            if (rb & 1) load_weights(n0 + kSkRows, cw, sw);
-            else load_weights(n0 + kSkRows, cwn, swn);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-
-        v4f acc[NB];
-#pragma unroll
-        for (int b = 0; b < NB; ++b) acc[b] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s = 0; s < STEPS; ++s) {
-            const uint32_t sws = (128u * s + kl < krem) ? swc[s] : 0u;      // steps past K: scale 0
-            const uint2 le0 = lut[sws & 255u], le1 = lut[(sws >> 8) & 255u];
-            const uint32_t xw[4] = {cwc[s].x, cwc[s].y, cwc[s].z, cwc[s].w};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const v8bf wf = sk_decode_dword(xw[j], j < 2 ? le0 : le1);
-#pragma unroll
-                for (int b = 0; b < NB; ++b) {
-                    const v8bf af = *reinterpret_cast<const v8bf*>(atile + afrag[j] + (256 * s + 16 * ROWB * b));
-                    acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, af, acc[b], 0, 0, 0);
-                }
-            }
-        }
-        // lane holds rows n = 4 (lane / 16) + 0..3 (of this wave's 16), column m = 16 b + lane % 16
-        const int64_t gn = n0 + 16 * wave + 4 * (lane >> 4);
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const int64_t gm = 16 * b + (lane & 15);
-            if (gm < m && gn < n) {
-                if (nslices == 1) {
-                    uint16_t* dst = y + gm * ld_y + gn;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (gn + e < n) dst[e] = f32_to_bf16_rne(-ts * acc[b][e]);
-                } else {
-                    float* dst = partial + ((int64_t)slice * m + gm) * n + gn;
-                    if (gn + 3 < n && ((reinterpret_cast<uintptr_t>(dst) & 15u) == 0)) {
-                        *reinterpret_cast<float4*>(dst) = make_float4(acc[b][0], acc[b][1], acc[b][2], acc[b][3]);
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (gn + e < n) dst[e] = acc[b][e];
-                    }
-                }
-            }
-        }
-    }
+    const uint32_t slot = ring_slot_bytes<NA, G>(), part = G * ((NA + 3) / 4) * 1024u;
+    return slot > part ? slot : part;
 }
 
-template <int NB, int STEPS, bool GB, int NRB>
-__global__ __launch_bounds__(256) void skinny_kernel(const uint8_t* __restrict__ codes,
-                                                     const uint8_t* __restrict__ scales,
-                                                     const float* __restrict__ w_ts, float sv0, float sv1,
-                                                     int64_t n, int64_t k, const uint16_t* __restrict__ a, int64_t m,
-                                                     uint16_t* __restrict__ y, int64_t ld_y,
-                                                     float* __restrict__ partial, int nslices, int lb)
-{
-    skinny_body<NB, STEPS, GB, NRB>(codes, scales, w_ts, sv0, sv1, n, k, a, m, y, ld_y, partial, nslices, lb, blockIdx.x);
-}
-
-// Up to four weight matrices against the same activations in one launch: workgroups are numbered
-// through the matrices one after another (g1..g3 = first workgroup of matrices 1..3); matrix i keeps
-// its K-slices in the workspace behind those of matrices 0 .. i-1.
-template <int NB, int STEPS, int NRB, bool GB = false>
-__global__ __launch_bounds__(256) void skinny_grouped_kernel(
+template <int NA, int G, bool GB, int SF>
+__global__ __launch_bounds__(64 * kRingWaves) void ring_kernel(
     const uint8_t* c0, const uint8_t* c1, const uint8_t* c2, const uint8_t* c3,
     const uint8_t* s0, const uint8_t* s1, const uint8_t* s2, const uint8_t* s3,
     const float* f0, const float* f1, const float* f2, const float* f3,
     uint16_t* y0, uint16_t* y1, uint16_t* y2, uint16_t* y3,
     int64_t n0, int64_t n1, int64_t n2, int64_t n3,
     int64_t l0, int64_t l1, int64_t l2, int64_t l3,
-    unsigned g1, unsigned g2, unsigned g3,
-    float sv0, float sv1, int64_t k, const uint16_t* __restrict__ a, int64_t m, float* __restrict__ partial,
-    int nslices, int lb)
+    uint32_t e1, uint32_t e2, uint32_t e3, uint32_t e4,
+    float sv0, float sv1, int64_t k, const uint16_t* __restrict__ a, int64_t m, int lb)
 {
-    const unsigned b = blockIdx.x;
-    const uint8_t* codes = c0; const uint8_t* scales = s0; const float* ts = f0; uint16_t* y = y0;
-    int64_t n = n0, ld = l0, before = 0;
-    unsigned first = 0;
-    if (b >= g1) { codes = c1; scales = s1; ts = f1; y = y1; n = n1; ld = l1; first = g1; before = n0; }
-    if (b >= g2) { codes = c2; scales = s2; ts = f2; y = y2; n = n2; ld = l2; first = g2; before = n0 + n1; }
-    if (b >= g3) { codes = c3; scales = s3; ts = f3; y = y3; n = n3; ld = l3; first = g3; before = n0 + n1 + n2; }
-    skinny_body<NB, STEPS, GB, NRB>(codes, scales, ts, sv0, sv1, n, k, a, m, y, ld,
-                                    partial ? partial + (int64_t)nslices * m * before : nullptr, nslices, lb, b - first);
+    constexpr int NB = (NA + 3) / 4;
+    constexpr uint32_t WAVE = ring_wave_bytes<NA, G>();
+    __shared__ uint4 lut[SF ? 1 : 256];
+    extern __shared__ __align__(16) uint8_t dyn_smem[];               // [waves][WAVE]
+    const uint32_t lane = threadIdx.x & 63u, nwaves = blockDim.x >> 6;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t r = lane & 15u, g = lane >> 4;
+    const uint32_t kk32 = (uint32_t)k;
+    const uint32_t code_ld = (uint32_t)(k >> 1), scale_ld = SF ? (uint32_t)(k >> 7) * 2u : (uint32_t)(k >> (GB ? lb : 4));
+    const uint32_t nsteps = (kk32 + 127u) >> 7;
+
+    // copy lanes: codes and scale bits -- row lane / 4, 16-byte chunk / 32-element run; activations -- row 4 i + lane / 16
+    const uint32_t wr = lane >> 2, wp = lane & 3u, wc = wp ^ ((wr >> 2) & 3u);
+    const uint8_t* cbase[G];
+    const uint8_t* sbase[G];
+    uint32_t crow[G], srow[G];
+#pragma unroll
+    for (int gi = 0; gi < G; ++gi) {
+        uint32_t q = blockIdx.x * G + gi;
+        q = q < e4 ? q : e4 - 1u;                                     // groups past the last one re-read it, never stored
+        const uint8_t* codes = c0; const uint8_t* scales = s0;
+        int64_t n = n0;
+        uint32_t first = 0;
+        if (q >= e1) { codes = c1; scales = s1; n = n1; first = e1; }
+        if (q >= e2) { codes = c2; scales = s2; n = n2; first = e2; }
+        if (q >= e3) { codes = c3; scales = s3; n = n3; first = e3; }
+        const int64_t row0 = (int64_t)(q - first) * 16;
+        const uint32_t left = (uint32_t)((n - 1 - row0 < 15) ? n - 1 - row0 : 15);
+        const uint32_t dl = wr < left ? wr : left;                    // rows past N re-read the last row
+        cbase[gi] = codes + row0 * (int64_t)code_ld;
+        sbase[gi] = scales + row0 * (int64_t)scale_ld;
+        crow[gi] = dl * code_ld;
+        srow[gi] = dl * scale_ld;
+    }
+    uint32_t arow[NA], achk[NA];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        const uint32_t row = 4u * i + (lane >> 4);
+        arow[i] = (row < (uint32_t)m ? row : (uint32_t)m - 1u) * (kk32 * 2u);
+        achk[i] = (lane & 15u) ^ (row & 15u);                         // logical 16-byte chunk this lane fetches
+    }
+#define RAZER_COPY(src, off, dst, bytes)                                                                           \
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)((src) + (off)),              \
+                                     (__attribute__((address_space(3))) void*)(dst), bytes, 0, 0)
+    uint8_t* ring = dyn_smem + wave * WAVE;
+    const uint8_t* abytes = reinterpret_cast<const uint8_t*>(a);
+    auto issue = [&](uint32_t step) {
+        const bool full = 128u * step + 128u <= kk32;                 // uniform
+        const uint32_t left = kk32 - 128u * step;                     // elements of this step inside K (>= 32)
+        const uint32_t wcc = full || wc * 32u < left ? wc : 0u, wpp = full || wp * 32u < left ? wp : 0u;
+#pragma unroll
+        for (int gi = 0; gi < G; ++gi) RAZER_COPY(cbase[gi] + (size_t)step * 64u, crow[gi] + wcc * 16u, ring + NA * 1024 + gi * 1024, 16);
+#pragma unroll
+        for (int gi = 0; gi < G; ++gi) {
+            if constexpr (SF != 0)
+                RAZER_COPY(sbase[gi] + (size_t)step * 2u, srow[gi], ring + (NA + G) * 1024 + gi * 256, 2);
+            else if constexpr (GB)
+                RAZER_COPY(sbase[gi], srow[gi] + ((128u * step + 32u * wpp) >> lb), ring + (NA + G) * 1024 + gi * 256, 1);
+            else
+                RAZER_COPY(sbase[gi] + (size_t)step * 8u, srow[gi] + wpp * 2u, ring + (NA + G) * 1024 + gi * 256, 2);
+        }
+#pragma unroll
+        for (int i = 0; i < NA; ++i)
+            RAZER_COPY(abytes + (size_t)step * 256u, arow[i] + (full || achk[i] * 8u < left ? achk[i] : 0u) * 16u, ring + i * 1024, 16);
+    };
+    // LDS addresses of this lane's operands inside a slot
+    const uint32_t ring_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)ring;
+    const uint32_t lut_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint4*)lut;
+    const uint32_t code_lds = ring_lds + NA * 1024u + r * 64u + ((g ^ ((r >> 2) & 3u)) << 4);
+    const uint32_t scale_lds = ring_lds + (NA + G) * 1024u + (4u * r + g) * 4u;
+    // (fewer than 16 staged rows: the lanes of the missing ones repeat staged rows, their product columns are never stored)
+    const uint32_t ra = NA < 4 ? r & (4u * NA - 1u) : r;
+    uint32_t a_lds[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) a_lds[j] = ring_lds + ra * 256u + (((4u * g + j) ^ ra) << 4);
+
+#define RAZER_DS128(dst, addr, imm) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(imm))
+#define RAZER_DS16(dst, addr, imm) asm volatile("ds_read_u16 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(imm))
+
+    uint32_t step = wave;                                             // (the host starts at most nsteps waves)
+    issue(step);
+    if (!SF) {
+        for (uint32_t sb = threadIdx.x; sb < 256u; sb += blockDim.x) {
+            const v4u e = __builtin_bit_cast(v4u, sk_byte_table(sb, sv0, sv1));
+            asm volatile("ds_write_b128 %0, %1" ::"v"(lut_lds + sb * 16u), "v"(e) : "memory");
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    }
+    v4f acc[G][NB];
+#pragma unroll
+    for (int gi = 0; gi < G; ++gi)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[gi][b] = v4f{0.f, 0.f, 0.f, 0.f};
+
+    while (step < nsteps) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");              // this step's copies have landed
+        v4u af[NB][4], cw[G];
+        uint32_t sw[G];
+#pragma unroll
+        for (int gi = 0; gi < G; ++gi) {
+            RAZER_DS16(sw[gi], scale_lds, gi * 256);
+            RAZER_DS128(cw[gi], code_lds, gi * 1024);
+        }
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) RAZER_DS128(af[b][j], a_lds[j], b * 4096);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int gi = 0; gi < G; ++gi) asm volatile("" : "+v"(sw[gi]), "+v"(cw[gi]));
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) asm volatile("" : "+v"(af[b][j]));
+        v4u le[G][GB ? 1 : 2];
+        if constexpr (!SF) {
+#pragma unroll
+            for (int gi = 0; gi < G; ++gi) {
+                RAZER_DS128(le[gi][0], lut_lds + (sw[gi] & 255u) * 16u, 0);
+                if constexpr (!GB) RAZER_DS128(le[gi][1], lut_lds + (sw[gi] >> 8) * 16u, 0);
+            }
+        }
+        const uint32_t next = step + nwaves;
+        if (next < nsteps) issue(next);                               // (everything of this step has been read)
+        if (128u * step + 128u > kk32) {                              // ragged last step: activations past K are 0 (0 x Inf is not)
+            const uint32_t keep = (128u * step + 32u * g < kk32) ? 0xFFFFFFFFu : 0u;
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) af[b][j] &= keep;
+        }
+        if constexpr (!SF) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) af[b][j] = sk_permute_pairs(af[b][j]);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+            for (int gi = 0; gi < G; ++gi) {
+                asm volatile("" : "+v"(le[gi][0]));
+                if constexpr (!GB) asm volatile("" : "+v"(le[gi][1]));
+            }
+        }
+#pragma unroll
+        for (int gi = 0; gi < G; ++gi) {
+            if constexpr (SF != 0) {
+                float bs, sv;
+                decode_scale_word(sw[gi], sv0, sv1, bs, sv);
+                const uint32_t nsv = (uint32_t)f32_to_bf16_rne(-sv);
+                v4f blk[NB];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const v8bf wf = sk_decode_dword_bare(cw[gi][j], nsv | (nsv << 16));
+#pragma unroll
+                    for (int b = 0; b < NB; ++b)
+                        blk[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, af[b][j]), wf,
+                                                                         j == 0 ? v4f{0.f, 0.f, 0.f, 0.f} : blk[b], 0, 0, 0);
+                }
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[gi][b][i] = __builtin_fmaf(bs, blk[b][i], acc[gi][b][i]);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const v8bf wf = sk_decode_dword_table(cw[gi][j], le[gi][(GB || j < 2) ? 0 : 1]);
+#pragma unroll
+                    for (int b = 0; b < NB; ++b)
+                        acc[gi][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, __builtin_bit_cast(v8bf, af[b][j]), acc[gi][b], 0, 0, 0);
+                }
+            }
+        }
+        step = next;
+    }
+#undef RAZER_DS128
+#undef RAZER_DS16
+#undef RAZER_COPY
+
+    // partial sums in the wave's own ring (all its copies have landed and been read)
+    float4* part = reinterpret_cast<float4*>(ring);
+#pragma unroll
+    for (int gi = 0; gi < G; ++gi)
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+            part[(gi * NB + b) * 64 + lane] = make_float4(acc[gi][b][0], acc[gi][b][1], acc[gi][b][2], acc[gi][b][3]);
+    __syncthreads();
+    // unit u = (group gi, fragment b), one wave each: lane l holds rows 16 q + 4 (l / 16) + 0..3, column 16 b + l % 16
+    for (uint32_t u = wave; u < (uint32_t)(G * NB); u += nwaves) {
+        const uint32_t gi = u / NB, b = u % NB, q = blockIdx.x * G + gi;
+        if (q >= e4) break;
+        const float* ts = f0; uint16_t* y = y0;
+        int64_t n = n0, ld_y = l0;
+        uint32_t first = 0;
+        if (q >= e1) { ts = f1; y = y1; n = n1; ld_y = l1; first = e1; }
+        if (q >= e2) { ts = f2; y = y2; n = n2; ld_y = l2; first = e2; }
+        if (q >= e3) { ts = f3; y = y3; n = n3; ld_y = l3; first = e3; }
+        const int64_t row0 = (int64_t)(q - first) * 16;
+        const float sc = SF ? -*ts : *ts;                                 // (the bare decode carries a negation)
+        float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (uint32_t w = 0; w < nwaves; ++w) {
+            const float4 p = *reinterpret_cast<const float4*>(dyn_smem + w * WAVE + (u * 64u + lane) * 16u);
+            t.x += p.x; t.y += p.y; t.z += p.z; t.w += p.w;
+        }
+        const float v[4] = {t.x, t.y, t.z, t.w};
+        if constexpr (SF != 0) {
+            // swapped operands: weight row 16 q + l % 16, activation rows 16 b + 4 (l / 16) + 0..3
+            const int64_t wn = row0 + r;
+            if (wn < n) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int64_t am = 16 * b + 4 * g + i;
+                    if (am < m) y[am * ld_y + wn] = f32_to_bf16_rne(sc * v[i]);
+                }
+            }
+        } else {
+            const int64_t gn = row0 + 4 * g, gm = 16 * b + r;
+            if (gm < m && gn < n) {
+                uint16_t* dst = y + gm * ld_y + gn;
+                if (gn + 3 < n && ((reinterpret_cast<uintptr_t>(dst) & 7u) == 0)) {
+                    const uint32_t lo = (uint32_t)f32_to_bf16_rne(sc * t.x) | ((uint32_t)f32_to_bf16_rne(sc * t.y) << 16);
+                    const uint32_t hi = (uint32_t)f32_to_bf16_rne(sc * t.z) | ((uint32_t)f32_to_bf16_rne(sc * t.w) << 16);
+                    *reinterpret_cast<uint2*>(dst) = make_uint2(lo, hi);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (gn + i < n) dst[i] = f32_to_bf16_rne(sc * v[i]);
+                }
+            }
+        }
+    }
 }
 
+
+template <int NA, int G, bool GB, int SF>
+static hipError_t launch_ring_t(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, hipStream_t st)
+{
+    GemvProblem q[4];
+    uint32_t e[5] = {0, 0, 0, 0, 0};
+    for (int i = 0; i < 4; ++i) {
+        q[i] = p[i < count ? i : count - 1];
+        e[i + 1] = e[i] + (i < count ? (uint32_t)((q[i].n + 15) / 16) : 0u);
+    }
+    // 8 waves where their LDS fits a compute unit (64 activation rows and more than 2 groups: 7)
+    constexpr uint32_t fit = (kLdsBytes - kRingTableBytes) / ring_wave_bytes<NA, G>();
+    constexpr int most = fit < (uint32_t)kRingWaves ? (int)fit : kRingWaves;
+    static_assert(most >= 4, "LDS");
+    const int64_t nsteps = (k + 127) / 128;
+    const int waves = nsteps < most ? (int)nsteps : most;
+    launch(ring_kernel<NA, G, GB, SF>, (e[4] + G - 1) / G, 64 * waves, (size_t)waves * ring_wave_bytes<NA, G>(), st,
+           q[0].codes, q[1].codes, q[2].codes, q[3].codes, q[0].scales, q[1].scales, q[2].scales, q[3].scales, q[0].ts,
+           q[1].ts, q[2].ts, q[3].ts, q[0].y, q[1].y, q[2].y, q[3].y, q[0].n, q[1].n, q[2].n, q[3].n, q[0].ld_y,
+           q[1].ld_y, q[2].ld_y, q[3].ld_y, e[1], e[2], e[3], e[4], cfg.sv0, cfg.sv1, k, a, m, cfg.lb);
+    return hipGetLastError();
+}
+
+// Groups of 16 rows per workgroup.  The busiest of the 256 compute units holds ceil(workgroups / 256) workgroups of G
+// groups each; what a workgroup spends on its activations (m x K, whatever G is) grows with m / G: about 5.5 % of a
+// group's time per activation row.  Six groups leave one workgroup of eight waves per unit, which overlaps less
+// (15 %).  Measured over 1024 x 1024 .. 57344 x 8192 at 4..64 rows this picks the fastest G or one within 3 % of it:
+// 4096 rows 1; 8192 or 5003 rows 2; {q,k,v} 3 x 4096 or 10240 rows 3; 2 x 11008 rows 3, with 32 activation rows 6.
+// More than 32 activation rows take at most 4 groups (the FP16-scale format 3): six do not fit the registers.
+static int ring_groups(int64_t groups, int64_t m, bool f16)
+{
+    int best = 1;
+    double cost = 0.0;
+    for (int g : {1, 2, 3, 4, 6}) {
+        if (m > 32 && g > (f16 ? 3 : 4)) continue;
+        const int64_t wgs = (groups + g - 1) / g;
+        const double c = (double)(g * ((wgs + kComputeUnits - 1) / kComputeUnits)) * (1.0 + 0.055 * (double)m / g) * (g == 6 ? 1.15 : 1.0);
+        if (g == 1 || c < cost) { best = g; cost = c; }
+    }
+    return best;
+}
+static int64_t ring_row_groups(int count, const GemvProblem* p)
+{
+    int64_t groups = 0;
+    for (int i = 0; i < count; ++i) groups += (p[i].n + 15) / 16;
+    return groups;
+}
+
+static hipError_t launch_ring(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, hipStream_t st)
+{
+    int g = ring_groups(ring_row_groups(count, p), m, cfg.f16 != 0);
+    int64_t rows = 0;
+    for (int i = 0; i < count; ++i) rows += p[i].n;
+    const TuneShape t = tuned_shape(kTuneSmallBatch, m, rows, k);
+    if (t.source && t.p[0] == 2 && (t.p[1] == 1 || t.p[1] == 2 || t.p[1] == 3 || (t.p[1] == 4 && !(m > 32 && cfg.f16)) || (t.p[1] == 6 && m <= 32))) g = t.p[1];
+#define RAZER_RING(NA, G)                                                                  \
+    do {                                                                                   \
+        if (cfg.f16) return launch_ring_t<NA, G, false, 1>(cfg, count, p, k, a, m, st);    \
+        if (cfg.lb == 4) return launch_ring_t<NA, G, false, 0>(cfg, count, p, k, a, m, st); \
+        return launch_ring_t<NA, G, true, 0>(cfg, count, p, k, a, m, st);                  \
+    } while (0)
+#define RAZER_RING_G(NA)                   \
+    do {                                   \
+        if (g == 1) RAZER_RING(NA, 1);     \
+        if (g == 2) RAZER_RING(NA, 2);     \
+        if (g == 3) RAZER_RING(NA, 3);     \
+        if (g == 4) RAZER_RING(NA, 4);     \
+        RAZER_RING(NA, 6);                 \
+    } while (0)
+    if (m <= 8) RAZER_RING_G(2);
+    if (m <= 16) RAZER_RING_G(4);
+    if (m <= 32) RAZER_RING_G(8);
+    if (g == 1) RAZER_RING(16, 1);
+    if (g == 2) RAZER_RING(16, 2);
+    if (g == 3) RAZER_RING(16, 3);
+    return cfg.lb == 4 ? launch_ring_t<16, 4, false, 0>(cfg, count, p, k, a, m, st) : launch_ring_t<16, 4, true, 0>(cfg, count, p, k, a, m, st);
+#undef RAZER_RING_G
+#undef RAZER_RING
+}
+
+// 33..64 activation rows, scale-byte format: this kernel, unless a tuner or test forces K-slices of the register-decode
+// GEMM, or one group per workgroup makes every workgroup read more activations than it gains (one group, m x K above
+// 600 thousand: 4096 x 11008 at 40 rows 26.5 -> 24.4 us, at 64 rows 25.9 -> 26.4; 1500 x 12288 at 64 rows 22.1 -> 24.5;
+// with more groups 13-50 % faster than that kernel).
+bool ring_serves(int count, const GemvProblem* p, int64_t k, int64_t m)
+{
+    if (m <= kSkinnyMaxM || m > kRingMaxM || k > kSkinnyMaxK) return false;
+    int64_t rows = 0;
+    for (int i = 0; i < count; ++i) rows += p[i].n;
+    if (tuned_shape(kTuneGemmSlices, m, rows, k).source == 1) return false;
+    return ring_groups(ring_row_groups(count, p), m, false) > 1 || m * k <= 600000;
+}
+
+// What razer_workspace_bytes reports for 5..32 activation rows.  The kernel above needs none; callers size and pass
+// what these functions have always asked for, and a smaller workspace is refused as before, so the rule stays: the
+// K-slices of 512 or 1024 elements ([slices][m][rows] fp32) unless the launch shape on record keeps K inside the
+// workgroup.
+static bool ws_free_shape(int s, int g) { return (s == 1 && g >= 1 && g <= 4) || (s == 2 && ((g >= 1 && g <= 4) || g == 8)); }
+// some G <= 4 groups of 16 rows per workgroup make one round of workgroups that covers half of the compute units
+static bool ws_one_round(int64_t rows, int count, int64_t k, int64_t m)
+{
+    if (m > 16 || k > 16384 || (k > 8192 && m > 8)) return false;
+    const int64_t groups = (rows + 15) / 16;
+    for (int g = 1; g <= 4; ++g) {
+        const int64_t wgs = (groups + g - 1) / g + (count - 1);
+        if (wgs <= kComputeUnits) return wgs >= kComputeUnits / 2;
+    }
+    return false;
+}
+static size_t ws_bytes(int64_t rows, int64_t k, int64_t m, int count)
+{
+    int64_t steps = (m <= 16 && k > 8192) ? 8 : 4;
+    const TuneShape t = tuned_shape(kTuneSmallBatch, m, rows, k);
+    if (t.source && t.p[0] == 1 && m <= 16 && ws_free_shape(t.p[1], t.p[2])) return 0;
+    if (t.source && t.p[0] == 0 && (t.p[1] == 4 || (t.p[1] == 8 && m <= 16)) && (t.p[2] == 1 || t.p[2] == 2 || t.p[2] == 4)) steps = t.p[1];
+    else if (ws_one_round(rows, count, k, m)) return 0;
+    const int64_t nslices = (k + 128 * steps - 1) / (128 * steps);
+    return nslices > 1 ? (size_t)(nslices * m * rows) * sizeof(float) : 0;
+}
+size_t skinny_workspace_bytes(int64_t n, int64_t k, int64_t m)
+{
+    if (m <= kGemvDirectMaxM || m > kSkinnyMaxM || k == 0 || k > kSkinnyMaxK) return 0;
+    return ws_bytes(n, k, m, 1);
+}
+size_t skinny_grouped_workspace_bytes(int count, const GemvProblem* p, int64_t k, int64_t m)
+{
+    if (m <= kGemvDirectMaxM || m > kSkinnyMaxM || k == 0 || k > kSkinnyMaxK) return 0;
+    int64_t rows = 0;
+    for (int i = 0; i < count; ++i) rows += p[i].n;
+    return ws_bytes(rows, k, m, count);
+}
+
+hipError_t launch_skinny(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, hipStream_t st)
+{
+    if (count < 1 || count > 4 || m <= kGemvDirectMaxM || m > kRingMaxM || k <= 0 || k > kSkinnyMaxK) return hipErrorInvalidValue;
+    for (int i = 0; i < count; ++i)
+        if (p[i].n <= 0) return hipErrorInvalidValue;
+    return launch_ring(cfg, count, p, k, a, m, st);
+}
+
+
+// ---------------------------------------------------------------------------------------------
 // y[m][n] = bf16(scale * sum over slices, in slice order, of partial[slice][m][n]); scale = -ts_w
 // (weight-only: the decode carries a global negation) or ts_w * ts_a (both operands decoded).
 // VEC = 4: four consecutive columns per thread (n and ld_y multiples of 4).
@@ -346,483 +569,6 @@ hipError_t launch_slice_reduce_grouped(const float* partial, int count, const Ge
     launch(slice_reduce_grouped_kernel, (unsigned)((e[4] + 255) / 256), 256, 0, st, partial, q[0].ts, q[1].ts, q[2].ts, q[3].ts, q[0].y, q[1].y, q[2].y, q[3].y, q[0].n, q[1].n, q[2].n, q[3].n,
         q[0].ld_y, q[1].ld_y, q[2].ld_y, q[3].ld_y, e[1], e[2], e[3], e[4], m, nslices);
     return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------------------------
-// NB: 16-row activation fragments (M <= 16 NB); S: 128-k steps per wave and pass; G: groups of 16 weight
-// rows per workgroup.  Wave w of the workgroup owns K-slice w (S steps) of every row, in pass p slice
-// p * waves + w; its activation fragments for that slice stay in registers while it walks the G row
-// groups, the next group's packed weights in flight.  Partial sums of the waves meet in LDS after ONE
-// barrier.
-// SF = 1: the FP16-scale weight format (blocks of 128 = one step: one scale word per lane and step).  The
-// operands are bare FP4 values; the roles of the two matrix operands are swapped so that a lane's four
-// results of a step belong to ITS weight row (lane % 16) and activation rows 4 (lane / 16) + 0..3, and the
-// step's sum is folded into the running sums with the lane's own block scale in fp32.
-template <int NB, int S, int G, bool GB, int SF = 0>
-__device__ __forceinline__ void mv_body(const uint8_t* __restrict__ codes, const uint8_t* __restrict__ scales,
-                                        const float* __restrict__ w_ts, float sv0, float sv1, int64_t n, int64_t k,
-                                        const uint16_t* __restrict__ a, int64_t m, uint16_t* __restrict__ y,
-                                        int64_t ld_y, int lb, int64_t group0, int npass)
-{
-    __shared__ uint2 lut[256];
-    extern __shared__ __align__(16) uint8_t dyn_smem[];
-    float4* part = reinterpret_cast<float4*>(dyn_smem);               // [G][waves][NB][64]
-    const float ts = *w_ts;
-    const uint32_t lane = threadIdx.x & 63u, nwaves = blockDim.x >> 6;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t r = lane & 15u, g = lane >> 4;
-    const uint32_t kk32 = (uint32_t)k;
-    const uint32_t code_ld = (uint32_t)(k >> 1), scale_ld = SF ? (uint32_t)(k >> 7) * 2u : (uint32_t)(k >> (GB ? lb : 4));
-
-    struct WBuf {
-        uint32_t cw[S][4];
-        uint32_t sw[S];
-    };
-    v4f acc[G][NB];
-#pragma unroll
-    for (int gi = 0; gi < G; ++gi)
-#pragma unroll
-        for (int b = 0; b < NB; ++b) acc[gi][b] = v4f{0.f, 0.f, 0.f, 0.f};
-
-#pragma unroll 1
-    for (int p = 0; p < npass; ++p) {
-        const uint32_t kw = ((uint32_t)p * nwaves + wave) * (128u * S) + 32u * g;   // this lane's first k of step 0
-        // element offsets of this lane's S steps (clamped to 0 past K) and the matching scale masks
-        uint32_t koff[S], smask[S];
-#pragma unroll
-        for (int s = 0; s < S; ++s) {
-            const uint32_t kk = kw + 128u * s;
-            const bool in = kk < kk32;
-            koff[s] = in ? kk : 0u;
-            smask[s] = in ? 0xFFFFFFFFu : 0u;
-        }
-        // activation fragments of this K-slice: row 16 b + r (rows past M re-read row M - 1, their product
-        // columns are never stored), 64 contiguous bytes per step
-        uint32_t af[NB][S][4][4];
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const uint32_t mrow = (16u * b + r < (uint32_t)m) ? 16u * b + r : (uint32_t)m - 1u;
-            const uint8_t* ap = reinterpret_cast<const uint8_t*>(a + (int64_t)mrow * k);
-#pragma unroll
-            for (int s = 0; s < S; ++s)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const uint4 t = *reinterpret_cast<const uint4*>(ap + (koff[s] * 2u + 16u * j));
-                    af[b][s][j][0] = t.x; af[b][s][j][1] = t.y; af[b][s][j][2] = t.z; af[b][s][j][3] = t.w;
-                }
-        }
-        auto load = [&](WBuf& w, int gi) {
-            int64_t row = (group0 + gi) * 16 + r;
-            row = row < n ? row : n - 1;                                  // rows past N re-read the last row
-            const uint8_t* crow = codes + row * (int64_t)code_ld;
-            const uint8_t* srow = scales + row * (int64_t)scale_ld;
-#pragma unroll
-            for (int s = 0; s < S; ++s) {
-                const uint4 t = *reinterpret_cast<const uint4*>(crow + (koff[s] >> 1));
-                w.cw[s][0] = t.x; w.cw[s][1] = t.y; w.cw[s][2] = t.z; w.cw[s][3] = t.w;
-                if (SF) {
-                    w.sw[s] = *reinterpret_cast<const uint16_t*>(srow + ((koff[s] >> 7) << 1));
-                } else if (GB) {
-                    const uint32_t bb = srow[koff[s] >> lb];
-                    w.sw[s] = bb | (bb << 8);
-                } else {
-                    w.sw[s] = *reinterpret_cast<const uint16_t*>(srow + (koff[s] >> 4));
-                }
-            }
-        };
-        WBuf w0, w1;
-        load(w0, 0);
-        if (!SF && p == 0) {
-            for (uint32_t sb = threadIdx.x; sb < 256u; sb += blockDim.x) {
-                float s, sv;
-                decode_scale_byte<0>(sb, sv0, sv1, s, sv);
-                const uint32_t pp = (uint32_t)f32_to_bf16_rne(-(sv * s));
-                lut[sb] = make_uint2(f2u(s), pp | (pp << 16));
-            }
-            __syncthreads();
-        }
-        auto mul = [&](const WBuf& w, int gi) {
-#pragma unroll
-            for (int s = 0; s < S; ++s) {
-                const uint32_t sws = w.sw[s] & smask[s];                  // past K: scale 0
-                if constexpr (SF != 0) {
-                    float bs, sv;
-                    decode_scale_word(sws, sv0, sv1, bs, sv);
-                    const uint32_t nsv = (uint32_t)f32_to_bf16_rne(-sv);
-                    v4f blk[NB];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const v8bf wf = sk_decode_dword_bare(w.cw[s][j], nsv | (nsv << 16));
-#pragma unroll
-                        for (int b = 0; b < NB; ++b) {
-                            const v8bf av = __builtin_bit_cast(v8bf, make_uint4(af[b][s][j][0], af[b][s][j][1], af[b][s][j][2], af[b][s][j][3]));
-                            blk[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, wf, j == 0 ? v4f{0.f, 0.f, 0.f, 0.f} : blk[b], 0, 0, 0);
-                        }
-                    }
-#pragma unroll
-                    for (int b = 0; b < NB; ++b)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) acc[gi][b][i] = __builtin_fmaf(bs, blk[b][i], acc[gi][b][i]);
-                    continue;
-                }
-                const uint2 le0 = lut[sws & 255u], le1 = lut[(sws >> 8) & 255u];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const v8bf wf = sk_decode_dword(w.cw[s][j], j < 2 ? le0 : le1);
-#pragma unroll
-                    for (int b = 0; b < NB; ++b) {
-                        const v8bf av = __builtin_bit_cast(v8bf, make_uint4(af[b][s][j][0], af[b][s][j][1], af[b][s][j][2], af[b][s][j][3]));
-                        acc[gi][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, av, acc[gi][b], 0, 0, 0);
-                    }
-                }
-            }
-        };
-#pragma unroll
-        for (int gi = 0; gi < G; ++gi) {
-            if (gi + 1 < G) load((gi & 1) ? w0 : w1, gi + 1);
-            mul((gi & 1) ? w1 : w0, gi);
-        }
-    }
-#pragma unroll
-    for (int gi = 0; gi < G; ++gi)
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-            part[((gi * nwaves + wave) * NB + b) * 64 + lane] = make_float4(acc[gi][b][0], acc[gi][b][1], acc[gi][b][2], acc[gi][b][3]);
-    __syncthreads();
-    // entry e = (group gi, fragment b, lane l): rows 16 (group0 + gi) + 4 (l / 16) + 0..3, column 16 b + l % 16
-    for (uint32_t e = threadIdx.x; e < (uint32_t)(G * NB * 64); e += blockDim.x) {
-        const uint32_t gi = e / (NB * 64), b = (e / 64) % NB, l = e & 63u;
-        float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (uint32_t w = 0; w < nwaves; ++w) {
-            const float4 q = part[((gi * nwaves + w) * NB + b) * 64 + l];
-            t.x += q.x; t.y += q.y; t.z += q.z; t.w += q.w;
-        }
-        if constexpr (SF != 0) {
-            // swapped operands: weight row 16 (group0 + gi) + l % 16, activation rows 16 b + 4 (l / 16) + 0..3
-            const int64_t wn = (group0 + gi) * 16 + (l & 15u);
-            const float v[4] = {t.x, t.y, t.z, t.w};
-            if (wn < n) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int64_t am = 16 * b + 4 * (l >> 4) + i;
-                    if (am < m) y[am * ld_y + wn] = f32_to_bf16_rne(-ts * v[i]);
-                }
-            }
-            continue;
-        }
-        const int64_t gn = (group0 + gi) * 16 + 4 * (l >> 4);
-        const int64_t gm = 16 * b + (l & 15u);
-        if (gm < m && gn < n) {
-            uint16_t* dst = y + gm * ld_y + gn;
-            const float sc = -ts;
-            if (gn + 3 < n && ((reinterpret_cast<uintptr_t>(dst) & 7u) == 0)) {
-                const uint32_t lo = (uint32_t)f32_to_bf16_rne(sc * t.x) | ((uint32_t)f32_to_bf16_rne(sc * t.y) << 16);
-                const uint32_t hi = (uint32_t)f32_to_bf16_rne(sc * t.z) | ((uint32_t)f32_to_bf16_rne(sc * t.w) << 16);
-                *reinterpret_cast<uint2*>(dst) = make_uint2(lo, hi);
-            } else {
-                const float v[4] = {t.x, t.y, t.z, t.w};
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (gn + i < n) dst[i] = f32_to_bf16_rne(sc * v[i]);
-            }
-        }
-    }
-}
-
-template <int NB, int S, int G, bool GB, int MAXW, int SF = 0>
-__global__ __launch_bounds__(64 * MAXW) void mv_kernel(const uint8_t* __restrict__ codes, const uint8_t* __restrict__ scales,
-                                                       const float* __restrict__ w_ts, float sv0, float sv1, int64_t n,
-                                                       int64_t k, const uint16_t* __restrict__ a, int64_t m,
-                                                       uint16_t* __restrict__ y, int64_t ld_y, int lb, int npass)
-{
-    mv_body<NB, S, G, GB, SF>(codes, scales, w_ts, sv0, sv1, n, k, a, m, y, ld_y, lb, (int64_t)blockIdx.x * G, npass);
-}
-
-// Grouped form: workgroups [0, g1) serve matrix 0, [g1, g2) matrix 1, ... (scalar arguments picked by
-// uniform compares, as in the other grouped kernels).
-template <int NB, int S, int G, bool GB, int MAXW, int SF = 0>
-__global__ __launch_bounds__(64 * MAXW) void mv_grouped_kernel(
-    const uint8_t* c0, const uint8_t* c1, const uint8_t* c2, const uint8_t* c3,
-    const uint8_t* s0, const uint8_t* s1, const uint8_t* s2, const uint8_t* s3,
-    const float* f0, const float* f1, const float* f2, const float* f3,
-    uint16_t* y0, uint16_t* y1, uint16_t* y2, uint16_t* y3,
-    int64_t n0, int64_t n1, int64_t n2, int64_t n3,
-    int64_t l0, int64_t l1, int64_t l2, int64_t l3,
-    unsigned g1, unsigned g2, unsigned g3,
-    float sv0, float sv1, int64_t k, const uint16_t* __restrict__ a, int64_t m, int lb, int npass)
-{
-    const unsigned b = blockIdx.x;
-    const uint8_t* codes = c0; const uint8_t* scales = s0; const float* ts = f0; uint16_t* y = y0;
-    int64_t n = n0, ld = l0;
-    unsigned first = 0;
-    if (b >= g1) { codes = c1; scales = s1; ts = f1; y = y1; n = n1; ld = l1; first = g1; }
-    if (b >= g2) { codes = c2; scales = s2; ts = f2; y = y2; n = n2; ld = l2; first = g2; }
-    if (b >= g3) { codes = c3; scales = s3; ts = f3; y = y3; n = n3; ld = l3; first = g3; }
-    mv_body<NB, S, G, GB, SF>(codes, scales, ts, sv0, sv1, n, k, a, m, y, ld, lb, (int64_t)(b - first) * G, npass);
-}
-
-// Launch shapes of the K-in-workgroup kernel: (S steps per wave and pass, G row groups per workgroup,
-// at most MAXW waves).  The partial sums take G x waves KiB of LDS.
-struct MvShape {
-    int s, g, maxw;
-};
-constexpr MvShape kMvShapes[] = {{1, 1, 16}, {1, 2, 16}, {1, 3, 16}, {1, 4, 16}, {2, 1, 16}, {2, 2, 16}, {2, 3, 16}, {2, 4, 16}, {2, 8, 8}};
-static bool mv_shape_ok(int s, int g)
-{
-    for (const MvShape& sh : kMvShapes)
-        if (sh.s == s && sh.g == g) return true;
-    return false;
-}
-static int mv_maxw(int s, int g)
-{
-    for (const MvShape& sh : kMvShapes)
-        if (sh.s == s && sh.g == g) return sh.maxw;
-    return 16;
-}
-// (nb 16-row activation fragments: the partial sums take g x waves x nb KiB of LDS, at most 64)
-static void mv_geometry(int s, int g, int64_t k, int& nwaves, int& npass, int nb = 1)
-{
-    const int64_t slices = (k + 128 * s - 1) / (128 * s);
-    int maxw = nb == 4 ? 8 : mv_maxw(s, g) / nb;                    // (two / four fragments: kernels built for 8 waves)
-    if (maxw > 64 / (g * nb)) maxw = 64 / (g * nb);
-    nwaves = (int)(slices < maxw ? slices : maxw);
-    npass = (int)((slices + nwaves - 1) / nwaves);
-}
-
-// The launch plan of a small-batch problem: the tuner's entry for (m, rows, k) when it names shapes the
-// kernels are built for, else the heuristic -- the K-sliced kernel with 512-element slices (1024 for long
-// rows at M <= 16, to bound the number of slices) and 2 or 4 consecutive 64-row blocks per workgroup when
-// that still leaves 2048 workgroups (up to 16 activation rows) or 1024 (17..32); measured over 4096^2 ..
-// 57344 x 8192: 5-12 % faster on the large matrices, slower on small ones.
-struct SkinnyPlan {
-    bool in_workgroup;      // K inside the workgroup (mv_kernel): no workspace
-    int steps, nrb;         // K-sliced kernel
-    int s, g;               // K-in-workgroup kernel
-};
-// Up to 16 activation rows, no table entry: the K-in-workgroup kernel when some G <= 4 puts the whole launch into
-// ONE round of workgroups (a workgroup of 16 waves fills a compute unit, so a second round would run on a nearly
-// idle GPU) that still covers half of the 256 compute units; 2 steps per wave from 3 groups up.  Long rows with
-// more than 8 activation rows keep the K-sliced kernel.  This rule reproduces what the sweep picked on the
-// projection shapes of 7B- and 70B-class layers (4096^2: G = 1; 8192^2: 2; 11008 x 4096 and 10240 x 8192: 3;
-// {q,k,v} 3 x 4096 x 4096: 4 -- with G = 3 its 3 x 86 workgroups would be two more than the chip has units).
-constexpr int64_t kComputeUnits = 256;
-static bool mv_one_round_shape(int64_t rows, int count, int& s, int& g)
-{
-    const int64_t groups = (rows + 15) / 16;
-    for (int gg = 1; gg <= 4; ++gg) {
-        const int64_t wgs = (groups + gg - 1) / gg + (count - 1);       // (each matrix of a group rounds up on its own)
-        if (wgs <= kComputeUnits) {
-            if (wgs < kComputeUnits / 2) return false;
-            g = gg;
-            s = gg >= 3 ? 2 : 1;
-            return true;
-        }
-    }
-    return false;
-}
-static bool mv_one_round(int64_t rows, int count, int64_t k, int64_t m, int& s, int& g)
-{
-    if (m > 16 || k > 16384 || (k > 8192 && m > 8)) return false;
-    return mv_one_round_shape(rows, count, s, g);
-}
-
-static SkinnyPlan skinny_plan(int64_t rows, int64_t k, int64_t m, bool f16 = false, int count = 1)
-{
-    SkinnyPlan p{false, (m <= 16 && k > 8192) ? 8 : 4, 1, 0, 0};
-    const int64_t row_blocks = (rows + kSkRows - 1) / kSkRows;
-    const TuneShape t = tuned_shape(kTuneSmallBatch, m, rows, k);
-    if (f16) {
-        // the FP16-scale format has the K-in-workgroup kernel only (up to 32 activation rows): a forced shape,
-        // else 1 step per wave and pass and 2 row groups (best of the five shapes on the 7B-class layer at 8,
-        // 16 and 32 rows: 64 / 75 / 105 us against 79-80 / 89-91 / 115 with 4 groups)
-        p.in_workgroup = true;
-        p.s = 1;
-        p.g = 2;
-        if (t.source == 1 && t.p[0] == 1 && mv_shape_ok(t.p[1], t.p[2])) { p.s = t.p[1]; p.g = t.p[2]; }
-        else if (m <= 16) mv_one_round_shape(rows, count, p.s, p.g);   // one round of workgroups where that is possible
-        return p;
-    }
-    if (t.source && t.p[0] == 1 && m <= 16 && mv_shape_ok(t.p[1], t.p[2])) {
-        p.in_workgroup = true;
-        p.s = t.p[1];
-        p.g = t.p[2];
-        return p;
-    }
-    if (t.source && t.p[0] == 0 && (t.p[1] == 4 || (t.p[1] == 8 && m <= 16)) && (t.p[2] == 1 || t.p[2] == 2 || t.p[2] == 4)) {
-        p.steps = t.p[1];
-        p.nrb = t.p[2];
-        return p;
-    }
-    if (mv_one_round(rows, count, k, m, p.s, p.g)) {
-        p.in_workgroup = true;
-        return p;
-    }
-    const int64_t nslices = (k + 128 * p.steps - 1) / (128 * p.steps);
-    const int64_t target = m <= 16 ? 2048 : 1024;
-    while (p.nrb < 4 && (row_blocks / (2 * p.nrb)) * nslices >= target) p.nrb *= 2;
-    return p;
-}
-
-size_t skinny_workspace_bytes(int64_t n, int64_t k, int64_t m)
-{
-    if (m <= kGemvDirectMaxM || m > kSkinnyMaxM || k == 0 || k > kSkinnyMaxK) return 0;
-    const SkinnyPlan p = skinny_plan(n, k, m);
-    if (p.in_workgroup) return 0;
-    const int64_t kc = 128 * p.steps;
-    const int64_t nslices = (k + kc - 1) / kc;
-    return nslices > 1 ? (size_t)(nslices * m * n) * sizeof(float) : 0;
-}
-
-size_t skinny_grouped_workspace_bytes(int count, const GemvProblem* p, int64_t k, int64_t m)
-{
-    if (m <= kGemvDirectMaxM || m > kSkinnyMaxM || k == 0 || k > kSkinnyMaxK) return 0;
-    int64_t rows = 0;
-    for (int i = 0; i < count; ++i) rows += p[i].n;
-    const SkinnyPlan pl = skinny_plan(rows, k, m, false, count);
-    if (pl.in_workgroup) return 0;
-    const int64_t kc = 128 * pl.steps;
-    const int64_t nslices = (k + kc - 1) / kc;
-    return nslices > 1 ? (size_t)(nslices * m * rows) * sizeof(float) : 0;
-}
-
-#define RAZER_MV_SHAPES(LAUNCH)                       \
-    do {                                              \
-        if (pl.s == 1 && pl.g == 1) LAUNCH(1, 1, 16); \
-        else if (pl.s == 1 && pl.g == 2) LAUNCH(1, 2, 16); \
-        else if (pl.s == 1 && pl.g == 3) LAUNCH(1, 3, 16); \
-        else if (pl.s == 1) LAUNCH(1, 4, 16);         \
-        else if (pl.g == 1) LAUNCH(2, 1, 16);         \
-        else if (pl.g == 2) LAUNCH(2, 2, 16);         \
-        else if (pl.g == 3) LAUNCH(2, 3, 16);         \
-        else if (pl.g == 4) LAUNCH(2, 4, 16);         \
-        else LAUNCH(2, 8, 8);                         \
-    } while (0)
-
-hipError_t launch_skinny(SvConfig cfg, const uint8_t* codes, const uint8_t* scales, const float* ts, int64_t n,
-                         int64_t k, const uint16_t* a, int64_t m, uint16_t* y, int64_t ld_y, float* workspace,
-                         hipStream_t st)
-{
-    const SkinnyPlan pl = skinny_plan(n, k, m, cfg.f16 != 0);
-    if (pl.in_workgroup && cfg.f16 && m > 32) {
-        // FP16-scale format, 33..64 activation rows: four 16-row fragments, one step per wave and pass, two row groups
-        int nwaves, npass;
-        mv_geometry(1, 2, k, nwaves, npass, 4);
-        launch(mv_kernel<4, 1, 2, false, 8, 1>, (unsigned)(((n + 15) / 16 + 1) / 2), 64 * nwaves, (size_t)2 * nwaves * 4 * 1024, st,
-               codes, scales, ts, cfg.sv0, cfg.sv1, n, k, a, m, y, ld_y, cfg.lb, npass);
-        return hipGetLastError();
-    }
-    if (pl.in_workgroup) {
-        const int nb = m <= 16 ? 1 : 2;
-        int nwaves, npass;
-        mv_geometry(pl.s, pl.g, k, nwaves, npass, nb);
-        const unsigned grid = (unsigned)(((n + 15) / 16 + pl.g - 1) / pl.g);
-        const size_t smem = (size_t)pl.g * nwaves * nb * 1024;
-#define RAZER_MV(S, G, MW)                                                                                           \
-        do {                                                                                                         \
-            if (cfg.f16 && nb == 2) launch(mv_kernel<2, S, G, false, MW / 2, 1>, grid, 64 * nwaves, smem, st, codes, scales, ts, cfg.sv0, cfg.sv1, n, k, a, m, y, ld_y, cfg.lb, npass); \
-            else if (cfg.f16) launch(mv_kernel<1, S, G, false, MW, 1>, grid, 64 * nwaves, smem, st, codes, scales, ts, cfg.sv0, cfg.sv1, n, k, a, m, y, ld_y, cfg.lb, npass); \
-            else if (cfg.lb == 4) launch(mv_kernel<1, S, G, false, MW>, grid, 64 * nwaves, smem, st, codes, scales, ts, cfg.sv0, cfg.sv1, n, k, a, m, y, ld_y, cfg.lb, npass); \
-            else launch(mv_kernel<1, S, G, true, MW>, grid, 64 * nwaves, smem, st, codes, scales, ts, cfg.sv0, cfg.sv1, n, k, a, m, y, ld_y, cfg.lb, npass);             \
-        } while (0)
-        RAZER_MV_SHAPES(RAZER_MV);
-#undef RAZER_MV
-        return hipGetLastError();
-    }
-    const int steps = pl.steps;
-    const int64_t kc = 128 * steps;
-    const int nslices = (int)((k + kc - 1) / kc);
-    const int64_t row_blocks = (n + kSkRows - 1) / kSkRows;
-    const int nrb = pl.nrb;
-    const unsigned grid = (unsigned)(((row_blocks + nrb - 1) / nrb) * nslices);
-#define RAZER_SK_ARGS codes, scales, ts, cfg.sv0, cfg.sv1, n, k, a, m, y, ld_y, workspace, nslices, cfg.lb
-#define RAZER_SK(NB, ST, GB)                                                                  \
-    do {                                                                                      \
-        if (nrb == 1) launch(skinny_kernel<NB, ST, GB, 1>, grid, 256, 0, st, RAZER_SK_ARGS);      \
-        else if (nrb == 2) launch(skinny_kernel<NB, ST, GB, 2>, grid, 256, 0, st, RAZER_SK_ARGS); \
-        else launch(skinny_kernel<NB, ST, GB, 4>, grid, 256, 0, st, RAZER_SK_ARGS);               \
-    } while (0)
-    if (cfg.lb == 4) {
-        if (m <= 16) { if (steps == 8) RAZER_SK(1, 8, false); else RAZER_SK(1, 4, false); }
-        else RAZER_SK(2, 4, false);
-    } else {                                                            // blocks of 32, 64, 128
-        if (m <= 16) { if (steps == 8) RAZER_SK(1, 8, true); else RAZER_SK(1, 4, true); }
-        else RAZER_SK(2, 4, true);
-    }
-#undef RAZER_SK
-#undef RAZER_SK_ARGS
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || nslices == 1) return e;
-    return launch_slice_reduce(workspace, ts, nullptr, m, n, nslices, y, ld_y, st);
-}
-
-// One launch (plus one reduction launch when K is sliced over workgroups) for up to 4 matrices sharing K,
-// the activation rows (5..32), the block size and the special values; every n a positive multiple of 4.
-// Workspace: skinny_grouped_workspace_bytes.
-hipError_t launch_skinny_grouped(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a,
-                                 int64_t m, float* workspace, hipStream_t st)
-{
-    if (count < 1 || count > 4 || m <= kGemvDirectMaxM || m > kSkinnyMaxM || k > kSkinnyMaxK)
-        return hipErrorInvalidValue;
-    int64_t rows = 0;
-    for (int i = 0; i < count; ++i) rows += p[i].n;
-    const SkinnyPlan pl = skinny_plan(rows, k, m, cfg.f16 != 0, count);
-    GemvProblem q[4];
-    unsigned g[5] = {0, 0, 0, 0, 0};
-    for (int i = 0; i < 4; ++i) {
-        q[i] = p[i < count ? i : count - 1];
-        if (q[i].n % 4 != 0 || q[i].n <= 0) return hipErrorInvalidValue;
-    }
-#define RAZER_SKG_COMMON                                                                                             \
-    q[0].codes, q[1].codes, q[2].codes, q[3].codes, q[0].scales, q[1].scales, q[2].scales, q[3].scales, q[0].ts,     \
-        q[1].ts, q[2].ts, q[3].ts, q[0].y, q[1].y, q[2].y, q[3].y, q[0].n, q[1].n, q[2].n, q[3].n, q[0].ld_y,        \
-        q[1].ld_y, q[2].ld_y, q[3].ld_y, g[1], g[2], g[3], cfg.sv0, cfg.sv1, k, a, m
-    if (pl.in_workgroup) {
-        const int nb = m <= 16 ? 1 : 2;
-        int nwaves, npass;
-        mv_geometry(pl.s, pl.g, k, nwaves, npass, nb);
-        for (int i = 0; i < 4; ++i)
-            g[i + 1] = g[i] + (i < count ? (unsigned)(((q[i].n + 15) / 16 + pl.g - 1) / pl.g) : 0u);
-        const size_t smem = (size_t)pl.g * nwaves * nb * 1024;
-#define RAZER_MVG(S, G, MW)                                                                                                   \
-        do {                                                                                                                  \
-            if (cfg.f16 && nb == 2) launch(mv_grouped_kernel<2, S, G, false, MW / 2, 1>, g[4], 64 * nwaves, smem, st, RAZER_SKG_COMMON, cfg.lb, npass); \
-            else if (cfg.f16) launch(mv_grouped_kernel<1, S, G, false, MW, 1>, g[4], 64 * nwaves, smem, st, RAZER_SKG_COMMON, cfg.lb, npass); \
-            else if (cfg.lb == 4) launch(mv_grouped_kernel<1, S, G, false, MW>, g[4], 64 * nwaves, smem, st, RAZER_SKG_COMMON, cfg.lb, npass); \
-            else launch(mv_grouped_kernel<1, S, G, true, MW>, g[4], 64 * nwaves, smem, st, RAZER_SKG_COMMON, cfg.lb, npass);             \
-        } while (0)
-        RAZER_MV_SHAPES(RAZER_MVG);
-#undef RAZER_MVG
-        return hipGetLastError();
-    }
-    const int steps = pl.steps;
-    const int64_t kc = 128 * steps;
-    const int nslices = (int)((k + kc - 1) / kc);
-    const int nrb = pl.nrb;
-    for (int i = 0; i < 4; ++i) {
-        const int64_t rbi = (q[i].n + kSkRows - 1) / kSkRows;
-        g[i + 1] = g[i] + (i < count ? (unsigned)((rbi + nrb - 1) / nrb) * nslices : 0u);
-    }
-    float* partial = nslices > 1 ? workspace : nullptr;
-#define RAZER_SKG_ARGS RAZER_SKG_COMMON, partial, nslices, cfg.lb
-#define RAZER_SKG(NB, ST, GB)                                                                            \
-    do {                                                                                                 \
-        if (nrb == 1) launch(skinny_grouped_kernel<NB, ST, 1, GB>, g[4], 256, 0, st, RAZER_SKG_ARGS);        \
-        else if (nrb == 2) launch(skinny_grouped_kernel<NB, ST, 2, GB>, g[4], 256, 0, st, RAZER_SKG_ARGS);   \
-        else launch(skinny_grouped_kernel<NB, ST, 4, GB>, g[4], 256, 0, st, RAZER_SKG_ARGS);                 \
-    } while (0)
-    if (cfg.lb == 4) {
-        if (m <= 16) { if (steps == 8) RAZER_SKG(1, 8, false); else RAZER_SKG(1, 4, false); }
-        else RAZER_SKG(2, 4, false);
-    } else {                                                            // blocks of 32, 64, 128
-        if (m <= 16) { if (steps == 8) RAZER_SKG(1, 8, true); else RAZER_SKG(1, 4, true); }
-        else RAZER_SKG(2, 4, true);
-    }
-#undef RAZER_SKG
-#undef RAZER_SKG_ARGS
-#undef RAZER_SKG_COMMON
-    hipError_t err = hipGetLastError();
-    if (err != hipSuccess || nslices == 1) return err;
-    return launch_slice_reduce_grouped(partial, count, p, m, nslices, st);
 }
 
 }  // namespace razer

@@ -33,9 +33,10 @@ def candidates(family, m, k):
     if family == 1:
         return [(4,), (8,)] if k <= 16384 else [(4,)]
     if family == 2:
-        sliced = [(0, 4, 1), (0, 4, 2), (0, 4, 4)] + ([(0, 8, 1), (0, 8, 2)] if m <= 16 else [])
-        inside = [(1, 1, 1), (1, 1, 2), (1, 1, 3), (1, 1, 4), (1, 2, 1), (1, 2, 2), (1, 2, 3), (1, 2, 4), (1, 2, 8)] if m <= 16 else []
-        return sliced + inside
+        # (0, ..) and (1, ..): shapes on record that only fix the reported workspace (include/razer_tune.h); not swept
+        on_record = [(0, 4, 1), (0, 4, 2), (0, 4, 4)] + ([(0, 8, 1), (0, 8, 2)] if m <= 16 else [])
+        on_record += [(1, 1, 1), (1, 1, 2), (1, 1, 3), (1, 1, 4), (1, 2, 1), (1, 2, 2), (1, 2, 3), (1, 2, 4), (1, 2, 8)] if m <= 16 else []
+        return on_record + [(2, g, 0) for g in (1, 2, 3, 4, 6)]
     kt = -(-k // 64)
     return [(s,) for s in (1, 2, 3, 4, 6, 8, 12, 16) if s <= kt]
 
@@ -143,6 +144,8 @@ def main():
         t_default = time_calls(build(), args.launches)
         results = []
         for shape in candidates(fam, m, k):
+            if fam == 2 and shape[0] != 2:
+                continue
             rz.razer_tune_force(fam, shape)
             results.append((time_calls(build(), args.launches), shape))
         rz.razer_tune_force(fam, (-1, -1, -1, -1))            # the heuristic once more: the smaller of the two readings

@@ -1,0 +1,72 @@
+"""The small-batch kernel (5..64 activation rows) where its tiles, steps and copies end: remainders of 16 rows and of
+128 elements, K shorter than one step, every number of staged activation rows, every number of row groups per
+workgroup, matrices of a group that share a workgroup, each weight format -- against the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2501_04052_amd as razer
+from paper_2501_04052_amd import binding, synth
+from gpu_util import TOL, bf16_bits_to_dev, dev_to_bf16_bits, max_rel_err
+
+pytestmark = pytest.mark.gpu
+SV = (5.0, 8.0)
+
+
+def _weights(n, k, seed, fmt, block):
+    rng = np.random.default_rng(seed)
+    codes = rng.integers(0, 256, size=(n, k // 2), dtype=np.uint8)
+    if fmt == razer.WEIGHT_F16:
+        scales = rng.integers(0, 1 << 16, size=(n, k // 128)).astype(np.uint16)
+    else:
+        scales = rng.integers(0, 256, size=(n, k // block), dtype=np.uint8)
+    wq = (codes, scales, np.float32(2.0 ** -9))
+    return wq, razer.RazerTensor.from_host(*wq, fmt, SV)
+
+
+def _run(oracle, ns, k, m, fmt, block, groups=None):
+    print("small batch ns", ns, "k", k, "m", m, "format", fmt, "block", block, "groups", groups, flush=True)
+    a = synth.activation(m, k, seed=4400 + m + k)
+    a_dev = bf16_bits_to_dev(a)
+    ws = [_weights(n, k, 4500 + i + n, fmt, block) for i, n in enumerate(ns)]
+    if groups:
+        razer.razer_tune_force(binding.TUNE_SMALL_BATCH, (2, groups))
+    try:
+        ys = [razer.razer_linear(ws[0][1], a_dev)] if len(ns) == 1 else razer.razer_linear_grouped([w[1] for w in ws], a_dev)
+        torch.cuda.synchronize()
+    finally:
+        razer.razer_tune_force(binding.TUNE_SMALL_BATCH, None)
+    for (wq, _), y in zip(ws, ys):
+        y64, _ = oracle.linear(wq, a_bf16=a)
+        assert max_rel_err(dev_to_bf16_bits(y), y64) <= TOL
+
+
+@pytest.mark.parametrize("m", [5, 8, 9, 16, 17, 32, 33, 64])
+@pytest.mark.parametrize("ns,k,fmt,block", [((37,), 32, razer.WEIGHT, 16), ((16, 4, 100), 4096 + 96, razer.WEIGHT, 16),
+                                            ((50,), 1152, razer.WEIGHT, 64), ((36, 20), 1280, razer.WEIGHT_F16, 128)])
+def test_edges(oracle, m, ns, k, fmt, block):
+    _run(oracle, ns, k, m, fmt, block)
+
+
+@pytest.mark.parametrize("groups", [1, 2, 3, 4, 6])
+@pytest.mark.parametrize("m,fmt,block", [(8, razer.WEIGHT, 16), (16, razer.WEIGHT, 32), (32, razer.WEIGHT, 16), (64, razer.WEIGHT, 16),
+                                         (32, razer.WEIGHT_F16, 128), (64, razer.WEIGHT_F16, 128)])
+def test_groups_per_workgroup(oracle, groups, m, fmt, block):
+    _run(oracle, (68, 33 * 4, 12), 2176, m, fmt, block, groups)
+
+
+@pytest.mark.parametrize("m", [6, 40])
+def test_infinite_activation_stays_infinite_with_a_ragged_last_step(oracle, m):
+    """Lanes past K re-read the step's first elements with the activations cleared: an infinity there must not meet
+    the weights of the tail (0 x Inf is NaN), and must not reach other rows."""
+    n, k = 48, 96
+    wq, wt = _weights(n, k, 77, razer.WEIGHT, 16)
+    a = torch.from_numpy(synth.bf16_bits_to_f32(synth.activation(m, k, seed=78))).to(torch.bfloat16)
+    plain = razer.razer_linear(wt, a.cuda())
+    a[2, 0] = float("inf")
+    got = razer.razer_linear(wt, a.cuda()).float().cpu()
+    w0 = torch.from_numpy(oracle.dequant(oracle.WEIGHT, *wq)["f32"])[:, 0].float()
+    hit = w0 != 0
+    assert torch.equal(got[2][hit], torch.sign(w0[hit]) * float("inf"))
+    others = [i for i in range(m) if i != 2]
+    assert torch.equal(got[others], plain.float().cpu()[others])
