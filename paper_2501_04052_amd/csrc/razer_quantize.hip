@@ -54,7 +54,12 @@ __global__ __launch_bounds__(256) void absmax_kernel(const T* __restrict__ x, in
     if (ld == cols) {                                   // dense: one flat array of vectors
         const int64_t total = rows * cols / VEC;
         const uint4* p = reinterpret_cast<const uint4*>(x);
-        for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += stride) fold(p[i]);
+        int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+        for (; i + 3 * stride < total; i += 4 * stride) {        // four loads in flight per lane
+            const uint4 v0 = p[i], v1 = p[i + stride], v2 = p[i + 2 * stride], v3 = p[i + 3 * stride];
+            fold(v0); fold(v1); fold(v2); fold(v3);
+        }
+        for (; i < total; i += stride) fold(p[i]);
     } else {                                            // strided rows: workgroups stride over rows
         const int64_t vec_per_row = cols / VEC;
         for (int64_t r = blockIdx.x; r < rows; r += gridDim.x) {
@@ -95,22 +100,123 @@ __device__ __forceinline__ uint32_t round_scale(float t)
     return code > kMaxCode ? kMaxCode : code;
 }
 
+// Nearest FP4 value, ties to the even code, saturating at +-6: the hardware conversion (verified against the threshold
+// form of the same rule on every boundary +- 1 ulp and 10^6 random values).  It writes the two codes into byte `i` of
+// the packed dword; a negative value that rounds to zero comes out as code 0x8 and is cleared later.
+__device__ __forceinline__ uint32_t encode_pair(uint32_t word, float a, float b, int i)
+{
+    return (i == 0)   ? __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(word, a, b, 1.0f, 0)
+           : (i == 1) ? __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(word, a, b, 1.0f, 1)
+           : (i == 2) ? __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(word, a, b, 1.0f, 2)
+                      : __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(word, a, b, 1.0f, 3);
+}
+__device__ __forceinline__ v2f decode_pair_f32(uint32_t word, int i)      // the values of those two codes
+{
+    return (i == 0)   ? __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(word, 1.0f, 0)
+           : (i == 1) ? __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(word, 1.0f, 1)
+           : (i == 2) ? __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(word, 1.0f, 2)
+                      : __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(word, 1.0f, 3);
+}
+
 // ---------------------------------------------------------------- block encoder
-// One thread encodes one run of 16 elements; G = block / 16 consecutive lanes share a block: they
+// A thread encodes runs of 16 elements; G = block / 16 consecutive lanes share a block: they
 // agree on the block maximum (hence on the scale) by exchanging their run's maximum, and on the
-// special value by forming Eq. 4's error sum as ONE chain over the block's elements in index order:
-// lane j of the block continues the sum where lane j - 1 ended (G rounds of 16 additions, of which
-// each lane keeps the one round that started from its predecessor's total).
+// special value.
+//
+// What bounds it: written out literally (IEEE division, four fp64 error sums) an element costs about 220 clocks of
+// a SIMD, twice what its bytes take from memory.  Two things make it cheaper without changing a bit:
+//  * division.  y = 1 / den is one IEEE division per block; q = x y, then twice q += (x - q den) y with the residual
+//    in one fma.  The first correction makes q faithful, and for a faithful q, a correctly rounded reciprocal and an
+//    exact residual the second yields the correctly rounded quotient (Markstein's theorem); 5 operations instead of
+//    ~12.  It needs normal operands: tensor scales outside [2^-60, 2^60] take the literal path.
+//  * the special-value search.  Candidate v lowers an element's squared error by (v - q)(2 x - q - v) when that is
+//    positive; sign and zero of that product are exact in fp32 (2 x - q is exact, and so is the difference to v where
+//    it is close to it), so "no element takes v" and the elements that take it are known exactly, and the sums of the
+//    gains to a relative error below (elements + 8) 2^-23.  The candidate with the largest gain has the smallest
+//    error; where the two largest gains are closer than that bound (and for non-finite blocks, blocks that exceed
+//    9 scales) the literal fp64 chain of Eq. 4 decides: about one block in 10^5 of continuous data.
+// 11008 x 4096 fp32, without the pass for Eq. 1: blocks of 16 61.6 -> 42.4 us (206 MB, 4.9 TB/s), blocks of 128
+// 108.5 -> 44.2 us; 4096 x 4096 bf16 activations 19.7 -> 18.8.
+
+// Eq. 4 and the codes literally: fp32 division, squared errors in fp64, one chain over the block's elements in index
+// order (lane j of the block continues where lane j - 1 ended).  lo / hi: the 16 codes as the hardware rounds them;
+// take: bit k set if element k takes the chosen special value.
+template <int FMT, int G>
+__device__ __forceinline__ void encode_literal(const float (&xv)[kBlock], float den, float sv0, float sv1, uint32_t& lo,
+                                               uint32_t& hi, uint32_t& meta, uint32_t& take)
+{
+    constexpr int NC = (FMT == 1) ? 2 : 4;
+    float xs[kBlock], q[kBlock];
+    lo = hi = 0;
+#pragma unroll
+    for (int k = 0; k < kBlock; k += 2) {
+        xs[k] = xv[k] / den;                                              // X^Scaled
+        xs[k + 1] = xv[k + 1] / den;
+        uint32_t& word = (k < 8) ? lo : hi;
+        word = encode_pair(word, xs[k], xs[k + 1], (k % 8) / 2);
+        const v2f p = decode_pair_f32(word, (k % 8) / 2);
+        q[k] = p.x;
+        q[k + 1] = p.y;
+    }
+    double best = 0.0;
+    meta = 0;
+    take = 0;
+#pragma unroll
+    for (int m = 0; m < NC; ++m) {
+        const double cand = (FMT == 1) ? (m ? -(double)sv0 : (double)sv0)
+                                       : (m & 2 ? -1.0 : 1.0) * (double)((m & 1) ? sv1 : sv0);
+        const int sub = (int)(threadIdx.x & 63u) & (G - 1), base = (int)(threadIdx.x & 63u) & ~(G - 1);
+        double sse = 0.0;
+        uint32_t bits = 0;
+        // round p is the one in which lane base + p of the block holds the right starting value (its
+        // predecessor's total of round p - 1)
+#pragma unroll 1
+        for (int p = 0; p < G; ++p) {
+            double a = (p == 0) ? 0.0 : __shfl(sse, base + p - 1);
+            bits = 0;
+#pragma unroll
+            for (int k = 0; k < kBlock; ++k) {
+                const double xd = (double)xs[k], eb = xd - (double)q[k], ev = xd - cand;
+                const bool sp = fabs(ev) < fabs(eb);
+                const double e = sp ? ev : eb;
+                a = __builtin_fma(e, e, a);                               // e*e is exact in fp64: same as a + e*e
+                bits |= (uint32_t)sp << k;
+            }
+            sse = (sub == p) ? a : sse;
+        }
+        if (G > 1) sse = __shfl(sse, base + G - 1);                       // every lane of the block: the block's sum
+        if (m == 0 || sse < best) {                                       // Eq. 4: smallest error, ties to the smallest index
+            best = sse;
+            meta = m;
+            take = bits;
+        }
+    }
+}
+
 template <typename T, int FMT, int G>
 __global__ __launch_bounds__(256) void encode_kernel(const T* __restrict__ x, int64_t rows, int64_t cols,
-                                                     int64_t ld, SvConfig cfg,
+                                                     int64_t ld, float sv0, float sv1,
                                                      const uint32_t* __restrict__ absmax_ws,
                                                      float* __restrict__ tensor_scale, int given_scale,
                                                      uint8_t* __restrict__ codes, uint8_t* __restrict__ scales)
 {
-    constexpr int NC = (FMT == 1) ? 2 : 4;
-    const int64_t nb = cols / kBlock;
-    const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    constexpr int NM = (FMT == 1) ? 1 : 2;                                // special magnitudes
+    constexpr int NV = (int)sizeof(T);                                    // 16-byte vectors per run
+    const int64_t nb = cols / kBlock, runs = rows * nb;
+    const int64_t first_run = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+    auto load = [&](uint4 (&v)[NV], int64_t run) {
+        // dense rows are one array of runs; only strided ones need the row number
+        int64_t src = run * kBlock;
+        if (ld != cols) {
+            const int64_t r = run / nb;
+            src = r * ld + (run - r * nb) * kBlock;
+        }
+        const uint4* xp = reinterpret_cast<const uint4*>(x + src);
+#pragma unroll
+        for (int j = 0; j < NV; ++j) v[j] = xp[j];
+    };
+    uint4 next[NV];
+    if (first_run < runs) load(next, first_run);
 
     float delta32;
     if (given_scale) {
@@ -119,144 +225,152 @@ __global__ __launch_bounds__(256) void encode_kernel(const T* __restrict__ x, in
         float amax = absmax_from_cells(absmax_ws);
         constexpr float kDenom = (FMT == 0) ? 180.0f : (FMT == 1) ? 2688.0f : 11.994140625f;   // Qmax_scale * 6
         delta32 = (amax == 0.0f) ? 1.0f : amax / kDenom;
-        if (gid == 0) *tensor_scale = delta32;
+        if (first_run == 0) *tensor_scale = delta32;
     }
-    if (gid >= rows * nb) return;
-    const int64_t r = gid / nb, b = gid - r * nb;
 
-    float xv[kBlock];
-    if (sizeof(T) == 4) {
-        const uint4* p = reinterpret_cast<const uint4*>(x + r * ld + b * kBlock);
+    // several runs per thread, the next one's elements on their way while one is encoded
+#pragma unroll 1
+    for (int64_t gid = first_run; gid < runs; gid += stride) {
+        float xv[kBlock];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            uint4 v = p[j];
-            xv[4 * j + 0] = u2f(v.x); xv[4 * j + 1] = u2f(v.y);
-            xv[4 * j + 2] = u2f(v.z); xv[4 * j + 3] = u2f(v.w);
-        }
-    } else {
-        const uint4* p = reinterpret_cast<const uint4*>(x + r * ld + b * kBlock);
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            uint4 v = p[j];
-            uint32_t w[4] = {v.x, v.y, v.z, v.w};
+        for (int j = 0; j < NV; ++j) {
+            const uint32_t w[4] = {next[j].x, next[j].y, next[j].z, next[j].w};
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                xv[8 * j + 2 * i + 0] = u2f(w[i] << 16);
-                xv[8 * j + 2 * i + 1] = u2f(w[i] & 0xFFFF0000u);
-            }
-        }
-    }
-
-    float bmax = 0.0f;
-#pragma unroll
-    for (int k = 0; k < kBlock; ++k) bmax = fmaxf(bmax, fabsf(xv[k]));
-#pragma unroll
-    for (int off = 1; off < G; off <<= 1) bmax = fmaxf(bmax, __shfl_xor(bmax, off));   // the block's maximum
-
-    // Eq. 2
-    const float d = delta32 * 6.0f;
-    const float t = bmax / d;
-    const uint32_t sc = round_scale<FMT>(t);
-    const float s = (FMT == 0) ? e3m3_value(sc) : (FMT == 1) ? e4m3_value(sc) : half14_value(sc);
-
-    uint32_t lo = 0, hi = 0, meta = 0;                                    // 16 nibbles, low dword = k 0..7
-    if (s != 0.0f) {
-        const float den = delta32 * s;
-        double cand[NC];
-        if (FMT != 1) { cand[0] = cfg.sv0; cand[1] = cfg.sv1; cand[2] = -cfg.sv0; cand[3] = -cfg.sv1; }
-        else { cand[0] = cfg.sv0; cand[1] = -cfg.sv0; }
-        double sse[NC];
-        double e2[G > 1 ? NC : 1][kBlock];                                // G > 1: the squared errors, summed as a chain below
-        uint32_t take[NC];                                                // bit k: element k takes the special value
-#pragma unroll
-        for (int m = 0; m < NC; ++m) { sse[m] = 0.0; take[m] = 0u; }
-#pragma unroll
-        for (int k = 0; k < kBlock; k += 2) {
-            const float xs0 = xv[k] / den, xs1 = xv[k + 1] / den;         // X^Scaled
-            // Nearest FP4 value, ties to the even code, saturating at +-6: the hardware conversion
-            // (verified against the threshold form of the same rule on every boundary +- 1 ulp and
-            // 10^6 random values).  It writes the two codes into byte k / 2 of the packed dword; a
-            // negative value that rounds to zero comes out as code 0x8 and is cleared below.
-            uint32_t& word = (k < 8) ? lo : hi;
-            word = (k % 8 == 0)   ? __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(word, xs0, xs1, 1.0f, 0)
-                   : (k % 8 == 2) ? __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(word, xs0, xs1, 1.0f, 1)
-                   : (k % 8 == 4) ? __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(word, xs0, xs1, 1.0f, 2)
-                                  : __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(word, xs0, xs1, 1.0f, 3);
-            const v2f q = (k % 8 == 0)   ? __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(word, 1.0f, 0)
-                          : (k % 8 == 2) ? __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(word, 1.0f, 1)
-                          : (k % 8 == 4) ? __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(word, 1.0f, 2)
-                                         : __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(word, 1.0f, 3);
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const double xd = (double)(j ? xs1 : xs0);
-                const double eb = xd - (double)(j ? q.y : q.x);           // exact (-0 for a negative zero changes nothing)
-#pragma unroll
-                for (int m = 0; m < NC; ++m) {
-                    const double ev = xd - cand[m];
-                    const bool sp = fabs(ev) < fabs(eb);
-                    const double e = sp ? ev : eb;
-                    if (G > 1) e2[m][k + j] = e * e;                      // exact in fp64
-                    else sse[m] = __builtin_fma(e, e, sse[m]);            // e*e is exact in fp64: same as sse + e*e
-                    take[m] |= (uint32_t)sp << (k + j);
+                if (sizeof(T) == 4) {
+                    xv[4 * j + i] = u2f(w[i]);
+                } else {
+                    xv[8 * j + 2 * i + 0] = u2f(w[i] << 16);
+                    xv[8 * j + 2 * i + 1] = u2f(w[i] & 0xFFFF0000u);
                 }
             }
         }
-        if (G > 1) {
-            // block error = sum over all 16 G elements in index order.  Round p is the one in which lane
-            // base + p of the block holds the right starting value (its predecessor's total of round p - 1).
-            const int sub = (int)(threadIdx.x & 63u) & (G - 1), base = (int)(threadIdx.x & 63u) & ~(G - 1);
+        load(next, gid + stride < runs ? gid + stride : gid);
+
+        float bmax = 0.0f;
 #pragma unroll
-            for (int p = 0; p < G; ++p) {
+        for (int k = 0; k < kBlock; ++k) bmax = fmaxf(bmax, fabsf(xv[k]));
+        bool finite = true;                                                   // (fmaxf drops a NaN)
+        if (given_scale) {                                                    // else Eq. 1's maximum has seen every element
+            float z = 0.0f;
 #pragma unroll
-                for (int m = 0; m < NC; ++m) {
-                    double a = (p == 0) ? 0.0 : __shfl(sse[m], base + p - 1);
-#pragma unroll
-                    for (int k = 0; k < kBlock; ++k) a += e2[m][k];
-                    sse[m] = (sub == p) ? a : sse[m];
-                }
-            }
-#pragma unroll
-            for (int m = 0; m < NC; ++m) sse[m] = __shfl(sse[m], base + G - 1);   // every lane of the block: the block's sum
+            for (int k = 0; k < kBlock; ++k) z = __builtin_fmaf(xv[k], 0.0f, z);
+            finite = z == 0.0f;
         }
-        // Eq. 4: smallest error, ties to the smallest metadata index
-        double best = sse[0];
 #pragma unroll
-        for (int m = 1; m < NC; ++m)
-            if (sse[m] < best) { best = sse[m]; meta = m; }
-        uint32_t tk = take[0];
+        for (int off = 1; off < G; off <<= 1) {                               // the block's maximum
+            bmax = fmaxf(bmax, __shfl_xor(bmax, off));
+            finite = __shfl_xor((int)finite, off) != 0 && finite;
+        }
+
+        // Eq. 2
+        const float d = delta32 * 6.0f;
+        const float t = bmax / d;
+        const uint32_t sc = round_scale<FMT>(t);
+        const float s = (FMT == 0) ? e3m3_value(sc) : (FMT == 1) ? e4m3_value(sc) : half14_value(sc);
+
+        uint32_t lo = 0, hi = 0, meta = 0;                                    // 16 nibbles, low dword = k 0..7
+        if (s != 0.0f) {
+            const float den = delta32 * s;
+            uint32_t tlo = 0, thi = 0;                                        // bit 3 of a nibble: the element takes the special value
+            bool decided = finite && delta32 >= 0x1p-60f && delta32 <= 0x1p60f && bmax <= 9.0625f * den;
+            if (decided) {
+                const float y = 1.0f / den;
+                float all[NM], dir[NM];                                       // gains / 16: sum, and sum with the element's sign
+                uint32_t took[NM][2];
 #pragma unroll
-        for (int m = 1; m < NC; ++m) tk = (meta == (uint32_t)m) ? take[m] : tk;
-        // Eq. 5 on the packed nibbles: zero keeps code 0x0 whatever its sign, taken elements get the
-        // remapped code 0x8.  spread() moves bit k of a byte-wide mask to bit 4 k.
-        auto spread = [](uint32_t b) {
-            b = (b | (b << 12)) & 0x000F000Fu;
-            b = (b | (b << 6)) & 0x03030303u;
-            return (b | (b << 3)) & 0x11111111u;
-        };
-        auto finish = [&](uint32_t w, uint32_t taken8) {
-            const uint32_t mag = w & 0x77777777u;
-            const uint32_t nz = (mag | (mag >> 1) | (mag >> 2)) & 0x11111111u;   // 1 per nibble with a non-zero magnitude
-            w &= 0x77777777u | (nz << 3);                                     // -0 -> +0
-            const uint32_t t1 = spread(taken8);
-            return (w & ~(t1 * 15u)) | (t1 << 3);
-        };
-        lo = finish(lo, tk & 0xFFu);
-        hi = finish(hi, (tk >> 8) & 0xFFu);
-    }
-    *reinterpret_cast<uint2*>(codes + r * (cols / 2) + b * 8) = make_uint2(lo, hi);
-    if ((b & (G - 1)) == 0) {
-        if (FMT == 2) reinterpret_cast<uint16_t*>(scales)[r * (nb / G) + b / G] = (uint16_t)((meta << 14) | sc);
-        else scales[r * (nb / G) + b / G] = (uint8_t)((meta << (FMT == 0 ? 6 : 7)) | sc);
+                for (int m = 0; m < NM; ++m) { all[m] = dir[m] = 0.0f; took[m][0] = took[m][1] = 0u; }
+#pragma unroll
+                for (int k = 0; k < kBlock; k += 2) {
+                    float xs[2];
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        float q = xv[k + j] * y;
+                        q = __builtin_fmaf(__builtin_fmaf(-q, den, xv[k + j]), y, q);
+                        xs[j] = __builtin_fmaf(__builtin_fmaf(-q, den, xv[k + j]), y, q);
+                    }
+                    uint32_t& word = (k < 8) ? lo : hi;
+                    word = encode_pair(word, xs[0], xs[1], (k % 8) / 2);
+                    const v2f q2 = decode_pair_f32(word, (k % 8) / 2);
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        const float q = j ? q2.y : q2.x;
+                        const float u = fabsf(__builtin_fmaf(2.0f, xs[j], -q));
+#pragma unroll
+                        for (int m = 0; m < NM; ++m) {
+                            const float v = m ? sv1 : sv0;
+                            // gain / 16 (below 1 up to 9 scales), 0 where the special value is no better
+                            const float g = __builtin_amdgcn_fmed3f(__builtin_fmaf(fabsf(q), -0.0625f, v * 0.0625f) * (u - v), 0.0f, 1.0f);
+                            all[m] += g;
+                            dir[m] += u2f(__builtin_amdgcn_bitop3_b32(f2u(g), f2u(xs[j]), 0x80000000u, 0xF8));
+                            // sign bit of 0 - g: set where g > 0; eight elements shift it into the nibbles' top bits
+                            uint32_t& b = took[m][k >= 8];
+                            b = __builtin_amdgcn_bitop3_b32(b >> 4, f2u(0.0f - g), 0x80000000u, 0xF8);
+                        }
+                    }
+                }
+                float gain[2 * NM], total = 0.0f;
+#pragma unroll
+                for (int m = 0; m < NM; ++m) {
+#pragma unroll
+                    for (int off = 1; off < G; off <<= 1) { all[m] += __shfl_xor(all[m], off); dir[m] += __shfl_xor(dir[m], off); }
+                    gain[m] = 0.5f * (all[m] + dir[m]);                       // metadata order: +sv0, (+sv1,) -sv0, (-sv1)
+                    gain[NM + m] = 0.5f * (all[m] - dir[m]);
+                    total += all[m];
+                }
+                float first = gain[0], second = -1.0f;
+#pragma unroll
+                for (int c = 1; c < 2 * NM; ++c) {
+                    const bool up = gain[c] > first;
+                    second = fmaxf(second, up ? first : gain[c]);
+                    meta = up ? (uint32_t)c : meta;
+                    first = up ? gain[c] : first;
+                }
+                // (the absolute term covers the rounding of the fp64 sums themselves)
+                decided = total == 0.0f || first - second > total * ((16.0f * G + 8.0f) * 0x1p-23f) + 1e-9f;
+                const bool one = NM == 2 && (meta & 1u) != 0;
+                const uint32_t mlo = one ? took[NM - 1][0] : took[0][0], mhi = one ? took[NM - 1][1] : took[0][1];
+                const uint32_t flip = meta >= (uint32_t)NM ? 0u : 0xFFFFFFFFu;  // + candidates: elements with a clear sign bit
+                tlo = mlo & (lo ^ flip);
+                thi = mhi & (hi ^ flip);
+            }
+            if (!decided) {
+                uint32_t bits;
+                encode_literal<FMT, G>(xv, den, sv0, sv1, lo, hi, meta, bits);
+                // bit k of a byte-wide mask to bit 4 k + 3
+                auto spread = [](uint32_t b) {
+                    b = (b | (b << 12)) & 0x000F000Fu;
+                    b = (b | (b << 6)) & 0x03030303u;
+                    return ((b | (b << 3)) & 0x11111111u) << 3;
+                };
+                tlo = spread(bits & 0xFFu);
+                thi = spread((bits >> 8) & 0xFFu);
+            }
+            // Eq. 5 on the packed nibbles: zero keeps code 0x0 whatever its sign, taken elements get the remapped code 0x8
+            auto finish = [](uint32_t w, uint32_t taken) {
+                const uint32_t nz = (w & 0x77777777u) + 0x77777777u;              // bit 3: magnitude not zero
+                w &= nz | 0x77777777u;                                            // -0 -> +0
+                return (w & ~(taken - (taken >> 3))) | taken;
+            };
+            lo = finish(lo, tlo);
+            hi = finish(hi, thi);
+        }
+        *reinterpret_cast<uint2*>(codes + gid * 8) = make_uint2(lo, hi);
+        if ((gid & (G - 1)) == 0) {                                           // (a row holds whole blocks)
+            if (FMT == 2) reinterpret_cast<uint16_t*>(scales)[gid / G] = (uint16_t)((meta << 14) | sc);
+            else scales[gid / G] = (uint8_t)((meta << (FMT == 0 ? 6 : 7)) | sc);
+        }
     }
 }
 
 // ---------------------------------------------------------------- host launchers
+constexpr int64_t kEncodeBlocks = 4096;    // workgroups of the encoder (1024 .. one run per thread: within 4 % of each other)
 template <typename T, int FMT>
 static void launch_encode(int lb, unsigned grid, unsigned threads, hipStream_t st, const T* x, int64_t rows,
                           int64_t cols, int64_t ld, SvConfig cfg, const uint32_t* ws, float* tensor_scale, int given,
                           uint8_t* codes, uint8_t* scales)
 {
-#define RAZER_ENC(G) launch(encode_kernel<T, FMT, G>, grid, threads, 0, st, x, rows, cols, ld, cfg, ws, tensor_scale, given, codes, scales)
+#define RAZER_ENC(G) launch(encode_kernel<T, FMT, G>, grid, threads, 0, st, x, rows, cols, ld, cfg.sv0, cfg.sv1, ws, tensor_scale, given, codes, scales)
     switch (lb) {
         case 4: RAZER_ENC(1); break;
         case 5: RAZER_ENC(2); break;
@@ -288,10 +402,10 @@ static hipError_t launch_quantize_t(int fmt, SvConfig cfg, const T* x, int64_t r
         launch(absmax_kernel<T>, (unsigned)blocks, 256, 0, st, x, rows, cols, ld, ws);
     }
     int64_t nblk = rows * (cols / kBlock);
-    unsigned grid = (unsigned)((nblk + 255) / 256);
+    unsigned grid = (unsigned)((nblk + 255) / 256 < kEncodeBlocks ? (nblk + 255) / 256 : kEncodeBlocks);
     if (fmt == 0) launch_encode<T, 0>(cfg.lb, grid, 256, st, x, rows, cols, ld, cfg, ws, tensor_scale, given, codes, scales);
     else if (fmt == 1) launch_encode<T, 1>(cfg.lb, grid, 256, st, x, rows, cols, ld, cfg, ws, tensor_scale, given, codes, scales);
-    else launch(encode_kernel<T, 2, 8>, grid, 256, 0, st, x, rows, cols, ld, cfg, ws, tensor_scale, given, codes, scales);
+    else launch(encode_kernel<T, 2, 8>, grid, 256, 0, st, x, rows, cols, ld, cfg.sv0, cfg.sv1, ws, tensor_scale, given, codes, scales);
     return hipGetLastError();
 }
 
