@@ -144,15 +144,19 @@ __device__ __forceinline__ float wave_sum_to_lane63(float v)
 // A 16-bit lane that is exactly 0 is therefore a special-value slot.  The
 // callers undo the global negation in their final scale.
 
-// Replace all-zero 16-bit halves of d by the matching half of patch.
-__device__ __forceinline__ uint32_t patch_zero_halves(uint32_t d, uint32_t patch)
+// 1 in each 16-bit half of d that is all-zero, else 0
+__device__ __forceinline__ uint32_t zero_flags(uint32_t d)
 {
-    v2us dv = __builtin_bit_cast(v2us, d);
     v2us one = {1, 1};
-    v2us flag = __builtin_elementwise_sub_sat(one, dv);          // 1 where the half is 0
-    v2us pv = __builtin_bit_cast(v2us, patch);
-    v2us r = flag * pv + dv;
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(one, __builtin_bit_cast(v2us, d)));
+}
+// d with the matching half of patch added where the flag is 1
+__device__ __forceinline__ uint32_t add_patch(uint32_t flag, uint32_t patch, uint32_t d)
+{
+    v2us r = __builtin_bit_cast(v2us, flag) * __builtin_bit_cast(v2us, patch) + __builtin_bit_cast(v2us, d);
     return __builtin_bit_cast(uint32_t, r);
 }
+// Replace all-zero 16-bit halves of d by the matching half of patch.
+__device__ __forceinline__ uint32_t patch_zero_halves(uint32_t d, uint32_t patch) { return add_patch(zero_flags(d), patch, d); }
 
 }  // namespace razer

@@ -127,8 +127,8 @@ __device__ __forceinline__ void store_tile(const v16f (&acc)[TN][TM], const floa
 #pragma unroll
                     for (int e = 0; e < 2; ++e) {
                         const int v = 4 * (2 * gp + h) + 2 * e;
-                        pk[h][e] = (uint32_t)f32_to_bf16_rne(acc[i][j][v] * scale) |
-                                   ((uint32_t)f32_to_bf16_rne(acc[i][j][v + 1] * scale) << 16);
+                        const v2f t = {acc[i][j][v] * scale, acc[i][j][v + 1] * scale};
+                        pk[h][e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(t, v2bf));   // round to nearest even
                     }
                 uint32_t o[4];
 #pragma unroll
@@ -149,6 +149,7 @@ __device__ __forceinline__ void store_tile(const v16f (&acc)[TN][TM], const floa
                     }
                 }
             }
+            if constexpr (TN * TM > 8) __builtin_amdgcn_sched_barrier(0);   // (256 live accumulators: no room to overlap the blocks)
         }
 }
 
@@ -1104,6 +1105,434 @@ __global__ __launch_bounds__(64 * NW, (rb_waves_per_simd<NW, KG, MT>())) void ge
                                     kt_per_slice, lb);
 }
 
+// ---------------------------------------------------------------------------------------------
+// 256 x 256 tiles for problems with many of them: the register-decode kernel above with 64 weight rows per wave, so
+// that every fragment read from LDS feeds two MFMAs (half the LDS reads per MFMA; 256 accumulator registers, one wave
+// per SIMD, three stages).  With nothing else to run while the wave waits, the order of its instructions is the
+// performance: see compute.  What bounds it: instruction issue -- 365 operations besides the 64 MFMAs of a K-tile, at
+// about 5 clocks each when a wave has its SIMD to itself.  The straightforward order (both MFMAs of a slice together, a
+// code pair's six operations in a row) took 1.6-1.8 us per K-tile, this one 1.3.  Against 32 rows per wave:
+// 4096 x 11008 x 4096 379 -> 338 us, 4096 x 8192 x 28672 1768 -> 1613 us.
+template <bool GB>
+__device__ __forceinline__ void gemm_wide_body(
+    const uint8_t* __restrict__ w_codes, const uint8_t* __restrict__ w_scales, const float* __restrict__ w_ts,
+    float sv0, float sv1, int64_t n, int64_t k, const uint16_t* __restrict__ a, int64_t m,
+    uint16_t* __restrict__ y, int64_t ld_y, int tile_m, int tile_n, int lb)
+{
+    constexpr int NW = 4, S = 3, MT = 8, NR = 2;        // waves, stages, 32-row activation groups, 32-row weight blocks per wave
+    constexpr int NT = 64 * NW, BM = 32 * MT, BN = 32 * NW * NR;
+    constexpr int NU_A = BM * 8 / NT;                   // 1-KiB activation copies per wave and K-tile
+    constexpr int L = NU_A + 2 * NR;                    // copy instructions per wave and K-tile
+    constexpr int A_STAGE = BM * 128, B_CODES = NW * NR * 1024, B_STAGE = NW * NR * 1280;
+
+    extern __shared__ __align__(16) uint8_t smem[];
+    uint8_t* As = smem;                                 // S stages x 256 rows x 128 B
+    uint8_t* Bs = smem + S * A_STAGE;                   // S stages x NW NR x (1 KiB of codes + 256 B of scale entries)
+    uint2* wlut = reinterpret_cast<uint2*>(smem + S * (A_STAGE + B_STAGE));
+
+    // the wave index is uniform: as a scalar it keeps the LDS destinations of the copies (M0) and the
+    // base addresses below on the scalar unit
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 31, h = lane >> 5;
+    const int64_t m0 = (int64_t)tile_m * BM, n0 = (int64_t)tile_n * BN;
+    const int KT = (int)((k + kBK - 1) / kBK);
+    const int last = KT - 1;
+    const int64_t scale_ld = GB ? (k >> lb) : (k / 16);
+    const uint32_t s_lane = GB ? ((32u * h) >> lb) : 2u * h;          // this lane's byte inside a K-tile's scale bytes
+    // this lane's weight row of each block as a uniform base (first row of the block, advanced per K-tile on the
+    // scalar unit) plus a 32-bit lane offset that never changes: a full K-tile's copies need no vector address
+    // arithmetic at all.  Rows past N re-read the last row, never stored.
+    const uint8_t* cfirst[NR];
+    const uint8_t* sfirst[NR];
+    uint32_t c_off[NR], s_off[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        const int64_t f = n0 + 32 * (NR * wave + i), wrow_first = f < n ? f : n - 1;
+        const int64_t wrow = f + r < n ? f + r : n - 1;
+        cfirst[i] = w_codes + wrow_first * (k / 2);
+        sfirst[i] = w_scales + wrow_first * scale_ld;
+        c_off[i] = (uint32_t)(wrow - wrow_first) * (uint32_t)(k / 2) + 16u * h;
+        s_off[i] = (uint32_t)(wrow - wrow_first) * (uint32_t)scale_ld + s_lane;
+    }
+
+    // Activation copy i of this wave fills LDS rows 8 (wave NU_A + i) .. + 7 of a stage: lane l writes
+    // physical chunk l % 8 of row 8 (..) + l / 8, which must hold logical chunk (l % 8) ^ swizzle(row).
+    // Rows past M re-read the last row; byte offsets from the tile's first row fit 32 bits.
+    const uint8_t* abase = reinterpret_cast<const uint8_t*>(a + m0 * k);
+    const uint32_t rows_here = (uint32_t)((m - m0 < BM) ? m - m0 : BM);
+    const uint32_t row_bytes = (uint32_t)k * 2u;
+    uint32_t a_src[NU_A];                               // byte offset of (row, k = 0) + 16 * logical chunk
+    uint32_t a_chunk[NU_A];
+#pragma unroll
+    for (int i = 0; i < NU_A; ++i) {
+        const uint32_t row = 8u * (wave * NU_A + i) + (lane >> 3);
+        const uint32_t c = (lane & 7u) ^ ((row >> 1) & 7u);
+        a_chunk[i] = c;
+        a_src[i] = (row < rows_here ? row : rows_here - 1) * row_bytes + c * 16u;
+    }
+    // all copies of K-tile kt into stage st (kt already clamped to the last tile by the caller)
+    auto issue = [&](int kt, int st) {
+        if ((int64_t)(kt + 1) * kBK <= k) {             // a full K-tile (uniform): scalar base + constant lane offsets
+            const uint8_t* ab = abase + (size_t)kt * (kBK * 2);
+#pragma unroll
+            for (int i = 0; i < NU_A; ++i)
+                __builtin_amdgcn_global_load_lds(
+                    (const __attribute__((address_space(1))) void*)(ab + a_src[i]),
+                    (__attribute__((address_space(3))) void*)(As + st * A_STAGE + (wave * NU_A + i) * 1024), 16, 0, 0);
+#pragma unroll
+            for (int i = 0; i < NR; ++i) {
+                uint8_t* bc = Bs + st * B_STAGE + (wave * NR + i) * 1024;
+                uint8_t* bs = Bs + st * B_STAGE + B_CODES + (wave * NR + i) * 256;
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(cfirst[i] + (size_t)kt * 32 + c_off[i]),
+                                                 (__attribute__((address_space(3))) void*)bc, 16, 0, 0);
+                if (GB)
+                    __builtin_amdgcn_global_load_lds(
+                        (const __attribute__((address_space(1))) void*)(sfirst[i] + (((size_t)kt * kBK) >> lb) + s_off[i]),
+                        (__attribute__((address_space(3))) void*)bs, 1, 0, 0);
+                else
+                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(sfirst[i] + (size_t)kt * 4 + s_off[i]),
+                                                     (__attribute__((address_space(3))) void*)bs, 2, 0, 0);
+            }
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < NU_A; ++i) {
+            const uint32_t kk = (uint32_t)kt * kBK + a_chunk[i] * 8u;
+            const uint32_t off = kk < (uint32_t)k ? a_src[i] + (uint32_t)kt * (kBK * 2u) : a_src[i] - a_chunk[i] * 16u;
+            __builtin_amdgcn_global_load_lds(
+                (const __attribute__((address_space(1))) void*)(abase + off),           // past K: any finite data
+                (__attribute__((address_space(3))) void*)(As + st * A_STAGE + (wave * NU_A + i) * 1024), 16, 0, 0);
+        }
+        const int kc = ((int64_t)kt * kBK + 32 * h < k) ? kt : 0;                       // past K: masked where used
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            uint8_t* bc = Bs + st * B_STAGE + (wave * NR + i) * 1024;
+            uint8_t* bs = Bs + st * B_STAGE + B_CODES + (wave * NR + i) * 256;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(cfirst[i] + 32 * (uint32_t)kc + c_off[i]),
+                                             (__attribute__((address_space(3))) void*)bc, 16, 0, 0);
+            if (GB)
+                __builtin_amdgcn_global_load_lds(
+                    (const __attribute__((address_space(1))) void*)(sfirst[i] + (((size_t)kc * kBK) >> lb) + s_off[i]),
+                    (__attribute__((address_space(3))) void*)bs, 1, 0, 0);
+            else
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(sfirst[i] + 4 * (uint32_t)kc + s_off[i]),
+                                                 (__attribute__((address_space(3))) void*)bs, 2, 0, 0);
+        }
+    };
+
+    v16f acc[NR][MT];
+#pragma unroll
+    for (int i = 0; i < NR; ++i)
+#pragma unroll
+        for (int j = 0; j < MT; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+
+    const uint32_t a_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)As;
+    const uint32_t lut_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)wlut;
+    // this lane's own codes / scale bytes inside a B stage
+    const uint32_t bc_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)Bs + wave * NR * 1024 + lane * 16;
+    const uint32_t bs_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)Bs + B_CODES + wave * NR * 256 + lane * 4;
+#define RAZER_LDS_READ128(dst, addr, imm) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(imm))
+#define RAZER_LDS_READ64(dst, addr) asm volatile("ds_read_b64 %0, %1" : "=v"(dst) : "v"(addr))
+#define RAZER_LDS_READ32(dst, addr, imm) asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(imm))
+#define RAZER_LDS_WAIT(n, reg) asm volatile("s_waitcnt lgkmcnt(" #n ")" : "+v"(reg))
+    // LDS byte address of this lane's activation chunk in step j (row r of group 0, stage 0; group mi
+    // adds 4096 mi, stage st adds st * A_STAGE)
+    uint32_t aoff[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) aoff[j] = a_lds + lds_off(r, 4 * h + j);
+    // Weights of the tile about to be computed: sign-flipped codes, LUT entries of its two blocks,
+    // decoded pairs of step 0.
+    uint32_t xw[NR][4], wq0[NR][4];
+    uint2 le0[NR], le1[NR];
+    auto flip_and_mask = [&](int kt, int i, const v4u& c, uint32_t& sc) {
+        // past K: code 0, scale byte 0 -> weight 0
+        const uint32_t msk = (kt < KT && (int64_t)kt * kBK + 32 * h < k) ? 0xFFFFFFFFu : 0u;
+        xw[i][0] = (c.x & msk) ^ kRemapXor;
+        xw[i][1] = (c.y & msk) ^ kRemapXor;
+        xw[i][2] = (c.z & msk) ^ kRemapXor;
+        xw[i][3] = (c.w & msk) ^ kRemapXor;
+        if (GB) sc = (sc & 255u) * 0x101u;              // one scale byte for both halves
+        sc &= msk;
+    };
+
+    auto mfma1 = [&](int i, int mi, const v8bf& w, const v4u& f) {
+        acc[i][mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, __builtin_bit_cast(v8bf, f), acc[i][mi], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    v4u af[2][MT];                                      // af[0] enters compute() holding step 0 of its tile (requested, not yet waited for)
+    // One K-tile.  One wave per SIMD: nothing else runs while this wave waits, so every operation
+    // has to fit into the 32 clocks of the MFMA ahead of it and no operation may follow the one it depends on: two
+    // code pairs are decoded side by side over four MFMAs (three operations behind each), the next tile's codes and
+    // table entries are fetched during step 2 so that step 3 decodes the next tile's step 0 like any other, and the
+    // copies (here of tile kt + 2, three stages) go out one per slice during steps 0 and 1.
+    auto cvt_raw = [](int p, uint32_t x) -> v2f {
+        switch (p) {
+            case 0: return __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(x, 1.0f, 0);
+            case 1: return __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(x, 1.0f, 1);
+            case 2: return __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(x, 1.0f, 2);
+            default: return __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(x, 1.0f, 3);
+        }
+    };
+    // copy instruction c (0 .. NU_A - 1: activations, then codes and scale entries) of K-tile kt into stage st
+    auto issue_one = [&](int kt, int st, int c) {
+        if (c < NU_A) {
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(abase + (size_t)kt * (kBK * 2) + a_src[c]),
+                                             (__attribute__((address_space(3))) void*)(As + st * A_STAGE + (wave * NU_A + c) * 1024), 16, 0, 0);
+        } else if (c < NU_A + NR) {
+            const int i = c - NU_A;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(cfirst[i] + (size_t)kt * 32 + c_off[i]),
+                                             (__attribute__((address_space(3))) void*)(Bs + st * B_STAGE + (wave * NR + i) * 1024), 16, 0, 0);
+        } else if (c < NU_A + 2 * NR) {
+            const int i = c - NU_A - NR;
+            if (GB)
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(sfirst[i] + (((size_t)kt * kBK) >> lb) + s_off[i]),
+                                                 (__attribute__((address_space(3))) void*)(Bs + st * B_STAGE + B_CODES + (wave * NR + i) * 256), 1, 0, 0);
+            else
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(sfirst[i] + (size_t)kt * 4 + s_off[i]),
+                                                 (__attribute__((address_space(3))) void*)(Bs + st * B_STAGE + B_CODES + (wave * NR + i) * 256), 2, 0, 0);
+        }
+    };
+    // Once only copies of a ragged last tile are left: its second 32 elements do not exist, the lanes that would fetch
+    // them fetch the first ones of the same row again (their weights are masked).
+    auto ragged_offsets = [&]() {
+        if ((k & (kBK - 1)) == 0) return;
+#pragma unroll
+        for (int i = 0; i < NU_A; ++i) a_src[i] -= a_chunk[i] >= 4u ? 64u : 0u;
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            c_off[i] -= 16u * h;
+            s_off[i] -= s_lane;
+        }
+    };
+    auto compute = [&](int kt, int st, int st_next, int st_copy) {
+        const int kc = kt + 2 < last ? kt + 2 : last;
+        if (kt + 2 == last) ragged_offsets();
+        uint32_t wq[2][NR][4];
+#pragma unroll
+        for (int i = 0; i < NR; ++i)
+#pragma unroll
+            for (int p = 0; p < 4; ++p) wq[0][i][p] = wq0[i][p];
+        v4u cn[NR];
+        uint32_t sn[NR];
+        uint2 l0n[NR], l1n[NR];
+        uint32_t x0n[NR];
+        const uint32_t bnext = st_next * B_STAGE;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int cb = j & 1, nb = cb ^ 1;
+            v8bf wf[NR];
+#pragma unroll
+            for (int i = 0; i < NR; ++i) wf[i] = __builtin_bit_cast(v8bf, make_uint4(wq[cb][i][0], wq[cb][i][1], wq[cb][i][2], wq[cb][i][3]));
+            const uint32_t an = aoff[(j + 1) & 3] + (j < 3 ? st : st_next) * A_STAGE;
+            if (j == 2) {
+                // this wave's copies of tile kt + 1 have landed (those of tile kt + 2 are in flight)
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(L) : "memory");
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                // slices 2 q and 2 q + 1; code pairs p0, p0 + 1 of block b for the next step
+                const int b = q / 2, p0 = (2 * q) & 3;
+                const uint32_t x = j < 3 ? xw[b][j + 1] : x0n[b];
+                const uint2 le = j == 0 ? le0[b] : j < 3 ? le1[b] : l0n[b];
+                v2f d0, d1;
+                uint32_t e0, e1, z0, z1;
+                auto part = [&](int i) {
+                    if (i == 0) { d0 = cvt_raw(p0, x); d1 = cvt_raw(p0 + 1, x); d0.x *= u2f(le.x); }
+                    if (i == 1) { d0.y *= u2f(le.x); d1.x *= u2f(le.x); d1.y *= u2f(le.x); }
+                    if (i == 2) {
+                        e0 = __builtin_bit_cast(uint32_t, __builtin_convertvector(d0, v2bf));
+                        e1 = __builtin_bit_cast(uint32_t, __builtin_convertvector(d1, v2bf));
+                        z0 = zero_flags(e0);
+                    }
+                    if (i == 3) {
+                        z1 = zero_flags(e1);
+                        wq[nb][b][p0] = add_patch(z0, le.y, e0);
+                        wq[nb][b][p0 + 1] = add_patch(z1, le.y, e1);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                };
+                // Waits (not tied to the fragments: sched_barrier keeps everything in this order, and a tied wait counts as a
+                // register write that the compiler separates from the MFMA by a no-op).  Steps 0..2: at most the 8 newest
+                // LDS operations are still in flight, this pair's fragments are older; in step 2 also the codes of tile
+                // kt + 1 (q = 1, 4 fragments requested since) and its table entries (q = 3).
+                if (j < 3) {
+                    if (j == 2 && q == 0) {
+#pragma unroll
+                        for (int i = 0; i < NR; ++i) {
+                            RAZER_LDS_READ128(cn[i], bc_lds + bnext, 1024 * i);
+                            RAZER_LDS_READ32(sn[i], bs_lds + bnext, 256 * i);
+                        }
+                    }
+                    RAZER_LDS_READ128(af[nb][2 * q], an, 4096 * (2 * q));
+                    RAZER_LDS_READ128(af[nb][2 * q + 1], an, 4096 * (2 * q + 1));
+                    if (j == 2 && (q & 1)) asm volatile("s_waitcnt lgkmcnt(4)" ::: "memory");
+                    else asm volatile("s_waitcnt lgkmcnt(8)" ::: "memory");
+                } else if (q == 1) {
+                    // every fragment of tile kt is read, and every wave here has seen its copies of tile kt + 1 land: past
+                    // the barrier that tile is complete and tile kt's stage is free
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                    __builtin_amdgcn_s_barrier();
+                    asm volatile("" ::: "memory");
+                    RAZER_LDS_READ128(af[nb][0], an, 4096 * 0);
+                    RAZER_LDS_READ128(af[nb][1], an, 4096 * 1);
+                    RAZER_LDS_READ128(af[nb][2], an, 4096 * 2);
+                } else if (q == 2) {
+                    RAZER_LDS_READ128(af[nb][3], an, 4096 * 3);
+                    RAZER_LDS_READ128(af[nb][4], an, 4096 * 4);
+                    RAZER_LDS_READ128(af[nb][5], an, 4096 * 5);
+                } else if (q == 3) {
+                    RAZER_LDS_READ128(af[nb][6], an, 4096 * 6);
+                    RAZER_LDS_READ128(af[nb][7], an, 4096 * 7);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const int mi = 2 * q + u;
+                    mfma1(0, mi, wf[0], af[cb][mi]);
+                    part(2 * u);
+                    mfma1(1, mi, wf[1], af[cb][mi]);
+                    part(2 * u + 1);
+                    if (j < 2) {
+                        issue_one(kc, st_copy, 8 * j + mi);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if (j == 2 && mi == 3) {
+#pragma unroll
+                        for (int i = 0; i < NR; ++i) {
+                            asm volatile("" : "+v"(cn[i]), "+v"(sn[i]));
+                            const uint32_t msk = (kt + 1 < KT && (int64_t)(kt + 1) * kBK + 32 * h < k) ? 0xFFFFFFFFu : 0u;
+                            if (GB) sn[i] = (sn[i] & 255u) * 0x101u;
+                            sn[i] &= msk;
+                            x0n[i] = (cn[i].x & msk) ^ kRemapXor;
+                            RAZER_LDS_READ64(l0n[i], lut_lds + (sn[i] & 255u) * 8u);
+                            RAZER_LDS_READ64(l1n[i], lut_lds + ((sn[i] >> 8) & 255u) * 8u);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if (j == 2 && mi == 7) {
+#pragma unroll
+                        for (int i = 0; i < NR; ++i) asm volatile("" : "+v"(l0n[i]), "+v"(l1n[i]));
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            flip_and_mask(kt + 1, i, cn[i], sn[i]);
+            le0[i] = l0n[i];
+            le1[i] = l1n[i];
+#pragma unroll
+            for (int p = 0; p < 4; ++p) wq0[i][p] = wq[0][i][p];
+        }
+    };
+
+    issue(0, 0);
+    fill_scaled_lut<0>(wlut, sv0, sv1, tid, NT);
+    __syncthreads();                                    // the first tile has landed, LUT ready
+    issue(last < 1 ? last : 1, 1);                      // (a single K-tile repeats itself)
+    {
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            v4u c0;
+            uint32_t s0;
+            RAZER_LDS_READ128(c0, bc_lds, 1024 * i);
+            RAZER_LDS_READ32(s0, bs_lds, 256 * i);
+            RAZER_LDS_WAIT(0, c0);
+            RAZER_LDS_WAIT(0, s0);
+            flip_and_mask(0, i, c0, s0);
+            RAZER_LDS_READ64(le0[i], lut_lds + (s0 & 255u) * 8u);
+            RAZER_LDS_READ64(le1[i], lut_lds + ((s0 >> 8) & 255u) * 8u);
+            RAZER_LDS_WAIT(0, le0[i]);
+            RAZER_LDS_WAIT(0, le1[i]);
+            wq0[i][0] = cvt_scaled_pair<0>(xw[i][0], u2f(le0[i].x), le0[i].y);
+            wq0[i][1] = cvt_scaled_pair<1>(xw[i][0], u2f(le0[i].x), le0[i].y);
+            wq0[i][2] = cvt_scaled_pair<2>(xw[i][0], u2f(le0[i].x), le0[i].y);
+            wq0[i][3] = cvt_scaled_pair<3>(xw[i][0], u2f(le0[i].x), le0[i].y);
+        }
+#pragma unroll
+        for (int mi = 0; mi < MT; ++mi) RAZER_LDS_READ128(af[0][mi], aoff[0], 4096 * mi);
+    }
+    if (last < 2) ragged_offsets();
+    int st = 0;                                         // stage of tile kt; tile kt + 3 follows it into the same stage
+    for (int kt = 0; kt < KT; ++kt) {
+        const int st_next = st == S - 1 ? 0 : st + 1;
+        compute(kt, st, st_next, st == 0 ? S - 1 : st - 1);
+        st = st_next;
+    }
+    // copies and fragment reads requested for tiles past the end: let them finish before the registers
+    // and the stages they target are used for anything else
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+#undef RAZER_LDS_READ128
+#undef RAZER_LDS_READ64
+#undef RAZER_LDS_READ32
+#undef RAZER_LDS_WAIT
+    // (the lane number is counted again: no register is free to keep it through the loop)
+    store_tile<MT, NR, false>(acc, w_ts, nullptr, m0, n0 + 32 * NR * wave, m, n, y, ld_y,
+                              (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)));
+}
+
+constexpr size_t kWideLds = 3 * (256 * 128 + 8 * 1280) + 256 * sizeof(uint2);
+
+template <bool GB>
+__global__ __launch_bounds__(256, 1) void gemm_wide_kernel(
+    const uint8_t* __restrict__ w_codes, const uint8_t* __restrict__ w_scales, const float* __restrict__ w_ts,
+    float sv0, float sv1, int64_t n, int64_t k, const uint16_t* __restrict__ a, int64_t m,
+    uint16_t* __restrict__ y, int64_t ld_y, int tiles_m, int lb)
+{
+    gemm_wide_body<GB>(w_codes, w_scales, w_ts, sv0, sv1, n, k, a, m, y, ld_y, (int)(blockIdx.x % tiles_m),
+                       (int)(blockIdx.x / tiles_m), lb);
+}
+
+// The grouped form, as gemm_rb_grouped_kernel.
+template <bool GB>
+__global__ __launch_bounds__(256, 1) void gemm_wide_grouped_kernel(
+    const uint8_t* c0, const uint8_t* c1, const uint8_t* c2, const uint8_t* c3,
+    const uint8_t* s0, const uint8_t* s1, const uint8_t* s2, const uint8_t* s3,
+    const float* f0, const float* f1, const float* f2, const float* f3,
+    uint16_t* y0, uint16_t* y1, uint16_t* y2, uint16_t* y3,
+    int64_t n0, int64_t n1, int64_t n2, int64_t n3,
+    int64_t l0, int64_t l1, int64_t l2, int64_t l3,
+    int t1, int t2, int t3,
+    float sv0, float sv1, int64_t k, const uint16_t* __restrict__ a, int64_t m, int tiles_m, int lb)
+{
+    const int tile_m = (int)(blockIdx.x % tiles_m), t = (int)(blockIdx.x / tiles_m);
+    const uint8_t* codes = c0; const uint8_t* scales = s0; const float* ts = f0; uint16_t* y = y0;
+    int64_t n = n0, ld = l0;
+    int first = 0;
+    if (t >= t1) { codes = c1; scales = s1; ts = f1; y = y1; n = n1; ld = l1; first = t1; }
+    if (t >= t2) { codes = c2; scales = s2; ts = f2; y = y2; n = n2; ld = l2; first = t2; }
+    if (t >= t3) { codes = c3; scales = s3; ts = f3; y = y3; n = n3; ld = l3; first = t3; }
+    gemm_wide_body<GB>(codes, scales, ts, sv0, sv1, n, k, a, m, y, ld, tile_m, t - first, lb);
+}
+
+template <bool GB>
+static hipError_t launch_wide(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, hipStream_t st)
+{
+    const int tiles_m = (int)((m + 255) / 256);
+    GemvProblem q[4];
+    int t[5] = {0, 0, 0, 0, 0};
+    for (int i = 0; i < 4; ++i) {
+        q[i] = p[i < count ? i : count - 1];
+        t[i + 1] = t[i] + (i < count ? (int)((q[i].n + 255) / 256) : 0);
+    }
+    const dim3 grid((unsigned)(tiles_m * t[4]));
+    if (count == 1) {
+        auto kern = gemm_wide_kernel<GB>;
+        RAZER_RAISE_LDS_LIMIT(kern, kWideLds);
+        launch(kern, grid, dim3(256), kWideLds, st, q[0].codes, q[0].scales, q[0].ts, cfg.sv0, cfg.sv1, q[0].n, k, a, m, q[0].y, q[0].ld_y, tiles_m, cfg.lb);
+    } else {
+        auto kern = gemm_wide_grouped_kernel<GB>;
+        RAZER_RAISE_LDS_LIMIT(kern, kWideLds);
+        launch(kern, grid, dim3(256), kWideLds, st, q[0].codes, q[1].codes, q[2].codes, q[3].codes, q[0].scales, q[1].scales, q[2].scales, q[3].scales, q[0].ts,
+            q[1].ts, q[2].ts, q[3].ts, q[0].y, q[1].y, q[2].y, q[3].y, q[0].n, q[1].n, q[2].n, q[3].n, q[0].ld_y,
+            q[1].ld_y, q[2].ld_y, q[3].ld_y, t[1], t[2], t[3], cfg.sv0, cfg.sv1, k, a, m, tiles_m, cfg.lb);
+    }
+    return hipGetLastError();
+}
+
 // split > 1 (KG == 1 only, workspace of slices * m * n floats): K in slices of whole K-tiles, summed by
 // launch_slice_reduce.
 template <int NW, int S, int KG = 1, int MT = 8, bool GB = false>
@@ -1154,7 +1583,7 @@ static hipError_t launch_cfg(const uint8_t* w_codes, const uint8_t* w_scales, co
 
 // Which kernel and how many K-slices.  Tiles: 0 = 32x256, 1 = 64x256, 2 = 128x128 (one stage pair, all
 // waves alike), 3 = 256x256 and 4 = 256x128 (two wave groups out of phase), 5 / 6 = register-decode
-// kernel with 256x256 / 256x128 tiles, 7 = register-decode kernel, 256x128 tiles, K halved inside
+// kernels with 256x256 tiles (64 weight rows per wave) / 256x128 tiles, 7 = register-decode kernel, 256x128 tiles, K halved inside
 // the workgroup, 8 / 9 = register-decode kernel with 64x128 / 128x128 tiles and K-slices (33..64 /
 // 65..128 activation rows: measured 1.3-2.1x faster than tiles 1 / 2 on 4096^2, 11008 x 4096 and
 // 4096 x 11008).  A K-tile costs about 1 us of latency however small the tile, so
@@ -1177,6 +1606,19 @@ static int rb_split(int64_t tiles, int64_t kt_all, int64_t m = 0, int64_t rows =
     if (split > kt_all / 8) split = kt_all / 8;
     return split >= 2 ? (int)split : 1;
 }
+// 256-row activation tiles: whether the register-decode kernel with 64 weight rows per wave (256 x 256 tiles, one
+// workgroup per compute unit) beats the one with 32 (256 x 128 tiles, two workgroups).  Per K-tile a full round takes
+// 1.8 against 2.0 us, a 128-wide round that is at most half full only 1.4; a 256-wide tile costs about 3 us more to
+// start and to store.  So: one round of 256-wide tiles where the 128-wide ones need more than one workgroup per unit
+// (2 x 11008 x 4096 at 512 rows 120 -> 101 us, {q,k,v} 3 x 4096 at 1024 rows 128 -> 107), else wherever the last
+// 128-wide round is more than half full or the rounds are many (2 x 11008 at 2048 rows 380 -> 348 us, 8192 x 28672 at
+// 4096 rows 1768 -> 1613; but 2 x 11008 at 1024 rows 202 -> 213, not taken).
+static bool wide_tiles(int64_t t256, int64_t t128, int64_t k)
+{
+    if (k < 2048 || t128 <= 256 || t256 <= 128) return false;
+    const int64_t last = t128 % 512;
+    return t256 <= 256 || last == 0 || last > 256 || t128 >= 1536;
+}
 static GemmPlan gemm_plan(int64_t m, int64_t n, int64_t k, bool register_decode_ok)
 {
     GemmPlan p{0, 1};
@@ -1190,11 +1632,9 @@ static GemmPlan gemm_plan(int64_t m, int64_t n, int64_t k, bool register_decode_
         // 256-row activation tiles so every weight is decoded once per 256 rows
         const int64_t tm = (m + 255) / 256;
         const int64_t t256 = tm * ((n + 255) / 256), t128 = tm * ((n + 127) / 128);
+        if (register_decode_ok && wide_tiles(t256, t128, k)) return GemmPlan{5, 1};
         // enough tiles for two resident waves per SIMD: the kernel that decodes weights in registers
         // (measured 5-28 % faster than the LDS-staged one on the 7B projection shapes from M = 2048)
-        // (256-wide weight tiles from four rounds of workgroups up, or when they fill whole rounds: 4 % over
-        // the 128-wide ones on 4096 x 8192 x 8192)
-        if (register_decode_ok && (t256 >= 1024 || (t256 >= 512 && t256 % 256 == 0))) return GemmPlan{5, 1};
         if (register_decode_ok && t128 >= 512) return GemmPlan{6, 1};
         // one round of 256x128 tiles (one workgroup per compute unit): the register-decode kernel with
         // two K groups of four waves keeps two waves on every SIMD (measured 9-10 % over the LDS-staged
@@ -1255,7 +1695,10 @@ static hipError_t launch_gemm_t(const uint8_t* w_codes, const uint8_t* w_scales,
     if constexpr (!AQ) {
         if (p.tile == 8) return launch_rb<4, 2, 1, 2, GB>(w_codes, w_scales, w_ts, wcfg, n, k, a, m, y, ld_y, st, p.split, workspace);
         if (p.tile == 9) return launch_rb<4, 2, 1, 4, GB>(w_codes, w_scales, w_ts, wcfg, n, k, a, m, y, ld_y, st, p.split, workspace);
-        if (p.tile == 5) return launch_rb<8, 2, 1, 8, GB>(w_codes, w_scales, w_ts, wcfg, n, k, a, m, y, ld_y, st);
+        if (p.tile == 5) {
+            const GemvProblem one{w_codes, w_scales, w_ts, n, y, ld_y};
+            return launch_wide<GB>(wcfg, 1, &one, k, a, m, st);
+        }
         if (p.tile == 7) return launch_rb<8, 2, 2, 8, GB>(w_codes, w_scales, w_ts, wcfg, n, k, a, m, y, ld_y, st);
         return launch_rb<4, 2, 1, 8, GB>(w_codes, w_scales, w_ts, wcfg, n, k, a, m, y, ld_y, st);
     }
@@ -1279,7 +1722,7 @@ static int grouped_tile_width(int count, const GemvProblem* p, int64_t m, int64_
         t256 += tm * ((p[i].n + 255) / 256);
         t128 += tm * ((p[i].n + 127) / 128);
     }
-    if (t256 >= 1024 || (t256 >= 512 && t256 % 256 == 0)) return 256;
+    if (wide_tiles(t256, t128, k)) return 256;
     if (t128 >= 512) return 128;
     if (t128 >= 192 && t128 <= 256 && k >= 16 * kBK) return 129;
     return 8;                                           // fewer tiles, or between one and two rounds: K-slices
@@ -1340,7 +1783,7 @@ static hipError_t launch_gemm_grouped_t(SvConfig cfg, int count, const GemvProbl
                                         int64_t m, float* workspace, hipStream_t st)
 {
     const int w = grouped_tile_width(count, p, m, k);
-    if (w == 256) return launch_rb_grouped<8, 2, 1, 8, GB>(cfg, count, p, k, a, m, st);
+    if (w == 256) return launch_wide<GB>(cfg, count, p, k, a, m, st);
     if (w == 128) return launch_rb_grouped<4, 2, 1, 8, GB>(cfg, count, p, k, a, m, st);
     if (w == 129) return launch_rb_grouped<8, 2, 2, 8, GB>(cfg, count, p, k, a, m, st);
     if (w == 2 || w == 4 || w == 8) {

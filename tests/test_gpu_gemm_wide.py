@@ -1,0 +1,34 @@
+"""The 256 x 256 tiles of the register-decode GEMM (64 weight rows per wave, three copy stages) where they end: ragged
+rows, ragged K (a last tile of 32 elements), odd and even numbers of K-tiles, tiles past the matrices of a group, each
+block size -- against the CPU oracle on sampled rows."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2501_04052_amd as razer
+from paper_2501_04052_amd import synth
+from gpu_util import TOL, bf16_bits_to_dev, dev_to_bf16_bits, max_rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("m,ns,k,block", [(300, (16500,), 2048, 16), (257, (16640, 40), 2080, 16), (512, (12000, 5000), 2112, 32),
+                                          (300, (17000,), 2176, 128), (512, (33000,), 2080, 32)])
+def test_wide_tiles(oracle, m, ns, k, block):
+    print("wide tiles m", m, "ns", ns, "k", k, "block", block, flush=True)
+    a = synth.activation(m, k, seed=8100 + m)
+    rows = np.sort(np.random.default_rng(8).choice(m, size=12, replace=False))
+    rows[-1], rows[0] = m - 1, 0
+    rng = np.random.default_rng(81 + k)
+    ws = []
+    for n in ns:
+        wq = (rng.integers(0, 256, size=(n, k // 2), dtype=np.uint8), rng.integers(0, 256, size=(n, k // block), dtype=np.uint8),
+              np.float32(2.0 ** -9))
+        ws.append((wq, razer.RazerTensor.from_host(*wq, razer.WEIGHT, (5.0, 8.0))))
+    a_dev = bf16_bits_to_dev(a)
+    ys = [razer.razer_linear(ws[0][1], a_dev)] if len(ns) == 1 else razer.razer_linear_grouped([w[1] for w in ws], a_dev)
+    torch.cuda.synchronize()
+    for (wq, _), y in zip(ws, ys):
+        cols = np.r_[0:40, 240:272, wq[0].shape[0] - 40:wq[0].shape[0]] if wq[0].shape[0] > 300 else np.arange(wq[0].shape[0])
+        y64, _ = oracle.linear((wq[0][cols], wq[1][cols], wq[2]), a_bf16=a[rows])
+        assert max_rel_err(dev_to_bf16_bits(y)[rows][:, cols], y64) <= TOL
