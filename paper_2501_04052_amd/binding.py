@@ -171,7 +171,9 @@ def razer_probe_mfma_fp4(iters, workgroups, sink):
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # The handle of torch.cuda.current_stream(), asked for each time; building that Stream object took 2.7 of the
+    # 6.7 us the host spent on a prepared call (this: 0.3).
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ptr(t):
@@ -179,13 +181,7 @@ def _ptr(t):
 
 
 def _cfg(fmt, sv, block=16, layout=LAYOUT_CANONICAL):
-    c = _Config()
-    c.format = fmt
-    c.sv[0] = float(sv[0])
-    c.sv[1] = float(sv[1]) if len(sv) > 1 else 0.0
-    c.block = int(block)
-    c.layout = int(layout)
-    return c
+    return _Config(fmt, (float(sv[0]), float(sv[1]) if len(sv) > 1 else 0.0), int(block), int(layout))
 
 
 class RazerTensor:
@@ -197,13 +193,9 @@ class RazerTensor:
         self.layout = int(layout)                      # LAYOUT_INTERLEAVED: codes is the packed buffer, scales None
 
     def c_struct(self):
-        t = _Tensor()
-        t.codes = self.codes.data_ptr()
-        t.scales = None if self.scales is None else self.scales.data_ptr()
-        t.tensor_scale = self.tensor_scale.data_ptr()
-        t.rows, t.cols = self.rows, self.cols
-        t.cfg = _cfg(self.fmt, self.sv, self.block, self.layout)
-        return t
+        return _Tensor(self.codes.data_ptr(), None if self.scales is None else self.scales.data_ptr(),
+                       self.tensor_scale.data_ptr(), self.rows, self.cols,
+                       _cfg(self.fmt, self.sv, self.block, self.layout))
 
     @staticmethod
     def from_host(codes, scales, tensor_scale, fmt, sv, device="cuda"):
