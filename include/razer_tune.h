@@ -18,8 +18,9 @@
  *                           workgroup (4 or 8)
  *   RAZER_TUNE_SMALL_BATCH  5 <= m <= 64 where the small-batch kernel serves the call: p[0] = 2, p[1] = groups of 16
  *                           rows per workgroup (1, 2, 3, 4, 6; above 32 rows at most 4, FP16-scale format 3).
+ *                           A forced shape of any kind also fixes the order of the sum over K (8 waves).
  *                           p[0] = 0 or 1 (5 <= m <= 32) names a shape on record of the kernels this one replaced;
- *                           it selects nothing but the size razer_workspace_bytes reports: p[0] = 0: fp32 K-slices
+ *                           other than that it selects only the size razer_workspace_bytes reports: p[0] = 0: fp32 K-slices
  *                           of p[1] = 4 or 8 steps of 128 elements (p[2] = 1, 2, 4); p[0] = 1 (m <= 16): none
  *                           (p[1] = 1, 2; p[2] = 1, 2, 3, 4, 8; 8 only with p[1] = 2)
  *   RAZER_TUNE_GEMM_SLICES  33 <= m <= 128: p[0] = K-slices of the register-decode kernel (1 .. 16; forced, also

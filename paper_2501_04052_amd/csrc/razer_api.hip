@@ -290,6 +290,8 @@ razer_status razer_linear(const razer_tensor* w, const void* a_bf16, const razer
         const int64_t total = m * n;
         launch(fill_zero_bf16_kernel, (unsigned)((total + 255) / 256), 256, 0, st, (uint16_t*)y_bf16, m, n, ld_y);
         e = hipGetLastError();
+    } else if (!a_q && m <= kGemvDirectMaxM && ring_serves(wsv, 1, &one, k, m)) {
+        e = launch_skinny(wsv, 1, &one, k, (const uint16_t*)a_bf16, m, st);
     } else if (wsv.f16) {
         // FP16-scale format: the GEMV kernels up to 4 activation rows, the K-in-workgroup small-batch kernel up
         // to 64, beyond that the tiled matrix-core kernels; all matrix-core kernels multiply bare FP4 operands
@@ -316,7 +318,7 @@ razer_status razer_linear(const razer_tensor* w, const void* a_bf16, const razer
     } else {
         const size_t need = gemm_workspace_bytes(n, k, m);
         if (need > 0 && (!workspace || workspace_bytes < need || !aligned16(workspace))) return RAZER_ERR_WORKSPACE;
-        if (!a_q && ring_serves(1, &one, k, m))
+        if (!a_q && ring_serves(wsv, 1, &one, k, m))
             e = launch_skinny(wsv, 1, &one, k, (const uint16_t*)a_bf16, m, st);
         else
             e = launch_gemm(wsv, w->codes, w->scales, w->tensor_scale, n, k, (const uint16_t*)a_bf16, asv,
@@ -397,7 +399,7 @@ razer_status razer_linear_grouped(const razer_tensor* const* w, int32_t count, c
     enum { SEQUENCE, GEMV, SKINNY, GEMM } path = SEQUENCE;
     if (one_launch) {
         if (m <= kGemvDirectMaxM) {
-            path = GEMV;                                 // every block size and both weight formats
+            path = ring_serves(sv0, count, p, k, m) ? SKINNY : GEMV;   // every block size and both weight formats
         } else if (sv0.f16 && m > kSkinnyMaxM) {
             // FP16 scale words: no grouped launch of the tiled matrix-core kernels
             path = m <= kRingMaxM && k <= kSkinnyMaxK ? SKINNY : SEQUENCE;
@@ -429,7 +431,7 @@ razer_status razer_linear_grouped(const razer_tensor* const* w, int32_t count, c
         case GEMV: e = launch_gemv_grouped(sv0, count, p, k, (const uint16_t*)a_bf16, m, st); break;
         case SKINNY: e = launch_skinny(sv0, count, p, k, (const uint16_t*)a_bf16, m, st); break;
         case GEMM:
-            if (ring_serves(count, p, k, m)) e = launch_skinny(sv0, count, p, k, (const uint16_t*)a_bf16, m, st);
+            if (ring_serves(sv0, count, p, k, m)) e = launch_skinny(sv0, count, p, k, (const uint16_t*)a_bf16, m, st);
             else e = launch_gemm_grouped(sv0, count, p, k, (const uint16_t*)a_bf16, m, (float*)workspace, st);
             break;
         case SEQUENCE:

@@ -93,11 +93,12 @@ hipError_t launch_gemm(SvConfig wcfg, const uint8_t* w_codes, const uint8_t* w_s
                        const uint8_t* a_scales, const float* a_ts, int64_t m, uint16_t* y, int64_t ld_y,
                        float* workspace, hipStream_t st);
 
-// 5 <= m <= kRingMaxM: decode-once MFMA kernel, one launch for up to 4 matrices sharing K, the activation rows, the
+// 2 <= m <= kRingMaxM: decode-once MFMA kernel, one launch for up to 4 matrices sharing K, the activation rows, the
 // format, the block size and the special values (every n > 0, 0 < k <= kSkinnyMaxK).  No workspace.
 hipError_t launch_skinny(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, hipStream_t st);
-// 33..64 rows of the scale-byte format: whether that kernel or the register-decode GEMM is the faster one.
-bool ring_serves(int count, const GemvProblem* p, int64_t k, int64_t m);
+// 2..4 rows, and 33..64 of the scale-byte format: whether that kernel is faster than the 4x4x4 GEMV / the register-
+// decode GEMM.
+bool ring_serves(SvConfig cfg, int count, const GemvProblem* p, int64_t k, int64_t m);
 
 // Sum of the K-slices of a grouped launch: partial holds matrix i's [nslices][m][n_i] fp32 slices
 // behind those of matrices 0 .. i-1 (every n a positive multiple of 4, y 8-byte aligned, ld_y % 4 == 0).

@@ -1,9 +1,9 @@
-// Linear layer for 5..64 activation rows on gfx950 (small-batch decode, Sec. 4.3 / App. D.2 of arxiv 2501.04052):
+// Linear layer for 5..64 activation rows (long rows: from 2) on gfx950 (small-batch decode, Sec. 4.3 / App. D.2 of arxiv 2501.04052):
 // every packed weight is read from HBM and decoded exactly once, in registers, straight into the operand of
 // v_mfma_f32_16x16x32_bf16 it is used in.
 //
 // Mapping (ring_kernel).  A workgroup owns G groups of 16 weight rows, numbered through all matrices of the launch
-// one after another; its 8 waves take the 128-k steps of K in turn (wave w: steps w, w + 8, ...).  What a step needs
+// one after another; its 8 (or 16) waves take the 128-k steps of K in turn (wave w: steps w, w + 8, ...).  What a step needs
 // -- G x (1 KiB of codes, 64 scale entries) and the step's activation rows -- is copied global -> LDS by the load
 // unit into memory that only this wave reads, so the K loop has no barrier: the wave waits for its own copies, takes
 // the operands into registers, requests its next step into the same place and multiplies while that one is on its
@@ -99,17 +99,29 @@ constexpr uint32_t ring_wave_bytes()
     return slot > part ? slot : part;
 }
 
-template <int NA, int G, bool GB, int SF>
-__global__ __launch_bounds__(64 * kRingWaves) void ring_kernel(
-    const uint8_t* c0, const uint8_t* c1, const uint8_t* c2, const uint8_t* c3,
-    const uint8_t* s0, const uint8_t* s1, const uint8_t* s2, const uint8_t* s3,
-    const float* f0, const float* f1, const float* f2, const float* f3,
-    uint16_t* y0, uint16_t* y1, uint16_t* y2, uint16_t* y3,
-    int64_t n0, int64_t n1, int64_t n2, int64_t n3,
-    int64_t l0, int64_t l1, int64_t l2, int64_t l3,
-    uint32_t e1, uint32_t e2, uint32_t e3, uint32_t e4,
-    float sv0, float sv1, int64_t k, const uint16_t* __restrict__ a, int64_t m, int lb)
+// One argument, not the 33 values it holds: the runtime copies arguments one by one (0.5 us of host time per launch).
+// e: first group of 16 rows behind each matrix; matrices past the last one repeat it.
+struct RingArgs {
+    const uint8_t* codes[4];
+    const uint8_t* scales[4];
+    const float* ts[4];
+    uint16_t* y[4];
+    int64_t n[4], ld_y[4];
+    uint32_t e[4];
+    float sv0, sv1;
+    int64_t k, m;
+    const uint16_t* a;
+    int lb;
+};
+
+template <int NA, int G, bool GB, int SF, int W, bool IL = false>
+__global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
 {
+    const uint32_t e1 = arg.e[0], e2 = arg.e[1], e3 = arg.e[2], e4 = arg.e[3];
+    const float sv0 = arg.sv0, sv1 = arg.sv1;
+    const int64_t k = arg.k, m = arg.m;
+    const int lb = arg.lb;
+    const uint16_t* a = arg.a;
     constexpr int NB = (NA + 3) / 4;
     constexpr uint32_t WAVE = ring_wave_bytes<NA, G>();
     __shared__ uint4 lut[SF ? 1 : 256];
@@ -118,7 +130,9 @@ __global__ __launch_bounds__(64 * kRingWaves) void ring_kernel(
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t r = lane & 15u, g = lane >> 4;
     const uint32_t kk32 = (uint32_t)k;
-    const uint32_t code_ld = (uint32_t)(k >> 1), scale_ld = SF ? (uint32_t)(k >> 7) * 2u : (uint32_t)(k >> (GB ? lb : 4));
+    static_assert(!IL || (!GB && !SF), "interleaved layout: 16-element blocks, scale bytes");
+    const uint32_t code_ld = IL ? (uint32_t)il_row_bytes(k) : (uint32_t)(k >> 1);
+    const uint32_t scale_ld = IL ? code_ld : SF ? (uint32_t)(k >> 7) * 2u : (uint32_t)(k >> (GB ? lb : 4));
     const uint32_t nsteps = (kk32 + 127u) >> 7;
 
     // copy lanes: codes and scale bits -- row lane / 4, 16-byte chunk / 32-element run; activations -- row 4 i + lane / 16
@@ -130,17 +144,17 @@ __global__ __launch_bounds__(64 * kRingWaves) void ring_kernel(
     for (int gi = 0; gi < G; ++gi) {
         uint32_t q = blockIdx.x * G + gi;
         q = q < e4 ? q : e4 - 1u;                                     // groups past the last one re-read it, never stored
-        const uint8_t* codes = c0; const uint8_t* scales = s0;
-        int64_t n = n0;
+        const uint8_t* codes = arg.codes[0]; const uint8_t* scales = arg.scales[0];
+        int64_t n = arg.n[0];
         uint32_t first = 0;
-        if (q >= e1) { codes = c1; scales = s1; n = n1; first = e1; }
-        if (q >= e2) { codes = c2; scales = s2; n = n2; first = e2; }
-        if (q >= e3) { codes = c3; scales = s3; n = n3; first = e3; }
+        if (q >= e1) { codes = arg.codes[1]; scales = arg.scales[1]; n = arg.n[1]; first = e1; }
+        if (q >= e2) { codes = arg.codes[2]; scales = arg.scales[2]; n = arg.n[2]; first = e2; }
+        if (q >= e3) { codes = arg.codes[3]; scales = arg.scales[3]; n = arg.n[3]; first = e3; }
         const int64_t row0 = (int64_t)(q - first) * 16;
         const uint32_t left = (uint32_t)((n - 1 - row0 < 15) ? n - 1 - row0 : 15);
         const uint32_t dl = wr < left ? wr : left;                    // rows past N re-read the last row
         cbase[gi] = codes + row0 * (int64_t)code_ld;
-        sbase[gi] = scales + row0 * (int64_t)scale_ld;
+        sbase[gi] = (IL ? codes + 1024 : scales) + row0 * (int64_t)scale_ld;
         crow[gi] = dl * code_ld;
         srow[gi] = dl * scale_ld;
     }
@@ -159,9 +173,12 @@ __global__ __launch_bounds__(64 * kRingWaves) void ring_kernel(
     auto issue = [&](uint32_t step) {
         const bool full = 128u * step + 128u <= kk32;                 // uniform
         const uint32_t left = kk32 - 128u * step;                     // elements of this step inside K (>= 32)
+        // byte of this step's codes / scale entries inside a row (interleaved layout: 16 steps per run of 2048 elements)
+        const size_t cstep = IL ? (size_t)((step >> 4) * kIlRun + (step & 15u) * 64u) : (size_t)step * 64u;
+        const size_t sstep = IL ? (size_t)((step >> 4) * kIlRun + (step & 15u) * 8u) : (size_t)step * 8u;
         const uint32_t wcc = full || wc * 32u < left ? wc : 0u, wpp = full || wp * 32u < left ? wp : 0u;
 #pragma unroll
-        for (int gi = 0; gi < G; ++gi) RAZER_COPY(cbase[gi] + (size_t)step * 64u, crow[gi] + wcc * 16u, ring + NA * 1024 + gi * 1024, 16);
+        for (int gi = 0; gi < G; ++gi) RAZER_COPY(cbase[gi] + cstep, crow[gi] + wcc * 16u, ring + NA * 1024 + gi * 1024, 16);
 #pragma unroll
         for (int gi = 0; gi < G; ++gi) {
             if constexpr (SF != 0)
@@ -169,7 +186,7 @@ __global__ __launch_bounds__(64 * kRingWaves) void ring_kernel(
             else if constexpr (GB)
                 RAZER_COPY(sbase[gi], srow[gi] + ((128u * step + 32u * wpp) >> lb), ring + (NA + G) * 1024 + gi * 256, 1);
             else
-                RAZER_COPY(sbase[gi] + (size_t)step * 8u, srow[gi] + wpp * 2u, ring + (NA + G) * 1024 + gi * 256, 2);
+                RAZER_COPY(sbase[gi] + sstep, srow[gi] + wpp * 2u, ring + (NA + G) * 1024 + gi * 256, 2);
         }
 #pragma unroll
         for (int i = 0; i < NA; ++i)
@@ -302,12 +319,12 @@ __global__ __launch_bounds__(64 * kRingWaves) void ring_kernel(
     for (uint32_t u = wave; u < (uint32_t)(G * NB); u += nwaves) {
         const uint32_t gi = u / NB, b = u % NB, q = blockIdx.x * G + gi;
         if (q >= e4) break;
-        const float* ts = f0; uint16_t* y = y0;
-        int64_t n = n0, ld_y = l0;
+        const float* ts = arg.ts[0]; uint16_t* y = arg.y[0];
+        int64_t n = arg.n[0], ld_y = arg.ld_y[0];
         uint32_t first = 0;
-        if (q >= e1) { ts = f1; y = y1; n = n1; ld_y = l1; first = e1; }
-        if (q >= e2) { ts = f2; y = y2; n = n2; ld_y = l2; first = e2; }
-        if (q >= e3) { ts = f3; y = y3; n = n3; ld_y = l3; first = e3; }
+        if (q >= e1) { ts = arg.ts[1]; y = arg.y[1]; n = arg.n[1]; ld_y = arg.ld_y[1]; first = e1; }
+        if (q >= e2) { ts = arg.ts[2]; y = arg.y[2]; n = arg.n[2]; ld_y = arg.ld_y[2]; first = e2; }
+        if (q >= e3) { ts = arg.ts[3]; y = arg.y[3]; n = arg.n[3]; ld_y = arg.ld_y[3]; first = e3; }
         const int64_t row0 = (int64_t)(q - first) * 16;
         const float sc = SF ? -*ts : *ts;                                 // (the bare decode carries a negation)
         float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -345,26 +362,49 @@ __global__ __launch_bounds__(64 * kRingWaves) void ring_kernel(
 }
 
 
-template <int NA, int G, bool GB, int SF>
-static hipError_t launch_ring_t(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, hipStream_t st)
+template <int NA, int G, bool GB, int SF, bool IL, int W>
+static hipError_t launch_ring_w(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, hipStream_t st)
 {
-    GemvProblem q[4];
-    uint32_t e[5] = {0, 0, 0, 0, 0};
+    RingArgs arg;
+    uint32_t groups = 0;
     for (int i = 0; i < 4; ++i) {
-        q[i] = p[i < count ? i : count - 1];
-        e[i + 1] = e[i] + (i < count ? (uint32_t)((q[i].n + 15) / 16) : 0u);
+        const GemvProblem& q = p[i < count ? i : count - 1];
+        arg.codes[i] = q.codes;
+        arg.scales[i] = q.scales;
+        arg.ts[i] = q.ts;
+        arg.y[i] = q.y;
+        arg.n[i] = q.n;
+        arg.ld_y[i] = q.ld_y;
+        if (i < count) groups += (uint32_t)((q.n + 15) / 16);
+        arg.e[i] = groups;
     }
-    // 8 waves where their LDS fits a compute unit (64 activation rows and more than 2 groups: 7)
+    arg.sv0 = cfg.sv0;
+    arg.sv1 = cfg.sv1;
+    arg.k = k;
+    arg.m = m;
+    arg.a = a;
+    arg.lb = cfg.lb;
+    // as many of the W waves as their LDS leaves room for (64 activation rows and more than 2 groups: 7 of 8)
     constexpr uint32_t fit = (kLdsBytes - kRingTableBytes) / ring_wave_bytes<NA, G>();
-    constexpr int most = fit < (uint32_t)kRingWaves ? (int)fit : kRingWaves;
+    constexpr int most = fit < (uint32_t)W ? (int)fit : W;
     static_assert(most >= 4, "LDS");
     const int64_t nsteps = (k + 127) / 128;
     const int waves = nsteps < most ? (int)nsteps : most;
-    launch(ring_kernel<NA, G, GB, SF>, (e[4] + G - 1) / G, 64 * waves, (size_t)waves * ring_wave_bytes<NA, G>(), st,
-           q[0].codes, q[1].codes, q[2].codes, q[3].codes, q[0].scales, q[1].scales, q[2].scales, q[3].scales, q[0].ts,
-           q[1].ts, q[2].ts, q[3].ts, q[0].y, q[1].y, q[2].y, q[3].y, q[0].n, q[1].n, q[2].n, q[3].n, q[0].ld_y,
-           q[1].ld_y, q[2].ld_y, q[3].ld_y, e[1], e[2], e[3], e[4], cfg.sv0, cfg.sv1, k, a, m, cfg.lb);
+    launch(ring_kernel<NA, G, GB, SF, W, IL>, (groups + G - 1) / G, 64 * waves, (size_t)waves * ring_wave_bytes<NA, G>(), st, arg);
     return hipGetLastError();
+}
+
+// 8 waves; 16 for one group of rows and at most 8 activation rows: such a launch has at most one workgroup per compute
+// unit and little data under way, so twice the waves pay (4096 x 11008 at 4 rows 11.0 -> 8.8 us, at 8 rows 11.1 -> 9.8;
+// at 16 rows 12.2 -> 12.7, and with two groups or more 0-15 % slower).  The number of waves is the order of the sum over
+// K; a forced shape keeps 8, so that it stands for one order whatever the number of rows.
+template <int NA, int G, bool GB, int SF, bool IL = false>
+static hipError_t launch_ring_t(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, bool forced, hipStream_t st)
+{
+    if constexpr (G == 1 && NA <= 2) {
+        if (!forced) return launch_ring_w<NA, G, GB, SF, IL, 16>(cfg, count, p, k, a, m, st);
+    }
+    return launch_ring_w<NA, G, GB, SF, IL, kRingWaves>(cfg, count, p, k, a, m, st);
 }
 
 // Groups of 16 rows per workgroup.  The busiest of the 256 compute units holds ceil(workgroups / 256) workgroups of G
@@ -398,12 +438,13 @@ static hipError_t launch_ring(SvConfig cfg, int count, const GemvProblem* p, int
     int64_t rows = 0;
     for (int i = 0; i < count; ++i) rows += p[i].n;
     const TuneShape t = tuned_shape(kTuneSmallBatch, m, rows, k);
-    if (t.source && t.p[0] == 2 && (t.p[1] == 1 || t.p[1] == 2 || t.p[1] == 3 || (t.p[1] == 4 && !(m > 32 && cfg.f16)) || (t.p[1] == 6 && m <= 32))) g = t.p[1];
+    if (t.source && m > kGemvDirectMaxM && t.p[0] == 2 && (t.p[1] == 1 || t.p[1] == 2 || t.p[1] == 3 || (t.p[1] == 4 && !(m > 32 && cfg.f16)) || (t.p[1] == 6 && m <= 32))) g = t.p[1];
+    const bool forced = t.source == 1;
 #define RAZER_RING(NA, G)                                                                  \
     do {                                                                                   \
-        if (cfg.f16) return launch_ring_t<NA, G, false, 1>(cfg, count, p, k, a, m, st);    \
-        if (cfg.lb == 4) return launch_ring_t<NA, G, false, 0>(cfg, count, p, k, a, m, st); \
-        return launch_ring_t<NA, G, true, 0>(cfg, count, p, k, a, m, st);                  \
+        if (cfg.f16) return launch_ring_t<NA, G, false, 1>(cfg, count, p, k, a, m, forced, st);    \
+        if (cfg.lb == 4) return launch_ring_t<NA, G, false, 0>(cfg, count, p, k, a, m, forced, st); \
+        return launch_ring_t<NA, G, true, 0>(cfg, count, p, k, a, m, forced, st);                  \
     } while (0)
 #define RAZER_RING_G(NA)                   \
     do {                                   \
@@ -413,28 +454,54 @@ static hipError_t launch_ring(SvConfig cfg, int count, const GemvProblem* p, int
         if (g == 4) RAZER_RING(NA, 4);     \
         RAZER_RING(NA, 6);                 \
     } while (0)
+    if (m <= 4 && cfg.il) {                                       // the interleaved layout is a form of 2..4 rows
+        if (g == 1) return launch_ring_t<1, 1, false, 0, true>(cfg, count, p, k, a, m, forced, st);
+        if (g == 2) return launch_ring_t<1, 2, false, 0, true>(cfg, count, p, k, a, m, forced, st);
+        if (g == 3) return launch_ring_t<1, 3, false, 0, true>(cfg, count, p, k, a, m, forced, st);
+        if (g == 4) return launch_ring_t<1, 4, false, 0, true>(cfg, count, p, k, a, m, forced, st);
+        return launch_ring_t<1, 6, false, 0, true>(cfg, count, p, k, a, m, forced, st);
+    }
+    if (cfg.il) return hipErrorInvalidValue;
+    if (m <= 4) RAZER_RING_G(1);
     if (m <= 8) RAZER_RING_G(2);
     if (m <= 16) RAZER_RING_G(4);
     if (m <= 32) RAZER_RING_G(8);
     if (g == 1) RAZER_RING(16, 1);
     if (g == 2) RAZER_RING(16, 2);
     if (g == 3) RAZER_RING(16, 3);
-    return cfg.lb == 4 ? launch_ring_t<16, 4, false, 0>(cfg, count, p, k, a, m, st) : launch_ring_t<16, 4, true, 0>(cfg, count, p, k, a, m, st);
+    return cfg.lb == 4 ? launch_ring_t<16, 4, false, 0>(cfg, count, p, k, a, m, forced, st) : launch_ring_t<16, 4, true, 0>(cfg, count, p, k, a, m, forced, st);
 #undef RAZER_RING_G
 #undef RAZER_RING
 }
 
-// 33..64 activation rows, scale-byte format: this kernel, unless a tuner or test forces K-slices of the register-decode
-// GEMM, or one group per workgroup makes every workgroup read more activations than it gains (one group, m x K above
-// 600 thousand: 4096 x 11008 at 40 rows 26.5 -> 24.4 us, at 64 rows 25.9 -> 26.4; 1500 x 12288 at 64 rows 22.1 -> 24.5;
-// with more groups 13-50 % faster than that kernel).
-bool ring_serves(int count, const GemvProblem* p, int64_t k, int64_t m)
+// Where this kernel takes over from its neighbours (unless a tuner or test forces one of their launch shapes).
+// 33..64 activation rows, scale-byte format, against the K-sliced register-decode GEMM: except where one group per
+// workgroup makes every workgroup read more activations than it gains (one group, m x K above 600 thousand:
+// 4096 x 11008 at 40 rows 26.5 -> 24.4 us, at 64 rows 25.9 -> 26.4; 1500 x 12288 at 64 rows 22.1 -> 24.5; with more
+// groups 13-50 % faster).
+// 2..4 activation rows, against the 4x4x4 kernel of razer_gemv.hip, whose waves cross all of K in one or two passes:
+// long rows and not too many of them (1024 groups) -- at 4 rows 8192 x 28672 38.0 -> 30.4 us, {q,k,v} 10240 x 8192
+// 16.6 -> 14.6, 2 x 3000 x 6144 10.0 -> 9.0; at 2 rows one group per workgroup only (4096 x 11008 9.7 -> 8.7; but
+// 10240 x 8192 14.5 -> 15.8) -- and 4 rows with one group per workgroup from 2048 elements up (4096 x 4096
+// 5.35 -> 5.15).  57344 x 8192 at 4 rows would take 63 instead of 57 us.
+// This kernel scales its operands; a special value of 9.5 times a block scale does not always fit a bf16, which the
+// 4x4x4 kernel (bare operands) does not need, so up to 4 rows such tensors stay there.  The layout of the weights has
+// no say: canonical and interleaved tensors give the same bits.
+bool ring_serves(SvConfig cfg, int count, const GemvProblem* p, int64_t k, int64_t m)
 {
-    if (m <= kSkinnyMaxM || m > kRingMaxM || k > kSkinnyMaxK) return false;
+    if (k > kSkinnyMaxK) return false;
     int64_t rows = 0;
     for (int i = 0; i < count; ++i) rows += p[i].n;
+    const int64_t groups = ring_row_groups(count, p);
+    if (m >= 2 && m <= kGemvDirectMaxM) {
+        if (!cfg.f16 && (cfg.sv0 == 9.5f || cfg.sv1 == 9.5f)) return false;
+        if (tuned_shape(kTuneGemvQuad, m, rows, k).source == 1 || tuned_shape(kTuneGemv, m, rows, k).source == 1) return false;
+        if (groups <= kComputeUnits) return m == 2 ? k >= 8192 : m == 3 ? k >= 6144 : k >= 2048;
+        return m >= 3 && k >= 6144 && groups <= 1024;
+    }
+    if (m <= kSkinnyMaxM || m > kRingMaxM || cfg.f16) return false;
     if (tuned_shape(kTuneGemmSlices, m, rows, k).source == 1) return false;
-    return ring_groups(ring_row_groups(count, p), m, false) > 1 || m * k <= 600000;
+    return ring_groups(groups, m, false) > 1 || m * k <= 600000;
 }
 
 // What razer_workspace_bytes reports for 5..32 activation rows.  The kernel above needs none; callers size and pass
@@ -478,7 +545,7 @@ size_t skinny_grouped_workspace_bytes(int count, const GemvProblem* p, int64_t k
 
 hipError_t launch_skinny(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, hipStream_t st)
 {
-    if (count < 1 || count > 4 || m <= kGemvDirectMaxM || m > kRingMaxM || k <= 0 || k > kSkinnyMaxK) return hipErrorInvalidValue;
+    if (count < 1 || count > 4 || m < 2 || m > kRingMaxM || k <= 0 || k > kSkinnyMaxK) return hipErrorInvalidValue;
     for (int i = 0; i < count; ++i)
         if (p[i].n <= 0) return hipErrorInvalidValue;
     return launch_ring(cfg, count, p, k, a, m, st);

@@ -1,5 +1,5 @@
-"""The small-batch kernel (5..64 activation rows) where its tiles, steps and copies end: remainders of 16 rows and of
-128 elements, K shorter than one step, every number of staged activation rows, every number of row groups per
+"""The small-batch kernel (5..64 activation rows, 2..4 with long rows) where its tiles, steps and copies end: remainders
+of 16 rows and of 128 elements, K shorter than one step, every number of staged activation rows, every number of row groups per
 workgroup, matrices of a group that share a workgroup, each weight format -- against the CPU oracle."""
 import numpy as np
 import pytest
@@ -53,6 +53,13 @@ def test_edges(oracle, m, ns, k, fmt, block):
                                          (32, razer.WEIGHT_F16, 128), (64, razer.WEIGHT_F16, 128)])
 def test_groups_per_workgroup(oracle, groups, m, fmt, block):
     _run(oracle, (68, 33 * 4, 12), 2176, m, fmt, block, groups)
+
+
+@pytest.mark.parametrize("m", [2, 3, 4])
+@pytest.mark.parametrize("ns,k,fmt,block", [((37,), 8192 + 32, razer.WEIGHT, 16), ((2100, 2100, 4), 6144, razer.WEIGHT, 16),
+                                            ((50, 3), 8192 + 64, razer.WEIGHT, 64), ((36, 20), 8192 + 128, razer.WEIGHT_F16, 128)])
+def test_few_rows_with_long_k(oracle, m, ns, k, fmt, block):
+    _run(oracle, ns, k, m, fmt, block)
 
 
 @pytest.mark.parametrize("m", [6, 40])
