@@ -16,7 +16,7 @@
  *                           with p[0] = 2)
  *   RAZER_TUNE_GEMV_QUAD    m = 2 .. 4, every block size and weight format: p[0] = groups of 4 rows per
  *                           workgroup (4 or 8)
- *   RAZER_TUNE_SMALL_BATCH  5 <= m <= 64 where the small-batch kernel serves the call: p[0] = 2, p[1] = groups of 16
+ *   RAZER_TUNE_SMALL_BATCH  5 <= m where the small-batch kernel serves the call: p[0] = 2, p[1] = groups of 16
  *                           rows per workgroup (1, 2, 3, 4, 6; above 32 rows at most 4, FP16-scale format 3).
  *                           A forced shape of any kind also fixes the order of the sum over K (8 waves).
  *                           p[0] = 0 or 1 (5 <= m <= 32) names a shape on record of the kernels this one replaced;

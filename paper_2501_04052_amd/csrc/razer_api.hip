@@ -305,8 +305,11 @@ razer_status razer_linear(const razer_tensor* w, const void* a_bf16, const razer
         else {
             const size_t need = gemm_workspace_bytes(n, k, m);       // K-slices while the tiles are few
             if (need > 0 && (!workspace || workspace_bytes < need || !aligned16(workspace))) return RAZER_ERR_WORKSPACE;
-            e = launch_gemm(wsv, w->codes, w->scales, w->tensor_scale, n, k, (const uint16_t*)a_bf16, asv, nullptr,
-                            nullptr, nullptr, m, (uint16_t*)y_bf16, ld_y, need > 0 ? (float*)workspace : nullptr, st);
+            if (ring_serves(wsv, 1, &one, k, m))
+                e = launch_skinny(wsv, 1, &one, k, (const uint16_t*)a_bf16, m, st);
+            else
+                e = launch_gemm(wsv, w->codes, w->scales, w->tensor_scale, n, k, (const uint16_t*)a_bf16, asv, nullptr,
+                                nullptr, nullptr, m, (uint16_t*)y_bf16, ld_y, need > 0 ? (float*)workspace : nullptr, st);
         }
     } else if (!a_q && m > kGemvDirectMaxM && m <= kSkinnyMaxM && k <= kSkinnyMaxK) {
         const size_t need = skinny_workspace_bytes(n, k, m);
@@ -401,8 +404,14 @@ razer_status razer_linear_grouped(const razer_tensor* const* w, int32_t count, c
         if (m <= kGemvDirectMaxM) {
             path = ring_serves(sv0, count, p, k, m) ? SKINNY : GEMV;   // every block size and both weight formats
         } else if (sv0.f16 && m > kSkinnyMaxM) {
-            // FP16 scale words: no grouped launch of the tiled matrix-core kernels
-            path = m <= kRingMaxM && k <= kSkinnyMaxK ? SKINNY : SEQUENCE;
+            // FP16 scale words: no grouped launch of the tiled matrix-core kernels, whose workspace is asked for above
+            // 64 rows whichever kernel runs
+            bool ok = m <= kRingMaxM ? k <= kSkinnyMaxK : ring_serves(sv0, count, p, k, m);
+            for (int i = 0; ok && i < count; ++i) {
+                const size_t need = m <= kRingMaxM ? 0 : gemm_workspace_bytes(p[i].n, k, m);
+                ok = need == 0 || (workspace && workspace_bytes >= need && aligned16(workspace));
+            }
+            path = ok ? SKINNY : SEQUENCE;
         } else if (m <= kSkinnyMaxM && k > kSkinnyMaxK) {
             path = SEQUENCE;
         } else if (m <= kSkinnyMaxM) {

@@ -51,7 +51,7 @@ hipError_t launch_dequant(int fmt, SvConfig cfg, const uint8_t* codes, const uin
 constexpr int kGemvMaxM = 16;
 constexpr int kGemvDirectMaxM = 4;     // rows the GEMV kernel takes in one pass
 constexpr int kSkinnyMaxM = 32;        // up to here the small-batch kernel always
-constexpr int kRingMaxM = 64;          // ... and from 33 rows where it is the faster one (FP16-scale format: always)
+constexpr int kRingMaxM = 64;          // its activation rows per workgroup; from 33 rows (FP16 scales: 65) it runs where it is faster
 constexpr int64_t kComputeUnits = 256;
 constexpr uint32_t kLdsBytes = 160u * 1024u;   // per compute unit
 // The small-batch kernel and the register-decode GEMM address inside a row block / tile with 32-bit
@@ -93,11 +93,12 @@ hipError_t launch_gemm(SvConfig wcfg, const uint8_t* w_codes, const uint8_t* w_s
                        const uint8_t* a_scales, const float* a_ts, int64_t m, uint16_t* y, int64_t ld_y,
                        float* workspace, hipStream_t st);
 
-// 2 <= m <= kRingMaxM: decode-once MFMA kernel, one launch for up to 4 matrices sharing K, the activation rows, the
-// format, the block size and the special values (every n > 0, 0 < k <= kSkinnyMaxK).  No workspace.
+// m >= 2: decode-once MFMA kernel (runs of up to kRingMaxM activation rows), one launch for up to 4 matrices sharing K,
+// the activation rows, the format, the block size and the special values (every n > 0, 0 < k <= kSkinnyMaxK).  No
+// workspace.
 hipError_t launch_skinny(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, hipStream_t st);
-// 2..4 rows, and 33..64 of the scale-byte format: whether that kernel is faster than the 4x4x4 GEMV / the register-
-// decode GEMM.
+// 2..4 rows, 33..64 of the scale-byte format, and above 64: whether that kernel is faster than the 4x4x4 GEMV / the
+// GEMMs.
 bool ring_serves(SvConfig cfg, int count, const GemvProblem* p, int64_t k, int64_t m);
 
 // Sum of the K-slices of a grouped launch: partial holds matrix i's [nslices][m][n_i] fp32 slices

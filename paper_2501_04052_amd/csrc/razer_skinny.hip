@@ -111,7 +111,7 @@ struct RingArgs {
     float sv0, sv1;
     int64_t k, m;
     const uint16_t* a;
-    int lb;
+    int chunk, lb;
 };
 
 template <int NA, int G, bool GB, int SF, int W, bool IL = false>
@@ -119,9 +119,9 @@ __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
 {
     const uint32_t e1 = arg.e[0], e2 = arg.e[1], e3 = arg.e[2], e4 = arg.e[3];
     const float sv0 = arg.sv0, sv1 = arg.sv1;
-    const int64_t k = arg.k, m = arg.m;
+    const int64_t k = arg.k, m0 = (int64_t)blockIdx.y * arg.chunk, m = arg.m - m0 < arg.chunk ? arg.m - m0 : arg.chunk;
     const int lb = arg.lb;
-    const uint16_t* a = arg.a;
+    const uint16_t* a = arg.a + m0 * k;
     constexpr int NB = (NA + 3) / 4;
     constexpr uint32_t WAVE = ring_wave_bytes<NA, G>();
     __shared__ uint4 lut[SF ? 1 : 256];
@@ -325,6 +325,7 @@ __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
         if (q >= e1) { ts = arg.ts[1]; y = arg.y[1]; n = arg.n[1]; ld_y = arg.ld_y[1]; first = e1; }
         if (q >= e2) { ts = arg.ts[2]; y = arg.y[2]; n = arg.n[2]; ld_y = arg.ld_y[2]; first = e2; }
         if (q >= e3) { ts = arg.ts[3]; y = arg.y[3]; n = arg.n[3]; ld_y = arg.ld_y[3]; first = e3; }
+        y += m0 * ld_y;
         const int64_t row0 = (int64_t)(q - first) * 16;
         const float sc = SF ? -*ts : *ts;                                 // (the bare decode carries a negation)
         float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -362,6 +363,13 @@ __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
 }
 
 
+// More than 64 activation rows go in equal runs of at most 64, blockIdx.y counting them.
+static int64_t ring_chunk(int64_t m)
+{
+    const int64_t chunks = (m + kRingMaxM - 1) / kRingMaxM;
+    return (m + chunks - 1) / chunks;
+}
+
 template <int NA, int G, bool GB, int SF, bool IL, int W>
 static hipError_t launch_ring_w(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, hipStream_t st)
 {
@@ -382,6 +390,7 @@ static hipError_t launch_ring_w(SvConfig cfg, int count, const GemvProblem* p, i
     arg.sv1 = cfg.sv1;
     arg.k = k;
     arg.m = m;
+    arg.chunk = (int)ring_chunk(m);
     arg.a = a;
     arg.lb = cfg.lb;
     // as many of the W waves as their LDS leaves room for (64 activation rows and more than 2 groups: 7 of 8)
@@ -390,7 +399,7 @@ static hipError_t launch_ring_w(SvConfig cfg, int count, const GemvProblem* p, i
     static_assert(most >= 4, "LDS");
     const int64_t nsteps = (k + 127) / 128;
     const int waves = nsteps < most ? (int)nsteps : most;
-    launch(ring_kernel<NA, G, GB, SF, W, IL>, (groups + G - 1) / G, 64 * waves, (size_t)waves * ring_wave_bytes<NA, G>(), st, arg);
+    launch(ring_kernel<NA, G, GB, SF, W, IL>, dim3((groups + G - 1) / G, (unsigned)((m + arg.chunk - 1) / arg.chunk)), 64 * waves, (size_t)waves * ring_wave_bytes<NA, G>(), st, arg);
     return hipGetLastError();
 }
 
@@ -417,9 +426,11 @@ static int ring_groups(int64_t groups, int64_t m, bool f16)
 {
     int best = 1;
     double cost = 0.0;
+    const int64_t chunks = (m + kRingMaxM - 1) / kRingMaxM;
+    m = ring_chunk(m);
     for (int g : {1, 2, 3, 4, 6}) {
         if (m > 32 && g > (f16 ? 3 : 4)) continue;
-        const int64_t wgs = (groups + g - 1) / g;
+        const int64_t wgs = chunks * ((groups + g - 1) / g);
         const double c = (double)(g * ((wgs + kComputeUnits - 1) / kComputeUnits)) * (1.0 + 0.055 * (double)m / g) * (g == 6 ? 1.15 : 1.0);
         if (g == 1 || c < cost) { best = g; cost = c; }
     }
@@ -484,6 +495,15 @@ static hipError_t launch_ring(SvConfig cfg, int count, const GemvProblem* p, int
 // 16.6 -> 14.6, 2 x 3000 x 6144 10.0 -> 9.0; at 2 rows one group per workgroup only (4096 x 11008 9.7 -> 8.7; but
 // 10240 x 8192 14.5 -> 15.8) -- and 4 rows with one group per workgroup from 2048 elements up (4096 x 4096
 // 5.35 -> 5.15).  57344 x 8192 at 4 rows would take 63 instead of 57 us.
+// Above 64 rows, against the register-decode and the tiled GEMM, whose workgroups are too few or wait on one K-tile
+// after the other as long as the product is small; a unit is a group of 16 weight rows times a run of up to 64
+// activation rows.  Scale bytes (us): 768 x 1536 at 96 rows 13.5 -> 5.9, at 512 23.1 -> 7.1, at 4096 (3072 units)
+// 32.1 -> 34.9; 4096 x 4096 at 192 rows 26.6 -> 17.9, at 512 39.3 -> 33.7; 2560 x 2560 at 700 rows (4.5 million
+// units x K) 32.1 -> 26.4, at 1024 (6.6) 37.0 -> 38.4; 300 x 16384 at 128 rows (the GEMM cuts K) 23.5 -> 27.0, at 512
+// 44.5 -> 31.2; 4096 x 11008 at 256 rows 45.8 -> 38.7, at 384 64.5 -> 72.3; 2 x 11008 x 4096 at 96 rows (11.3 million)
+// 46.1 -> 49.6.  FP16 scales, whose GEMM multiplies every block apart and has one launch per matrix: 28672 x 8192 at
+// 128 rows 237 -> 114, at 160 145 -> 173; 4096 x 4096 at 384 rows 38.1 -> 30.6, 4096 x 11008 at 160 rows
+// 40.6 -> 42.8; 3 x 1536 x 1536 at 512 rows 78.1 -> 26.9; 2 x 2048 x 2048 at 1024 rows 62.9 -> 53.0, at 1500 73.7 -> 78.7.
 // This kernel scales its operands; a special value of 9.5 times a block scale does not always fit a bf16, which the
 // 4x4x4 kernel (bare operands) does not need, so up to 4 rows such tensors stay there.  The layout of the weights has
 // no say: canonical and interleaved tensors give the same bits.
@@ -499,7 +519,14 @@ bool ring_serves(SvConfig cfg, int count, const GemvProblem* p, int64_t k, int64
         if (groups <= kComputeUnits) return m == 2 ? k >= 8192 : m == 3 ? k >= 6144 : k >= 2048;
         return m >= 3 && k >= 6144 && groups <= 1024;
     }
-    if (m <= kSkinnyMaxM || m > kRingMaxM || cfg.f16) return false;
+    if (m > kRingMaxM) {
+        if (!cfg.f16 && tuned_shape(kTuneGemmSlices, m, rows, k).source == 1) return false;
+        const int64_t units = (m + kRingMaxM - 1) / kRingMaxM * groups, work = units * k;
+        if (cfg.f16) return m <= 128 || (units <= 2500 * count && work <= (int64_t)5000000 * count);
+        if (m <= 128) return work <= 5700000 && k <= 11264;
+        return (units <= 2500 && work <= 6000000) || (m <= 256 && units <= 1100 && k <= 12288);
+    }
+    if (m <= kSkinnyMaxM || cfg.f16) return false;
     if (tuned_shape(kTuneGemmSlices, m, rows, k).source == 1) return false;
     return ring_groups(groups, m, false) > 1 || m * k <= 600000;
 }
@@ -545,7 +572,7 @@ size_t skinny_grouped_workspace_bytes(int count, const GemvProblem* p, int64_t k
 
 hipError_t launch_skinny(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, hipStream_t st)
 {
-    if (count < 1 || count > 4 || m < 2 || m > kRingMaxM || k <= 0 || k > kSkinnyMaxK) return hipErrorInvalidValue;
+    if (count < 1 || count > 4 || m < 2 || k <= 0 || k > kSkinnyMaxK) return hipErrorInvalidValue;
     for (int i = 0; i < count; ++i)
         if (p[i].n <= 0) return hipErrorInvalidValue;
     return launch_ring(cfg, count, p, k, a, m, st);

@@ -1,6 +1,6 @@
-"""The small-batch kernel (5..64 activation rows, 2..4 with long rows) where its tiles, steps and copies end: remainders
-of 16 rows and of 128 elements, K shorter than one step, every number of staged activation rows, every number of row groups per
-workgroup, matrices of a group that share a workgroup, each weight format -- against the CPU oracle."""
+"""The small-batch kernel (5..64 activation rows, 2..4 with long rows, runs of 64 in small products) where its tiles,
+steps and copies end: remainders of 16 rows and of 128 elements, K shorter than one step, every number of staged
+activation rows, every number of row groups per workgroup, matrices of a group that share a workgroup, each weight format -- against the CPU oracle."""
 import numpy as np
 import pytest
 import torch
@@ -60,6 +60,24 @@ def test_groups_per_workgroup(oracle, groups, m, fmt, block):
                                             ((50, 3), 8192 + 64, razer.WEIGHT, 64), ((36, 20), 8192 + 128, razer.WEIGHT_F16, 128)])
 def test_few_rows_with_long_k(oracle, m, ns, k, fmt, block):
     _run(oracle, ns, k, m, fmt, block)
+
+
+@pytest.mark.parametrize("m", [65, 128, 129, 321])
+@pytest.mark.parametrize("ns,k,fmt,block", [((37,), 32, razer.WEIGHT, 16), ((16, 4, 100), 1024 + 96, razer.WEIGHT, 16),
+                                            ((50,), 1152, razer.WEIGHT, 64), ((36, 20), 1280, razer.WEIGHT_F16, 128)])
+def test_runs_of_activation_rows(oracle, m, ns, k, fmt, block):
+    _run(oracle, ns, k, m, fmt, block)
+
+
+def test_runs_of_activation_rows_keep_to_a_strided_output(oracle):
+    n, k, m = 37, 256, 130
+    a = synth.activation(m, k, seed=4700)
+    wq, w = _weights(n, k, 4701, razer.WEIGHT, 16)
+    buf = torch.full((m + 1, n + 11), 77.0, dtype=torch.bfloat16, device="cuda")
+    razer.razer_linear(w, bf16_bits_to_dev(a), out=buf[:m, :n])
+    y64, _ = oracle.linear(wq, a_bf16=a)
+    assert max_rel_err(dev_to_bf16_bits(buf[:m, :n].contiguous()), y64) <= TOL
+    assert bool((buf[:m, n:] == 77.0).all()) and bool((buf[m] == 77.0).all())
 
 
 @pytest.mark.parametrize("m", [6, 40])
