@@ -66,9 +66,9 @@ typedef enum {
      * block must be 0 or 128; cols a multiple of 128.  A weight format: accepted wherever
      * RAZER_FMT_WEIGHT is, except that razer_linear takes bf16 activations only: wavefront dot products
      * up to 4 activation rows; beyond that matrix-core kernels that multiply bare FP4 operands and fold
-     * each block's partial sums with the block's scale in fp32 (no workspace is used up to 64 rows; from
-     * 65 rows the usual razer_workspace_bytes rule -- K is cut into slices of whole blocks while tiles are
-     * few). */
+     * each block's partial sums with the block's scale in fp32 (no workspace is asked for up to 64 rows; from
+     * 65 rows the usual razer_workspace_bytes rule -- large products cut K into slices of whole blocks while
+     * tiles are few). */
     RAZER_FMT_WEIGHT_F16 = 2
 } razer_format;
 
@@ -164,9 +164,9 @@ razer_status razer_dequant(const razer_tensor *t, void *out, int32_t dtype, int6
  * dynamic-LDS limit (hipFuncSetAttribute, once per kernel and device, race-free): a caller that captures
  * a stream into a HIP graph makes one ordinary call of each shape first.
  * workspace: device, 16-byte aligned, >= razer_workspace_bytes(RAZER_OP_LINEAR, N, K, m) bytes
- * (non-zero where K is split over workgroups and the slices meet in fp32: W4A16 with 5 <= m <= 32,
- * and m > 32 with too few output tiles to occupy the GPU -- ask razer_workspace_bytes; else may be
- * NULL); too small -> RAZER_ERR_WORKSPACE. */
+ * (non-zero for W4A16 with 5 <= m <= 32, whose kernel no longer writes to it, and for m > 32 with too few
+ * output tiles to occupy the GPU, where K may be split over workgroups and the slices meet in fp32 -- ask
+ * razer_workspace_bytes; else may be NULL); too small -> RAZER_ERR_WORKSPACE. */
 razer_status razer_linear(const razer_tensor *w, const void *a_bf16, const razer_tensor *a_q,
                           int64_t m, void *y_bf16, int64_t ld_y,
                           void *workspace, size_t workspace_bytes, void *hip_stream);
@@ -205,11 +205,13 @@ razer_status razer_linear_static(const razer_tensor *w, const void *a_bf16, cons
  *   m <= 4 (RAZER_FMT_WEIGHT or RAZER_FMT_WEIGHT_F16);
  *   RAZER_FMT_WEIGHT, 5 <= m <= 32, every rows[i] and ld_y[i] a multiple of 4, y_bf16[i] 8-byte
  *     aligned, and the workspace holds razer_workspace_bytes_grouped(count, rows, cols, m) bytes
- *     (plus one launch that adds the K-slices up); RAZER_FMT_WEIGHT_F16 under the same conditions on
+ *     (which the kernel does not write to); RAZER_FMT_WEIGHT_F16 under the same conditions on
  *     rows, ld_y and y_bf16, without a workspace;
+ *   RAZER_FMT_WEIGHT_F16, 33 <= m <= 128 and small products beyond (from 65 rows with a workspace that
+ *     would satisfy each matrix's own razer_linear call);
  *   RAZER_FMT_WEIGHT, m >= 33: without a workspace when m > 128 and the matrices together have
- *     >= 512 output tiles of 256 x 128, or 192..256 of them with cols >= 1024; otherwise K is cut into
- *     slices (plus one launch that adds them up) under the conditions of the 5 <= m <= 32 case --
+ *     >= 512 output tiles of 256 x 128, or 192..256 of them with cols >= 1024; otherwise (K cut into
+ *     slices plus one launch that adds them up, or the small-batch kernel where the product is small) under the conditions of the 5 <= m <= 32 case --
  *     rows, ld_y, alignment of y_bf16, and a workspace of razer_workspace_bytes_grouped bytes.
  * Otherwise it is the sequence of razer_linear calls with the same workspace (which then must
  * satisfy each call).  y_bf16[i] is device [m][ld_y[i]].  The pointer arrays are HOST arrays. */

@@ -19,8 +19,8 @@
 //   gemm_pp_kernel   256-row tiles, two wave groups half a step out of phase (decode | MFMA): few-tile
 //                    problems above 128 rows, the fused W4A4 kernel, the FP16-scale format
 //   gemm_rb_kernel   W4A16, 16-element blocks: weights decoded in registers by the wave that uses them,
-//                    global -> LDS copies by the load unit; 256-row activation tiles when there are
-//                    many output tiles, 64- / 128-row tiles for 33..128 activation rows; KG = 2 halves
+//                    global -> LDS copies by the load unit; 256-row activation tiles (gemm_wide_kernel: 64
+//                    instead of 32 weight rows per wave) when there are many output tiles, 64- / 128-row tiles for 33..128 activation rows; KG = 2 halves
 //                    K inside the workgroup when there is about one tile per compute unit; the grouped
 //                    form runs up to four matrices (fused q/k/v, gate/up) as one launch
 // Problems with too few tiles split K over workgroups (fp32 slices in the caller's workspace).
