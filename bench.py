@@ -359,7 +359,7 @@ def main():
         return ms, fl
 
     def gemm_roofline(ms, fl):
-        # dominant kernel of the M=2048 layer: the {gate,up} launch (gemm_rb_grouped_kernel), per dispatch
+        # dominant kernel of the M=2048 layer: the {gate,up} launch (gemm_wide_grouped_kernel), per dispatch
         m = 2048
         a2k = make_act(m, 4096, 2100 + m)
         o2k = [torch.empty((m, 11008), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
@@ -369,7 +369,7 @@ def main():
         dfl = 2.0 * m * 2 * 11008 * 4096
         return {"bound": "mfma", "achieved": dfl / dms / 1e9, "peak": MFMA_BF16_PEAK_TFLOPS,
                 "unit": "TFLOP/s", "frac": dfl / dms / 1e9 / MFMA_BF16_PEAK_TFLOPS, "traffic": None,
-                "kernel": "gemm_rb_grouped_kernel<4,2,1,8,false> on {gate,up} 2 x 11008x4096 at M=2048 (44 % of the layer's flops), "
+                "kernel": "gemm_wide_grouped_kernel<false> on {gate,up} 2 x 11008x4096 at M=2048 (44 % of the layer's flops), "
                           "flops = 2MNK, per-dispatch duration from the dispatch's own time stamps",
                 "avg_dispatch_us": dms * 1e3, "flops_per_launch": dfl,
                 "layer_TFLOP/s": fl / ms / 1e9, "layer_frac": fl / ms / 1e9 / MFMA_BF16_PEAK_TFLOPS,
@@ -551,7 +551,7 @@ def main():
                     legs["linear_m%d_block128_fp16_scale" % mm] = {
                         "TFLOP/s": flm / msm / 1e9, "ms_per_step": msm,
                         "note": "bare FP4 operands on the matrix cores, each 128-element block's partial sums folded with its "
-                                "FP16 scale in fp32: K-in-workgroup kernel up to 64 rows, LDS-staged tiled kernels beyond"}
+                                "FP16 scale in fp32: the LDS-ring kernel up to 128 rows and in small products, LDS-staged tiled kernels beyond"}
                     del plansm, actm, outm
             del sets, plans
             torch.cuda.empty_cache()

@@ -293,8 +293,8 @@ razer_status razer_linear(const razer_tensor* w, const void* a_bf16, const razer
     } else if (!a_q && m <= kGemvDirectMaxM && ring_serves(wsv, 1, &one, k, m)) {
         e = launch_skinny(wsv, 1, &one, k, (const uint16_t*)a_bf16, m, st);
     } else if (wsv.f16) {
-        // FP16-scale format: the GEMV kernels up to 4 activation rows, the K-in-workgroup small-batch kernel up
-        // to 64, beyond that the tiled matrix-core kernels; all matrix-core kernels multiply bare FP4 operands
+        // FP16-scale format: the GEMV kernels up to 4 activation rows, the small-batch kernel up to 64 and where
+        // ring_serves() says so, else the tiled matrix-core kernels; all matrix-core kernels multiply bare FP4 operands
         // and fold each block's partial sums with its scale in fp32
         if (a_q) return RAZER_ERR_CONFIG;
         if (m <= kGemvDirectMaxM || (m <= kSkinnyMaxM && k > kSkinnyMaxK))
