@@ -1,12 +1,11 @@
 // RaZeR block encoder for gfx950: Eq. 1 (tensor scale), Eq. 2 (block scale),
 // Eq. 4 (special-value search) and Eq. 5 (final rounding) of arxiv 2501.04052.
 //
-// Bit-exactness contract: every fp32 operation below is a single IEEE operation
-// (true division, no reciprocal, no contraction), squared errors are summed in
-// fp64 over the block's elements in index order (also for blocks of 32, 64, 128
-// -- the block-size study of Sec. 5.4 -- where the lanes that share a block
-// hand the running sum from one to the next), and ties are broken as documented
-// in razer.h.
+// Bit-exactness contract: codes, scales and the tensor scale are those of the literal computation -- every fp32
+// operation a single IEEE operation (true division), squared errors summed in fp64 over the block's elements in index
+// order (also for blocks of 32, 64, 128 -- the block-size study of Sec. 5.4 -- where the lanes that share a block
+// hand the running sum from one to the next), ties broken as documented in razer.h.  The block encoder reaches most
+// of these results by cheaper operations that are proven to give the same bits; the proofs are stated there.
 // Compile without fast-math.
 #include "razer_device.hpp"
 #include "razer_kernels.hpp"
@@ -128,69 +127,167 @@ __device__ __forceinline__ v2f decode_pair_f32(uint32_t word, int i)      // the
 //  * division.  y = 1 / den is one IEEE division per block; q = x y, then twice q += (x - q den) y with the residual
 //    in one fma.  The first correction makes q faithful, and for a faithful q, a correctly rounded reciprocal and an
 //    exact residual the second yields the correctly rounded quotient (Markstein's theorem); 5 operations instead of
-//    ~12.  It needs normal operands: tensor scales outside [2^-60, 2^60] take the literal path.
+//    ~12.  It needs normal operands: den below 2^-70 and tensor scales above 2^60 take the literal path (an element
+//    whose residual is still subnormal is below 2^-30 after scaling and leaves no trace in a sum that decides anything).
 //  * the special-value search.  Candidate v lowers an element's squared error by (v - q)(2 x - q - v) when that is
 //    positive; sign and zero of that product are exact in fp32 (2 x - q is exact, and so is the difference to v where
 //    it is close to it), so "no element takes v" and the elements that take it are known exactly, and the sums of the
-//    gains to a relative error below (elements + 8) 2^-23.  The candidate with the largest gain has the smallest
-//    error; where the two largest gains are closer than that bound (and for non-finite blocks, blocks that exceed
-//    9 scales) the literal fp64 chain of Eq. 4 decides: about one block in 10^5 of continuous data.
-// 11008 x 4096 fp32, without the pass for Eq. 1: blocks of 16 61.6 -> 42.4 us (206 MB, 4.9 TB/s), blocks of 128
-// 108.5 -> 44.2 us; 4096 x 4096 bf16 activations 19.7 -> 18.8.
+//    gains to a relative error below (elements + 8) 2^-23.  The candidate with the largest gain has the smallest error
+//    where the others are further away than that bound.  Where one other is not, the fp64 sums of Eq. 4 are formed for
+//    those two alone (nearest_two): 16-bit data, with few distinct magnitudes, ties in about one block of 400, so one
+//    wave in seven goes there.  Only what is left -- three candidates that close, non-finite blocks, blocks beyond 512
+//    scales -- takes the literal chain.
+// A thread has one run until the launch has 2^20; such launches wait for loads and for the slowest wave, the larger
+// ones for vector issue with as many waves as registers allow.  Hence the next run is fetched while one is encoded for
+// 16-bit elements only (8 registers, 3 % at 4096 x 4096; the 16 of fp32 cost 5 %), scaled 16-bit elements are kept for
+// nearest_two, and fp32 ones are scaled again there.
+// Measured against the kernel that formed all four fp64 sums for every block (us per dispatch, tensor scale given; in
+// parentheses with ties decided by the literal chain): bf16 activations 4096 wide, 64 rows 5.0 (5.8) -> 5.0, 512 rows
+// 6.1 (6.9) -> 5.6, 1024 rows 8.3 (8.8) -> 7.6, 4096 rows 20.2 (18.1) -> 15.6; bf16 weights in blocks of 128, 256 rows
+// 7.1 (10.7) -> 6.9, 4096 rows 45.0 (27.4) -> 20.6; fp32 weights 11008 x 4096 in blocks of 16 62.0 (42.5) -> 42.2 (206 MB,
+// 4.9 TB/s), of 128 120 (49.6) -> 42.4.
 
 // Eq. 4 and the codes literally: fp32 division, squared errors in fp64, one chain over the block's elements in index
 // order (lane j of the block continues where lane j - 1 ended).  lo / hi: the 16 codes as the hardware rounds them;
-// take: bit k set if element k takes the chosen special value.
-template <int FMT, int G>
+// take: bit k set if element k takes the chosen special value.  NP candidates go side by side; with more than one such
+// pass the empty asm keeps the compiler from holding what does not depend on the candidate (the base errors, in fp64)
+// over all of them: where this path is the rare one, its registers count against the occupancy of the other.
+template <int FMT, int G, int NP>
 __device__ __forceinline__ void encode_literal(const float (&xv)[kBlock], float den, float sv0, float sv1, uint32_t& lo,
                                                uint32_t& hi, uint32_t& meta, uint32_t& take)
 {
     constexpr int NC = (FMT == 1) ? 2 : 4;
-    float xs[kBlock], q[kBlock];
+    float xs[kBlock];                                                     // X^Scaled
     lo = hi = 0;
 #pragma unroll
     for (int k = 0; k < kBlock; k += 2) {
-        xs[k] = xv[k] / den;                                              // X^Scaled
+        xs[k] = xv[k] / den;
         xs[k + 1] = xv[k + 1] / den;
         uint32_t& word = (k < 8) ? lo : hi;
         word = encode_pair(word, xs[k], xs[k + 1], (k % 8) / 2);
-        const v2f p = decode_pair_f32(word, (k % 8) / 2);
-        q[k] = p.x;
-        q[k + 1] = p.y;
     }
+    const int sub = (int)(threadIdx.x & 63u) & (G - 1), base = (int)(threadIdx.x & 63u) & ~(G - 1);
     double best = 0.0;
     meta = 0;
     take = 0;
-#pragma unroll
-    for (int m = 0; m < NC; ++m) {
-        const double cand = (FMT == 1) ? (m ? -(double)sv0 : (double)sv0)
-                                       : (m & 2 ? -1.0 : 1.0) * (double)((m & 1) ? sv1 : sv0);
-        const int sub = (int)(threadIdx.x & 63u) & (G - 1), base = (int)(threadIdx.x & 63u) & ~(G - 1);
-        double sse = 0.0;
-        uint32_t bits = 0;
-        // round p is the one in which lane base + p of the block holds the right starting value (its
-        // predecessor's total of round p - 1)
 #pragma unroll 1
-        for (int p = 0; p < G; ++p) {
-            double a = (p == 0) ? 0.0 : __shfl(sse, base + p - 1);
-            bits = 0;
+    for (int pass = 0; pass < NC / NP; ++pass) {
+        // metadata index of candidate c of this pass: +sv0, (+sv1,) -sv0, (-sv1); two of four at once: one magnitude's signs
+        auto index = [&](int c) { return NP == 2 && NC == 4 ? pass + 2 * c : NP == 1 ? pass : c; };
+        double sse[NP], e2[G > 1 ? NP : 1][kBlock];
+        uint32_t bits[NP];
 #pragma unroll
-            for (int k = 0; k < kBlock; ++k) {
-                const double xd = (double)xs[k], eb = xd - (double)q[k], ev = xd - cand;
-                const bool sp = fabs(ev) < fabs(eb);
-                const double e = sp ? ev : eb;
-                a = __builtin_fma(e, e, a);                               // e*e is exact in fp64: same as a + e*e
-                bits |= (uint32_t)sp << k;
+        for (int c = 0; c < NP; ++c) { sse[c] = 0.0; bits[c] = 0u; }
+#pragma unroll
+        for (int k = 0; k < kBlock; k += 2) {
+            float x0 = xs[k], x1 = xs[k + 1];
+            uint32_t word = (k < 8) ? lo : hi;
+            if constexpr (NP < NC) {
+                asm volatile("" : "+v"(x0), "+v"(x1), "+v"(word));
+#pragma unroll
+                for (int c = 0; c < NP; ++c) asm volatile("" : "+v"(sse[c]), "+v"(bits[c]));
             }
-            sse = (sub == p) ? a : sse;
+            const v2f q = decode_pair_f32(word, (k % 8) / 2);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const double xd = (double)(j ? x1 : x0), eb = xd - (double)(j ? q.y : q.x);
+#pragma unroll
+                for (int c = 0; c < NP; ++c) {
+                    const int m = index(c);
+                    const float mag = (FMT != 1 && (m & 1)) ? sv1 : sv0;
+                    const double ev = xd - (double)(m >= NC / 2 ? -mag : mag);
+                    const bool sp = fabs(ev) < fabs(eb);
+                    const double e = sp ? ev : eb;
+                    if (G > 1) e2[c][k + j] = e * e;                      // exact in fp64
+                    else sse[c] = __builtin_fma(e, e, sse[c]);            // the same as sse + e*e
+                    bits[c] |= (uint32_t)sp << (k + j);
+                }
+            }
         }
-        if (G > 1) sse = __shfl(sse, base + G - 1);                       // every lane of the block: the block's sum
-        if (m == 0 || sse < best) {                                       // Eq. 4: smallest error, ties to the smallest index
-            best = sse;
-            meta = m;
-            take = bits;
+        if constexpr (G > 1) {
+            // round p is the one in which lane base + p of the block holds the right starting value (its predecessor's
+            // total of round p - 1)
+#pragma unroll 1
+            for (int p = 0; p < G; ++p) {
+#pragma unroll
+                for (int c = 0; c < NP; ++c) {
+                    double a = (p == 0) ? 0.0 : __shfl(sse[c], base + p - 1);
+#pragma unroll
+                    for (int k = 0; k < kBlock; ++k) a += e2[c][k];
+                    sse[c] = (sub == p) ? a : sse[c];
+                }
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < NP; ++c) {                                    // Eq. 4: smallest error, ties to the smallest index
+            const uint32_t m = (uint32_t)index(c);
+            const double s = G > 1 ? __shfl(sse[c], base + G - 1) : sse[c];   // (every lane of the block: the block's sum)
+            if (m == 0 || s < best || (s == best && m < meta)) {
+                best = s;
+                meta = m;
+                take = bits[c];
+            }
         }
     }
+}
+
+// x / den, correctly rounded, from y = 1 / den (correctly rounded)
+__device__ __forceinline__ float quotient(float x, float den, float y)
+{
+    float q = x * y;
+    q = __builtin_fmaf(__builtin_fmaf(-q, den, x), y, q);
+    return __builtin_fmaf(__builtin_fmaf(-q, den, x), y, q);
+}
+
+// Eq. 4 between the two candidates a and b alone, the sums as above: the block is scaled and rounded, and which elements
+// take a candidate is seen in fp32 -- xs - q is exact, and so is xs - v where v is the nearer of the two.
+template <int FMT, int G, bool SCALED>
+__device__ __forceinline__ uint32_t nearest_two(const float (&xv)[kBlock], float den, uint32_t lo, uint32_t hi, float sv0, float sv1,
+                                                uint32_t a, uint32_t b)
+{
+    constexpr uint32_t NM = (FMT == 1) ? 1 : 2;
+    const uint32_t m0 = a < b ? a : b, m1 = a < b ? b : a;
+    auto value = [&](uint32_t m) { const float v = (NM == 2 && (m & 1u)) ? sv1 : sv0; return m >= NM ? -v : v; };
+    const float v0 = value(m0), v1 = value(m1), y = SCALED ? 1.0f : 1.0f / den;
+    double e0[G > 1 ? kBlock : 1], e1[G > 1 ? kBlock : 1];                // squared errors
+    double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+    for (int k = 0; k < kBlock; k += 2) {
+        float x0 = xv[k], x1 = xv[k + 1];
+        uint32_t word = (k < 8) ? lo : hi;
+        asm volatile("" : "+v"(x0), "+v"(x1), "+v"(word), "+v"(s0), "+v"(s1));   // (one pair after the other: registers)
+        const v2f q = decode_pair_f32(word, (k % 8) / 2);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const float xk = j ? x1 : x0, x = SCALED ? xk : quotient(xk, den, y), eb = x - (j ? q.y : q.x), f0 = x - v0, f1 = x - v1;
+            const double t0 = (double)(fabsf(f0) < fabsf(eb) ? f0 : eb), t1 = (double)(fabsf(f1) < fabsf(eb) ? f1 : eb);
+            if constexpr (G > 1) {
+                e0[k + j] = t0 * t0;                                      // exact
+                e1[k + j] = t1 * t1;
+                asm volatile("" : "+v"(e0[k + j]), "+v"(e1[k + j]));
+            } else {
+                s0 = __builtin_fma(t0, t0, s0);
+                s1 = __builtin_fma(t1, t1, s1);
+            }
+        }
+    }
+    if constexpr (G > 1) {
+        const int sub = (int)(threadIdx.x & 63u) & (G - 1), base = (int)(threadIdx.x & 63u) & ~(G - 1);
+#pragma unroll 1
+        for (int p = 0; p < G; ++p) {
+            double c0 = (p == 0) ? 0.0 : __shfl(s0, base + p - 1), c1 = (p == 0) ? 0.0 : __shfl(s1, base + p - 1);
+#pragma unroll
+            for (int k = 0; k < kBlock; ++k) {
+                c0 += e0[k];
+                c1 += e1[k];
+            }
+            s0 = (sub == p) ? c0 : s0;
+            s1 = (sub == p) ? c1 : s1;
+        }
+        s0 = __shfl(s0, base + G - 1);
+        s1 = __shfl(s1, base + G - 1);
+    }
+    return s1 < s0 ? m1 : m0;
 }
 
 template <typename T, int FMT, int G>
@@ -202,6 +299,7 @@ __global__ __launch_bounds__(256) void encode_kernel(const T* __restrict__ x, in
 {
     constexpr int NM = (FMT == 1) ? 1 : 2;                                // special magnitudes
     constexpr int NV = (int)sizeof(T);                                    // 16-byte vectors per run
+    constexpr bool B16 = sizeof(T) == 2;
     const int64_t nb = cols / kBlock, runs = rows * nb;
     const int64_t first_run = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
     auto load = [&](uint4 (&v)[NV], int64_t run) {
@@ -228,7 +326,7 @@ __global__ __launch_bounds__(256) void encode_kernel(const T* __restrict__ x, in
         if (first_run == 0) *tensor_scale = delta32;
     }
 
-    // several runs per thread, the next one's elements on their way while one is encoded
+    // several runs per thread
 #pragma unroll 1
     for (int64_t gid = first_run; gid < runs; gid += stride) {
         float xv[kBlock];
@@ -245,7 +343,7 @@ __global__ __launch_bounds__(256) void encode_kernel(const T* __restrict__ x, in
                 }
             }
         }
-        load(next, gid + stride < runs ? gid + stride : gid);
+        if (B16) load(next, gid + stride < runs ? gid + stride : gid);
 
         float bmax = 0.0f;
 #pragma unroll
@@ -271,26 +369,24 @@ __global__ __launch_bounds__(256) void encode_kernel(const T* __restrict__ x, in
 
         uint32_t lo = 0, hi = 0, meta = 0;                                    // 16 nibbles, low dword = k 0..7
         if (s != 0.0f) {
-            const float den = delta32 * s;
+            float den = delta32 * s;
             uint32_t tlo = 0, thi = 0;                                        // bit 3 of a nibble: the element takes the special value
-            bool decided = finite && delta32 >= 0x1p-60f && delta32 <= 0x1p60f && bmax <= 9.0625f * den;
+            uint32_t runner = 0;
+            bool two = false, decided = finite && den >= 0x1p-70f && delta32 <= 0x1p60f && bmax <= 512.0f * den;
+            uint32_t took[NM][2];
+#pragma unroll
+            for (int m = 0; m < NM; ++m) took[m][0] = took[m][1] = 0u;
             if (decided) {
                 const float y = 1.0f / den;
-                float all[NM], dir[NM];                                       // gains / 16: sum, and sum with the element's sign
-                uint32_t took[NM][2];
+                float all[NM], dir[NM];                                       // gains / 4096: sum, and sum with the element's sign
 #pragma unroll
-                for (int m = 0; m < NM; ++m) { all[m] = dir[m] = 0.0f; took[m][0] = took[m][1] = 0u; }
+                for (int m = 0; m < NM; ++m) all[m] = dir[m] = 0.0f;
 #pragma unroll
                 for (int k = 0; k < kBlock; k += 2) {
-                    float xs[2];
-#pragma unroll
-                    for (int j = 0; j < 2; ++j) {
-                        float q = xv[k + j] * y;
-                        q = __builtin_fmaf(__builtin_fmaf(-q, den, xv[k + j]), y, q);
-                        xs[j] = __builtin_fmaf(__builtin_fmaf(-q, den, xv[k + j]), y, q);
-                    }
+                    const float xs[2] = {quotient(xv[k], den, y), quotient(xv[k + 1], den, y)};
                     uint32_t& word = (k < 8) ? lo : hi;
                     word = encode_pair(word, xs[0], xs[1], (k % 8) / 2);
+                    if constexpr (B16) { xv[k] = xs[0]; xv[k + 1] = xs[1]; }  // (kept: the next pass needs them often)
                     const v2f q2 = decode_pair_f32(word, (k % 8) / 2);
 #pragma unroll
                     for (int j = 0; j < 2; ++j) {
@@ -299,8 +395,8 @@ __global__ __launch_bounds__(256) void encode_kernel(const T* __restrict__ x, in
 #pragma unroll
                         for (int m = 0; m < NM; ++m) {
                             const float v = m ? sv1 : sv0;
-                            // gain / 16 (below 1 up to 9 scales), 0 where the special value is no better
-                            const float g = __builtin_amdgcn_fmed3f(__builtin_fmaf(fabsf(q), -0.0625f, v * 0.0625f) * (u - v), 0.0f, 1.0f);
+                            // gain / 4096 (below 1 up to 512 scales), 0 where the special value is no better
+                            const float g = __builtin_amdgcn_fmed3f(__builtin_fmaf(fabsf(q), -0x1p-12f, v * 0x1p-12f) * (u - v), 0.0f, 1.0f);
                             all[m] += g;
                             dir[m] += u2f(__builtin_amdgcn_bitop3_b32(f2u(g), f2u(xs[j]), 0x80000000u, 0xF8));
                             // sign bit of 0 - g: set where g > 0; eight elements shift it into the nibbles' top bits
@@ -326,17 +422,24 @@ __global__ __launch_bounds__(256) void encode_kernel(const T* __restrict__ x, in
                     meta = up ? (uint32_t)c : meta;
                     first = up ? gain[c] : first;
                 }
-                // (the absolute term covers the rounding of the fp64 sums themselves)
-                decided = total == 0.0f || first - second > total * ((16.0f * G + 8.0f) * 0x1p-23f) + 1e-9f;
-                const bool one = NM == 2 && (meta & 1u) != 0;
-                const uint32_t mlo = one ? took[NM - 1][0] : took[0][0], mhi = one ? took[NM - 1][1] : took[0][1];
-                const uint32_t flip = meta >= (uint32_t)NM ? 0u : 0xFFFFFFFFu;  // + candidates: elements with a clear sign bit
-                tlo = mlo & (lo ^ flip);
-                thi = mhi & (hi ^ flip);
+                // (the second term covers the rounding of the fp64 sums themselves: each at most 16 G xm^2)
+                const float xm = bmax * y, margin = total * ((16.0f * G + 8.0f) * 0x1p-23f) + 1e-15f * xm * xm;
+                decided = total == 0.0f || first - second > margin;
+                if (!decided) {
+                    int near = 0;
+#pragma unroll
+                    for (int c = 0; c < 2 * NM; ++c) {
+                        const bool close = meta != (uint32_t)c && !(first - gain[c] > margin);
+                        near += close;
+                        runner = close ? (uint32_t)c : runner;
+                    }
+                    two = decided = near == 1;
+                }
+                if (B16) den = 1.0f;
             }
             if (!decided) {
                 uint32_t bits;
-                encode_literal<FMT, G>(xv, den, sv0, sv1, lo, hi, meta, bits);
+                encode_literal<FMT, G, (G == 1 ? 2 : 1)>(xv, den, sv0, sv1, lo, hi, meta, bits);
                 // bit k of a byte-wide mask to bit 4 k + 3
                 auto spread = [](uint32_t b) {
                     b = (b | (b << 12)) & 0x000F000Fu;
@@ -345,6 +448,14 @@ __global__ __launch_bounds__(256) void encode_kernel(const T* __restrict__ x, in
                 };
                 tlo = spread(bits & 0xFFu);
                 thi = spread((bits >> 8) & 0xFFu);
+            }
+            if (two) meta = nearest_two<FMT, G, B16>(xv, den, lo, hi, sv0, sv1, meta, runner);   // (here the elements are needed no more)
+            if (decided) {
+                const bool one = NM == 2 && (meta & 1u) != 0;
+                const uint32_t mlo = one ? took[NM - 1][0] : took[0][0], mhi = one ? took[NM - 1][1] : took[0][1];
+                const uint32_t flip = meta >= (uint32_t)NM ? 0u : 0xFFFFFFFFu;  // + candidates: elements with a clear sign bit
+                tlo = mlo & (lo ^ flip);
+                thi = mhi & (hi ^ flip);
             }
             // Eq. 5 on the packed nibbles: zero keeps code 0x0 whatever its sign, taken elements get the remapped code 0x8
             auto finish = [](uint32_t w, uint32_t taken) {
@@ -360,6 +471,7 @@ __global__ __launch_bounds__(256) void encode_kernel(const T* __restrict__ x, in
             if (FMT == 2) reinterpret_cast<uint16_t*>(scales)[gid / G] = (uint16_t)((meta << 14) | sc);
             else scales[gid / G] = (uint8_t)((meta << (FMT == 0 ? 6 : 7)) | sc);
         }
+        if (!B16 && gid + stride < runs) load(next, gid + stride);
     }
 }
 

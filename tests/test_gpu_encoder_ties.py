@@ -52,3 +52,46 @@ def test_more_runs_than_threads(oracle):
     codes, scales, rts = oracle.quantize(razer.ACT, x, sv=(5.0, 5.0))
     assert np.array_equal(t.codes.cpu().numpy(), codes) and np.array_equal(t.scales.cpu().numpy(), scales)
     assert np.float32(t.tensor_scale.cpu().numpy()[0]) == rts
+
+
+def _lattice(rng, shape, top):
+    """Integers up to 64 under block maxima of `top`: elements scaled to multiples of 6 / top, so that the gains of two
+    special values tie, exactly or up to the rounding of the quotients, in a good part of the blocks."""
+    x = rng.integers(-64, 65, size=shape).astype(np.float32)
+    x[:, ::16] = top
+    return x
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("fmt,sv,block", [(f, sv, b) for f, sv in [(razer.WEIGHT, (5.0, 8.0)), (razer.WEIGHT, (5.0, 5.0)), (razer.WEIGHT, (7.5, 2.5)),
+                                                                    (razer.ACT, (5.0, 5.0))] for b in (16, 32, 64, 128)] +
+                         [(razer.WEIGHT_F16, (5.0, 8.0), 128)])
+def test_two_candidates_that_tie(oracle, dtype, fmt, sv, block):
+    rng = np.random.default_rng(33 + block)
+    x = _lattice(rng, (96, 1024), 64.0)
+    xs = x / np.float32(64.0 / 6.0)
+    gain = np.maximum((5.0 - np.floor(np.abs(xs))) * (2 * np.abs(xs) - np.floor(np.abs(xs)) - 5.0), 0.0) * (np.abs(xs) >= 4.5) * (np.abs(xs) < 5.0)
+    side = [np.where(s * xs > 0, gain, 0.0).reshape(96, -1, block).sum(-1) for s in (1, -1)]
+    assert np.count_nonzero((np.abs(side[0] - side[1]) < 1e-3) & (side[0] > 0)) >= 5        # (exact ties of +5 and -5 from below)
+    for given in (None, 64.0 / 6.0, 64.0 / 6.0 * 2.0 ** -62):
+        v = x * np.float32(2.0 ** -62) if given and given < 1e-9 else x
+        dev = None if given is None else torch.tensor([given], dtype=torch.float32, device="cuda")
+        t = razer.razer_quantize(torch.from_numpy(v).cuda().to(dtype), fmt, sv, tensor_scale=dev, block=block)
+        codes, scales, rts = oracle.quantize(fmt, v, sv=sv, given_tensor_scale=None if given is None else np.float32(given), block=block)
+        assert np.array_equal(t.codes.cpu().numpy(), codes), given
+        assert np.array_equal(t.scales.cpu().numpy().view(scales.dtype), scales), given
+
+
+@pytest.mark.parametrize("fmt,sv,block", [(razer.WEIGHT, (5.0, 8.0), 16), (razer.ACT, (9.5, 9.5), 64), (razer.WEIGHT_F16, (5.0, 9.0), 128)])
+@pytest.mark.parametrize("clip", [8.0, 64.0, 511.0, 513.0, 4096.0])
+def test_blocks_far_above_a_given_scale(oracle, fmt, sv, block, clip):
+    """Block maxima of about `clip` times what the largest scale covers: below 512 the gains decide, above the fp64 sums."""
+    grid = {razer.WEIGHT: 30.0, razer.ACT: 448.0, razer.WEIGHT_F16: 1.9990234375}[fmt]
+    rng = np.random.default_rng(34)
+    x = rng.standard_normal((64, 1024)).astype(np.float32)
+    x[:, 5::block] = -clip * np.float32(grid)
+    x[:, 6::2 * block] = clip * np.float32(grid)
+    t = razer.razer_quantize(torch.from_numpy(x).cuda(), fmt, sv, tensor_scale=torch.tensor([1.0], device="cuda"), block=block)
+    codes, scales, _ = oracle.quantize(fmt, x, sv=sv, given_tensor_scale=np.float32(1.0), block=block)
+    assert np.array_equal(t.codes.cpu().numpy(), codes)
+    assert np.array_equal(t.scales.cpu().numpy().view(scales.dtype), scales)
