@@ -1003,8 +1003,11 @@ __device__ __forceinline__ void gemm_rb_body(
         st = st_next;
     }
     // copies and fragment reads requested for tiles past the end: let them finish before the registers
-    // and the stages they target are used for anything else
+    // and the stages they target are used for anything else (the fragments are named after the wait: to the
+    // compiler their registers are free from their last use on, and it gave them to the epilogue ahead of the wait)
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int mi = 0; mi < MT; ++mi) asm volatile("" : "+v"(af[0][mi]));
 #undef RAZER_LDS_READ128
 #undef RAZER_LDS_READ64
 #undef RAZER_LDS_READ32

@@ -3,6 +3,7 @@ dispatch packet: both were measured to cost far more than the short decode kerne
 (a private array that the compiler failed to keep in registers, or a by-value argument struct
 indexed at run time, each silently add microseconds per workgroup).  Checked on the compiler's
 assembly output; needs hipcc, not a GPU."""
+import functools
 import os
 import re
 import subprocess
@@ -13,6 +14,7 @@ from paper_2501_04052_amd import build
 ALLOWED_SCRATCH = {}      # kernel-name substring -> bytes (none at present)
 
 
+@functools.lru_cache(maxsize=None)
 def _asm(src):
     cmd = [build.hipcc()] + [f for f in build.HIPCC_FLAGS if f != "-fPIC"] + \
           ["--cuda-device-only", "-S", os.path.join(build.CSRC, src), "-o", "-"]
@@ -29,6 +31,80 @@ def test_encoder_keeps_its_waves():
     for name, n in regs.items():
         single = "ELi1EEv" in name                 # last template argument: runs per block
         assert n <= (96 if single else 128), (name, n)
+
+
+def _vector_registers(operands):
+    out = set()
+    for kind, lo, hi in re.findall(r"\b([va])\[(\d+):(\d+)\]", operands):
+        out |= {(kind, i) for i in range(int(lo), int(hi) + 1)}
+    return out | {(kind, int(i)) for kind, i in re.findall(r"\b([va])(\d+)\b", operands)}
+
+
+def _uses_before_wait(lines):
+    """Instructions that touch a register which an LDS read may still be writing, on any path through the kernel.  LDS
+    reads return in order, so s_waitcnt lgkmcnt(n) leaves the newest n in flight; a scalar load among them (None below)
+    may return out of order, then only lgkmcnt(0) tells anything.  The counter has four bits: with 15 in flight the next
+    one waits."""
+    code, labels = [], {}
+    for line in lines:
+        label = re.match(r"(\.L\w+):", line)
+        if label:
+            labels[label.group(1)] = len(code)
+        line = line.split(";")[0].strip()
+        if line and not line.startswith(".") and not line.endswith(":"):
+            op, _, operands = line.partition(" ")
+            code.append((op, operands, _vector_registers(operands)))
+    targets = set(labels.values())
+    found, seen, work = set(), set(), [(0, ())]
+    while work:
+        pc, flying = work.pop()
+        while pc < len(code):
+            if pc in targets:
+                if (pc, flying) in seen:
+                    break
+                seen.add((pc, flying))
+            op, operands, regs = code[pc]
+            if op == "s_endpgm":
+                break
+            if op == "s_waitcnt":
+                n = re.search(r"lgkmcnt\((\d+)\)", operands)
+                if n and (n.group(1) == "0" or None not in flying):
+                    flying = flying[len(flying) - min(len(flying), int(n.group(1))):]
+            else:
+                if regs and any(r and regs & r for r in flying):
+                    found.add("%s %s" % (op, operands))
+                if op.startswith("ds_"):
+                    returns = re.match(r"ds_(read|bpermute|permute|swizzle|\w+_rtn)", op)
+                    flying += (frozenset(_vector_registers(operands.split(",")[0])) if returns else frozenset(),)
+                elif re.match(r"s_(buffer_)?load|s_mem", op):
+                    flying += (None,)
+                flying = flying[-16:]
+            if op.startswith(("s_branch", "s_cbranch")):
+                work.append((labels[operands.strip()], flying))
+                if op == "s_branch":
+                    break
+            pc += 1
+    return found
+
+
+def test_registers_of_lds_reads_are_left_alone_until_their_wait():
+    """The GEMM and small-batch kernels read LDS in inline assembly and place the waits by hand.  To the compiler such a
+    register is written at once and free after its last use: where a wait does not name the registers it guards, only
+    the order of the generated code keeps their users behind it."""
+    kernels = checked = 0
+    for src in ("razer_gemm.hip", "razer_skinny.hip"):
+        for m in re.finditer(r"^(_ZN5razer\S*):[^\n]*\n(.*?)^\.Lfunc_end", _asm(src), re.S | re.M):
+            kernels += 1
+            checked += m.group(2).count("ds_read")
+            bad = _uses_before_wait(m.group(2).split("\n"))
+            assert not bad, (m.group(1), sorted(bad)[:4])
+    assert kernels >= 100 and checked >= 1000
+    # the check itself: a use ahead of the wait, one behind it, a wait that leaves the read in flight, a loop's back edge
+    read, use = "ds_read_b128 v[0:3], v9", "v_mov_b32_e32 v2, 0"
+    assert _uses_before_wait([read, use, "s_waitcnt lgkmcnt(0)", "s_endpgm"]) == {"v_mov_b32_e32 v2, 0"}
+    assert not _uses_before_wait([read, "s_waitcnt lgkmcnt(0)", use, "s_endpgm"])
+    assert _uses_before_wait([read, "ds_read_b32 v5, v9", "s_waitcnt lgkmcnt(1)", "v_add_f32 v1, v5, v6", "s_endpgm"]) == {"v_add_f32 v1, v5, v6"}
+    assert _uses_before_wait([".LBB0_1:", use, read, "s_cbranch_scc1 .LBB0_1", "s_waitcnt lgkmcnt(0)", "s_endpgm"]) == {use, read}
 
 
 def test_no_scratch_no_dispatch_packet():
