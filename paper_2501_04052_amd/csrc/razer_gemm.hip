@@ -1113,9 +1113,10 @@ __global__ __launch_bounds__(64 * NW, (rb_waves_per_simd<NW, KG, MT>())) void ge
 // that every fragment read from LDS feeds two MFMAs (half the LDS reads per MFMA; 256 accumulator registers, one wave
 // per SIMD, three stages).  With nothing else to run while the wave waits, the order of its instructions is the
 // performance: see compute.  What bounds it: instruction issue -- 365 operations besides the 64 MFMAs of a K-tile, at
-// about 5 clocks each when a wave has its SIMD to itself.  The straightforward order (both MFMAs of a slice together, a
-// code pair's six operations in a row) took 1.6-1.8 us per K-tile, this one 1.3.  Against 32 rows per wave:
-// 4096 x 11008 x 4096 379 -> 338 us, 4096 x 8192 x 28672 1768 -> 1613 us.
+// about 5 clocks each when a wave has its SIMD to itself.  One tile alone took 113 us per 64 K-tiles in the
+// straightforward order (both MFMAs of a slice together, a code pair's six operations in a row), 88 us in this one;
+// with every compute unit busy it is 1.8 us per K-tile.  Against 32 rows per wave: 4096 x 11008 x 4096 379 -> 338 us,
+// 4096 x 8192 x 28672 1768 -> 1613 us.  K is at least 2048 (wide_tiles).
 template <bool GB>
 __device__ __forceinline__ void gemm_wide_body(
     const uint8_t* __restrict__ w_codes, const uint8_t* __restrict__ w_scales, const float* __restrict__ w_ts,
@@ -1139,7 +1140,7 @@ __device__ __forceinline__ void gemm_wide_body(
     const int r = lane & 31, h = lane >> 5;
     const int64_t m0 = (int64_t)tile_m * BM, n0 = (int64_t)tile_n * BN;
     const int KT = (int)((k + kBK - 1) / kBK);
-    const int last = KT - 1;
+    const int last = KT - 1;                            // (at least 31: the first two K-tiles are full ones)
     const int64_t scale_ld = GB ? (k >> lb) : (k / 16);
     const uint32_t s_lane = GB ? ((32u * h) >> lb) : 2u * h;          // this lane's byte inside a K-tile's scale bytes
     // this lane's weight row of each block as a uniform base (first row of the block, advanced per K-tile on the
@@ -1173,56 +1174,6 @@ __device__ __forceinline__ void gemm_wide_body(
         a_chunk[i] = c;
         a_src[i] = (row < rows_here ? row : rows_here - 1) * row_bytes + c * 16u;
     }
-    // all copies of K-tile kt into stage st (kt already clamped to the last tile by the caller)
-    auto issue = [&](int kt, int st) {
-        if ((int64_t)(kt + 1) * kBK <= k) {             // a full K-tile (uniform): scalar base + constant lane offsets
-            const uint8_t* ab = abase + (size_t)kt * (kBK * 2);
-#pragma unroll
-            for (int i = 0; i < NU_A; ++i)
-                __builtin_amdgcn_global_load_lds(
-                    (const __attribute__((address_space(1))) void*)(ab + a_src[i]),
-                    (__attribute__((address_space(3))) void*)(As + st * A_STAGE + (wave * NU_A + i) * 1024), 16, 0, 0);
-#pragma unroll
-            for (int i = 0; i < NR; ++i) {
-                uint8_t* bc = Bs + st * B_STAGE + (wave * NR + i) * 1024;
-                uint8_t* bs = Bs + st * B_STAGE + B_CODES + (wave * NR + i) * 256;
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(cfirst[i] + (size_t)kt * 32 + c_off[i]),
-                                                 (__attribute__((address_space(3))) void*)bc, 16, 0, 0);
-                if (GB)
-                    __builtin_amdgcn_global_load_lds(
-                        (const __attribute__((address_space(1))) void*)(sfirst[i] + (((size_t)kt * kBK) >> lb) + s_off[i]),
-                        (__attribute__((address_space(3))) void*)bs, 1, 0, 0);
-                else
-                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(sfirst[i] + (size_t)kt * 4 + s_off[i]),
-                                                     (__attribute__((address_space(3))) void*)bs, 2, 0, 0);
-            }
-            return;
-        }
-#pragma unroll
-        for (int i = 0; i < NU_A; ++i) {
-            const uint32_t kk = (uint32_t)kt * kBK + a_chunk[i] * 8u;
-            const uint32_t off = kk < (uint32_t)k ? a_src[i] + (uint32_t)kt * (kBK * 2u) : a_src[i] - a_chunk[i] * 16u;
-            __builtin_amdgcn_global_load_lds(
-                (const __attribute__((address_space(1))) void*)(abase + off),           // past K: any finite data
-                (__attribute__((address_space(3))) void*)(As + st * A_STAGE + (wave * NU_A + i) * 1024), 16, 0, 0);
-        }
-        const int kc = ((int64_t)kt * kBK + 32 * h < k) ? kt : 0;                       // past K: masked where used
-#pragma unroll
-        for (int i = 0; i < NR; ++i) {
-            uint8_t* bc = Bs + st * B_STAGE + (wave * NR + i) * 1024;
-            uint8_t* bs = Bs + st * B_STAGE + B_CODES + (wave * NR + i) * 256;
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(cfirst[i] + 32 * (uint32_t)kc + c_off[i]),
-                                             (__attribute__((address_space(3))) void*)bc, 16, 0, 0);
-            if (GB)
-                __builtin_amdgcn_global_load_lds(
-                    (const __attribute__((address_space(1))) void*)(sfirst[i] + (((size_t)kc * kBK) >> lb) + s_off[i]),
-                    (__attribute__((address_space(3))) void*)bs, 1, 0, 0);
-            else
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(sfirst[i] + 4 * (uint32_t)kc + s_off[i]),
-                                                 (__attribute__((address_space(3))) void*)bs, 2, 0, 0);
-        }
-    };
-
     v16f acc[NR][MT];
 #pragma unroll
     for (int i = 0; i < NR; ++i)
@@ -1297,6 +1248,10 @@ __device__ __forceinline__ void gemm_wide_body(
                                                  (__attribute__((address_space(3))) void*)(Bs + st * B_STAGE + B_CODES + (wave * NR + i) * 256), 2, 0, 0);
         }
     };
+    auto issue = [&](int kt, int st) {                  // all copies of a K-tile
+#pragma unroll
+        for (int c = 0; c < L; ++c) issue_one(kt, st, c);
+    };
     // Once only copies of a ragged last tile are left: its second 32 elements do not exist, the lanes that would fetch
     // them fetch the first ones of the same row again (their weights are masked).
     auto ragged_offsets = [&]() {
@@ -1358,7 +1313,8 @@ __device__ __forceinline__ void gemm_wide_body(
                     __builtin_amdgcn_sched_barrier(0);
                 };
                 // Waits (not tied to the fragments: sched_barrier keeps everything in this order, and a tied wait counts as a
-                // register write that the compiler separates from the MFMA by a no-op).  Steps 0..2: at most the 8 newest
+                // register write that the compiler separates from the MFMA by a no-op: 0.2-0.8 % slower.  That no use of a
+                // fragment comes ahead of its wait is tested on the generated code).  Steps 0..2: at most the 8 newest
                 // LDS operations are still in flight, this pair's fragments are older; in step 2 also the codes of tile
                 // kt + 1 (q = 1, 4 fragments requested since) and its table entries (q = 3).
                 if (j < 3) {
@@ -1435,7 +1391,7 @@ __device__ __forceinline__ void gemm_wide_body(
     issue(0, 0);
     fill_scaled_lut<0>(wlut, sv0, sv1, tid, NT);
     __syncthreads();                                    // the first tile has landed, LUT ready
-    issue(last < 1 ? last : 1, 1);                      // (a single K-tile repeats itself)
+    issue(1, 1);
     {
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
@@ -1458,7 +1414,6 @@ __device__ __forceinline__ void gemm_wide_body(
 #pragma unroll
         for (int mi = 0; mi < MT; ++mi) RAZER_LDS_READ128(af[0][mi], aoff[0], 4096 * mi);
     }
-    if (last < 2) ragged_offsets();
     int st = 0;                                         // stage of tile kt; tile kt + 3 follows it into the same stage
     for (int kt = 0; kt < KT; ++kt) {
         const int st_next = st == S - 1 ? 0 : st + 1;
@@ -1514,6 +1469,7 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_grouped_kernel(
 template <bool GB>
 static hipError_t launch_wide(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, hipStream_t st)
 {
+    if (k < 2048) return hipErrorInvalidValue;          // (wide_tiles never asks for it)
     const int tiles_m = (int)((m + 255) / 256);
     GemvProblem q[4];
     int t[5] = {0, 0, 0, 0, 0};

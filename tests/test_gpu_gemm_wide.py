@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("m,ns,k,block", [(300, (16500,), 2048, 16), (257, (16640, 40), 2080, 16), (512, (12000, 5000), 2112, 32),
-                                          (300, (17000,), 2176, 128), (512, (33000,), 2080, 32)])
+                                          (300, (17000,), 2176, 128), (512, (17000,), 2080, 32), (512, (12000, 5000), 2080, 32),
+                                          (2048, (24600,), 2080, 16)])          # (the last one: more than three rounds of 128-wide tiles)
 def test_wide_tiles(oracle, m, ns, k, block):
     print("wide tiles m", m, "ns", ns, "k", k, "block", block, flush=True)
     a = synth.activation(m, k, seed=8100 + m)
