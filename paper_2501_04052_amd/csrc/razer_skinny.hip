@@ -405,15 +405,19 @@ static hipError_t launch_ring_w(SvConfig cfg, int count, const GemvProblem* p, i
 
 // 8 waves; 16 for one group of rows and at most 8 activation rows: such a launch has at most one workgroup per compute
 // unit and little data under way, so twice the waves pay (4096 x 11008 at 4 rows 11.0 -> 8.8 us, at 8 rows 11.1 -> 9.8;
-// at 16 rows 12.2 -> 12.7, and with two groups or more 0-15 % slower).  The number of waves is the order of the sum over
-// K; a forced shape keeps 8, so that it stands for one order whatever the number of rows.
+// at 16 rows 12.2 -> 12.7, and with two groups or more 0-15 % slower).  The number of waves decides the order of the sum
+// over K: eight: a launch shape that asks for 8.
 template <int NA, int G, bool GB, int SF, bool IL = false>
-static hipError_t launch_ring_t(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, bool forced, hipStream_t st)
+static hipError_t launch_ring_t(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, bool eight, hipStream_t st)
 {
-    if constexpr (G == 1 && NA <= 2) {
-        if (!forced) return launch_ring_w<NA, G, GB, SF, IL, 16>(cfg, count, p, k, a, m, st);
+    if constexpr (G == 1 && NA == 1) {                            // (up to 4 rows no launch shape is asked for)
+        return launch_ring_w<NA, G, GB, SF, IL, 16>(cfg, count, p, k, a, m, st);
+    } else {
+        if constexpr (G == 1 && NA == 2) {
+            if (!eight) return launch_ring_w<NA, G, GB, SF, IL, 16>(cfg, count, p, k, a, m, st);
+        }
+        return launch_ring_w<NA, G, GB, SF, IL, kRingWaves>(cfg, count, p, k, a, m, st);
     }
-    return launch_ring_w<NA, G, GB, SF, IL, kRingWaves>(cfg, count, p, k, a, m, st);
 }
 
 // Groups of 16 rows per workgroup.  The busiest of the 256 compute units holds ceil(workgroups / 256) workgroups of G
@@ -448,14 +452,18 @@ static hipError_t launch_ring(SvConfig cfg, int count, const GemvProblem* p, int
     int g = ring_groups(ring_row_groups(count, p), m, cfg.f16 != 0);
     int64_t rows = 0;
     for (int i = 0; i < count; ++i) rows += p[i].n;
-    const TuneShape t = tuned_shape(kTuneSmallBatch, m, rows, k);
-    if (t.source && m > kGemvDirectMaxM && t.p[0] == 2 && (t.p[1] == 1 || t.p[1] == 2 || t.p[1] == 3 || (t.p[1] == 4 && !(m > 32 && cfg.f16)) || (t.p[1] == 6 && m <= 32))) g = t.p[1];
-    const bool forced = t.source == 1;
+    // the launch shape on record, a family of 5 rows and more; any forced shape that does not ask for 16 waves keeps 8, so
+    // that it stands for one order of the sum whatever the number of rows
+    TuneShape t{{0, 0, 0, 0}, 0};
+    if (m > kGemvDirectMaxM) t = tuned_shape(kTuneSmallBatch, m, rows, k);
+    const bool shaped = t.source && t.p[0] == 2;
+    if (shaped && (t.p[1] == 1 || t.p[1] == 2 || t.p[1] == 3 || (t.p[1] == 4 && !(m > 32 && cfg.f16)) || (t.p[1] == 6 && m <= 32))) g = t.p[1];
+    const bool eight = shaped && t.p[2] ? t.p[2] != 16 : t.source == 1;
 #define RAZER_RING(NA, G)                                                                  \
     do {                                                                                   \
-        if (cfg.f16) return launch_ring_t<NA, G, false, 1>(cfg, count, p, k, a, m, forced, st);    \
-        if (cfg.lb == 4) return launch_ring_t<NA, G, false, 0>(cfg, count, p, k, a, m, forced, st); \
-        return launch_ring_t<NA, G, true, 0>(cfg, count, p, k, a, m, forced, st);                  \
+        if (cfg.f16) return launch_ring_t<NA, G, false, 1>(cfg, count, p, k, a, m, eight, st);    \
+        if (cfg.lb == 4) return launch_ring_t<NA, G, false, 0>(cfg, count, p, k, a, m, eight, st); \
+        return launch_ring_t<NA, G, true, 0>(cfg, count, p, k, a, m, eight, st);                  \
     } while (0)
 #define RAZER_RING_G(NA)                   \
     do {                                   \
@@ -466,11 +474,11 @@ static hipError_t launch_ring(SvConfig cfg, int count, const GemvProblem* p, int
         RAZER_RING(NA, 6);                 \
     } while (0)
     if (m <= 4 && cfg.il) {                                       // the interleaved layout is a form of 2..4 rows
-        if (g == 1) return launch_ring_t<1, 1, false, 0, true>(cfg, count, p, k, a, m, forced, st);
-        if (g == 2) return launch_ring_t<1, 2, false, 0, true>(cfg, count, p, k, a, m, forced, st);
-        if (g == 3) return launch_ring_t<1, 3, false, 0, true>(cfg, count, p, k, a, m, forced, st);
-        if (g == 4) return launch_ring_t<1, 4, false, 0, true>(cfg, count, p, k, a, m, forced, st);
-        return launch_ring_t<1, 6, false, 0, true>(cfg, count, p, k, a, m, forced, st);
+        if (g == 1) return launch_ring_t<1, 1, false, 0, true>(cfg, count, p, k, a, m, eight, st);
+        if (g == 2) return launch_ring_t<1, 2, false, 0, true>(cfg, count, p, k, a, m, eight, st);
+        if (g == 3) return launch_ring_t<1, 3, false, 0, true>(cfg, count, p, k, a, m, eight, st);
+        if (g == 4) return launch_ring_t<1, 4, false, 0, true>(cfg, count, p, k, a, m, eight, st);
+        return launch_ring_t<1, 6, false, 0, true>(cfg, count, p, k, a, m, eight, st);
     }
     if (cfg.il) return hipErrorInvalidValue;
     if (m <= 4) RAZER_RING_G(1);
@@ -480,7 +488,7 @@ static hipError_t launch_ring(SvConfig cfg, int count, const GemvProblem* p, int
     if (g == 1) RAZER_RING(16, 1);
     if (g == 2) RAZER_RING(16, 2);
     if (g == 3) RAZER_RING(16, 3);
-    return cfg.lb == 4 ? launch_ring_t<16, 4, false, 0>(cfg, count, p, k, a, m, forced, st) : launch_ring_t<16, 4, true, 0>(cfg, count, p, k, a, m, forced, st);
+    return cfg.lb == 4 ? launch_ring_t<16, 4, false, 0>(cfg, count, p, k, a, m, eight, st) : launch_ring_t<16, 4, true, 0>(cfg, count, p, k, a, m, eight, st);
 #undef RAZER_RING_G
 #undef RAZER_RING
 }
@@ -515,9 +523,8 @@ bool ring_serves(SvConfig cfg, int count, const GemvProblem* p, int64_t k, int64
     const int64_t groups = ring_row_groups(count, p);
     if (m >= 2 && m <= kGemvDirectMaxM) {
         if (!cfg.f16 && (cfg.sv0 == 9.5f || cfg.sv1 == 9.5f)) return false;
-        if (tuned_shape(kTuneGemvQuad, m, rows, k).source == 1 || tuned_shape(kTuneGemv, m, rows, k).source == 1) return false;
-        if (groups <= kComputeUnits) return m == 2 ? k >= 8192 : m == 3 ? k >= 6144 : k >= 2048;
-        return m >= 3 && k >= 6144 && groups <= 1024;
+        if (groups <= kComputeUnits ? k < (m == 2 ? 8192 : m == 3 ? 6144 : 2048) : m == 2 || k < 6144 || groups > 1024) return false;
+        return tuned_shape(kTuneGemvQuad, m, rows, k).source != 1 && tuned_shape(kTuneGemv, m, rows, k).source != 1;
     }
     if (m > kRingMaxM) {
         if (!cfg.f16 && tuned_shape(kTuneGemmSlices, m, rows, k).source == 1) return false;

@@ -36,6 +36,7 @@ TuneShape tuned_shape(int family, int64_t m, int64_t n, int64_t k)
     TuneShape out{{0, 0, 0, 0}, 0};
     if (family < 0 || family >= RAZER_TUNE_FAMILIES) return out;
     const Forced& f = forced();
+    if (f.on[family] && f.p[family][0] == -1) return out;
     if (f.on[family]) {
         for (int i = 0; i < 4; ++i) out.p[i] = f.p[family][i];
         out.source = 1;

@@ -31,3 +31,14 @@ def tensor_to_host(t):
     if scales.dtype == np.int16:                       # 16-bit scale words of the FP16-scale format
         scales = scales.view(np.uint16)
     return (t.codes.cpu().numpy(), scales, np.float32(t.tensor_scale.cpu().numpy()[0]))
+
+
+def launched_kernels(fn):
+    """Names of the device kernels that fn() launches: which kernel a case runs on is part of what a test of that
+    kernel claims, and the dispatch is free to change it."""
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        fn()
+        torch.cuda.synchronize()
+    return [e.name for e in p.events() if "razer::" in e.name]

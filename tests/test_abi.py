@@ -42,28 +42,32 @@ def test_header_symbols_are_exported(razer):
 
 
 def test_tuning_hooks_force_lookup_and_workspace(razer):
-    """Forcing a launch shape is visible through the lookup and through the workspace query (the
-    K-in-workgroup small-batch kernel needs none); clearing restores the table / heuristic; a forced
-    shape the kernels are not built for falls back to the heuristic."""
+    """Forcing a launch shape is visible through the lookup and through the workspace query (shapes on record of
+    former small-batch kernels decide the size it reports); clearing restores the table / heuristic; a forced
+    shape the kernels are not built for falls back to the heuristic; -1 is as if nothing were forced or on record."""
     from paper_2501_04052_amd import binding as b
     fam = b.TUNE_SMALL_BATCH
-    # 30000 rows: no table entry, and too many 16-row groups for one round of workgroups -> K-sliced by default
+    # 30000 rows: no table entry, and too many 16-row groups for one round of workgroups -> room for K-slices is reported
     base = razer.razer_workspace_bytes(2, 30000, 4096, 16)
     src0, shape0 = razer.razer_tune_lookup(fam, 16, 30000, 4096)
     assert src0 == 0 and shape0 is None and base == 8 * 16 * 30000 * 4
     razer.razer_tune_force(fam, (1, 1, 2))
     assert razer.razer_tune_lookup(fam, 16, 30000, 4096) == (1, (1, 1, 2, 0))
     assert razer.razer_workspace_bytes(2, 30000, 4096, 16) == 0
-    assert razer.razer_workspace_bytes(2, 30000, 4096, 20) == 8 * 20 * 30000 * 4   # more than 16 rows: K-sliced kernel
+    assert razer.razer_workspace_bytes(2, 30000, 4096, 20) == 8 * 20 * 30000 * 4   # more than 16 rows: K-slices
     razer.razer_tune_force(fam, (0, 8, 1))
     assert razer.razer_workspace_bytes(2, 30000, 4096, 16) == 4 * 16 * 30000 * 4
     assert razer.razer_workspace_bytes(2, 4100, 4096, 16) == 4 * 16 * 4100 * 4
     razer.razer_tune_force(fam, (1, 3, 5))                                        # not a built shape
     assert razer.razer_workspace_bytes(2, 30000, 4096, 16) == base
+    assert razer.razer_tune_lookup(fam, 8, 12288, 4096)[0] == 1
+    razer.razer_tune_force(fam, (-1,))
+    assert razer.razer_tune_lookup(fam, 8, 12288, 4096) == (0, None)               # (an entry of the table)
     razer.razer_tune_force(fam, None)
+    assert razer.razer_tune_lookup(fam, 8, 12288, 4096)[0] == 2
     assert razer.razer_tune_lookup(fam, 16, 30000, 4096)[0] == 0
     assert razer.razer_workspace_bytes(2, 30000, 4096, 16) == base
-    # 4100 rows = 257 groups of 16: two groups per workgroup make one round -> K inside the workgroup, no workspace
+    # 4100 rows = 257 groups of 16: two groups per workgroup make one round -> no workspace is reported
     assert razer.razer_tune_lookup(fam, 16, 4100, 4096)[0] == 0 and razer.razer_workspace_bytes(2, 4100, 4096, 16) == 0
     razer.razer_tune_force(-1, None)
     with pytest.raises(razer.RazerError):

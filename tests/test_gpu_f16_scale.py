@@ -94,8 +94,8 @@ def test_linear_matches_oracle(oracle, m, n, k):
                                    (300, 200, 2048 + 384), (129, 8, 128 * 9), (48, 1000, 34944), (50, 72, 128), (64, 4104, 1152)])
 def test_linear_matrix_core_path_matches_oracle(oracle, m, n, k):
     """From 5 activation rows up the format runs on the matrix cores with bare FP4 operands and a per-block
-    fold in fp32 (up to 64 rows: the K-in-workgroup kernel with one, two or four 16-row fragments; beyond: tiled
-    kernels with K-slices): ragged M and N, odd and even numbers of blocks, several passes per wave, every scale
+    fold in fp32 (the small-batch kernel with one, two or four 16-row fragments, above 64 rows in runs; large products
+    on tiled kernels, tested below): ragged M and N, odd and even numbers of blocks, several steps per wave, every scale
     word field (zero, subnormal and saturated scales included)."""
     print("f16-scale matrix-core linear", m, n, k, flush=True)
     rng = np.random.default_rng(3700 + m + n)
@@ -134,16 +134,13 @@ def test_linear_two_group_kernel_many_tiles(oracle, m, n, k):
     assert max_rel_err(got, y64) <= TOL
 
 
-MV_SHAPES = [None, (1, 1, 1), (1, 1, 2), (1, 1, 3), (1, 1, 4), (1, 2, 1), (1, 2, 2), (1, 2, 3), (1, 2, 4), (1, 2, 8)]
-
-
-@pytest.mark.parametrize("shape", MV_SHAPES)
+@pytest.mark.parametrize("shape", [None, (2, 1, 8), (2, 1, 16), (2, 2, 8), (2, 3, 8), (2, 4, 8), (2, 6, 8), (1, 1, 2)])
 @pytest.mark.parametrize("m,ns,k", [(5, (1000,), 4096 + 128), (16, (328, 200), 1152), (9, (72,), 128), (17, (40, 24, 4), 34944),
                                     (32, (333,), 2048 + 384), (24, (100, 36), 11008)])
 def test_small_batch_kernel_every_launch_shape(oracle, shape, m, ns, k):
-    """5..32 activation rows run on the K-in-workgroup matrix-core kernel with bare FP4 operands and the block
+    """5..32 activation rows run on the small-batch kernel with bare FP4 operands and the block
     scale folded per 128-element step (one and two 16-row activation fragments; single and grouped launches;
-    ragged N; one block to 273 blocks per row, several passes per wave): the default launch shape and every
+    ragged N; one block to 273 blocks per row, several steps per wave): the default launch shape and every
     shape the tuner may force, every scale word field."""
     from paper_2501_04052_amd import binding
     print("f16-scale small batch", shape, m, ns, k, flush=True)

@@ -7,7 +7,7 @@ import torch
 
 import paper_2501_04052_amd as razer
 from paper_2501_04052_amd import binding, synth
-from gpu_util import TOL, bf16_bits_to_dev, dev_to_bf16_bits, max_rel_err, tensor_to_host
+from gpu_util import TOL, bf16_bits_to_dev, dev_to_bf16_bits, launched_kernels, max_rel_err, tensor_to_host
 
 pytestmark = pytest.mark.gpu
 W, A = 0, 1
@@ -210,15 +210,18 @@ def test_block_sizes_register_decode_kernel(oracle, block, m, n, k):
 
 
 @pytest.mark.parametrize("m,n,k", [(64, 4096, 4096), (128, 4096, 11008), (256, 4096, 4096), (100, 11008, 4096)])
-def test_config2_3_mid_batch_single_calls(oracle, m, n, k):
+def test_config2_3_mid_batch_single_calls(oracle, m, n, k, route):
     """o- and down-shaped projections (and a gate-shaped one) at the batch sizes between decode and large
-    GEMMs: register-decode kernel with 64 / 128-row tiles and K-slices, the LDS-staged split-K kernel at 256."""
+    GEMMs: the small-batch kernel, and the kernels it took these shapes from -- register-decode kernel with 64 / 128-row
+    tiles and K-slices, the LDS-staged split-K kernel at 256."""
     _say("mid batch at full size, m=%d n=%d k=%d" % (m, n, k))
     wq = _rand_packed(n, k, seed=8300 + m)
     wt = razer.RazerTensor.from_host(*wq, W, SV)
     a = synth.activation(m, k, seed=2300 + m)
     y = razer.razer_linear(wt, bf16_bits_to_dev(a))
-    torch.cuda.synchronize()
+    names = launched_kernels(lambda: razer.razer_linear(wt, bf16_bits_to_dev(a), out=y))
+    kernel = "ring_kernel<16" if route != "gemm" else {64: "gemm_rb_kernel<4, 2, 1, 2,", 256: "gemm_pp_kernel<"}.get(m, "gemm_rb_kernel<4, 2, 1, 4,")
+    assert any(kernel in x for x in names), names
     rows = np.unique(np.concatenate([synth.sample_indices(m, 32, 9400), [0, m - 1]]))
     cols = np.unique(np.concatenate([synth.sample_indices(n, 160, 9401), [0, n - 1]]))
     y64, _ = oracle.linear(wq, a_bf16=a, rows=rows, cols=cols)
@@ -269,11 +272,13 @@ def test_rows_longer_than_the_32_bit_offset_kernels_take(oracle, m, k):
 
 
 @pytest.mark.parametrize("m", [1, 4, 16, 64, 128, 256, 512, 2048])
-def test_config2_3_grouped_launches_as_benchmarked(oracle, m):
+def test_config2_3_grouped_launches_as_benchmarked(oracle, m, route):
     """The launch configuration bench.py times: {q,k,v} and {gate,up} of the Llama-7B-shaped layer each
-    as ONE razer_linear_grouped call (grouped GEMV, matrix-instruction GEMV, grouped small-batch kernel
-    with its grouped reduction, grouped register-decode GEMM -- with K-slices and the grouped reduction
-    at M = 64, 128, 256).  Whole outputs up to M = 16, sampled rows x columns beyond."""
+    as ONE razer_linear_grouped call (grouped GEMV, matrix-instruction GEMV, small-batch kernel up to M = 64,
+    grouped register-decode GEMM -- kept on it also at M = 64, with K-slices and the grouped reduction at M = 64, 128,
+    256).  Whole outputs up to M = 16, sampled rows x columns beyond."""
+    if route == "gemm" and m <= 32:
+        return                                                    # (the GEMM kernels start at 33 rows)
     _say("grouped launches at full size, m=%d" % m)
     a = synth.activation(m, 4096, seed=2100 + m)
     a_dev = bf16_bits_to_dev(a)

@@ -171,7 +171,7 @@ def test_linear_gemv_many_rows_matches_oracle(oracle, m, n, k):
                                    (17, 70, 32), (32, 129, 4096 + 32), (12, 65, 8192 + 512), (31, 64, 544),
                                    (100, 130, 4096), (129, 384, 512), (300, 260, 1120), (512, 512, 1024),
                                    (257, 257, 224)])
-def test_linear_gemm_matches_oracle(oracle, m, n, k):
+def test_linear_gemm_matches_oracle(oracle, m, n, k, route):
     print("gemm", m, n, k, flush=True)
     err = _linear_case(oracle, m, n, k, seed=500 + m)
     assert err <= TOL, err
@@ -180,15 +180,15 @@ def test_linear_gemm_matches_oracle(oracle, m, n, k):
 @pytest.mark.parametrize("m,n,k", [(33, 100, 96), (48, 130, 1024), (64, 513, 4096 + 32), (64, 64, 11008), (65, 100, 544),
                                    (96, 260, 2048), (128, 513, 4096 + 32), (128, 32, 11008), (100, 1, 4096),
                                    (128, 300, 64), (40, 70, 32)])
-def test_linear_mid_batch_matches_oracle(oracle, m, n, k):
-    """33..128 activation rows: the register-decode kernel with 64- and 128-row tiles; one to sixteen
-    K-slices (the slices meet in the workspace), ragged last K-tile, ragged rows on both sides."""
+def test_linear_mid_batch_matches_oracle(oracle, m, n, k, route):
+    """33..128 activation rows: the small-batch kernel where the dispatch prefers it; the register-decode kernel with 64- and
+    128-row tiles, one to sixteen K-slices (the slices meet in the workspace), ragged last K-tile, ragged rows on both sides."""
     print("gemm mid batch", m, n, k, flush=True)
     err = _linear_case(oracle, m, n, k, seed=900 + m)
     assert err <= TOL, err
 
 
-def test_linear_mid_batch_random_codes_all_scale_bytes(oracle):
+def test_linear_mid_batch_random_codes_all_scale_bytes(oracle, route):
     rng = np.random.default_rng(78)
     n, k = 200, 2048
     codes, scales, ts = _rand_tensor(rng, W, n, k)
@@ -199,7 +199,7 @@ def test_linear_mid_batch_random_codes_all_scale_bytes(oracle):
         assert max_rel_err(dev_to_bf16_bits(razer.razer_linear(wt, bf16_bits_to_dev(a))), y64) <= TOL
 
 
-def test_linear_shapes_around_every_dispatch_boundary(oracle):
+def test_linear_shapes_around_every_dispatch_boundary(oracle, route):
     """Seeded random (n, k) at every activation-row count where the dispatch changes kernels (4|5, 32|33,
     64|65, 128|129, 256|257) plus a few in between; single calls and grouped calls on the same operands."""
     rng = np.random.default_rng(4242)
@@ -362,11 +362,11 @@ def test_linear_grouped_matches_oracle(oracle, m, k):
 
 @pytest.mark.parametrize("m,k,ns", [(5, 512 + 64, [132, 64, 200]), (16, 11008, [132, 64, 200]),
                                     (17, 1024, [132, 64, 200]), (32, 512 + 64, [132, 64, 200]),
-                                    # enough workgroups that each walks through two 64-row blocks; 4100 rows
-                                    # leave the last workgroup of the first matrix one ragged block
+                                    # more groups of 16 rows than compute units; a workgroup that holds the end of the
+                                    # first matrix and the beginning of the second
                                     (8, 8192, [4100, 4096])])
 def test_linear_grouped_small_batch_one_launch(oracle, m, k, ns):
-    """5 <= m <= 32: the matrices' K-slices share one workspace and one reduction launch."""
+    """5 <= m <= 32: one launch of the small-batch kernel for the group, the bits of the single calls."""
     print("grouped small batch", m, k, ns, flush=True)
     rng = np.random.default_rng(2000 + m)
     a = synth.activation(m, k, seed=2001 + m)
@@ -374,8 +374,8 @@ def test_linear_grouped_small_batch_one_launch(oracle, m, k, ns):
     wqs = [_rand_tensor(rng, W, n, k) for n in ns]
     wts = [razer.RazerTensor.from_host(*wq, W, (5.0, 8.0)) for wq in wqs]
     bufs = [torch.full((m, n + 4), 2.0, dtype=torch.bfloat16, device="cuda") for n in ns]
-    # the large case: the K-sliced kernel with two 64-row blocks per workgroup, for the group and for the single
-    # calls alike (left to itself the dispatch picks a launch shape per problem size, and with it a summation order)
+    # the large case: a forced shape, so that the group and the single calls have eight waves alike (left to itself the
+    # dispatch picks the number of waves, and with it a summation order, per problem size)
     from paper_2501_04052_amd import binding
     if max(ns) > 1000:
         razer.razer_tune_force(binding.TUNE_SMALL_BATCH, (0, 4, 2))
@@ -386,7 +386,7 @@ def test_linear_grouped_small_batch_one_launch(oracle, m, k, ns):
             y64, _ = oracle.linear(wq, a_bf16=a)
             assert max_rel_err(dev_to_bf16_bits(b[:, :n]), y64) <= TOL
             assert torch.all(b[:, n:] == 2.0)
-            # the same kernels, one matrix per call: identical bits (same slices, same order)
+            # the same kernel, one matrix per call: identical bits (same order)
             assert torch.equal(b[:, :n], razer.razer_linear(wt, a_dev))
     finally:
         razer.razer_tune_force(binding.TUNE_SMALL_BATCH, None)
@@ -396,8 +396,8 @@ def test_linear_grouped_small_batch_one_launch(oracle, m, k, ns):
                                     (300, [4100, 4096, 4200], 1088)])
 def test_linear_grouped_gemm_one_launch(oracle, m, ns, k):
     """m > 32 with enough output tiles over all matrices: one launch of the register-decode GEMM
-    (128-wide weight tiles in the first case, 256-wide in the second, one round of 128-wide tiles
-    with K halved inside the workgroup in the third); ragged m, n and K-tile."""
+    (128-wide weight tiles in the first and second case, one round of 128-wide tiles with K halved inside
+    the workgroup in the third; the 256-wide ones start at K = 2048); ragged m, n and K-tile."""
     print("grouped gemm", m, ns, k, flush=True)
     rng = np.random.default_rng(2100 + k)
     a = synth.activation(m, k, seed=2101 + k)
@@ -415,9 +415,9 @@ def test_linear_grouped_gemm_one_launch(oracle, m, ns, k):
 
 @pytest.mark.parametrize("m,k,ns", [(33, 512 + 64, [132, 64, 200]), (64, 4096, [132, 64, 200]), (100, 11008, [132, 64]),
                                     (128, 2048 + 32, [132, 64, 200, 4]), (48, 1024, [130, 61])])
-def test_linear_grouped_mid_batch_one_launch(oracle, m, k, ns):
-    """33 <= m <= 128: one launch of the register-decode GEMM over all matrices, K-slices of all of
-    them in one workspace and one reduction launch (one slice in the first case, eight and more in the
+def test_linear_grouped_mid_batch_one_launch(oracle, m, k, ns, route):
+    """33 <= m <= 128: one launch of the small-batch kernel, or of the register-decode GEMM over all matrices, K-slices of all
+    of them in one workspace and one reduction launch (one slice in the first case, eight and more in the
     others); the last case (row counts that are not multiples of 4) runs matrix by matrix."""
     print("grouped mid batch", m, k, ns, flush=True)
     rng = np.random.default_rng(2200 + m)
@@ -481,7 +481,7 @@ def test_block_sizes_quantize_and_dequant_bit_exact(oracle, block, fmt, sv):
 @pytest.mark.parametrize("m,n,k", [(1, 130, 2048 + 256), (3, 66, 11008), (4, 20, 28672),
                                    (2, 12, 2048 * 17 + 128), (8, 300, 1024 + 128), (20, 70, 8192 + 512),
                                    (40, 100, 256), (200, 260, 1152), (300, 513, 1024), (64, 257, 128)])
-def test_block_sizes_linear_matches_oracle(oracle, block, m, n, k):
+def test_block_sizes_linear_matches_oracle(oracle, block, m, n, k, route):
     """Every kernel family (GEMV streaming / multi-pass, small batch, tiled GEMM) with 32-, 64- and
     128-element blocks, random codes and scale bytes."""
     print("block linear", block, m, n, k, flush=True)
@@ -532,7 +532,7 @@ def test_block_sizes_grouped_small_batch_one_launch(oracle, block, m, k, ns):
 @pytest.mark.parametrize("block", [32, 64, 128])
 @pytest.mark.parametrize("m,k,ns", [(8, 1024, (132, 64, 200)), (32, 4096 + 128, (64, 260)), (16, 11008, (132, 64)),
                                     (64, 4096, (132, 64, 200)), (100, 2048 + 128, (132, 64)), (300, 1152, (4100, 4096, 4200))])
-def test_block_sizes_grouped_larger_batches_one_launch(oracle, block, m, k, ns):
+def test_block_sizes_grouped_larger_batches_one_launch(oracle, block, m, k, ns, route):
     """5 <= m: the grouped small-batch kernel and the grouped register-decode GEMM (with and without
     K-slices, two-K-group round) take 32-, 64- and 128-element blocks as well."""
     print("block grouped batch", block, m, k, ns, flush=True)
@@ -659,8 +659,8 @@ def test_grouped_linear_under_graph_replay(oracle):
             assert max_rel_err(dev_to_bf16_bits(e), oracle.linear(wq, a_bf16=a)[0]) <= TOL
 
 
-def test_linear_is_deterministic(oracle):
-    """The kernels that split K (small batch, GEMM with few tiles) add their slices in a fixed order."""
+def test_linear_is_deterministic(oracle, route):
+    """The kernels that split K (small batch over waves, GEMM with few tiles over workgroups) add the parts in a fixed order."""
     rng = np.random.default_rng(1800)
     wq = _rand_tensor(rng, W, 200, 4096)
     wt = razer.RazerTensor.from_host(*wq, W, (5.0, 8.0))

@@ -8,7 +8,7 @@ import torch
 
 import paper_2501_04052_amd as razer
 from paper_2501_04052_amd import binding, synth
-from gpu_util import TOL, bf16_bits_to_dev, dev_to_bf16_bits, max_rel_err
+from gpu_util import TOL, bf16_bits_to_dev, dev_to_bf16_bits, launched_kernels, max_rel_err
 
 pytestmark = pytest.mark.gpu
 W = 0
@@ -75,6 +75,27 @@ def test_grouped_on_packed_weights_is_bit_identical(oracle, m):
     for (wq, _), yc, yp in zip(ws, ys_c, ys_p):
         assert torch.equal(yc, yp)
         assert max_rel_err(dev_to_bf16_bits(yp), oracle.linear(wq, a_bf16=a)[0]) <= TOL
+
+
+@pytest.mark.parametrize("m", [3, 4])
+@pytest.mark.parametrize("n,per_workgroup", [(257 * 16 - 5, 2), (513 * 16 - 8, 3), (800 * 16, 4)])
+def test_many_row_groups_on_the_small_batch_kernel(oracle, m, n, per_workgroup):
+    """3 and 4 rows with long K and 257..1024 groups of 16 rows: two to four groups per workgroup of the small-batch kernel,
+    in both layouts."""
+    k = 6144
+    print("prepack small batch", m, n, k, flush=True)
+    wq, wt = _weights(n, k, 90 + n + m)
+    pk = razer.razer_prepack(wt)
+    a = synth.activation(m, k, seed=91 + m)
+    a_dev = bf16_bits_to_dev(a)
+    y_c, y_p = razer.razer_linear(wt, a_dev), razer.razer_linear(pk, a_dev)
+    for w, il in ((wt, "false"), (pk, "true")):
+        names = launched_kernels(lambda: razer.razer_linear(w, a_dev))
+        assert any("ring_kernel<1, %d, false, 0, 8, %s>" % (per_workgroup, il) in x for x in names), names
+    assert torch.equal(y_c, y_p)
+    cols = np.unique(np.r_[0:40, n // 2:n // 2 + 80, n - 70:n])
+    y64, _ = oracle.linear((wq[0][cols], wq[1][cols], wq[2]), a_bf16=a)
+    assert max_rel_err(dev_to_bf16_bits(y_p)[:, cols], y64) <= TOL
 
 
 def test_uses_outside_the_decode_regime_are_refused():

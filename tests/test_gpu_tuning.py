@@ -7,7 +7,7 @@ import torch
 
 import paper_2501_04052_amd as razer
 from paper_2501_04052_amd import binding, synth
-from gpu_util import TOL, bf16_bits_to_dev, dev_to_bf16_bits, max_rel_err
+from gpu_util import TOL, bf16_bits_to_dev, dev_to_bf16_bits, launched_kernels, max_rel_err
 
 pytestmark = pytest.mark.gpu
 W = 0
@@ -44,21 +44,23 @@ def _check(oracle, family, shape, m, ns, k, block=16, seed=0):
         assert err <= TOL, (family, shape, err)
 
 
-SMALL_BATCH_SHAPES = [(1, 1, 1), (1, 1, 2), (1, 1, 3), (1, 1, 4), (1, 2, 1), (1, 2, 2), (1, 2, 3), (1, 2, 4), (1, 2, 8),
-                      (0, 4, 1), (0, 4, 2), (0, 4, 4), (0, 8, 1)]
+# groups of 16 rows per workgroup and waves (6 groups: up to 32 rows, else the heuristic; 16 waves: one group, up to 8 rows)
+SMALL_BATCH_SHAPES = [(2, 1, 8), (2, 1, 16), (2, 2, 8), (2, 3, 8), (2, 4, 8), (2, 6, 8), (2, 2)]
 
 
 @pytest.mark.parametrize("shape", SMALL_BATCH_SHAPES)
 @pytest.mark.parametrize("m,ns,k,block", [(5, (1000,), 4160, 16), (16, (328, 200), 4160, 16), (9, (72,), 512, 64),
-                                          (16, (100, 36, 4), 34944, 16), (12, (40, 24), 2048 + 128, 128)])
+                                          (16, (100, 36, 4), 34944, 16), (12, (40, 24), 2048 + 128, 128),
+                                          (33, (200, 72), 2048 + 64, 64), (64, (300,), 1152, 128), (40, (68, 36), 96, 32)])
 def test_small_batch_shapes(oracle, shape, m, ns, k, block):
     _check(oracle, binding.TUNE_SMALL_BATCH, shape, m, ns, k, block)
 
 
-def test_small_batch_in_workgroup_shape_is_ignored_above_16_rows(oracle):
-    """17..32 activation rows always take the K-sliced kernel: a forced K-in-workgroup shape falls back."""
-    _check(oracle, binding.TUNE_SMALL_BATCH, (1, 2, 4), 20, (200,), 1024)
-    _check(oracle, binding.TUNE_SMALL_BATCH, (1, 2, 4), 32, (64, 64), 4096)
+@pytest.mark.parametrize("shape", [(1, 1, 2), (1, 2, 8), (0, 4, 4), (0, 8, 1)])
+def test_small_batch_shapes_on_record_only_size_the_workspace(oracle, shape):
+    """Shapes of the kernels that the small-batch kernel replaced: they are accepted, and the call runs as ever."""
+    _check(oracle, binding.TUNE_SMALL_BATCH, shape, 20, (200,), 1024)
+    _check(oracle, binding.TUNE_SMALL_BATCH, shape, 16, (64, 64), 4096)
 
 
 @pytest.mark.parametrize("shape", [(2, 1), (2, 2), (4, 1), (8, 1)])
@@ -86,7 +88,7 @@ def test_gemm_slice_counts(oracle, shape, m, ns, k):
                                           (5, (4100,), 11008, 16), (16, (8200,), 8192, 64)])
 def test_untabled_small_batch_one_round_of_workgroups(oracle, m, ns, k, block):
     """Up to 16 activation rows, no table entry, and a number of 16-row groups that some G <= 4 turns into one
-    round of workgroups: the heuristic takes the K-in-workgroup kernel (no workspace), results as the oracle's."""
+    round of workgroups: no workspace is asked for, results as the oracle's."""
     print("one-round heuristic m", m, "ns", ns, "k", k, "block", block, flush=True)
     assert razer.razer_tune_lookup(binding.TUNE_SMALL_BATCH, m, sum(ns), k)[0] == 0       # the heuristic applies
     if len(ns) == 1:
@@ -104,3 +106,28 @@ def test_untabled_small_batch_one_round_of_workgroups(oracle, m, ns, k, block):
     for (wq, _), y in zip(ws, ys):
         y64, _ = oracle.linear(wq, a_bf16=a)
         assert max_rel_err(dev_to_bf16_bits(y), y64) <= TOL
+
+
+@pytest.mark.parametrize("m,family,shape,kernel", [
+    (8, None, None, "ring_kernel<2, 1, false, 0, 16,"), (8, binding.TUNE_SMALL_BATCH, (2, 1, 8), "ring_kernel<2, 1, false, 0, 8,"),
+    (8, binding.TUNE_SMALL_BATCH, (2, 1, 16), "ring_kernel<2, 1, false, 0, 16,"), (8, binding.TUNE_SMALL_BATCH, (2, 1), "ring_kernel<2, 1, false, 0, 8,"),
+    (8, binding.TUNE_SMALL_BATCH, (-1,), "ring_kernel<2, 1, false, 0, 16,"), (8, binding.TUNE_SMALL_BATCH, (2, 3, 16), "ring_kernel<2, 3, false, 0, 8,"),
+    (4, binding.TUNE_SMALL_BATCH, (2, 3, 8), "ring_kernel<1, 1, false, 0, 16,"), (4, binding.TUNE_GEMV_QUAD, (8,), "gemv_quad_kernel"),
+    (4, binding.TUNE_GEMV_QUAD, (-1,), "ring_kernel<1, 1, false, 0, 16,"), (64, binding.TUNE_GEMM_SLICES, (4,), "gemm_rb_kernel<4, 2, 1, 2,"),
+    (64, binding.TUNE_GEMM_SLICES, (-1,), "ring_kernel<16, 1, false, 0, 8,"), (300, binding.TUNE_GEMM_SLICES, (4,), "gemm_pp_kernel")])
+def test_a_forced_shape_launches_what_its_entry_would(m, family, shape, kernel):
+    """A shape is timed by forcing it and used through the table: the same kernel, waves included.  -1 is the call as it
+    runs with nothing forced, whichever kernel serves it."""
+    n, k = 700, 4096
+    _, wt = _rand_weights(n, k, 9990)
+    a = bf16_bits_to_dev(synth.activation(m, k, seed=9991))
+    if family is not None:
+        razer.razer_tune_force(family, shape)
+    try:
+        razer.razer_linear(wt, a)
+        names = launched_kernels(lambda: razer.razer_linear(wt, a))
+        src = None if family is None else razer.razer_tune_lookup(family, m, n, k)[0]
+    finally:
+        razer.razer_tune_force(-1, None)
+    assert src in (None, 0 if shape == (-1,) else 1)
+    assert any(kernel in x for x in names), names
