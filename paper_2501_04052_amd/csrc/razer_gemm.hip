@@ -24,7 +24,6 @@
 //                    K inside the workgroup when there is about one tile per compute unit; the grouped
 //                    form runs up to four matrices (fused q/k/v, gate/up) as one launch
 // Problems with too few tiles split K over workgroups (fp32 slices in the caller's workspace).
-#include <mutex>
 #include <type_traits>
 
 #include "razer_device.hpp"
@@ -33,24 +32,6 @@
 namespace razer {
 
 constexpr int kBK = 64;
-
-// The large-tile kernels need more dynamic LDS than the default limit; the limit is raised once per
-// kernel and device, on first use.  RAZER_RAISE_LDS_LIMIT expands inside a launch helper that is
-// instantiated once per kernel configuration, so its flags are per kernel; std::call_once makes the
-// first use safe when several host threads launch at once.
-constexpr int kMaxDevices = 16;
-#define RAZER_RAISE_LDS_LIMIT(kern, smem)                                                                  \
-    do {                                                                                                   \
-        static std::once_flag once[kMaxDevices];                                                           \
-        static hipError_t result[kMaxDevices];                                                             \
-        int dev = 0;                                                                                       \
-        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice; \
-        std::call_once(once[dev], [&] {                                                                    \
-            result[dev] = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                         \
-                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)(smem));    \
-        });                                                                                                \
-        if (result[dev] != hipSuccess) return result[dev];                                                 \
-    } while (0)
 
 // LUT entry per scale byte: { block scale (fp32 bits), -(special * scale) as a bf16 pair }.
 template <int FMT>

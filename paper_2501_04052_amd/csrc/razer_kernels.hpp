@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 #include <stdint.h>
+#include <mutex>
 #include "razer_device.hpp"
 
 namespace razer {
@@ -24,6 +25,24 @@ inline void launch(void (*kern)(KArgs...), dim3 grid, dim3 block, size_t smem, h
     const ProbeEvents& ev = probe_events();
     hipExtLaunchKernelGGL(kern, grid, block, (uint32_t)smem, st, ev.start, ev.stop, 0u, static_cast<KArgs>(args)...);
 }
+
+// A kernel that needs more dynamic LDS than the default limit of 64 KiB asks for it first; the limit is raised once per
+// kernel and device, on first use.  RAZER_RAISE_LDS_LIMIT expands inside a launch helper that is
+// instantiated once per kernel configuration, so its flags are per kernel; std::call_once makes the
+// first use safe when several host threads launch at once.
+constexpr int kMaxDevices = 16;
+#define RAZER_RAISE_LDS_LIMIT(kern, smem)                                                                  \
+    do {                                                                                                   \
+        static std::once_flag once[kMaxDevices];                                                           \
+        static hipError_t result[kMaxDevices];                                                             \
+        int dev = 0;                                                                                       \
+        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice; \
+        std::call_once(once[dev], [&] {                                                                    \
+            result[dev] = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                         \
+                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)(smem));    \
+        });                                                                                                \
+        if (result[dev] != hipSuccess) return result[dev];                                                 \
+    } while (0)
 
 // Launch shape of a problem: this thread's forced shape (source 1), else the entry of the built-in table
 // (source 2), else source 0 -- the caller's heuristic applies (razer_tune.hip; families and parameters as in

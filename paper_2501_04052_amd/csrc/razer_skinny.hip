@@ -399,7 +399,10 @@ static hipError_t launch_ring_w(SvConfig cfg, int count, const GemvProblem* p, i
     static_assert(most >= 4, "LDS");
     const int64_t nsteps = (k + 127) / 128;
     const int waves = nsteps < most ? (int)nsteps : most;
-    launch(ring_kernel<NA, G, GB, SF, W, IL>, dim3((groups + G - 1) / G, (unsigned)((m + arg.chunk - 1) / arg.chunk)), 64 * waves, (size_t)waves * ring_wave_bytes<NA, G>(), st, arg);
+    auto kern = ring_kernel<NA, G, GB, SF, W, IL>;
+    constexpr uint32_t lds = (uint32_t)most * ring_wave_bytes<NA, G>();
+    if constexpr (lds > 64u * 1024u) RAZER_RAISE_LDS_LIMIT(kern, lds);
+    launch(kern, dim3((groups + G - 1) / G, (unsigned)((m + arg.chunk - 1) / arg.chunk)), 64 * waves, (size_t)waves * ring_wave_bytes<NA, G>(), st, arg);
     return hipGetLastError();
 }
 
