@@ -170,10 +170,15 @@ def razer_probe_mfma_fp4(iters, workgroups, sink):
     return fl.value
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)   # (not part of torch's documented interface)
+
+
 def _stream():
     # The handle of torch.cuda.current_stream(), asked for each time; building that Stream object took 2.7 of the
     # 6.7 us the host spent on a prepared call (this: 0.3).
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _ptr(t):

@@ -623,6 +623,17 @@ def test_linear_on_side_stream_and_under_graph_replay(oracle):
     assert max_rel_err(dev_to_bf16_bits(eager), y64) <= TOL
 
 
+def test_stream_handle_is_the_current_streams(monkeypatch):
+    from paper_2501_04052_amd import binding
+    side = torch.cuda.Stream()
+    for raw in (binding._raw_stream, None):
+        monkeypatch.setattr(binding, "_raw_stream", raw)
+        assert binding._stream() == torch.cuda.current_stream().cuda_stream
+        with torch.cuda.stream(side):
+            assert binding._stream() == side.cuda_stream
+        assert binding._stream() == torch.cuda.current_stream().cuda_stream != side.cuda_stream
+
+
 def test_grouped_linear_under_graph_replay(oracle):
     """The grouped launches (grouped GEMV, matrix-instruction GEMV, grouped small-batch kernel with
     its grouped reduction through the prepared-call path) captured into a HIP graph: every replay,
