@@ -138,14 +138,15 @@ __device__ __forceinline__ v2f decode_pair_f32(uint32_t word, int i)      // the
 //    wave in seven goes there.  Only what is left -- three candidates that close, non-finite blocks, blocks beyond 512
 //    scales -- takes the literal chain.
 // A thread has one run until the launch has 2^20; such launches wait for loads and for the slowest wave, the larger
-// ones for vector issue with as many waves as registers allow.  Hence the next run is fetched while one is encoded for
-// 16-bit elements only (8 registers, 3 % at 4096 x 4096; the 16 of fp32 cost 5 %), scaled 16-bit elements are kept for
-// nearest_two, and fp32 ones are scaled again there.
+// ones for vector issue with as many waves as registers allow.  Hence the next run is fetched while one is encoded
+// (AHEAD) for 16-bit elements (8 registers, 3 % at 4096 x 4096) and for fp32 weights in blocks of 16 (11008 x 4096 with
+// Eq. 1's pass 78.2 -> 76.0), not where the 16 registers of fp32 cost more waves (blocks of 64 and 128, 3-5 %) or launches
+// seldom reach 2^20 runs (activations); scaled 16-bit elements are kept for nearest_two, fp32 ones are scaled again there.
 // Measured against the kernel that formed all four fp64 sums for every block (us per dispatch, tensor scale given; in
 // parentheses with ties decided by the literal chain): bf16 activations 4096 wide, 64 rows 5.0 (5.8) -> 5.0, 512 rows
 // 6.1 (6.9) -> 5.6, 1024 rows 8.3 (8.8) -> 7.6, 4096 rows 20.2 (18.1) -> 15.6; bf16 weights in blocks of 128, 256 rows
-// 7.1 (10.7) -> 6.9, 4096 rows 45.0 (27.4) -> 20.6; fp32 weights 11008 x 4096 in blocks of 16 62.0 (42.5) -> 42.2 (206 MB,
-// 4.9 TB/s), of 128 120 (49.6) -> 42.4.
+// 7.1 (10.7) -> 6.9, 4096 rows 45.0 (27.4) -> 20.6; fp32 weights 11008 x 4096 in blocks of 16 62.0 (41.5) -> 39.3 (206 MB,
+// 5.2 TB/s), of 128 120 (49.6) -> 42.4.
 
 // Eq. 4 and the codes literally: fp32 division, squared errors in fp64, one chain over the block's elements in index
 // order (lane j of the block continues where lane j - 1 ended).  lo / hi: the 16 codes as the hardware rounds them;
@@ -299,7 +300,7 @@ __global__ __launch_bounds__(256) void encode_kernel(const T* __restrict__ x, in
 {
     constexpr int NM = (FMT == 1) ? 1 : 2;                                // special magnitudes
     constexpr int NV = (int)sizeof(T);                                    // 16-byte vectors per run
-    constexpr bool B16 = sizeof(T) == 2;
+    constexpr bool B16 = sizeof(T) == 2, AHEAD = B16 || (G == 1 && FMT == 0);
     const int64_t nb = cols / kBlock, runs = rows * nb;
     const int64_t first_run = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
     auto load = [&](uint4 (&v)[NV], int64_t run) {
@@ -343,7 +344,7 @@ __global__ __launch_bounds__(256) void encode_kernel(const T* __restrict__ x, in
                 }
             }
         }
-        if (B16) load(next, gid + stride < runs ? gid + stride : gid);
+        if (AHEAD) load(next, gid + stride < runs ? gid + stride : gid);
 
         float bmax = 0.0f;
 #pragma unroll
@@ -471,7 +472,7 @@ __global__ __launch_bounds__(256) void encode_kernel(const T* __restrict__ x, in
             if (FMT == 2) reinterpret_cast<uint16_t*>(scales)[gid / G] = (uint16_t)((meta << 14) | sc);
             else scales[gid / G] = (uint8_t)((meta << (FMT == 0 ? 6 : 7)) | sc);
         }
-        if (!B16 && gid + stride < runs) load(next, gid + stride);
+        if (!AHEAD && gid + stride < runs) load(next, gid + stride);
     }
 }
 

@@ -23,13 +23,14 @@ def _asm(src):
 
 def test_encoder_keeps_its_waves():
     """The block encoder is bound by vector issue and by waiting waves; its rare paths (near ties, non-finite blocks) are
-    compiled into the same kernels and must not take the registers that four waves per SIMD (five for blocks of 16) leave."""
+    compiled into the same kernels and must not take the registers that four waves per SIMD (five for 16-bit elements in
+    blocks of 16) leave: 512 / 4, and 512 / 5 in steps of 8."""
     text = _asm("razer_quantize.hip")
     regs = {m.group(1): int(re.search(r"\.amdhsa_next_free_vgpr (\d+)", m.group(2)).group(1))
             for m in re.finditer(r"\.amdhsa_kernel (\S*encode_kernel\S*)(.*?)\.end_amdhsa_kernel", text, re.S)}
     assert len(regs) == 18
     for name, n in regs.items():
-        single = "ELi1EEv" in name                 # last template argument: runs per block
+        single = "kernelIt" in name and "ELi1EEv" in name        # element type; last template argument: runs per block
         assert n <= (96 if single else 128), (name, n)
 
 
