@@ -1093,11 +1093,13 @@ __global__ __launch_bounds__(64 * NW, (rb_waves_per_simd<NW, KG, MT>())) void ge
 // 256 x 256 tiles for problems with many of them: the register-decode kernel above with 64 weight rows per wave, so
 // that every fragment read from LDS feeds two MFMAs (half the LDS reads per MFMA; 256 accumulator registers, one wave
 // per SIMD, three stages).  With nothing else to run while the wave waits, the order of its instructions is the
-// performance: see compute.  What bounds it: instruction issue -- 365 operations besides the 64 MFMAs of a K-tile, at
-// about 5 clocks each when a wave has its SIMD to itself.  One tile alone took 113 us per 64 K-tiles in the
-// straightforward order (both MFMAs of a slice together, a code pair's six operations in a row), 88 us in this one;
-// with every compute unit busy it is 1.8 us per K-tile.  Against 32 rows per wave: 4096 x 11008 x 4096 379 -> 338 us,
-// 4096 x 8192 x 28672 1768 -> 1613 us.  K is at least 2048 (wide_tiles).
+// performance: see compute.  What bounds it: 365 operations besides the 64 MFMAs of a K-tile, at about 5 clocks each when
+// a wave has its SIMD to itself, which take issue slots from the MFMAs: 2 x 11008 x 4096 at 2048 rows keeps the matrix cores
+// busy 52 % of the cycles; the wave issues in 53 % of its cycles and waits to issue in 31 % (32 rows per wave, on 3 x 4096 x 4096:
+// 50; two waves of 36 and 42).  One tile alone took 113 us per 64 K-tiles in the straightforward order (both MFMAs of a
+// slice together, a code pair's six operations in a row), 88 us in this one; with every compute unit busy it is 1.8 us
+// per K-tile.  Against 32 rows per wave: 4096 x 11008 x 4096 379 -> 338 us, 4096 x 8192 x 28672 1768 -> 1613 us.  K is at
+// least 2048 (wide_tiles).
 template <bool GB>
 __device__ __forceinline__ void gemm_wide_body(
     const uint8_t* __restrict__ w_codes, const uint8_t* __restrict__ w_scales, const float* __restrict__ w_ts,

@@ -329,7 +329,7 @@ def test_prepacked_layout_as_benchmarked(oracle, m):
 @pytest.mark.parametrize("m", [1, 16, 64, 2048])
 def test_fp16_scale_format_as_benchmarked(oracle, m):
     """bench.py's FP16-scale legs: {gate,up}-shaped tensors (2 x 11008 x 4096, blocks of 128, random scale words) as
-    one razer_linear_grouped call -- grouped GEMV at M = 1, the grouped K-in-workgroup kernel at 16, per matrix the
+    one razer_linear_grouped call -- grouped GEMV at M = 1, the small-batch kernel at 16, per matrix the
     four-fragment kernel at 64 and the two-group tiled kernel at 2048.  Whole outputs up to M = 16, sampled beyond."""
     from paper_2501_04052_amd import binding
     _say("FP16-scale format at full size, m=%d" % m)
