@@ -7,7 +7,8 @@
 // -- G x (1 KiB of codes, 64 scale entries) and the step's activation rows -- is copied global -> LDS by the load
 // unit into memory that only this wave reads, so the K loop has no barrier: the wave waits for its own copies, takes
 // the operands into registers, requests its next step into the same place and multiplies while that one is on its
-// way.  Partial sums of the waves meet in LDS after one barrier.  One launch, no workspace.
+// way.  Above 8 rows the activations come in halves of 64 k (one 128-byte line per row), codes and scales still a step
+// at a time and ahead of the step's second half.  Partial sums of the waves meet in LDS after one barrier.  One launch, no workspace.
 //
 // Why through LDS although nothing is shared: the matrix instruction wants 16 rows in 16 neighbouring lanes, and a
 // load whose neighbouring lanes lie in 16 different rows costs the address unit a cache-line lookup per lane.  Read
@@ -15,14 +16,21 @@
 // 16 rows: 35.7 us, 24.6 us with the same bytes read contiguously, 16.5 us without activations).  The copies read
 // 64 to 256 consecutive bytes per row; the order the lanes need comes from the LDS addresses, xor-swizzled so that a
 // 128-bit read of 16 rows hits 16 different bank groups.
-// What bounds it: at 16 rows and 22016 x 4096 the copies alone take 10.6 us, decode and matrix instructions alone 12.
+// What bounds it: the load path of a compute unit, which codes, scales and activations pass one after the other, then
+// the decode.  22016 x 4096 at 16 rows (us; an empty loop 6.6): decode and matrix instructions alone 12.9, codes alone
+// 11.5, with scales 13.5, with activations too 16.7, everything 18.3; 4096 x 11008 at 64 rows: activations alone 18, all
+// copies and all of it 25.5.  More copies in flight per wave (two to four steps) only delay the last wave's data.
 // Measured against the kernels this replaced (K cut into slices that met in a workspace; activations loaded into
 // registers), 7B-shaped layer as 4 calls: 8 rows 59 -> 44 us, 16 rows 65 -> 48, 32 rows 84 -> 60, 64 rows (they took
 // the 64-row tiles of the register-decode GEMM) 110 -> 89; FP16-scale format 8 rows 56 -> 41, 64 rows 215 -> 84.
+#include <type_traits>
+
 #include "razer_device.hpp"
 #include "razer_kernels.hpp"
 
 namespace razer {
+
+typedef uint32_t v2u __attribute__((ext_vector_type(2)));
 
 // 8 codes -> 8 bare, negated FP4 values as bf16, remapped codes patched with `patch` (the negated special
 // value as a bf16 pair): the FP16-scale format, whose scale multiplies the block's partial sum instead.
@@ -82,16 +90,24 @@ __device__ __forceinline__ v4u sk_permute_pairs(v4u a)
 }
 
 // ---------------------------------------------------------------------------------------------
-// NA: activation copies of 4 rows per step (m <= 4 NA); G: groups of 16 weight rows per workgroup.  LDS of a wave: the
-// activations of its step [4 NA rows][256 B], the codes [G][16 rows][64 B], the scale entries [G][16 rows][4] (a 1- or
-// 2-byte copy lands zero-extended in 4 bytes); the partial sums reuse it.
+// NA: activation KiB per step (m <= 4 NA); G: groups of 16 weight rows per workgroup.  LDS of a wave: the activations
+// of its step [4 NA rows][256 B], above 8 rows of half a step [4 NA rows][128 B], the codes [G][16 rows][64 B], the scale
+// entries [G][16 rows][4] (a 1- or 2-byte copy lands zero-extended in 4 bytes); the partial sums reuse it.
+// Halves: half the LDS and half the operand registers, so that all eight waves fit at 64 rows (seven did) and smaller
+// workgroups share a unit; a lane then has 16 elements of each half instead of 32 of the step.  Against whole steps (us):
+// {q,k,v} 3 x 4096 x 4096 at 64 rows 19.0 -> 17.0, 4096 x 4096 11.0 -> 9.5, 2 x 11008 x 4096 at 32 rows 21.9 -> 20.9; at
+// 8 rows, where a half is a quarter of a line per lane group, slower (8192 x 28672 34.7 -> 40), hence whole steps there.
 // SF = 1: the FP16-scale format (one step = one block of 128: one scale word per row).  The operands are bare FP4
 // values and swap roles, so that a lane's four results of a step belong to ITS weight row (lane % 16) and activation
 // rows 4 (lane / 16) + 0..3, and the step's sum is folded into the running sums with the lane's own scale in fp32.
 constexpr int kRingWaves = 8;
 constexpr uint32_t kRingTableBytes = 4096;
+template <int NA>
+constexpr int ring_parts() { return NA > 2 ? 2 : 1; }
+template <int NA>
+constexpr uint32_t ring_act_bytes() { return NA * 1024u / ring_parts<NA>(); }
 template <int NA, int G>
-constexpr uint32_t ring_slot_bytes() { return NA * 1024u + G * 1280u; }
+constexpr uint32_t ring_slot_bytes() { return ring_act_bytes<NA>() + G * 1280u; }
 template <int NA, int G>
 constexpr uint32_t ring_wave_bytes()
 {
@@ -122,7 +138,8 @@ __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
     const int64_t k = arg.k, m0 = (int64_t)blockIdx.y * arg.chunk, m = arg.m - m0 < arg.chunk ? arg.m - m0 : arg.chunk;
     const int lb = arg.lb;
     const uint16_t* a = arg.a + m0 * k;
-    constexpr int NB = (NA + 3) / 4;
+    constexpr int NB = (NA + 3) / 4, H = ring_parts<NA>(), J = 4 / H, AC = NA / H;
+    constexpr uint32_t ACT = ring_act_bytes<NA>(), AROW = 256u / H;
     constexpr uint32_t WAVE = ring_wave_bytes<NA, G>();
     __shared__ uint4 lut[SF ? 1 : 256];
     extern __shared__ __align__(16) uint8_t dyn_smem[];               // [waves][WAVE]
@@ -158,19 +175,19 @@ __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
         crow[gi] = dl * code_ld;
         srow[gi] = dl * scale_ld;
     }
-    uint32_t arow[NA], achk[NA];
+    uint32_t arow[AC], achk[AC];
 #pragma unroll
-    for (int i = 0; i < NA; ++i) {
-        const uint32_t row = 4u * i + (lane >> 4);
+    for (int i = 0; i < AC; ++i) {
+        const uint32_t row = 4u * H * i + (H == 2 ? lane >> 3 : lane >> 4);
         arow[i] = (row < (uint32_t)m ? row : (uint32_t)m - 1u) * (kk32 * 2u);
-        achk[i] = (lane & 15u) ^ (row & 15u);                         // logical 16-byte chunk this lane fetches
+        achk[i] = H == 2 ? (lane & 7u) ^ ((row >> 1) & 7u) : (lane & 15u) ^ (row & 15u);   // logical 16-byte chunk this lane fetches
     }
 #define RAZER_COPY(src, off, dst, bytes)                                                                           \
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)((src) + (off)),              \
                                      (__attribute__((address_space(3))) void*)(dst), bytes, 0, 0)
     uint8_t* ring = dyn_smem + wave * WAVE;
     const uint8_t* abytes = reinterpret_cast<const uint8_t*>(a);
-    auto issue = [&](uint32_t step) {
+    auto issue_weights = [&](uint32_t step) {
         const bool full = 128u * step + 128u <= kk32;                 // uniform
         const uint32_t left = kk32 - 128u * step;                     // elements of this step inside K (>= 32)
         // byte of this step's codes / scale entries inside a row (interleaved layout: 16 steps per run of 2048 elements)
@@ -178,36 +195,45 @@ __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
         const size_t sstep = IL ? (size_t)((step >> 4) * kIlRun + (step & 15u) * 8u) : (size_t)step * 8u;
         const uint32_t wcc = full || wc * 32u < left ? wc : 0u, wpp = full || wp * 32u < left ? wp : 0u;
 #pragma unroll
-        for (int gi = 0; gi < G; ++gi) RAZER_COPY(cbase[gi] + cstep, crow[gi] + wcc * 16u, ring + NA * 1024 + gi * 1024, 16);
+        for (int gi = 0; gi < G; ++gi) RAZER_COPY(cbase[gi] + cstep, crow[gi] + wcc * 16u, ring + ACT + gi * 1024, 16);
 #pragma unroll
         for (int gi = 0; gi < G; ++gi) {
             if constexpr (SF != 0)
-                RAZER_COPY(sbase[gi] + (size_t)step * 2u, srow[gi], ring + (NA + G) * 1024 + gi * 256, 2);
+                RAZER_COPY(sbase[gi] + (size_t)step * 2u, srow[gi], ring + ACT + G * 1024 + gi * 256, 2);
             else if constexpr (GB)
-                RAZER_COPY(sbase[gi], srow[gi] + ((128u * step + 32u * wpp) >> lb), ring + (NA + G) * 1024 + gi * 256, 1);
+                RAZER_COPY(sbase[gi], srow[gi] + ((128u * step + 32u * wpp) >> lb), ring + ACT + G * 1024 + gi * 256, 1);
             else
-                RAZER_COPY(sbase[gi] + sstep, srow[gi] + wpp * 2u, ring + (NA + G) * 1024 + gi * 256, 2);
+                RAZER_COPY(sbase[gi] + sstep, srow[gi] + wpp * 2u, ring + ACT + G * 1024 + gi * 256, 2);
         }
+    };
+    auto issue_acts = [&](uint32_t step, uint32_t part) {
+        const uint32_t left = kk32 - 128u * step, first = part * 64u;      // elements past K: the step's first ones again
 #pragma unroll
-        for (int i = 0; i < NA; ++i)
-            RAZER_COPY(abytes + (size_t)step * 256u, arow[i] + (full || achk[i] * 8u < left ? achk[i] : 0u) * 16u, ring + i * 1024, 16);
+        for (int i = 0; i < AC; ++i)
+            RAZER_COPY(abytes + (size_t)step * 256u, arow[i] + (first + achk[i] * 8u < left ? first + achk[i] * 8u : 0u) * 2u, ring + i * 1024, 16);
     };
     // LDS addresses of this lane's operands inside a slot
     const uint32_t ring_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)ring;
     const uint32_t lut_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint4*)lut;
-    const uint32_t code_lds = ring_lds + NA * 1024u + r * 64u + ((g ^ ((r >> 2) & 3u)) << 4);
-    const uint32_t scale_lds = ring_lds + (NA + G) * 1024u + (4u * r + g) * 4u;
+    // H = 1: the lane's MFMA k-range are 32 elements of the step; H = 2: 16 elements of each half
+    const uint32_t swz = (r >> 2) & 3u;
+    const uint32_t code_lds0 = ring_lds + ACT + r * 64u + (H == 1 ? (g ^ swz) << 4 : (((g >> 1) ^ swz) << 4) + (g & 1u) * 8u);
+    const uint32_t code_lds1 = code_lds0 ^ 32u;
+    const uint32_t scale_lds = ring_lds + ACT + G * 1024u + (H == 1 || SF ? (4u * r + g) * 4u : (4u * r + (g >> 1)) * 4u + (GB ? 0u : g & 1u));
     // (fewer than 16 staged rows: the lanes of the missing ones repeat staged rows, their product columns are never stored)
     const uint32_t ra = NA < 4 ? r & (4u * NA - 1u) : r;
-    uint32_t a_lds[4];
+    uint32_t a_lds[J];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) a_lds[j] = ring_lds + ra * 256u + (((4u * g + j) ^ ra) << 4);
+    for (int j = 0; j < J; ++j) a_lds[j] = ring_lds + ra * AROW + (((J * g + j) ^ (H == 1 ? ra : (ra >> 1) & 7u)) << 4);
 
 #define RAZER_DS128(dst, addr, imm) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(imm))
+#define RAZER_DS64(dst, addr, imm) asm volatile("ds_read_b64 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(imm))
+#define RAZER_DS8(dst, addr, imm) asm volatile("ds_read_u8 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(imm))
 #define RAZER_DS16(dst, addr, imm) asm volatile("ds_read_u16 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(imm))
 
     uint32_t step = wave;                                             // (the host starts at most nsteps waves)
-    issue(step);
+    issue_weights(step);
+    issue_acts(step, 0u);
     if (!SF) {
         for (uint32_t sb = threadIdx.x; sb < 256u; sb += blockDim.x) {
             const v4u e = __builtin_bit_cast(v4u, sk_byte_table(sb, sv0, sv1));
@@ -223,88 +249,113 @@ __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
 #pragma unroll
         for (int b = 0; b < NB; ++b) acc[gi][b] = v4f{0.f, 0.f, 0.f, 0.f};
 
+    typedef typename std::conditional<H == 1, v4u, v2u>::type Codes;
     while (step < nsteps) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");              // this step's copies have landed
-        v4u af[NB][4], cw[G];
-        uint32_t sw[G];
-#pragma unroll
-        for (int gi = 0; gi < G; ++gi) {
-            RAZER_DS16(sw[gi], scale_lds, gi * 256);
-            RAZER_DS128(cw[gi], code_lds, gi * 1024);
-        }
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) RAZER_DS128(af[b][j], a_lds[j], b * 4096);
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-        for (int gi = 0; gi < G; ++gi) asm volatile("" : "+v"(sw[gi]), "+v"(cw[gi]));
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) asm volatile("" : "+v"(af[b][j]));
-        v4u le[G][GB ? 1 : 2];
-        if constexpr (!SF) {
-#pragma unroll
-            for (int gi = 0; gi < G; ++gi) {
-                RAZER_DS128(le[gi][0], lut_lds + (sw[gi] & 255u) * 16u, 0);
-                if constexpr (!GB) RAZER_DS128(le[gi][1], lut_lds + (sw[gi] >> 8) * 16u, 0);
-            }
-        }
         const uint32_t next = step + nwaves;
-        if (next < nsteps) issue(next);                               // (everything of this step has been read)
-        if (128u * step + 128u > kk32) {                              // ragged last step: activations past K are 0 (0 x Inf is not)
-            const uint32_t keep = (128u * step + 32u * g < kk32) ? 0xFFFFFFFFu : 0u;
+        Codes cw[G][H];
+        uint32_t sw[G][SF ? 1 : H];
 #pragma unroll
-            for (int b = 0; b < NB; ++b)
+        for (int h = 0; h < H; ++h) {
+            // what this part reads has landed: in the second half the next step's codes and scales may be under way
+            if (h == 1 && next < nsteps) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * G) : "memory");
+            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            v4u af[NB][J];
+            if (h == 0) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) af[b][j] &= keep;
-        }
-        if constexpr (!SF) {
-#pragma unroll
-            for (int b = 0; b < NB; ++b)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) af[b][j] = sk_permute_pairs(af[b][j]);
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-            for (int gi = 0; gi < G; ++gi) {
-                asm volatile("" : "+v"(le[gi][0]));
-                if constexpr (!GB) asm volatile("" : "+v"(le[gi][1]));
-            }
-        }
-#pragma unroll
-        for (int gi = 0; gi < G; ++gi) {
-            if constexpr (SF != 0) {
-                float bs, sv;
-                decode_scale_word(sw[gi], sv0, sv1, bs, sv);
-                const uint32_t nsv = (uint32_t)f32_to_bf16_rne(-sv);
-                v4f blk[NB];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const v8bf wf = sk_decode_dword_bare(cw[gi][j], nsv | (nsv << 16));
-#pragma unroll
-                    for (int b = 0; b < NB; ++b)
-                        blk[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, af[b][j]), wf,
-                                                                         j == 0 ? v4f{0.f, 0.f, 0.f, 0.f} : blk[b], 0, 0, 0);
+                for (int gi = 0; gi < G; ++gi) {
+                    if constexpr (H == 1 || SF) RAZER_DS16(sw[gi][0], scale_lds, gi * 256);
+                    else { RAZER_DS8(sw[gi][0], scale_lds, gi * 256); RAZER_DS8(sw[gi][H - 1], scale_lds, gi * 256 + 8); }
+                    if constexpr (H == 1) RAZER_DS128(cw[gi][0], code_lds0, gi * 1024);
+                    else { RAZER_DS64(cw[gi][0], code_lds0, gi * 1024); RAZER_DS64(cw[gi][H - 1], code_lds1, gi * 1024); }
                 }
+            }
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int j = 0; j < J; ++j) RAZER_DS128(af[b][j], a_lds[j], b * 16 * AROW);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            if (h == 0) {
+#pragma unroll
+                for (int gi = 0; gi < G; ++gi)
+#pragma unroll
+                    for (int i = 0; i < H; ++i) {
+                        asm volatile("" : "+v"(cw[gi][i]));
+                        if (!SF || i == 0) asm volatile("" : "+v"(sw[gi][SF ? 0 : i]));
+                    }
+            }
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int j = 0; j < J; ++j) asm volatile("" : "+v"(af[b][j]));
+            v4u le[G][GB || H == 2 ? 1 : 2];
+            if constexpr (!SF) {
+#pragma unroll
+                for (int gi = 0; gi < G; ++gi) {
+                    RAZER_DS128(le[gi][0], lut_lds + (H == 2 ? sw[gi][h] : sw[gi][h] & 255u) * 16u, 0);
+                    if constexpr (!GB && H == 1) RAZER_DS128(le[gi][1], lut_lds + (sw[gi][0] >> 8) * 16u, 0);
+                }
+            }
+            // (everything that the copies overwrite has been read)
+            if (h + 1 < H) issue_acts(step, 1u);
+            if (next < nsteps) {
+                if (h == 0) issue_weights(next);
+                if (h + 1 == H) issue_acts(next, 0u);
+            }
+            if (128u * step + 128u > kk32) {                              // ragged last step: activations past K are 0 (0 x Inf is not)
+                const uint32_t keep = (128u * step + 64u * h + 8u * J * g < kk32) ? 0xFFFFFFFFu : 0u;
 #pragma unroll
                 for (int b = 0; b < NB; ++b)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) acc[gi][b][i] = __builtin_fmaf(bs, blk[b][i], acc[gi][b][i]);
-            } else {
+                    for (int j = 0; j < J; ++j) af[b][j] &= keep;
+            }
+            if constexpr (!SF) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const v8bf wf = sk_decode_dword_table(cw[gi][j], le[gi][(GB || j < 2) ? 0 : 1]);
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int j = 0; j < J; ++j) af[b][j] = sk_permute_pairs(af[b][j]);
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+                for (int gi = 0; gi < G; ++gi) {
+                    asm volatile("" : "+v"(le[gi][0]));
+                    if constexpr (!GB && H == 1) asm volatile("" : "+v"(le[gi][1]));
+                }
+            }
+#pragma unroll
+            for (int gi = 0; gi < G; ++gi) {
+                if constexpr (SF != 0) {
+                    float bs, sv;
+                    decode_scale_word(sw[gi][0], sv0, sv1, bs, sv);
+                    const uint32_t nsv = (uint32_t)f32_to_bf16_rne(-sv);
+                    v4f blk[NB];
+#pragma unroll
+                    for (int j = 0; j < J; ++j) {
+                        const v8bf wf = sk_decode_dword_bare(cw[gi][h][j], nsv | (nsv << 16));
+#pragma unroll
+                        for (int b = 0; b < NB; ++b)
+                            blk[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, af[b][j]), wf,
+                                                                             j == 0 ? v4f{0.f, 0.f, 0.f, 0.f} : blk[b], 0, 0, 0);
+                    }
 #pragma unroll
                     for (int b = 0; b < NB; ++b)
-                        acc[gi][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, __builtin_bit_cast(v8bf, af[b][j]), acc[gi][b], 0, 0, 0);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) acc[gi][b][i] = __builtin_fmaf(bs, blk[b][i], acc[gi][b][i]);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < J; ++j) {
+                        const v8bf wf = sk_decode_dword_table(cw[gi][h][j], le[gi][(GB || H == 2 || j < 2) ? 0 : 1]);
+#pragma unroll
+                        for (int b = 0; b < NB; ++b)
+                            acc[gi][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, __builtin_bit_cast(v8bf, af[b][j]), acc[gi][b], 0, 0, 0);
+                    }
                 }
             }
         }
         step = next;
     }
 #undef RAZER_DS128
+#undef RAZER_DS64
 #undef RAZER_DS16
+#undef RAZER_DS8
 #undef RAZER_COPY
 
     // partial sums in the wave's own ring (all its copies have landed and been read)
@@ -371,7 +422,7 @@ static int64_t ring_chunk(int64_t m)
 }
 
 template <int NA, int G, bool GB, int SF, bool IL, int W>
-static hipError_t launch_ring_w(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, hipStream_t st)
+static hipError_t launch_ring_w(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, bool eight, hipStream_t st)
 {
     RingArgs arg;
     uint32_t groups = 0;
@@ -393,12 +444,14 @@ static hipError_t launch_ring_w(SvConfig cfg, int count, const GemvProblem* p, i
     arg.chunk = (int)ring_chunk(m);
     arg.a = a;
     arg.lb = cfg.lb;
-    // as many of the W waves as their LDS leaves room for (64 activation rows and more than 2 groups: 7 of 8)
+    // as many of the W waves as their LDS leaves room for
     constexpr uint32_t fit = (kLdsBytes - kRingTableBytes) / ring_wave_bytes<NA, G>();
     constexpr int most = fit < (uint32_t)W ? (int)fit : W;
     static_assert(most >= 4, "LDS");
     const int64_t nsteps = (k + 127) / 128;
-    const int waves = nsteps < most ? (int)nsteps : most;
+    const int64_t wgs = (int64_t)((groups + G - 1) / G) * ((m + arg.chunk - 1) / arg.chunk);
+    const int use = NA == 16 && wgs > kComputeUnits && !eight ? 4 : most;
+    const int waves = nsteps < use ? (int)nsteps : use;
     auto kern = ring_kernel<NA, G, GB, SF, W, IL>;
     constexpr uint32_t lds = (uint32_t)most * ring_wave_bytes<NA, G>();
     if constexpr (lds > 64u * 1024u) RAZER_RAISE_LDS_LIMIT(kern, lds);
@@ -406,28 +459,32 @@ static hipError_t launch_ring_w(SvConfig cfg, int count, const GemvProblem* p, i
     return hipGetLastError();
 }
 
-// 8 waves; 16 for one group of rows and at most 8 activation rows: such a launch has at most one workgroup per compute
-// unit and little data under way, so twice the waves pay (4096 x 11008 at 4 rows 11.0 -> 8.8 us, at 8 rows 11.1 -> 9.8;
-// at 16 rows 12.2 -> 12.7, and with two groups or more 0-15 % slower).  The number of waves decides the order of the sum
-// over K: eight: a launch shape that asks for 8.
+// 8 waves; 16 for one group of rows and at most 16 activation rows: such a launch has at most one workgroup per compute
+// unit and little data under way, so twice the waves pay (4096 x 11008 at 4 rows 11.0 -> 8.8 us, at 8 rows 11.1 -> 9.8, at
+// 16 rows 13.7 -> 12.3, 2048 x 8192 8.7 -> 7.6; at 24 and 32 rows within 2 %, and with two groups or more 0-15 % slower).
+// 4 above 32 rows when the workgroups outnumber the compute units: three or four of them then share a unit, each at
+// another point of its steps (2 x 11008 x 4096 at 64 rows 31.4 -> 28.9; with one workgroup per unit 8 stay faster:
+// {q,k,v} 3 x 4096 x 4096 17.0, with 4 waves 18.4).  The number of waves decides the order of the sum over K: eight: a
+// launch shape that asks for 8.
 template <int NA, int G, bool GB, int SF, bool IL = false>
 static hipError_t launch_ring_t(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, bool eight, hipStream_t st)
 {
     if constexpr (G == 1 && NA == 1) {                            // (up to 4 rows no launch shape is asked for)
-        return launch_ring_w<NA, G, GB, SF, IL, 16>(cfg, count, p, k, a, m, st);
+        return launch_ring_w<NA, G, GB, SF, IL, 16>(cfg, count, p, k, a, m, eight, st);
     } else {
-        if constexpr (G == 1 && NA == 2) {
-            if (!eight) return launch_ring_w<NA, G, GB, SF, IL, 16>(cfg, count, p, k, a, m, st);
+        if constexpr (G == 1 && NA <= 4) {
+            if (!eight) return launch_ring_w<NA, G, GB, SF, IL, 16>(cfg, count, p, k, a, m, eight, st);
         }
-        return launch_ring_w<NA, G, GB, SF, IL, kRingWaves>(cfg, count, p, k, a, m, st);
+        return launch_ring_w<NA, G, GB, SF, IL, kRingWaves>(cfg, count, p, k, a, m, eight, st);
     }
 }
 
 // Groups of 16 rows per workgroup.  The busiest of the 256 compute units holds ceil(workgroups / 256) workgroups of G
 // groups each; what a workgroup spends on its activations (m x K, whatever G is) grows with m / G: about 5.5 % of a
 // group's time per activation row.  Six groups leave one workgroup of eight waves per unit, which overlaps less
-// (15 %).  Measured over 1024 x 1024 .. 57344 x 8192 at 4..64 rows this picks the fastest G or one within 3 % of it:
-// 4096 rows 1; 8192 or 5003 rows 2; {q,k,v} 3 x 4096 or 10240 rows 3; 2 x 11008 rows 3, with 32 activation rows 6.
+// (15 %, with activations in halves 30 %: 2 x 11008 x 4096 at 24 rows 21.3 us against 20.1 with three groups).  Measured
+// over 1024 x 1024 .. 57344 x 8192 at 4..64 rows this picks the fastest G or one within 5 % of it: 4096 rows 1; 8192 or
+// 5003 rows 2; {q,k,v} 3 x 4096, 10240 or 2 x 11008 rows 3.
 // More than 32 activation rows take at most 4 groups (the FP16-scale format 3): six do not fit the registers.
 static int ring_groups(int64_t groups, int64_t m, bool f16)
 {
@@ -438,7 +495,7 @@ static int ring_groups(int64_t groups, int64_t m, bool f16)
     for (int g : {1, 2, 3, 4, 6}) {
         if (m > 32 && g > (f16 ? 3 : 4)) continue;
         const int64_t wgs = chunks * ((groups + g - 1) / g);
-        const double c = (double)(g * ((wgs + kComputeUnits - 1) / kComputeUnits)) * (1.0 + 0.055 * (double)m / g) * (g == 6 ? 1.15 : 1.0);
+        const double c = (double)(g * ((wgs + kComputeUnits - 1) / kComputeUnits)) * (1.0 + 0.055 * (double)m / g) * (g == 6 ? (m > 8 ? 1.3 : 1.15) : 1.0);
         if (g == 1 || c < cost) { best = g; cost = c; }
     }
     return best;
