@@ -7,7 +7,7 @@
 // -- G x (1 KiB of codes, 64 scale entries) and the step's activation rows -- is copied global -> LDS by the load
 // unit into memory that only this wave reads, so the K loop has no barrier: the wave waits for its own copies, takes
 // the operands into registers, requests its next step into the same place and multiplies while that one is on its
-// way.  Above 8 rows the activations come in halves of 64 k (one 128-byte line per row), codes and scales still a step
+// way.  Above 32 rows the activations come in halves of 64 k (one 128-byte line per row), codes and scales still a step
 // at a time and ahead of the step's second half.  Partial sums of the waves meet in LDS after one barrier.  One launch, no workspace.
 //
 // Why through LDS although nothing is shared: the matrix instruction wants 16 rows in 16 neighbouring lanes, and a
@@ -91,27 +91,28 @@ __device__ __forceinline__ v4u sk_permute_pairs(v4u a)
 
 // ---------------------------------------------------------------------------------------------
 // NA: activation KiB per step (m <= 4 NA); G: groups of 16 weight rows per workgroup.  LDS of a wave: the activations
-// of its step [4 NA rows][256 B], above 8 rows of half a step [4 NA rows][128 B], the codes [G][16 rows][64 B], the scale
+// of its step [4 NA rows][256 B], in ring_parts() = 2 of half a step [4 NA rows][128 B], the codes [G][16 rows][64 B], the scale
 // entries [G][16 rows][4] (a 1- or 2-byte copy lands zero-extended in 4 bytes); the partial sums reuse it.
 // Halves: half the LDS and half the operand registers, so that all eight waves fit at 64 rows (seven did) and smaller
 // workgroups share a unit; a lane then has 16 elements of each half instead of 32 of the step.  Against whole steps (us):
-// {q,k,v} 3 x 4096 x 4096 at 64 rows 19.0 -> 17.0, 4096 x 4096 11.0 -> 9.5, 2 x 11008 x 4096 at 32 rows 21.9 -> 20.9; at
-// 8 rows, where a half is a quarter of a line per lane group, slower (8192 x 28672 34.7 -> 40), hence whole steps there.
+// {q,k,v} 3 x 4096 x 4096 at 64 rows 19.0 -> 17.0, 4096 x 4096 11.0 -> 9.5; with 16 waves (below) 4096 x 11008 at
+// 9 rows 11.8 -> 10.7.  Elsewhere up to 32 rows slower (8192 x 8192 at 9 rows 13.1 -> 14.1, 2 x 11008 x 4096 with FP16
+// scales at 32 rows 20.4 -> 22.2): whole steps there.
 // SF = 1: the FP16-scale format (one step = one block of 128: one scale word per row).  The operands are bare FP4
 // values and swap roles, so that a lane's four results of a step belong to ITS weight row (lane % 16) and activation
 // rows 4 (lane / 16) + 0..3, and the step's sum is folded into the running sums with the lane's own scale in fp32.
 constexpr int kRingWaves = 8;
 constexpr uint32_t kRingTableBytes = 4096;
-template <int NA>
-constexpr int ring_parts() { return NA > 2 ? 2 : 1; }
-template <int NA>
-constexpr uint32_t ring_act_bytes() { return NA * 1024u / ring_parts<NA>(); }
-template <int NA, int G>
-constexpr uint32_t ring_slot_bytes() { return ring_act_bytes<NA>() + G * 1280u; }
-template <int NA, int G>
+template <int NA, int W>
+constexpr int ring_parts() { return NA == 16 || (NA == 4 && W == 16) ? 2 : 1; }
+template <int NA, int W>
+constexpr uint32_t ring_act_bytes() { return NA * 1024u / ring_parts<NA, W>(); }
+template <int NA, int G, int W>
+constexpr uint32_t ring_slot_bytes() { return ring_act_bytes<NA, W>() + G * 1280u; }
+template <int NA, int G, int W>
 constexpr uint32_t ring_wave_bytes()
 {
-    const uint32_t slot = ring_slot_bytes<NA, G>(), part = G * ((NA + 3) / 4) * 1024u;
+    const uint32_t slot = ring_slot_bytes<NA, G, W>(), part = G * ((NA + 3) / 4) * 1024u;
     return slot > part ? slot : part;
 }
 
@@ -138,9 +139,9 @@ __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
     const int64_t k = arg.k, m0 = (int64_t)blockIdx.y * arg.chunk, m = arg.m - m0 < arg.chunk ? arg.m - m0 : arg.chunk;
     const int lb = arg.lb;
     const uint16_t* a = arg.a + m0 * k;
-    constexpr int NB = (NA + 3) / 4, H = ring_parts<NA>(), J = 4 / H, AC = NA / H;
-    constexpr uint32_t ACT = ring_act_bytes<NA>(), AROW = 256u / H;
-    constexpr uint32_t WAVE = ring_wave_bytes<NA, G>();
+    constexpr int NB = (NA + 3) / 4, H = ring_parts<NA, W>(), J = 4 / H, AC = NA / H;
+    constexpr uint32_t ACT = ring_act_bytes<NA, W>(), AROW = 256u / H;
+    constexpr uint32_t WAVE = ring_wave_bytes<NA, G, W>();
     __shared__ uint4 lut[SF ? 1 : 256];
     extern __shared__ __align__(16) uint8_t dyn_smem[];               // [waves][WAVE]
     const uint32_t lane = threadIdx.x & 63u, nwaves = blockDim.x >> 6;
@@ -187,31 +188,37 @@ __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
                                      (__attribute__((address_space(3))) void*)(dst), bytes, 0, 0)
     uint8_t* ring = dyn_smem + wave * WAVE;
     const uint8_t* abytes = reinterpret_cast<const uint8_t*>(a);
-    auto issue_weights = [&](uint32_t step) {
+    // the copies of a step: its codes and scales, the activations of a part of it
+    auto issue = [&](uint32_t step, auto weights, auto acts, uint32_t part) {
         const bool full = 128u * step + 128u <= kk32;                 // uniform
         const uint32_t left = kk32 - 128u * step;                     // elements of this step inside K (>= 32)
         // byte of this step's codes / scale entries inside a row (interleaved layout: 16 steps per run of 2048 elements)
         const size_t cstep = IL ? (size_t)((step >> 4) * kIlRun + (step & 15u) * 64u) : (size_t)step * 64u;
         const size_t sstep = IL ? (size_t)((step >> 4) * kIlRun + (step & 15u) * 8u) : (size_t)step * 8u;
         const uint32_t wcc = full || wc * 32u < left ? wc : 0u, wpp = full || wp * 32u < left ? wp : 0u;
+        if constexpr (decltype(weights)::value) {
 #pragma unroll
-        for (int gi = 0; gi < G; ++gi) RAZER_COPY(cbase[gi] + cstep, crow[gi] + wcc * 16u, ring + ACT + gi * 1024, 16);
+            for (int gi = 0; gi < G; ++gi) RAZER_COPY(cbase[gi] + cstep, crow[gi] + wcc * 16u, ring + ACT + gi * 1024, 16);
 #pragma unroll
-        for (int gi = 0; gi < G; ++gi) {
-            if constexpr (SF != 0)
-                RAZER_COPY(sbase[gi] + (size_t)step * 2u, srow[gi], ring + ACT + G * 1024 + gi * 256, 2);
-            else if constexpr (GB)
-                RAZER_COPY(sbase[gi], srow[gi] + ((128u * step + 32u * wpp) >> lb), ring + ACT + G * 1024 + gi * 256, 1);
-            else
-                RAZER_COPY(sbase[gi] + sstep, srow[gi] + wpp * 2u, ring + ACT + G * 1024 + gi * 256, 2);
+            for (int gi = 0; gi < G; ++gi) {
+                if constexpr (SF != 0)
+                    RAZER_COPY(sbase[gi] + (size_t)step * 2u, srow[gi], ring + ACT + G * 1024 + gi * 256, 2);
+                else if constexpr (GB)
+                    RAZER_COPY(sbase[gi], srow[gi] + ((128u * step + 32u * wpp) >> lb), ring + ACT + G * 1024 + gi * 256, 1);
+                else
+                    RAZER_COPY(sbase[gi] + sstep, srow[gi] + wpp * 2u, ring + ACT + G * 1024 + gi * 256, 2);
+            }
+        }
+        if constexpr (decltype(acts)::value) {
+            if constexpr (NA == 8) __builtin_amdgcn_sched_barrier(0); // (the first copies ahead of these addresses: 2 %)
+            const uint32_t first = part * (128u / H);                 // elements past K: the step's first ones again
+#pragma unroll
+            for (int i = 0; i < AC; ++i)
+                RAZER_COPY(abytes + (size_t)step * 256u, arow[i] + (full || first + achk[i] * 8u < left ? first / 8u + achk[i] : 0u) * 16u, ring + i * 1024, 16);
         }
     };
-    auto issue_acts = [&](uint32_t step, uint32_t part) {
-        const uint32_t left = kk32 - 128u * step, first = part * 64u;      // elements past K: the step's first ones again
-#pragma unroll
-        for (int i = 0; i < AC; ++i)
-            RAZER_COPY(abytes + (size_t)step * 256u, arow[i] + (first + achk[i] * 8u < left ? first + achk[i] * 8u : 0u) * 2u, ring + i * 1024, 16);
-    };
+    constexpr std::true_type yes;
+    constexpr std::false_type no;
     // LDS addresses of this lane's operands inside a slot
     const uint32_t ring_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)ring;
     const uint32_t lut_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint4*)lut;
@@ -232,8 +239,7 @@ __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
 #define RAZER_DS16(dst, addr, imm) asm volatile("ds_read_u16 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(imm))
 
     uint32_t step = wave;                                             // (the host starts at most nsteps waves)
-    issue_weights(step);
-    issue_acts(step, 0u);
+    issue(step, yes, yes, 0u);
     if (!SF) {
         for (uint32_t sb = threadIdx.x; sb < 256u; sb += blockDim.x) {
             const v4u e = __builtin_bit_cast(v4u, sk_byte_table(sb, sv0, sv1));
@@ -251,13 +257,12 @@ __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
 
     typedef typename std::conditional<H == 1, v4u, v2u>::type Codes;
     while (step < nsteps) {
-        const uint32_t next = step + nwaves;
         Codes cw[G][H];
         uint32_t sw[G][SF ? 1 : H];
 #pragma unroll
         for (int h = 0; h < H; ++h) {
             // what this part reads has landed: in the second half the next step's codes and scales may be under way
-            if (h == 1 && next < nsteps) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * G) : "memory");
+            if (h == 1 && step + nwaves < nsteps) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * G) : "memory");
             else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             v4u af[NB][J];
             if (h == 0) {
@@ -296,10 +301,12 @@ __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
                 }
             }
             // (everything that the copies overwrite has been read)
-            if (h + 1 < H) issue_acts(step, 1u);
+            const uint32_t next = step + nwaves;
+            if (h + 1 < H) issue(step, no, yes, 1u);
             if (next < nsteps) {
-                if (h == 0) issue_weights(next);
-                if (h + 1 == H) issue_acts(next, 0u);
+                if constexpr (H == 1) issue(next, yes, yes, 0u);
+                else if (h == 0) issue(next, yes, no, 0u);
+                else issue(next, no, yes, 0u);
             }
             if (128u * step + 128u > kk32) {                              // ragged last step: activations past K are 0 (0 x Inf is not)
                 const uint32_t keep = (128u * step + 64u * h + 8u * J * g < kk32) ? 0xFFFFFFFFu : 0u;
@@ -350,7 +357,7 @@ __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
                 }
             }
         }
-        step = next;
+        step += nwaves;
     }
 #undef RAZER_DS128
 #undef RAZER_DS64
@@ -445,7 +452,7 @@ static hipError_t launch_ring_w(SvConfig cfg, int count, const GemvProblem* p, i
     arg.a = a;
     arg.lb = cfg.lb;
     // as many of the W waves as their LDS leaves room for
-    constexpr uint32_t fit = (kLdsBytes - kRingTableBytes) / ring_wave_bytes<NA, G>();
+    constexpr uint32_t fit = (kLdsBytes - kRingTableBytes) / ring_wave_bytes<NA, G, W>();
     constexpr int most = fit < (uint32_t)W ? (int)fit : W;
     static_assert(most >= 4, "LDS");
     const int64_t nsteps = (k + 127) / 128;
@@ -453,15 +460,16 @@ static hipError_t launch_ring_w(SvConfig cfg, int count, const GemvProblem* p, i
     const int use = NA == 16 && wgs > kComputeUnits && !eight ? 4 : most;
     const int waves = nsteps < use ? (int)nsteps : use;
     auto kern = ring_kernel<NA, G, GB, SF, W, IL>;
-    constexpr uint32_t lds = (uint32_t)most * ring_wave_bytes<NA, G>();
+    constexpr uint32_t lds = (uint32_t)most * ring_wave_bytes<NA, G, W>();
     if constexpr (lds > 64u * 1024u) RAZER_RAISE_LDS_LIMIT(kern, lds);
-    launch(kern, dim3((groups + G - 1) / G, (unsigned)((m + arg.chunk - 1) / arg.chunk)), 64 * waves, (size_t)waves * ring_wave_bytes<NA, G>(), st, arg);
+    launch(kern, dim3((groups + G - 1) / G, (unsigned)((m + arg.chunk - 1) / arg.chunk)), 64 * waves, (size_t)waves * ring_wave_bytes<NA, G, W>(), st, arg);
     return hipGetLastError();
 }
 
 // 8 waves; 16 for one group of rows and at most 16 activation rows: such a launch has at most one workgroup per compute
 // unit and little data under way, so twice the waves pay (4096 x 11008 at 4 rows 11.0 -> 8.8 us, at 8 rows 11.1 -> 9.8, at
-// 16 rows 13.7 -> 12.3, 2048 x 8192 8.7 -> 7.6; at 24 and 32 rows within 2 %, and with two groups or more 0-15 % slower).
+// 16 rows 13.0 -> 12.3, 2048 x 8192 8.7 -> 7.6; at 24 and 32 rows within 2 %, with two groups or more 0-15 % slower, and
+// from 9 rows up rows of 4096 elements are needed: 1000 x 2048 at 9 rows 4.3 -> 4.6).
 // 4 above 32 rows when the workgroups outnumber the compute units: three or four of them then share a unit, each at
 // another point of its steps (2 x 11008 x 4096 at 64 rows 31.4 -> 28.9; with one workgroup per unit 8 stay faster:
 // {q,k,v} 3 x 4096 x 4096 17.0, with 4 waves 18.4).  The number of waves decides the order of the sum over K: eight: a
@@ -473,7 +481,7 @@ static hipError_t launch_ring_t(SvConfig cfg, int count, const GemvProblem* p, i
         return launch_ring_w<NA, G, GB, SF, IL, 16>(cfg, count, p, k, a, m, eight, st);
     } else {
         if constexpr (G == 1 && NA <= 4) {
-            if (!eight) return launch_ring_w<NA, G, GB, SF, IL, 16>(cfg, count, p, k, a, m, eight, st);
+            if (!eight && (NA < 4 || k >= 4096)) return launch_ring_w<NA, G, GB, SF, IL, 16>(cfg, count, p, k, a, m, eight, st);
         }
         return launch_ring_w<NA, G, GB, SF, IL, kRingWaves>(cfg, count, p, k, a, m, eight, st);
     }
@@ -482,9 +490,8 @@ static hipError_t launch_ring_t(SvConfig cfg, int count, const GemvProblem* p, i
 // Groups of 16 rows per workgroup.  The busiest of the 256 compute units holds ceil(workgroups / 256) workgroups of G
 // groups each; what a workgroup spends on its activations (m x K, whatever G is) grows with m / G: about 5.5 % of a
 // group's time per activation row.  Six groups leave one workgroup of eight waves per unit, which overlaps less
-// (15 %, with activations in halves 30 %: 2 x 11008 x 4096 at 24 rows 21.3 us against 20.1 with three groups).  Measured
-// over 1024 x 1024 .. 57344 x 8192 at 4..64 rows this picks the fastest G or one within 5 % of it: 4096 rows 1; 8192 or
-// 5003 rows 2; {q,k,v} 3 x 4096, 10240 or 2 x 11008 rows 3.
+// (15 %).  Measured over 1024 x 1024 .. 57344 x 8192 at 4..64 rows this picks the fastest G or one within 3 % of it:
+// 4096 rows 1; 8192 or 5003 rows 2; {q,k,v} 3 x 4096 or 10240 rows 3; 2 x 11008 rows 3, with 32 activation rows 6.
 // More than 32 activation rows take at most 4 groups (the FP16-scale format 3): six do not fit the registers.
 static int ring_groups(int64_t groups, int64_t m, bool f16)
 {
@@ -495,7 +502,7 @@ static int ring_groups(int64_t groups, int64_t m, bool f16)
     for (int g : {1, 2, 3, 4, 6}) {
         if (m > 32 && g > (f16 ? 3 : 4)) continue;
         const int64_t wgs = chunks * ((groups + g - 1) / g);
-        const double c = (double)(g * ((wgs + kComputeUnits - 1) / kComputeUnits)) * (1.0 + 0.055 * (double)m / g) * (g == 6 ? (m > 8 ? 1.3 : 1.15) : 1.0);
+        const double c = (double)(g * ((wgs + kComputeUnits - 1) / kComputeUnits)) * (1.0 + 0.055 * (double)m / g) * (g == 6 ? 1.15 : 1.0);
         if (g == 1 || c < cost) { best = g; cost = c; }
     }
     return best;
@@ -565,13 +572,17 @@ static hipError_t launch_ring(SvConfig cfg, int count, const GemvProblem* p, int
 // 5.35 -> 5.15).  57344 x 8192 at 4 rows would take 63 instead of 57 us.
 // Above 64 rows, against the register-decode and the tiled GEMM, whose workgroups are too few or wait on one K-tile
 // after the other as long as the product is small; a unit is a group of 16 weight rows times a run of up to 64
-// activation rows.  Scale bytes (us): 768 x 1536 at 96 rows 13.5 -> 5.9, at 512 23.1 -> 7.1, at 4096 (3072 units)
-// 32.1 -> 34.9; 4096 x 4096 at 192 rows 26.6 -> 17.9, at 512 39.3 -> 33.7; 2560 x 2560 at 700 rows (4.5 million
-// units x K) 32.1 -> 26.4, at 1024 (6.6) 37.0 -> 38.4; 300 x 16384 at 128 rows (the GEMM cuts K) 23.5 -> 27.0, at 512
-// 44.5 -> 31.2; 4096 x 11008 at 256 rows 45.8 -> 38.7, at 384 64.5 -> 72.3; 2 x 11008 x 4096 at 96 rows (11.3 million)
-// 46.1 -> 49.6.  FP16 scales, whose GEMM multiplies every block apart and has one launch per matrix: 28672 x 8192 at
-// 128 rows 237 -> 114, at 160 145 -> 173; 4096 x 4096 at 384 rows 38.1 -> 30.6, 4096 x 11008 at 160 rows
-// 40.6 -> 42.8; 3 x 1536 x 1536 at 512 rows 78.1 -> 26.9; 2 x 2048 x 2048 at 1024 rows 62.9 -> 53.0, at 1500 73.7 -> 78.7.
+// activation rows.  The line lies where the two meet: a run re-reads and decodes the weights, the GEMMs need the chip
+// full.  Scale bytes (us, GEMM -> this): {q,k,v} 3 x 4096 x 4096 at 128 rows 36.5 -> 27.1, at 256 (12.6 million
+// units x K) 59.8 -> 46.2, at 320 (15.7) 60.8 -> 54.6, at 512 (25) 65.7 -> 88; 2 x 11008 x 4096 at 128 rows 53 -> 46, at 192
+// (16.9) 77 -> 68, at 256 (22.5) 84.7 -> 81.4; 2 x 5120 x 5120 at 320 rows 88 -> 64; 4096 x 4096 at 512 rows 40.4 -> 29.8, at
+// 1024 (16.8) 58.6 -> 54.3; 4096 x 11008 at 384 rows (16.9) 65.5 -> 62; 8192 x 8192 at 128 rows 39.7 -> 32.4, at 256 58 -> 54;
+// 8192 x 28672 at 128 rows (29) 92 -> 96; 3 x 1536 x 1536 at 1024 rows (4608 units) 49 -> 33, at 2048 (9216) 44 -> 56;
+// 3 x 2048 x 2048 at 1024 rows (6144) 36 -> 47.  Up to 96 rows a run is at most 48 of its 64 rows: (8192, 1024, 1024) x 8192
+// at 65 rows (10.5) 41.4 -> 43.7, 2 x 11008 x 4096 (11.3) 48.4 -> 50.2, 8192 x 8192 (8.4) 36.0 -> 30.3.  FP16 scales, whose GEMM
+// multiplies every block apart and has one launch per matrix (a million units x K per matrix): 28672 x 8192 at 128
+// rows 237 -> 114; 4096 x 4096 at 512 rows (8.4) 41.0 -> 34.2; 4096 x 11008 at 192 rows (8.4) 42.7 -> 41.8; 8192 x 8192 at 160
+// rows (12.6) 52.0 -> 53.7; 2 x 11008 x 4096 at 192 rows (8.5) 103 -> 69; 3 x 4096 x 4096 at 512 rows (8.4) 122 -> 90.
 // This kernel scales its operands; a special value of 9.5 times a block scale does not always fit a bf16, which the
 // 4x4x4 kernel (bare operands) does not need, so up to 4 rows such tensors stay there.  The layout of the weights has
 // no say: canonical and interleaved tensors give the same bits.
@@ -589,9 +600,8 @@ bool ring_serves(SvConfig cfg, int count, const GemvProblem* p, int64_t k, int64
     if (m > kRingMaxM) {
         if (!cfg.f16 && tuned_shape(kTuneGemmSlices, m, rows, k).source == 1) return false;
         const int64_t units = (m + kRingMaxM - 1) / kRingMaxM * groups, work = units * k;
-        if (cfg.f16) return m <= 128 || (units <= 2500 * count && work <= (int64_t)5000000 * count);
-        if (m <= 128) return work <= 5700000 && k <= 11264;
-        return (units <= 2500 && work <= 6000000) || (m <= 256 && units <= 1100 && k <= 12288);
+        if (cfg.f16) return m <= 128 || (units <= 2500 * count && work <= (int64_t)8500000 * count);
+        return units <= 4800 && work <= (m <= 96 ? 8500000 : 17500000);
     }
     if (m <= kSkinnyMaxM || cfg.f16) return false;
     if (tuned_shape(kTuneGemmSlices, m, rows, k).source == 1) return false;

@@ -36,7 +36,7 @@ def candidates(family, m, k):
         # (0, ..) and (1, ..): shapes on record that only fix the reported workspace (include/razer_tune.h); not swept
         on_record = [(0, 4, 1), (0, 4, 2), (0, 4, 4)] + ([(0, 8, 1), (0, 8, 2)] if m <= 16 else [])
         on_record += [(1, 1, 1), (1, 1, 2), (1, 1, 3), (1, 1, 4), (1, 2, 1), (1, 2, 2), (1, 2, 3), (1, 2, 4), (1, 2, 8)] if m <= 16 else []
-        return on_record + [(2, g, 8) for g in (1, 2, 3, 4, 6)] + ([(2, 1, 16)] if m <= 16 else [])
+        return on_record + [(2, g, 8) for g in (1, 2, 3, 4, 6)] + ([(2, 1, 16)] if m <= 8 or (m <= 16 and k >= 4096) else [])
     kt = -(-k // 64)
     return [(s,) for s in (1, 2, 3, 4, 6, 8, 12, 16) if s <= kt]
 
