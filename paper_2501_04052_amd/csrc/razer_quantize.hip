@@ -17,7 +17,8 @@ namespace razer {
 // b % kAbsmaxCells): atomics on a single address serialize at roughly 10 ns each, so a thousand
 // workgroups on one cell cost more than the pass over a 32 MB tensor itself.
 constexpr int kAbsmaxCells = 64;
-constexpr int kAbsmaxBlocks = 1024;
+constexpr int kAbsmaxBlocks = 256, kAbsmaxRowBlocks = 1024;     // dense; strided rows (one load in flight per lane)
+constexpr int64_t kAbsmaxOnceBytes = (int64_t)96 << 20;
 __global__ void absmax_init_kernel(uint32_t* ws) { ws[threadIdx.x] = 0u; }
 
 // max over the cells, by every wavefront that needs it (64 lanes, one cell each)
@@ -29,7 +30,12 @@ __device__ __forceinline__ float absmax_from_cells(const uint32_t* __restrict__ 
     return u2f(m);
 }
 
-template <typename T>
+// Bound by the read.  One workgroup per compute unit with eight loads in flight per lane: more workgroups only add
+// atomics and a tail (encoder with this pass, 256 against 1024 workgroups of four loads: bf16 4096 x 4096 27.5 -> 24.8 us,
+// fp32 4096 x 4096 49.7 -> 48.0; eight loads alone 27.0, 48.9).  ONCE: a tensor too large to stay in the last-level
+// cache until the encoder reads it again is read around the caches (fp32 8192 x 8192 with its decoding 157 -> 146 us, bf16
+// 14336 x 4096, 117 MB, 111 -> 101; 67 MB of bf16 would take 42.2 instead of 41.5, hence the line at 96 MiB).
+template <typename T, bool ONCE>
 __global__ __launch_bounds__(256) void absmax_kernel(const T* __restrict__ x, int64_t rows, int64_t cols,
                                                      int64_t ld, uint32_t* __restrict__ ws)
 {
@@ -54,9 +60,15 @@ __global__ __launch_bounds__(256) void absmax_kernel(const T* __restrict__ x, in
         const int64_t total = rows * cols / VEC;
         const uint4* p = reinterpret_cast<const uint4*>(x);
         int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-        for (; i + 3 * stride < total; i += 4 * stride) {        // four loads in flight per lane
-            const uint4 v0 = p[i], v1 = p[i + stride], v2 = p[i + 2 * stride], v3 = p[i + 3 * stride];
-            fold(v0); fold(v1); fold(v2); fold(v3);
+        for (; i + 7 * stride < total; i += 8 * stride) {        // eight loads in flight per lane
+            uint4 v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                if constexpr (ONCE) v[j] = load_once16(p + i + j * stride);
+                else v[j] = p[i + j * stride];
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) fold(v[j]);
         }
         for (; i < total; i += stride) fold(p[i]);
     } else {                                            // strided rows: workgroups stride over rows
@@ -511,8 +523,12 @@ static hipError_t launch_quantize_t(int fmt, SvConfig cfg, const T* x, int64_t r
         constexpr int VEC = 16 / sizeof(T);
         int64_t total = rows * (cols / VEC);
         int64_t blocks = (total + 255) / 256;
-        if (blocks > kAbsmaxBlocks) blocks = kAbsmaxBlocks;
-        launch(absmax_kernel<T>, (unsigned)blocks, 256, 0, st, x, rows, cols, ld, ws);
+        const int64_t most = ld == cols ? kAbsmaxBlocks : kAbsmaxRowBlocks;
+        if (blocks > most) blocks = most;
+        if (rows * cols * (int64_t)sizeof(T) > kAbsmaxOnceBytes)
+            launch(absmax_kernel<T, true>, (unsigned)blocks, 256, 0, st, x, rows, cols, ld, ws);
+        else
+            launch(absmax_kernel<T, false>, (unsigned)blocks, 256, 0, st, x, rows, cols, ld, ws);
     }
     int64_t nblk = rows * (cols / kBlock);
     unsigned grid = (unsigned)((nblk + 255) / 256 < kEncodeBlocks ? (nblk + 255) / 256 : kEncodeBlocks);

@@ -95,3 +95,21 @@ def test_blocks_far_above_a_given_scale(oracle, fmt, sv, block, clip):
     codes, scales, _ = oracle.quantize(fmt, x, sv=sv, given_tensor_scale=np.float32(1.0), block=block)
     assert np.array_equal(t.codes.cpu().numpy(), codes)
     assert np.array_equal(t.scales.cpu().numpy().view(scales.dtype), scales)
+
+
+@pytest.mark.parametrize("dtype,rows", [(torch.float32, 65535), (torch.float32, 65536), (torch.float32, 65537), (torch.float32, 786433),
+                                        (torch.bfloat16, 131073), (torch.bfloat16, 1572865), (torch.float32, 3)])
+def test_tensor_scale_sees_every_element(dtype, rows):
+    """Eq. 1's maximum at the first and last element and around the end of the unrolled loads; below and above the size
+    that is read around the caches."""
+    cols = 32
+    n = rows * cols
+    x = torch.zeros(n, dtype=dtype, device="cuda")
+    unrolled = 256 * 256 * 8 * (16 // x.element_size())
+    for i in {0, n - 1, min(n, n // unrolled * unrolled) - 1, min(n - 1, n // unrolled * unrolled), n // 2}:
+        if i < 0:
+            continue
+        x[i] = -180.0
+        t = razer.razer_quantize(x.view(rows, cols), razer.WEIGHT, (5.0, 8.0))
+        assert float(t.tensor_scale) == 1.0, i
+        x[i] = 0.0
