@@ -469,7 +469,8 @@ static hipError_t launch_ring_w(SvConfig cfg, int count, const GemvProblem* p, i
 // 8 waves; 16 for one group of rows and at most 16 activation rows: such a launch has at most one workgroup per compute
 // unit and little data under way, so twice the waves pay (4096 x 11008 at 4 rows 11.0 -> 8.8 us, at 8 rows 11.1 -> 9.8, at
 // 16 rows 13.0 -> 12.3, 2048 x 8192 8.7 -> 7.6; at 24 and 32 rows within 2 %, with two groups or more 0-15 % slower, and
-// from 9 rows up rows of 4096 elements are needed: 1000 x 2048 at 9 rows 4.3 -> 4.6).
+// from 9 rows up rows of 4096 elements are needed: 1000 x 2048 at 9 rows 4.3 -> 4.6); 16 again above 32 rows with one
+// group and rows of 10240 elements and more (4096 x 11008 at 64 rows 25.2 -> 24.4; 4096 x 4096 9.5 -> 10.0).
 // 4 above 32 rows when the workgroups outnumber the compute units: three or four of them then share a unit, each at
 // another point of its steps (2 x 11008 x 4096 at 64 rows 31.4 -> 28.9; with one workgroup per unit 8 stay faster:
 // {q,k,v} 3 x 4096 x 4096 17.0, with 4 waves 18.4).  The number of waves decides the order of the sum over K: eight: a
@@ -482,6 +483,9 @@ static hipError_t launch_ring_t(SvConfig cfg, int count, const GemvProblem* p, i
     } else {
         if constexpr (G == 1 && NA <= 4) {
             if (!eight && (NA < 4 || k >= 4096)) return launch_ring_w<NA, G, GB, SF, IL, 16>(cfg, count, p, k, a, m, eight, st);
+        }
+        if constexpr (G == 1 && NA == 16) {
+            if (!eight && k >= 10240) return launch_ring_w<NA, G, GB, SF, IL, 16>(cfg, count, p, k, a, m, eight, st);
         }
         return launch_ring_w<NA, G, GB, SF, IL, kRingWaves>(cfg, count, p, k, a, m, eight, st);
     }
@@ -562,9 +566,10 @@ static hipError_t launch_ring(SvConfig cfg, int count, const GemvProblem* p, int
 
 // Where this kernel takes over from its neighbours (unless a tuner or test forces one of their launch shapes).
 // 33..64 activation rows, scale-byte format, against the K-sliced register-decode GEMM: except where one group per
-// workgroup makes every workgroup read more activations than it gains (one group, m x K above 600 thousand:
-// 4096 x 11008 at 40 rows 26.5 -> 24.4 us, at 64 rows 25.9 -> 26.4; 1500 x 12288 at 64 rows 22.1 -> 24.5; with more
-// groups 13-50 % faster).
+// workgroup makes every workgroup read more activations than it gains: one group and m x K above 600 thousand, where the
+// GEMM's K-slices fill the units that few rows leave idle (1500 x 12288 at 64 rows 21.4 -> 21.9 us, 1000 x 16384 22.4 ->
+// 25.3), from 161 groups on above 920 thousand (4096 x 11008 at 40 rows 27.0 -> 22.4, at 64 rows 25.5 -> 24.4; 4096 x 14336
+// at 64 rows 31.2 -> 30.3; 3000 x 28672 at 40 rows 38 -> 50); with more groups 13-50 % faster.
 // 2..4 activation rows, against the 4x4x4 kernel of razer_gemv.hip, whose waves cross all of K in one or two passes:
 // long rows and not too many of them (1024 groups) -- at 4 rows 8192 x 28672 38.0 -> 30.4 us, {q,k,v} 10240 x 8192
 // 16.6 -> 14.6, 2 x 3000 x 6144 10.0 -> 9.0; at 2 rows one group per workgroup only (4096 x 11008 9.7 -> 8.7; but
@@ -605,7 +610,7 @@ bool ring_serves(SvConfig cfg, int count, const GemvProblem* p, int64_t k, int64
     }
     if (m <= kSkinnyMaxM || cfg.f16) return false;
     if (tuned_shape(kTuneGemmSlices, m, rows, k).source == 1) return false;
-    return ring_groups(groups, m, false) > 1 || m * k <= 600000;
+    return ring_groups(groups, m, false) > 1 || m * k <= (groups > 160 ? 920000 : 600000);
 }
 
 // What razer_workspace_bytes reports for 5..32 activation rows.  The kernel above needs none; callers size and pass

@@ -70,9 +70,9 @@ def test_runs_of_activation_rows(oracle, m, ns, k, fmt, block):
 
 
 @pytest.mark.parametrize("m,n,k,fmt,block", [(9, 37, 4096 + 96, razer.WEIGHT, 16), (16, 70, 4096, razer.WEIGHT, 64), (16, 20, 4224, razer.WEIGHT_F16, 128),
-                                             (33, 16485, 160, razer.WEIGHT, 16), (64, 16485, 192, razer.WEIGHT, 32), (64, 16485, 128, razer.WEIGHT_F16, 128)])
+                                             (40, 37, 10240 + 96, razer.WEIGHT, 16), (64, 20, 10240, razer.WEIGHT_F16, 128), (33, 16485, 160, razer.WEIGHT, 16), (64, 16485, 192, razer.WEIGHT, 32), (64, 16485, 128, razer.WEIGHT_F16, 128)])
 def test_number_of_waves(oracle, m, n, k, fmt, block):
-    """16 waves at 9..16 rows with one group per workgroup; 4 above 32 rows with more workgroups than compute units."""
+    """16 waves with one group per workgroup and rows long enough; 4 above 32 rows with more workgroups than compute units."""
     _run(oracle, (n,), k, m, fmt, block)
 
 
