@@ -1038,7 +1038,10 @@ __device__ __forceinline__ void gemm_rb_body(
                 keep[0][j][4 * q + 2] += t.z;
                 keep[0][j][4 * q + 3] += t.w;
             }
-        store_tile<MT / 2, 1, false>(keep, w_ts, nullptr, m0 + 128 * kg, n0 + 32 * wn, m, n, y, ld_y, lane);
+        if (partial)
+            store_tile_partial<MT / 2, 1>(keep, m0 + 128 * kg, n0 + 32 * wn, m, n, partial + (int64_t)kslice * m * n, lane);
+        else
+            store_tile<MT / 2, 1, false>(keep, w_ts, nullptr, m0 + 128 * kg, n0 + 32 * wn, m, n, y, ld_y, lane);
     }
 }
 
@@ -1475,7 +1478,7 @@ static hipError_t launch_wide(SvConfig cfg, int count, const GemvProblem* p, int
     return hipGetLastError();
 }
 
-// split > 1 (KG == 1 only, workspace of slices * m * n floats): K in slices of whole K-tiles, summed by
+// split > 1 (workspace of slices * m * n floats): K in slices of whole K-tiles, summed by
 // launch_slice_reduce.
 template <int NW, int S, int KG = 1, int MT = 8, bool GB = false>
 static hipError_t launch_rb(const uint8_t* w_codes, const uint8_t* w_scales, const float* w_ts, SvConfig wcfg,
@@ -1486,7 +1489,7 @@ static hipError_t launch_rb(const uint8_t* w_codes, const uint8_t* w_scales, con
     constexpr size_t smem = S * (KG * BM * 128 + NW * 1280) + 256 * sizeof(uint2);
     auto kern = gemm_rb_kernel<NW, S, KG, MT, GB>;
     RAZER_RAISE_LDS_LIMIT(kern, smem);
-    if (KG != 1 || !workspace) split = 1;
+    if (!workspace) split = 1;
     const int tiles_m = (int)((m + BM - 1) / BM), tiles_n = (int)((n + BN - 1) / BN);
     // every K-slice must hold at least one K-tile: slices = ceil(KT / ceil(KT / split))
     const int kt_all = (int)((k + kBK - 1) / kBK), kt_per = (kt_all + split - 1) / split;
@@ -1623,6 +1626,11 @@ static hipError_t launch_gemm_t(const uint8_t* w_codes, const uint8_t* w_scales,
     // operand of W4A4, which that kernel does not decode)
     GemmPlan p = gemm_plan(m, n, k, !AQ && k <= kRbMaxK);
     if ((m <= kSkinnyMaxM && k <= kSkinnyMaxK) || !workspace) p.split = 1;   // not sized a workspace
+    // Few 256 x 128 tiles, K-slices on the other compute units: the same slices on the register-decode kernel with two K
+    // groups per workgroup, where a slice has at least 16 K-tiles (all measured have 21 and more).  Bound as that kernel is, and by the slices' way through the workspace; against the LDS-staged
+    // tiles (us): 4096 x 11008 at 384 rows 66.2 -> 64.5, at 700 107.9 -> 96.3, at 1000 120.8 -> 113.2, 8192 x 8192 at 512
+    // 95.4 -> 91.2, 2048 x 28672 at 512 90.0 -> 83.2, 1024 x 28672 at 512 75.3 -> 62.8.
+    if (!AQ && p.tile == 4 && p.split > 1 && k <= kRbMaxK && k >= (int64_t)p.split * 16 * kBK) p.tile = 10;
 #define RAZER_GEMM(BM, BN, WGM, WGN, PP) \
     launch_cfg<BM, BN, WGM, WGN, AQ, PP, GB>(w_codes, w_scales, w_ts, wcfg, n, k, a, a_codes, a_scales, a_ts, acfg, m, y, ld_y, p.split, workspace, st)
     switch (p.tile) {
@@ -1635,6 +1643,7 @@ static hipError_t launch_gemm_t(const uint8_t* w_codes, const uint8_t* w_scales,
     }
 #undef RAZER_GEMM
     if constexpr (!AQ) {
+        if (p.tile == 10) return launch_rb<8, 2, 2, 8, GB>(w_codes, w_scales, w_ts, wcfg, n, k, a, m, y, ld_y, st, p.split, workspace);
         if (p.tile == 8) return launch_rb<4, 2, 1, 2, GB>(w_codes, w_scales, w_ts, wcfg, n, k, a, m, y, ld_y, st, p.split, workspace);
         if (p.tile == 9) return launch_rb<4, 2, 1, 4, GB>(w_codes, w_scales, w_ts, wcfg, n, k, a, m, y, ld_y, st, p.split, workspace);
         if (p.tile == 5) {

@@ -582,7 +582,8 @@ static hipError_t launch_ring(SvConfig cfg, int count, const GemvProblem* p, int
 // units x K) 59.8 -> 46.2, at 320 (15.7) 60.8 -> 54.6, at 512 (25) 65.7 -> 88; 2 x 11008 x 4096 at 128 rows 53 -> 46, at 192
 // (16.9) 77 -> 68, at 256 (22.5) 84.7 -> 81.4; 2 x 5120 x 5120 at 320 rows 88 -> 64; 4096 x 4096 at 512 rows 40.4 -> 29.8, at
 // 1024 (16.8) 58.6 -> 54.3; 4096 x 11008 at 384 rows (16.9) 65.5 -> 62; 8192 x 8192 at 128 rows 39.7 -> 32.4, at 256 58 -> 54;
-// 8192 x 28672 at 128 rows (29) 92 -> 96; 3 x 1536 x 1536 at 1024 rows (4608 units) 49 -> 33, at 2048 (9216) 44 -> 56;
+// 8192 x 28672 at 128 rows (29) 92 -> 96; 5000 x 12288 at 192 rows 48.2 -> 44.0, but at 200 (15.4, runs of
+// 50) 52.5 -> 62; 3 x 1536 x 1536 at 1024 rows (4608 units) 49 -> 33, at 2048 (9216) 44 -> 56;
 // 3 x 2048 x 2048 at 1024 rows (6144) 36 -> 47.  Up to 96 rows a run is at most 48 of its 64 rows: (8192, 1024, 1024) x 8192
 // at 65 rows (10.5) 41.4 -> 43.7, 2 x 11008 x 4096 (11.3) 48.4 -> 50.2, 8192 x 8192 (8.4) 36.0 -> 30.3.  FP16 scales, whose GEMM
 // multiplies every block apart and has one launch per matrix (a million units x K per matrix): 28672 x 8192 at 128
@@ -606,7 +607,8 @@ bool ring_serves(SvConfig cfg, int count, const GemvProblem* p, int64_t k, int64
         if (!cfg.f16 && tuned_shape(kTuneGemmSlices, m, rows, k).source == 1) return false;
         const int64_t units = (m + kRingMaxM - 1) / kRingMaxM * groups, work = units * k;
         if (cfg.f16) return m <= 128 || (units <= 2500 * count && work <= (int64_t)8500000 * count);
-        return units <= 4800 && work <= (m <= 96 ? 8500000 : 17500000);
+        const bool full_runs = 5 * m >= 4 * kRingMaxM * ((m + kRingMaxM - 1) / kRingMaxM);      // four fifths of their rows
+        return units <= 4800 && work <= (m <= 96 ? 8500000 : full_runs ? 17500000 : 12000000);
     }
     if (m <= kSkinnyMaxM || cfg.f16) return false;
     if (tuned_shape(kTuneGemmSlices, m, rows, k).source == 1) return false;

@@ -6,7 +6,7 @@ import pytest
 import torch
 
 import paper_2501_04052_amd as razer
-from paper_2501_04052_amd import synth
+from paper_2501_04052_amd import binding, synth
 from gpu_util import TOL, bf16_bits_to_dev, dev_to_bf16_bits, max_rel_err
 
 pytestmark = pytest.mark.gpu
@@ -33,3 +33,21 @@ def test_wide_tiles(oracle, m, ns, k, block):
         cols = np.r_[0:40, 240:272, wq[0].shape[0] - 40:wq[0].shape[0]] if wq[0].shape[0] > 300 else np.arange(wq[0].shape[0])
         y64, _ = oracle.linear((wq[0][cols], wq[1][cols], wq[2]), a_bf16=a[rows])
         assert max_rel_err(dev_to_bf16_bits(y)[rows][:, cols], y64) <= TOL
+
+
+@pytest.mark.parametrize("m,n,k,block", [(129, 100, 8192, 16), (130, 37, 8224, 16), (257, 260, 8320, 32), (140, 130, 8256, 64), (300, 5, 8288, 16)])
+def test_k_slices_with_two_k_groups(oracle, m, n, k, block):
+    """256 x 128 tiles, K cut into slices whose two halves may differ by a K-tile, against the CPU oracle."""
+    rng = np.random.default_rng(m + n + k)
+    wq = (rng.integers(0, 256, size=(n, k // 2), dtype=np.uint8), rng.integers(0, 256, size=(n, k // block), dtype=np.uint8), np.float32(2.0 ** -9))
+    w = razer.RazerTensor.from_host(*wq, razer.WEIGHT, (5.0, 8.0))
+    a = synth.activation(m, k, seed=9100 + m)
+    print("k slices", m, n, k, block, flush=True)
+    razer.razer_tune_force(binding.TUNE_GEMM_SLICES, (2,))       # (a forced shape keeps the call off the small-batch kernel)
+    try:
+        y = razer.razer_linear(w, bf16_bits_to_dev(a))
+        torch.cuda.synchronize()
+    finally:
+        razer.razer_tune_force(binding.TUNE_GEMM_SLICES, None)
+    y64, _ = oracle.linear(wq, a_bf16=a)
+    assert max_rel_err(dev_to_bf16_bits(y), y64) <= TOL
