@@ -717,8 +717,8 @@ __device__ __forceinline__ void gemm_rb_body(
     const int KT = (int)((k + kBK - 1) / kBK);
     const int last = KT - 1;
     // This workgroup's K-tiles: slice kslice of the grid (kt_per_slice tiles; all of them without a
-    // workspace), of which K group g computes tiles g KTH .. (g + 1) KTH - 1; tiles past the end of the
-    // slice contribute zero weights
+    // workspace), of which K group g computes tiles g KTH .. (g + 1) KTH - 1; where their number is odd the second
+    // group has one less
     const int kt0 = kslice * kt_per_slice;
     const int kend = (KT - kt0 < kt_per_slice) ? KT : kt0 + kt_per_slice;
     const int KTH = (kend - kt0 + KG - 1) / KG, kbase = kt0 + kg * KTH;
@@ -978,11 +978,16 @@ __device__ __forceinline__ void gemm_rb_body(
         for (int mi = 0; mi < MT; ++mi) RAZER_LDS_READ128(af[0][mi], aoff[0], 4096 * mi);
     }
     int st = 0;                                         // stage of tile kt; tile kt + S follows it into the same stage
-    for (int kt = kbase; kt < kbase + KTH; ++kt) {
+    int kstop = kbase + KTH;
+    if constexpr (KG == 2) kstop = kstop < kend ? kstop : kend;
+    for (int kt = kbase; kt < kstop; ++kt) {
         const int st_next = st == S - 1 ? 0 : st + 1;
         compute(kt, st, st_next);
         st = st_next;
     }
+    // a group with one K-tile less meets the other at its last barrier (a tile of zero weights in its place would make a
+    // NaN of an infinity in the activations it re-reads)
+    if (KG == 2 && kstop < kbase + KTH) __builtin_amdgcn_s_barrier();
     // copies and fragment reads requested for tiles past the end: let them finish before the registers
     // and the stages they target are used for anything else (the fragments are named after the wait: to the
     // compiler their registers are free from their last use on, and it gave them to the epilogue ahead of the wait)
@@ -1629,8 +1634,9 @@ static hipError_t launch_gemm_t(const uint8_t* w_codes, const uint8_t* w_scales,
     // Few 256 x 128 tiles, K-slices on the other compute units: the same slices on the register-decode kernel with two K
     // groups per workgroup, where a slice has at least 16 K-tiles (all measured have 21 and more).  Bound as that kernel is, and by the slices' way through the workspace; against the LDS-staged
     // tiles (us): 4096 x 11008 at 384 rows 66.2 -> 64.5, at 700 107.9 -> 96.3, at 1000 120.8 -> 113.2, 8192 x 8192 at 512
-    // 95.4 -> 91.2, 2048 x 28672 at 512 90.0 -> 83.2, 1024 x 28672 at 512 75.3 -> 62.8.
-    if (!AQ && p.tile == 4 && p.split > 1 && k <= kRbMaxK && k >= (int64_t)p.split * 16 * kBK) p.tile = 10;
+    // 95.4 -> 91.2, 2048 x 28672 at 512 90.0 -> 83.2, 1024 x 28672 at 512 75.3 -> 62.8.  Only with whole K-tiles: past K this
+    // kernel multiplies re-read activations by weights of 0, a NaN where they are infinite (the LDS-staged one loads zeros).
+    if (!AQ && p.tile == 4 && p.split > 1 && k <= kRbMaxK && k % kBK == 0 && k >= (int64_t)p.split * 16 * kBK) p.tile = 10;
 #define RAZER_GEMM(BM, BN, WGM, WGN, PP) \
     launch_cfg<BM, BN, WGM, WGN, AQ, PP, GB>(w_codes, w_scales, w_ts, wcfg, n, k, a, a_codes, a_scales, a_ts, acfg, m, y, ld_y, p.split, workspace, st)
     switch (p.tile) {

@@ -7,7 +7,7 @@ import torch
 
 import paper_2501_04052_amd as razer
 from paper_2501_04052_amd import binding, synth
-from gpu_util import TOL, bf16_bits_to_dev, dev_to_bf16_bits, max_rel_err
+from gpu_util import TOL, bf16_bits_to_dev, dev_to_bf16_bits, launched_kernels, max_rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -51,3 +51,31 @@ def test_k_slices_with_two_k_groups(oracle, m, n, k, block):
         razer.razer_tune_force(binding.TUNE_GEMM_SLICES, None)
     y64, _ = oracle.linear(wq, a_bf16=a)
     assert max_rel_err(dev_to_bf16_bits(y), y64) <= TOL
+
+
+@pytest.mark.parametrize("m,n,k,column,kernel", [(257, 260, 22016, 43 * 64, "gemm_rb_kernel<8, 2, 2, 8,"),          # (K-slices of 43 tiles)
+                                                 (2000, 4096, 1088, 1087, "gemm_rb_kernel<8, 2, 2, 8,"),             # (17 tiles in one slice)
+                                                 (300, 389, 8224, 3, "gemm_pp_kernel"), (257, 260, 22048, 22016, "gemm_pp_kernel")])
+def test_infinite_activation_stays_infinite(oracle, m, n, k, column, kernel):
+    """256 x 128 tiles: a K-tile that one of two K groups does not have, and the half of a last K-tile past K, must not
+    multiply an infinity by a weight of 0 (NaN), and the infinity must not reach other rows."""
+    rng = np.random.default_rng(m + n + k)
+    wq = (rng.integers(0, 256, size=(n, k // 2), dtype=np.uint8), rng.integers(0, 256, size=(n, k // 16), dtype=np.uint8), np.float32(2.0 ** -9))
+    w = razer.RazerTensor.from_host(*wq, razer.WEIGHT, (5.0, 8.0))
+    a = torch.from_numpy(synth.bf16_bits_to_f32(synth.activation(m, k, seed=9200 + m))).to(torch.bfloat16)
+    print("infinity", m, n, k, column, flush=True)
+    razer.razer_tune_force(binding.TUNE_GEMM_SLICES, (1,))       # (keeps the call off the small-batch kernel)
+    try:
+        plain = razer.razer_linear(w, a.cuda()).float().cpu()
+        a[2, column] = float("inf")
+        got = []
+        names = launched_kernels(lambda: got.append(razer.razer_linear(w, a.cuda())))
+    finally:
+        razer.razer_tune_force(binding.TUNE_GEMM_SLICES, None)
+    assert any(kernel in x for x in names), names
+    got = got[0].float().cpu()
+    wc = torch.from_numpy(oracle.dequant(oracle.WEIGHT, *wq)["f32"])[:, column].float()
+    hit = wc != 0
+    assert bool((got[2][hit] == torch.sign(wc[hit]) * float("inf")).all())
+    others = [i for i in range(m) if i != 2]
+    assert bool((got[others] == plain[others]).all())
