@@ -1536,7 +1536,8 @@ static hipError_t launch_cfg(const uint8_t* w_codes, const uint8_t* w_scales, co
 // kernels with 256x256 tiles (64 weight rows per wave) / 256x128 tiles, 7 = register-decode kernel, 256x128 tiles, K halved inside
 // the workgroup, 8 / 9 = register-decode kernel with 64x128 / 128x128 tiles and K-slices (33..64 /
 // 65..128 activation rows: measured 1.3-2.1x faster than tiles 1 / 2 on 4096^2, 11008 x 4096 and
-// 4096 x 11008).  A K-tile costs about 1 us of latency however small the tile, so
+// 4096 x 11008), 10 = tile 7's kernel with the K-slices of tile 4, which launch_gemm_t puts in its place
+// where they are long.  A K-tile costs about 1 us of latency however small the tile, so
 // when the output tiles cannot occupy the 256 compute units K is split until they do (at most 8 ways,
 // at least 8 K-tiles per slice); the slices meet in the workspace.
 struct GemmPlan {
@@ -1631,12 +1632,16 @@ static hipError_t launch_gemm_t(const uint8_t* w_codes, const uint8_t* w_scales,
     // operand of W4A4, which that kernel does not decode)
     GemmPlan p = gemm_plan(m, n, k, !AQ && k <= kRbMaxK);
     if ((m <= kSkinnyMaxM && k <= kSkinnyMaxK) || !workspace) p.split = 1;   // not sized a workspace
-    // Few 256 x 128 tiles, K-slices on the other compute units: the same slices on the register-decode kernel with two K
-    // groups per workgroup, where a slice has at least 16 K-tiles (all measured have 21 and more).  Bound as that kernel is, and by the slices' way through the workspace; against the LDS-staged
-    // tiles (us): 4096 x 11008 at 384 rows 66.2 -> 64.5, at 700 107.9 -> 96.3, at 1000 120.8 -> 113.2, 8192 x 8192 at 512
-    // 95.4 -> 91.2, 2048 x 28672 at 512 90.0 -> 83.2, 1024 x 28672 at 512 75.3 -> 62.8.  Only with whole K-tiles: past K this
-    // kernel multiplies re-read activations by weights of 0, a NaN where they are infinite (the LDS-staged one loads zeros).
-    if (!AQ && p.tile == 4 && p.split > 1 && k <= kRbMaxK && k % kBK == 0 && k >= (int64_t)p.split * 16 * kBK) p.tile = 10;
+    // Few 256 x 128 tiles, K-slices on the other compute units: where the slices are long, the same slices on the
+    // register-decode kernel with two K groups per workgroup (tile 10).  Bound as that kernel is, and by the slices' way
+    // through the workspace; the second group costs a start and a meeting, which only long slices repay.  Time against the
+    // LDS-staged tiles at 8 / 16 / 32 / 40 / 43 / 64 K-tiles per slice: 1664 weight rows at 512 activation rows 1.08 /
+    // 1.06 / 1.00 / 1.00 / 0.99 / 0.97, 4096 at 384 1.08 / 1.05 / 1.00 / 1.02 / 0.97 / 0.99, 1664 at 1000 1.07 / 1.03 / 0.98
+    // / 0.98 / 0.95 / 0.95 (4096 x 11008 at 1000 rows 120.8 -> 113.2 us).  Not above 1024 rows (640 weight rows at 1500
+    // 1.04 .. 1.10 at any length), and only with whole K-tiles: past K this kernel multiplies re-read activations by weights
+    // of 0, a NaN where they are infinite (the LDS-staged one loads zeros), and rows that start inside a 128-byte line
+    // make its copies ask for every line twice (1.01 .. 1.26 of the time).
+    if (!AQ && p.tile == 4 && p.split > 1 && k <= kRbMaxK && m <= 1024 && k % kBK == 0 && k >= (int64_t)p.split * 42 * kBK) p.tile = 10;
 #define RAZER_GEMM(BM, BN, WGM, WGN, PP) \
     launch_cfg<BM, BN, WGM, WGN, AQ, PP, GB>(w_codes, w_scales, w_ts, wcfg, n, k, a, a_codes, a_scales, a_ts, acfg, m, y, ld_y, p.split, workspace, st)
     switch (p.tile) {

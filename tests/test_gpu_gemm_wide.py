@@ -35,22 +35,33 @@ def test_wide_tiles(oracle, m, ns, k, block):
         assert max_rel_err(dev_to_bf16_bits(y)[rows][:, cols], y64) <= TOL
 
 
-@pytest.mark.parametrize("m,n,k,block", [(129, 100, 8192, 16), (130, 37, 8224, 16), (257, 260, 8320, 32), (140, 130, 8256, 64), (300, 5, 8288, 16)])
-def test_k_slices_with_two_k_groups(oracle, m, n, k, block):
-    """256 x 128 tiles, K cut into slices whose two halves may differ by a K-tile, against the CPU oracle."""
+@pytest.mark.parametrize("m,n,k,block,kernel", [
+    # 256 x 128 tiles with two K groups: 37 to 43 K-tiles per slice, an odd and an even number of them, the shortest slices that take it
+    (257, 260, 21568, 16, "gemm_rb_kernel<8, 2, 2, 8, false>"), (140, 130, 22016, 16, "gemm_rb_kernel<8, 2, 2, 8, false>"),
+    (300, 389, 21696, 16, "gemm_rb_kernel<8, 2, 2, 8, false>"), (257, 389, 21760, 32, "gemm_rb_kernel<8, 2, 2, 8, true>"),
+    (300, 261, 21504, 64, "gemm_rb_kernel<8, 2, 2, 8, true>"),
+    # the LDS-staged tiles: shorter slices, K that ends inside a K-tile, one width of tiles as good as the other
+    (300, 261, 21440, 64, "gemm_pp_kernel<256, 128,"), (257, 260, 22048, 16, "gemm_pp_kernel<256, 128,"), (257, 260, 8320, 32, "gemm_pp_kernel<256, 128,"),
+    (140, 130, 8256, 64, "gemm_pp_kernel<256, 128,"), (129, 100, 8192, 16, "gemm_pp_kernel<256, 256,"), (130, 37, 8224, 16, "gemm_pp_kernel<256, 256,"),
+    (300, 5, 8288, 16, "gemm_pp_kernel<256, 256,")])
+def test_k_slices_of_few_tiles(oracle, m, n, k, block, kernel):
+    """Few tiles, K cut into slices whose last one is shorter, against the CPU oracle on sampled rows, each on the kernel
+    that its lengths call for."""
     rng = np.random.default_rng(m + n + k)
     wq = (rng.integers(0, 256, size=(n, k // 2), dtype=np.uint8), rng.integers(0, 256, size=(n, k // block), dtype=np.uint8), np.float32(2.0 ** -9))
     w = razer.RazerTensor.from_host(*wq, razer.WEIGHT, (5.0, 8.0))
     a = synth.activation(m, k, seed=9100 + m)
+    rows = np.unique(np.r_[0, rng.choice(m, size=22, replace=False), 127, 128, m - 1])
     print("k slices", m, n, k, block, flush=True)
     razer.razer_tune_force(binding.TUNE_GEMM_SLICES, (2,))       # (a forced shape keeps the call off the small-batch kernel)
     try:
-        y = razer.razer_linear(w, bf16_bits_to_dev(a))
-        torch.cuda.synchronize()
+        got = []
+        names = launched_kernels(lambda: got.append(razer.razer_linear(w, bf16_bits_to_dev(a))))
     finally:
         razer.razer_tune_force(binding.TUNE_GEMM_SLICES, None)
-    y64, _ = oracle.linear(wq, a_bf16=a)
-    assert max_rel_err(dev_to_bf16_bits(y), y64) <= TOL
+    assert any(kernel in x for x in names), names
+    y64, _ = oracle.linear(wq, a_bf16=a[rows])
+    assert max_rel_err(dev_to_bf16_bits(got[0])[rows], y64) <= TOL
 
 
 @pytest.mark.parametrize("m,n,k,column,kernel", [(257, 260, 22016, 43 * 64, "gemm_rb_kernel<8, 2, 2, 8,"),          # (K-slices of 43 tiles)
