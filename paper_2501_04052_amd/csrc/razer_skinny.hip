@@ -97,7 +97,7 @@ __device__ __forceinline__ v4u sk_permute_pairs(v4u a)
 // workgroups share a unit; a lane then has 16 elements of each half instead of 32 of the step.  Against whole steps (us):
 // {q,k,v} 3 x 4096 x 4096 at 64 rows 19.0 -> 17.0, 4096 x 4096 11.0 -> 9.5; with 16 waves (below) 4096 x 11008 at
 // 9 rows 11.8 -> 10.7.  Elsewhere up to 32 rows slower (8192 x 8192 at 9 rows 13.1 -> 14.1, 2 x 11008 x 4096 with FP16
-// scales at 32 rows 20.4 -> 22.2): whole steps there.
+// scales at 32 rows 20.4 -> 22.2): whole steps there, and where ring_split_lines says so.
 // SF = 1: the FP16-scale format (one step = one block of 128: one scale word per row).  The operands are bare FP4
 // values and swap roles, so that a lane's four results of a step belong to ITS weight row (lane % 16) and activation
 // rows 4 (lane / 16) + 0..3, and the step's sum is folded into the running sums with the lane's own scale in fp32.
@@ -105,14 +105,14 @@ constexpr int kRingWaves = 8;
 constexpr uint32_t kRingTableBytes = 4096;
 template <int NA, int W>
 constexpr int ring_parts() { return NA == 16 || (NA == 4 && W == 16) ? 2 : 1; }
-template <int NA, int W>
-constexpr uint32_t ring_act_bytes() { return NA * 1024u / ring_parts<NA, W>(); }
-template <int NA, int G, int W>
-constexpr uint32_t ring_slot_bytes() { return ring_act_bytes<NA, W>() + G * 1280u; }
-template <int NA, int G, int W>
+template <int NA, int H>
+constexpr uint32_t ring_act_bytes() { return NA * 1024u / H; }
+template <int NA, int G, int H>
+constexpr uint32_t ring_slot_bytes() { return ring_act_bytes<NA, H>() + G * 1280u; }
+template <int NA, int G, int H>
 constexpr uint32_t ring_wave_bytes()
 {
-    const uint32_t slot = ring_slot_bytes<NA, G, W>(), part = G * ((NA + 3) / 4) * 1024u;
+    const uint32_t slot = ring_slot_bytes<NA, G, H>(), part = G * ((NA + 3) / 4) * 1024u;
     return slot > part ? slot : part;
 }
 
@@ -131,7 +131,7 @@ struct RingArgs {
     int chunk, lb;
 };
 
-template <int NA, int G, bool GB, int SF, int W, bool IL = false>
+template <int NA, int G, bool GB, int SF, int W, bool IL, int H>
 __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
 {
     const uint32_t e1 = arg.e[0], e2 = arg.e[1], e3 = arg.e[2], e4 = arg.e[3];
@@ -139,9 +139,9 @@ __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
     const int64_t k = arg.k, m0 = (int64_t)blockIdx.y * arg.chunk, m = arg.m - m0 < arg.chunk ? arg.m - m0 : arg.chunk;
     const int lb = arg.lb;
     const uint16_t* a = arg.a + m0 * k;
-    constexpr int NB = (NA + 3) / 4, H = ring_parts<NA, W>(), J = 4 / H, AC = NA / H;
-    constexpr uint32_t ACT = ring_act_bytes<NA, W>(), AROW = 256u / H;
-    constexpr uint32_t WAVE = ring_wave_bytes<NA, G, W>();
+    constexpr int NB = (NA + 3) / 4, J = 4 / H, AC = NA / H;
+    constexpr uint32_t ACT = ring_act_bytes<NA, H>(), AROW = 256u / H;
+    constexpr uint32_t WAVE = ring_wave_bytes<NA, G, H>();
     __shared__ uint4 lut[SF ? 1 : 256];
     extern __shared__ __align__(16) uint8_t dyn_smem[];               // [waves][WAVE]
     const uint32_t lane = threadIdx.x & 63u, nwaves = blockDim.x >> 6;
@@ -212,6 +212,11 @@ __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
         if constexpr (decltype(acts)::value) {
             if constexpr (NA == 8) __builtin_amdgcn_sched_barrier(0); // (the first copies ahead of these addresses: 2 %)
             const uint32_t first = part * (128u / H);                 // elements past K: the step's first ones again
+            if (NA == 16 && H == 1 && full) {                         // (16 copies: without the selections 3-5 %)
+#pragma unroll
+                for (int i = 0; i < AC; ++i) RAZER_COPY(abytes + (size_t)step * 256u, arow[i] + achk[i] * 16u, ring + i * 1024, 16);
+                return;
+            }
 #pragma unroll
             for (int i = 0; i < AC; ++i)
                 RAZER_COPY(abytes + (size_t)step * 256u, arow[i] + (full || first + achk[i] * 8u < left ? first / 8u + achk[i] : 0u) * 16u, ring + i * 1024, 16);
@@ -427,8 +432,19 @@ static int64_t ring_chunk(int64_t m)
     const int64_t chunks = (m + kRingMaxM - 1) / kRingMaxM;
     return (m + chunks - 1) / chunks;
 }
+static int64_t ring_row_groups(int count, const GemvProblem* p)
+{
+    int64_t groups = 0;
+    for (int i = 0; i < count; ++i) groups += (p[i].n + 15) / 16;
+    return groups;
+}
+template <int G>
+static int64_t ring_wgs(int count, const GemvProblem* p, int64_t m)
+{
+    return (ring_row_groups(count, p) + G - 1) / G * ((m + kRingMaxM - 1) / kRingMaxM);
+}
 
-template <int NA, int G, bool GB, int SF, bool IL, int W>
+template <int NA, int G, bool GB, int SF, bool IL, int W, int H = ring_parts<NA, W>()>
 static hipError_t launch_ring_w(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, bool eight, hipStream_t st)
 {
     RingArgs arg;
@@ -452,18 +468,35 @@ static hipError_t launch_ring_w(SvConfig cfg, int count, const GemvProblem* p, i
     arg.a = a;
     arg.lb = cfg.lb;
     // as many of the W waves as their LDS leaves room for
-    constexpr uint32_t fit = (kLdsBytes - kRingTableBytes) / ring_wave_bytes<NA, G, W>();
+    constexpr uint32_t fit = (kLdsBytes - kRingTableBytes) / ring_wave_bytes<NA, G, H>();
     constexpr int most = fit < (uint32_t)W ? (int)fit : W;
     static_assert(most >= 4, "LDS");
     const int64_t nsteps = (k + 127) / 128;
-    const int64_t wgs = (int64_t)((groups + G - 1) / G) * ((m + arg.chunk - 1) / arg.chunk);
+    const int64_t wgs = ring_wgs<G>(count, p, m);
     const int use = NA == 16 && wgs > kComputeUnits && !eight ? 4 : most;
     const int waves = nsteps < use ? (int)nsteps : use;
-    auto kern = ring_kernel<NA, G, GB, SF, W, IL>;
-    constexpr uint32_t lds = (uint32_t)most * ring_wave_bytes<NA, G, W>();
+    auto kern = ring_kernel<NA, G, GB, SF, W, IL, H>;
+    constexpr uint32_t lds = (uint32_t)most * ring_wave_bytes<NA, G, H>();
     if constexpr (lds > 64u * 1024u) RAZER_RAISE_LDS_LIMIT(kern, lds);
-    launch(kern, dim3((groups + G - 1) / G, (unsigned)((m + arg.chunk - 1) / arg.chunk)), 64 * waves, (size_t)waves * ring_wave_bytes<NA, G, W>(), st, arg);
+    launch(kern, dim3((groups + G - 1) / G, (unsigned)((m + arg.chunk - 1) / arg.chunk)), 64 * waves, (size_t)waves * ring_wave_bytes<NA, G, H>(), st, arg);
     return hipGetLastError();
+}
+
+// Rows of an odd number of 32-element runs start in the middle of a 128-byte line, and half a step of such a row (128
+// bytes) lies in two lines: halves then ask for four lines where the whole step asks for three.  Whole steps (and 8 waves)
+// where that shows, which is where many rows are read or many workgroups read them (us, halves -> whole): one group,
+// 4096 x 3360 at 64 rows 10.3 -> 9.8, 4096 x 8224 22.1 -> 20.7; 100 x 11040 at 190 rows 26.0 -> 23.5, 500 x 16416 at 448
+// 35.2 -> 31.8; two groups, 8192 x 16416 at 64 rows 52.3 -> 49.3, 5003 x 8224 at 64 25.7 -> 24.9; 4096 x 8224 at 16 rows
+// 11.1 -> 10.5.  Below the lines halves stay ahead: 100 x 8224 at 64 rows 13.5, whole 14.8; 500 x 5792 at 190 13.0, 13.5; 5003 x 3360 at
+// 37 rows 10.5, 10.9; 1500 x 11040 at 12 rows 9.0, 9.7.
+template <int NA, int G>
+static bool ring_split_lines(int count, const GemvProblem* p, int64_t k, int64_t m)
+{
+    const int64_t wgs = ring_wgs<G>(count, p, m), rows = ring_chunk(m);
+    if (k % 64 == 0) return false;
+    if (NA == 4) return m > 12 || m * k > 200000 || wgs > 160;
+    if (NA != 16 || wgs > kComputeUnits) return false;
+    return m * k > 1200000 || (G == 1 ? rows > 48 && wgs > 192 : rows * k > 250000);
 }
 
 // 8 waves; 16 for one group of rows and at most 16 activation rows: such a launch has at most one workgroup per compute
@@ -482,7 +515,11 @@ static hipError_t launch_ring_t(SvConfig cfg, int count, const GemvProblem* p, i
         return launch_ring_w<NA, G, GB, SF, IL, 16>(cfg, count, p, k, a, m, eight, st);
     } else {
         if constexpr (G == 1 && NA <= 4) {
-            if (!eight && (NA < 4 || k >= 4096)) return launch_ring_w<NA, G, GB, SF, IL, 16>(cfg, count, p, k, a, m, eight, st);
+            if (!eight && (NA < 4 || (k >= 4096 && !ring_split_lines<NA, G>(count, p, k, m)))) return launch_ring_w<NA, G, GB, SF, IL, 16>(cfg, count, p, k, a, m, eight, st);
+        }
+        if constexpr (NA == 16 && G <= 2 && !SF) {
+            if (ring_split_lines<NA, G>(count, p, k, m))
+                return launch_ring_w<NA, G, GB, SF, IL, kRingWaves, 1>(cfg, count, p, k, a, m, eight, st);
         }
         if constexpr (G == 1 && NA == 16) {
             if (!eight && k >= 10240) return launch_ring_w<NA, G, GB, SF, IL, 16>(cfg, count, p, k, a, m, eight, st);
@@ -511,13 +548,6 @@ static int ring_groups(int64_t groups, int64_t m, bool f16)
     }
     return best;
 }
-static int64_t ring_row_groups(int count, const GemvProblem* p)
-{
-    int64_t groups = 0;
-    for (int i = 0; i < count; ++i) groups += (p[i].n + 15) / 16;
-    return groups;
-}
-
 static hipError_t launch_ring(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, hipStream_t st)
 {
     int g = ring_groups(ring_row_groups(count, p), m, cfg.f16 != 0);

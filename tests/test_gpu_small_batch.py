@@ -7,7 +7,7 @@ import torch
 
 import paper_2501_04052_amd as razer
 from paper_2501_04052_amd import binding, synth
-from gpu_util import TOL, bf16_bits_to_dev, dev_to_bf16_bits, max_rel_err
+from gpu_util import TOL, bf16_bits_to_dev, dev_to_bf16_bits, launched_kernels, max_rel_err
 
 pytestmark = pytest.mark.gpu
 SV = (5.0, 8.0)
@@ -74,6 +74,24 @@ def test_runs_of_activation_rows(oracle, m, ns, k, fmt, block):
 def test_number_of_waves(oracle, m, n, k, fmt, block):
     """16 waves with one group per workgroup and rows long enough; 4 above 32 rows with more workgroups than compute units."""
     _run(oracle, (n,), k, m, fmt, block)
+
+
+@pytest.mark.parametrize("m,n,k,block,groups,halves", [(130, 37, 9312, 16, None, 1), (130, 37, 9312, 32, None, 1), (130, 37, 4128, 16, None, 2), (64, 3077, 224, 16, None, 1),
+                                                       (64, 37, 4128, 16, 2, 1), (50, 37, 8224, 32, 2, 1), (64, 37, 3360, 16, 2, 2), (64, 37, 4160, 16, 2, 2),
+                                                       (16, 37, 4128, 16, None, 1), (12, 37, 4128, 32, None, 2)])
+def test_steps_of_rows_that_start_inside_a_line(oracle, m, n, k, block, groups, halves):
+    """K of an odd number of 32-element runs: whole steps where many rows are read, halves elsewhere (the last template
+    argument counts the parts)."""
+    a = bf16_bits_to_dev(synth.activation(m, k, seed=4800))
+    wt = _weights(n, k, 4801, razer.WEIGHT, block)[1]
+    if groups:
+        razer.razer_tune_force(binding.TUNE_SMALL_BATCH, (2, groups))
+    try:
+        names = launched_kernels(lambda: razer.razer_linear(wt, a))
+    finally:
+        razer.razer_tune_force(binding.TUNE_SMALL_BATCH, None)
+    assert any("ring_kernel" in x and "false, %d>" % halves in x for x in names), names
+    _run(oracle, (n,), k, m, razer.WEIGHT, block, groups)
 
 
 def test_runs_of_activation_rows_keep_to_a_strided_output(oracle):
