@@ -598,8 +598,10 @@ static hipError_t launch_ring(SvConfig cfg, int count, const GemvProblem* p, int
 // 33..64 activation rows, scale-byte format, against the K-sliced register-decode GEMM: except where one group per
 // workgroup makes every workgroup read more activations than it gains: one group and m x K above 600 thousand, where the
 // GEMM's K-slices fill the units that few rows leave idle (1500 x 12288 at 64 rows 21.4 -> 21.9 us, 1000 x 16384 22.4 ->
-// 25.3), from 161 groups on above 920 thousand (4096 x 11008 at 40 rows 27.0 -> 22.4, at 64 rows 25.5 -> 24.4; 4096 x 14336
-// at 64 rows 31.2 -> 30.3; 3000 x 28672 at 40 rows 38 -> 50); with more groups 13-50 % faster.
+// 25.3).  From 161 groups on the length of K decides, whatever the number of rows (time of this kernel / the GEMM's): 2600
+// weight rows at 64 activation rows 0.91 with 11264 elements, 0.95 with 12288, 1.04 with 14336, at 37 rows 1.15 with 20480;
+// 3200 at 64 rows 0.87, 0.91, 1.01; 3600 and 4096 at 56 rows 0.90 with 12288, 0.97 with 14336, 1.02 with 16384 and at 37
+// rows 1.05 with 20480.  With more groups 13-50 % faster.
 // 2..4 activation rows, against the 4x4x4 kernel of razer_gemv.hip, whose waves cross all of K in one or two passes:
 // long rows and not too many of them (1024 groups) -- at 4 rows 8192 x 28672 38.0 -> 30.4 us, {q,k,v} 10240 x 8192
 // 16.6 -> 14.6, 2 x 3000 x 6144 10.0 -> 9.0; at 2 rows one group per workgroup only (4096 x 11008 9.7 -> 8.7; but
@@ -642,7 +644,7 @@ bool ring_serves(SvConfig cfg, int count, const GemvProblem* p, int64_t k, int64
     }
     if (m <= kSkinnyMaxM || cfg.f16) return false;
     if (tuned_shape(kTuneGemmSlices, m, rows, k).source == 1) return false;
-    return ring_groups(groups, m, false) > 1 || m * k <= (groups > 160 ? 920000 : 600000);
+    return ring_groups(groups, m, false) > 1 || m * k <= 600000 || (groups > 160 && k <= (groups > 208 ? 14336 : 12288));
 }
 
 // What razer_workspace_bytes reports for 5..32 activation rows.  The kernel above needs none; callers size and pass

@@ -131,3 +131,16 @@ def test_a_forced_shape_launches_what_its_entry_would(m, family, shape, kernel):
         razer.razer_tune_force(-1, None)
     assert src in (None, 0 if shape == (-1,) else 1)
     assert any(kernel in x for x in names), names
+
+
+@pytest.mark.parametrize("m,ns,k,kernel", [
+    # 33..64 rows, one group of rows per workgroup: both sides of the length of K
+    (64, (2600,), 12288, "ring_kernel"), (64, (2600,), 12320, "gemm_rb_kernel"), (64, (4096,), 14336, "ring_kernel"), (48, (2600,), 16384, "gemm_rb_kernel"),
+    (37, (4096,), 20480, "gemm_rb_kernel"), (37, (2600,), 16192, "ring_kernel")])
+def test_the_faster_kernel_is_chosen(m, ns, k, kernel):
+    """Long rows of few weights are for the GEMM, which cuts K across workgroups; each call here is 5 % or more faster on
+    the kernel named, or lies right at the line."""
+    ws = [_rand_weights(n, k, 9996)[1] for n in ns]
+    a = bf16_bits_to_dev(synth.activation(m, k, seed=9997))
+    names = launched_kernels(lambda: razer.razer_linear(ws[0], a) if len(ws) == 1 else razer.razer_linear_grouped(ws, a))
+    assert all(kernel in x or "slice_reduce" in x for x in names) and names, names
