@@ -1604,6 +1604,20 @@ static GemmPlan gemm_plan(int64_t m, int64_t n, int64_t k, bool register_decode_
     return p;
 }
 
+// Few 256 x 128 tiles, K-slices on the other compute units: where the slices are long, the same slices on the
+// register-decode kernel with two K groups per workgroup (tile 10).  Bound as that kernel is, and by the slices' way
+// through the workspace; the second group costs a start and a meeting, which only long slices repay.  Time against the
+// LDS-staged tiles at 8 / 16 / 32 / 40 / 43 / 64 K-tiles per slice: 1664 weight rows at 512 activation rows 1.08 /
+// 1.06 / 1.00 / 1.00 / 0.99 / 0.97, 4096 at 384 1.08 / 1.05 / 1.00 / 1.02 / 0.97 / 0.99, 1664 at 1000 1.07 / 1.03 / 0.98
+// / 0.98 / 0.95 / 0.95 (4096 x 11008 at 1000 rows 120.8 -> 113.2 us).  Not above 1024 rows (640 weight rows at 1500
+// 1.04 .. 1.10 at any length), and only with whole K-tiles: past K this kernel multiplies re-read activations by weights
+// of 0, a NaN where they are infinite (the LDS-staged one loads zeros), and rows that start inside a 128-byte line
+// make its copies ask for every line twice (1.01 .. 1.26 of the time).
+static bool long_slices(const GemmPlan& p, int64_t m, int64_t k)
+{
+    return p.tile == 4 && p.split > 1 && k <= kRbMaxK && m <= 1024 && k % kBK == 0 && k >= (int64_t)p.split * 42 * kBK;
+}
+
 size_t gemm_workspace_bytes(int64_t n, int64_t k, int64_t m)
 {
     if (n == 0 || k == 0) return 0;
@@ -1632,16 +1646,7 @@ static hipError_t launch_gemm_t(const uint8_t* w_codes, const uint8_t* w_scales,
     // operand of W4A4, which that kernel does not decode)
     GemmPlan p = gemm_plan(m, n, k, !AQ && k <= kRbMaxK);
     if ((m <= kSkinnyMaxM && k <= kSkinnyMaxK) || !workspace) p.split = 1;   // not sized a workspace
-    // Few 256 x 128 tiles, K-slices on the other compute units: where the slices are long, the same slices on the
-    // register-decode kernel with two K groups per workgroup (tile 10).  Bound as that kernel is, and by the slices' way
-    // through the workspace; the second group costs a start and a meeting, which only long slices repay.  Time against the
-    // LDS-staged tiles at 8 / 16 / 32 / 40 / 43 / 64 K-tiles per slice: 1664 weight rows at 512 activation rows 1.08 /
-    // 1.06 / 1.00 / 1.00 / 0.99 / 0.97, 4096 at 384 1.08 / 1.05 / 1.00 / 1.02 / 0.97 / 0.99, 1664 at 1000 1.07 / 1.03 / 0.98
-    // / 0.98 / 0.95 / 0.95 (4096 x 11008 at 1000 rows 120.8 -> 113.2 us).  Not above 1024 rows (640 weight rows at 1500
-    // 1.04 .. 1.10 at any length), and only with whole K-tiles: past K this kernel multiplies re-read activations by weights
-    // of 0, a NaN where they are infinite (the LDS-staged one loads zeros), and rows that start inside a 128-byte line
-    // make its copies ask for every line twice (1.01 .. 1.26 of the time).
-    if (!AQ && p.tile == 4 && p.split > 1 && k <= kRbMaxK && m <= 1024 && k % kBK == 0 && k >= (int64_t)p.split * 42 * kBK) p.tile = 10;
+    if (!AQ && long_slices(p, m, k)) p.tile = 10;
 #define RAZER_GEMM(BM, BN, WGM, WGN, PP) \
     launch_cfg<BM, BN, WGM, WGN, AQ, PP, GB>(w_codes, w_scales, w_ts, wcfg, n, k, a, a_codes, a_scales, a_ts, acfg, m, y, ld_y, p.split, workspace, st)
     switch (p.tile) {
@@ -1711,6 +1716,48 @@ size_t gemm_grouped_workspace_bytes(int count, const GemvProblem* p, int64_t m, 
     int64_t n_all = 0;
     for (int i = 0; i < count; ++i) n_all += p[i].n;
     return (size_t)(slices * m * n_all) * sizeof(float);
+}
+
+// About how long (us) a scale-byte weight call above 64 activation rows takes on the kernels of this file: a start, the
+// K-tiles that a workgroup works through one after the other, and the slices' way through the workspace.  Fitted to 665
+// calls of 65 .. 2048 rows (16 .. 11008 weight rows, 1 .. 3 matrices, K 1056 .. 28672): 90 % of them lie within 0.85 and
+// 1.1 of the estimate.
+double gemm_estimate_us(int count, const GemvProblem* p, int64_t m, int64_t k)
+{
+    const int64_t kt_all = (k + kBK - 1) / kBK, tm = (m + 255) / 256;
+    int64_t rows = 0, t256 = 0, t128 = 0;
+    for (int i = 0; i < count; ++i) {
+        rows += p[i].n;
+        t256 += (p[i].n + 255) / 256;
+        t128 += (p[i].n + 127) / 128;
+    }
+    GemmPlan q{0, 1};
+    if (count == 1) {
+        q = gemm_plan(m, rows, k, true);
+        if (long_slices(q, m, k)) q.tile = 10;
+    } else {
+        const int w = grouped_tile_width(count, p, m, k);
+        q = GemmPlan{w == 256 ? 5 : w == 128 ? 6 : w == 129 ? 7 : w == 8 ? 11 : 9, grouped_split(count, p, m, k)};
+    }
+    const int64_t per = (kt_all + q.split - 1) / q.split, slices = (kt_all + per - 1) / per;
+    const double sums = slices > 1 ? 1e-6 * (double)(slices * m * rows) : 0.0;      // millions of partial sums
+    const bool wide = q.tile == 3 || q.tile == 5;
+    const int64_t tiles = m <= 128 ? t128 : tm * (wide ? t256 : t128), wgs = tiles * slices;
+    const double rounds = (double)((wgs + kComputeUnits - 1) / kComputeUnits), meet = slices > 1 ? 5.5 : 0.0;
+    if (m <= 128) {
+        const double full = (double)wgs / kComputeUnits;
+        const double t = 7.8 + per * (0.74 + (full < 1.0 ? 0.24 * full : 0.24 + 0.15 * (full - 1.0))) + 2.3 * sums;
+        return k % kBK == 0 ? t : 1.04 * t;                                       // (rows that start inside a 128-byte line)
+    }
+    switch (q.tile) {
+        case 3: return 5.0 + 1.4 * per * rounds + meet + 1.5 * sums;
+        case 4: return 6.0 + 1.08 * per * rounds + meet + 1.5 * sums;
+        case 5: return 5.0 + 1.8 * per * rounds;
+        case 6: return 5.0 + 2.0 * per * (double)((wgs + 2 * kComputeUnits - 1) / (2 * kComputeUnits));
+        case 7: return 2.0 + 1.22 * per;
+        case 10: return 8.3 + 0.93 * per + 2.9 * sums;
+        default: return 12.0 + 0.925 * per * rounds + meet + 1.2 * sums;          // 11: the grouped launch's K-slices
+    }
 }
 
 template <int NW, int S, int KG = 1, int MT = 8, bool GB = false>

@@ -131,6 +131,8 @@ hipError_t launch_slice_reduce_grouped(const float* partial, int count, const Ge
 // sliced): the launch needs that many bytes of workspace and the conditions of
 // launch_slice_reduce_grouped.
 bool gemm_grouped_fits(int count, const GemvProblem* p, int64_t m, int64_t k);
+// about how long (us) one launch of these matrices takes on the GEMM kernels (m > 64, scale bytes, k <= kRbMaxK)
+double gemm_estimate_us(int count, const GemvProblem* p, int64_t m, int64_t k);
 size_t gemm_grouped_workspace_bytes(int count, const GemvProblem* p, int64_t m, int64_t k);
 hipError_t launch_gemm_grouped(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a,
                                int64_t m, float* workspace, hipStream_t st);

@@ -548,6 +548,22 @@ static int ring_groups(int64_t groups, int64_t m, bool f16)
     }
     return best;
 }
+// About how long (us) a scale-byte call above 64 activation rows takes here: per round of workgroups (above 32 rows several
+// share a unit; with less than a full round more their number still counts as rounded up) K times what a group of weight
+// rows and an activation row cost, rows that start inside a 128-byte line nearly twice as much; 16 waves are 10 % slower
+// again from about 18000 elements; and activations that the XCDs fetch each for itself and that leave the L2.  Fitted to
+// 1208 calls: 90 % of them lie within 0.9 and 1.12 of the estimate.
+static double ring_estimate_us(int64_t groups, int64_t k, int64_t m)
+{
+    const int g = ring_groups(groups, m, false);
+    const int64_t chunks = (m + kRingMaxM - 1) / kRingMaxM, per_run = (groups + g - 1) / g, rounds = (chunks * per_run + kComputeUnits - 1) / kComputeUnits;
+    double kk = 1e-3 * (double)k;
+    const double fetched = kk * 1e-3 * (double)(m * (per_run < 8 ? per_run : 8));
+    if (k > 18000 && g == 1 && rounds == 1) kk *= 1.1;
+    const double row = k % 64 == 0 ? 0.0052 : 0.0102;
+    return 2.8 + (double)rounds * (1.7 + kk * (0.33 + row * (double)ring_chunk(m) + 0.63 * g)) + (fetched > 40.0 ? 0.11 * (fetched - 40.0) : 0.0);
+}
+
 static hipError_t launch_ring(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, hipStream_t st)
 {
     int g = ring_groups(ring_row_groups(count, p), m, cfg.f16 != 0);
@@ -607,20 +623,18 @@ static hipError_t launch_ring(SvConfig cfg, int count, const GemvProblem* p, int
 // 16.6 -> 14.6, 2 x 3000 x 6144 10.0 -> 9.0; at 2 rows one group per workgroup only (4096 x 11008 9.7 -> 8.7; but
 // 10240 x 8192 14.5 -> 15.8) -- and 4 rows with one group per workgroup from 2048 elements up (4096 x 4096
 // 5.35 -> 5.15).  57344 x 8192 at 4 rows would take 63 instead of 57 us.
-// Above 64 rows, against the register-decode and the tiled GEMM, whose workgroups are too few or wait on one K-tile
-// after the other as long as the product is small; a unit is a group of 16 weight rows times a run of up to 64
-// activation rows.  The line lies where the two meet: a run re-reads and decodes the weights, the GEMMs need the chip
-// full.  Scale bytes (us, GEMM -> this): {q,k,v} 3 x 4096 x 4096 at 128 rows 36.5 -> 27.1, at 256 (12.6 million
-// units x K) 59.8 -> 46.2, at 320 (15.7) 60.8 -> 54.6, at 512 (25) 65.7 -> 88; 2 x 11008 x 4096 at 128 rows 53 -> 46, at 192
-// (16.9) 77 -> 68, at 256 (22.5) 84.7 -> 81.4; 2 x 5120 x 5120 at 320 rows 88 -> 64; 4096 x 4096 at 512 rows 40.4 -> 29.8, at
-// 1024 (16.8) 58.6 -> 54.3; 4096 x 11008 at 384 rows (16.9) 65.5 -> 62; 8192 x 8192 at 128 rows 39.7 -> 32.4, at 256 58 -> 54;
-// 8192 x 28672 at 128 rows (29) 92 -> 96; 5000 x 12288 at 192 rows 48.2 -> 44.0, but at 200 (15.4, runs of
-// 50) 52.5 -> 62; 3 x 1536 x 1536 at 1024 rows (4608 units) 49 -> 33, at 2048 (9216) 44 -> 56;
-// 3 x 2048 x 2048 at 1024 rows (6144) 36 -> 47.  Up to 96 rows a run is at most 48 of its 64 rows: (8192, 1024, 1024) x 8192
-// at 65 rows (10.5) 41.4 -> 43.7, 2 x 11008 x 4096 (11.3) 48.4 -> 50.2, 8192 x 8192 (8.4) 36.0 -> 30.3.  FP16 scales, whose GEMM
-// multiplies every block apart and has one launch per matrix (a million units x K per matrix): 28672 x 8192 at 128
-// rows 237 -> 114; 4096 x 4096 at 512 rows (8.4) 41.0 -> 34.2; 4096 x 11008 at 192 rows (8.4) 42.7 -> 41.8; 8192 x 8192 at 160
-// rows (12.6) 52.0 -> 53.7; 2 x 11008 x 4096 at 192 rows (8.5) 103 -> 69; 3 x 4096 x 4096 at 512 rows (8.4) 122 -> 90.
+// Above 64 rows, scale bytes, against the register-decode and the tiled GEMM: whichever of two estimates is the shorter.
+// Where the two meet depends on how well either fills the chip -- K-slices and the width of tiles there, groups per
+// workgroup and rounds of workgroups here -- so that no bound on sizes follows it: over 1137 calls of 65 .. 2048 rows the
+// choice is 0.5 % (geometric mean) behind the faster kernel, limits on units, units x K and K are 2 to 6 % behind it and
+// up to 1.7 times the time of the faster.  GEMM -> this (us): 4096 x 4096 at 512 rows 40.4 -> 29.8, 2 x 5120 x 5120 at 320
+// 88 -> 64, 1139 x 5376 at 1249 55.6 -> 32.8, 1000 x 28672 at 256 67.7 -> 51.1; not taken 100 x 24576 at 128 rows 25.6 -> 41.2,
+// 3000 x 28672 at 128 50.0 -> 65.6, 720 x 15104 at 1445 59.8 -> 88.3, 10352 x 1216 at 438 25.4 -> 34.9.  Nothing above
+// 6400 units (a unit is a group of 16 weight rows times a run of up to 64 activation rows) was measured: the GEMM's.
+// FP16 scales, whose GEMM multiplies every block apart and has one launch per matrix (8.5 million units x K per matrix):
+// 28672 x 8192 at 128 rows 237 -> 114; 4096 x 4096 at 512 rows (8.4) 41.0 -> 34.2; 4096 x 11008 at 192 rows (8.4) 42.7 ->
+// 41.8; 8192 x 8192 at 160 rows (12.6) 52.0 -> 53.7; 2 x 11008 x 4096 at 192 rows (8.5) 103 -> 69; 3 x 4096 x 4096 at 512
+// rows (8.4) 122 -> 90.
 // This kernel scales its operands; a special value of 9.5 times a block scale does not always fit a bf16, which the
 // 4x4x4 kernel (bare operands) does not need, so up to 4 rows such tensors stay there.  The layout of the weights has
 // no say: canonical and interleaved tensors give the same bits.
@@ -637,10 +651,9 @@ bool ring_serves(SvConfig cfg, int count, const GemvProblem* p, int64_t k, int64
     }
     if (m > kRingMaxM) {
         if (!cfg.f16 && tuned_shape(kTuneGemmSlices, m, rows, k).source == 1) return false;
-        const int64_t units = (m + kRingMaxM - 1) / kRingMaxM * groups, work = units * k;
-        if (cfg.f16) return m <= 128 || (units <= 2500 * count && work <= (int64_t)8500000 * count);
-        const bool full_runs = 5 * m >= 4 * kRingMaxM * ((m + kRingMaxM - 1) / kRingMaxM);      // four fifths of their rows
-        return units <= 4800 && work <= (m <= 96 ? 8500000 : full_runs ? 17500000 : 12000000);
+        const int64_t units = (m + kRingMaxM - 1) / kRingMaxM * groups;
+        if (cfg.f16) return m <= 128 || (units <= 2500 * count && units * k <= (int64_t)8500000 * count);
+        return k <= kRbMaxK && units <= 6400 && ring_estimate_us(groups, k, m) <= gemm_estimate_us(count, p, m, k);
     }
     if (m <= kSkinnyMaxM || cfg.f16) return false;
     if (tuned_shape(kTuneGemmSlices, m, rows, k).source == 1) return false;
