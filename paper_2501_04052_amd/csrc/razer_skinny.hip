@@ -266,7 +266,8 @@ __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
         uint32_t sw[G][SF ? 1 : H];
 #pragma unroll
         for (int h = 0; h < H; ++h) {
-            // what this part reads has landed: in the second half the next step's codes and scales may be under way
+            // what this part reads has landed: in the second half the next step's codes and scales, the newest 2 G
+            // copies, may be under way (copies land in the order of their issue)
             if (h == 1 && step + nwaves < nsteps) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * G) : "memory");
             else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             v4u af[NB][J];
@@ -307,7 +308,10 @@ __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
             }
             // (everything that the copies overwrite has been read)
             const uint32_t next = step + nwaves;
-            if (h + 1 < H) issue(step, no, yes, 1u);
+            if (h + 1 < H) {
+                issue(step, no, yes, 1u);
+                __builtin_amdgcn_sched_barrier(0);                    // (the count of the second half's wait is about this order)
+            }
             if (next < nsteps) {
                 if constexpr (H == 1) issue(next, yes, yes, 0u);
                 else if (h == 0) issue(next, yes, no, 0u);

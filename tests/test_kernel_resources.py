@@ -108,6 +108,42 @@ def test_registers_of_lds_reads_are_left_alone_until_their_wait():
     assert _uses_before_wait([".LBB0_1:", use, read, "s_cbranch_scc1 .LBB0_1", "s_waitcnt lgkmcnt(0)", "s_endpgm"]) == {use, read}
 
 
+def _copies_before_counted_wait(lines):
+    """What stands between a full wait for copies and the next counted one, in the order of issue: a = 16-byte copy, s =
+    scale copy (1 or 2 bytes), | = branch."""
+    seq, found = "", []
+    for line in lines:
+        op = line.split(";")[0].strip()
+        if op.startswith("global_load_lds"):
+            seq += "a" if op.startswith("global_load_lds_dwordx4") else "s"
+        elif op.startswith(("s_cbranch", "s_branch")):
+            seq += "" if seq.endswith("|") else "|"
+        elif op.startswith("s_waitcnt") and "vmcnt" in op:
+            n = int(re.search(r"vmcnt\((\d+)\)", op).group(1))
+            if n:
+                found.append((n, seq))
+            elif not seq.strip("|").endswith("s") or not seq.strip("|"):      # (the wait in place of the counted one when nothing follows)
+                seq = ""
+    return found
+
+
+def test_small_batch_kernel_counts_the_copies_it_may_leave():
+    """With activations in halves the wait ahead of the second half leaves the newest 2 G copies in flight.  Copies land in
+    the order of their issue, so these must be the next step's G codes and G scales and every activation copy must stand
+    before them."""
+    kernels = 0
+    for m in re.finditer(r"^(_ZN5razer11ring_kernelILi(\d+)ELi(\d)ELb[01]ELi[01]ELi\d+ELb[01]ELi2EE\S*):[^\n]*\n(.*?)^\.Lfunc_end", _asm("razer_skinny.hip"), re.S | re.M):
+        na, g = int(m.group(2)), int(m.group(3))
+        kernels += 1
+        assert _copies_before_counted_wait(m.group(4).split("\n")) == [(2 * g, "a" * (na // 2) + "|" + "a" * g + "s" * g + "|")], m.group(1)
+    assert kernels >= 17
+    # the check itself: an activation copy behind the codes
+    copy, scale, wait = "global_load_lds_dwordx4 v1, s[0:1]", "global_load_lds_ushort v1, s[0:1]", "s_waitcnt vmcnt(2)"
+    full = ["s_waitcnt vmcnt(0)", copy, copy, "s_cbranch_scc1 .L1", copy, scale, ".L1:", "s_cbranch_scc1 .L2", "s_waitcnt vmcnt(0)", "s_cbranch_scc1 .L3", wait]
+    assert _copies_before_counted_wait(full) == [(2, "aa|as|")]
+    assert _copies_before_counted_wait(full[:2] + full[3:5] + [copy] + full[5:]) == [(2, "a|aas|")]
+
+
 def test_no_scratch_no_dispatch_packet():
     with ThreadPoolExecutor(max_workers=6) as ex:
         outs = list(ex.map(_asm, build.SOURCES))
