@@ -310,7 +310,7 @@ __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
             const uint32_t next = step + nwaves;
             if (h + 1 < H) {
                 issue(step, no, yes, 1u);
-                __builtin_amdgcn_sched_barrier(0);                    // (the count of the second half's wait is about this order)
+                __builtin_amdgcn_sched_barrier(0x40F);                // no memory operation crosses: the second half's wait counts on this order
             }
             if (next < nsteps) {
                 if constexpr (H == 1) issue(next, yes, yes, 0u);
