@@ -212,7 +212,7 @@ __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
         if constexpr (decltype(acts)::value) {
             if constexpr (NA == 8) __builtin_amdgcn_sched_barrier(0); // (the first copies ahead of these addresses: 2 %)
             const uint32_t first = part * (128u / H);                 // elements past K: the step's first ones again
-            if (NA == 16 && H == 1 && full) {                         // (16 copies: without the selections 3-5 %)
+            if (NA >= 2 && H == 1 && full) {                          // (without the selections: 2 %, 64 rows 3-5)
 #pragma unroll
                 for (int i = 0; i < AC; ++i) RAZER_COPY(abytes + (size_t)step * 256u, arow[i] + achk[i] * 16u, ring + i * 1024, 16);
                 return;
