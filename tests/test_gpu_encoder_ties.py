@@ -98,18 +98,17 @@ def test_blocks_far_above_a_given_scale(oracle, fmt, sv, block, clip):
 
 
 @pytest.mark.parametrize("dtype,rows", [(torch.float32, 65535), (torch.float32, 65536), (torch.float32, 65537), (torch.float32, 786433),
-                                        (torch.bfloat16, 131073), (torch.bfloat16, 1572865), (torch.float32, 3)])
+                                        (torch.bfloat16, 131073), (torch.bfloat16, 1572865), (torch.float32, 3), (torch.bfloat16, 40000), (torch.float32, 128001)])
 def test_tensor_scale_sees_every_element(dtype, rows):
-    """Eq. 1's maximum at the first and last element and around the end of the unrolled loads; below and above the size
-    that is read around the caches."""
+    """Eq. 1's maximum at the first and last element, around the end of the unrolled loads and at either side of each
+    stride of what is left; below and above the size that is read around the caches."""
     cols = 32
     n = rows * cols
-    x = torch.zeros(n, dtype=dtype, device="cuda")
-    unrolled = 256 * 256 * 8 * (16 // x.element_size())
-    for i in {0, n - 1, min(n, n // unrolled * unrolled) - 1, min(n - 1, n // unrolled * unrolled), n // 2}:
-        if i < 0:
-            continue
-        x[i] = -180.0
+    x = torch.full((n,), 90.0, dtype=dtype, device="cuda")             # (a tensor scale of 0.5; of an all-zero tensor 1)
+    stride = 256 * 256 * (16 // x.element_size())
+    whole = n // (8 * stride) * 8 * stride
+    for i in {0, n - 1, n // 2} | {min(max(whole + j * stride + d, 0), n - 1) for j in range(9) for d in (-1, 0)}:
+        x[i] = -360.0
         t = razer.razer_quantize(x.view(rows, cols), razer.WEIGHT, (5.0, 8.0))
-        assert float(t.tensor_scale) == 1.0, i
-        x[i] = 0.0
+        assert float(t.tensor_scale) == 2.0, i
+        x[i] = 90.0
