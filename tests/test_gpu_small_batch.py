@@ -72,8 +72,35 @@ def test_runs_of_activation_rows(oracle, m, ns, k, fmt, block):
 @pytest.mark.parametrize("m,n,k,fmt,block", [(9, 37, 4096 + 96, razer.WEIGHT, 16), (16, 70, 4096, razer.WEIGHT, 64), (16, 20, 4224, razer.WEIGHT_F16, 128),
                                              (40, 37, 10240 + 96, razer.WEIGHT, 16), (64, 20, 10240, razer.WEIGHT_F16, 128), (33, 16485, 160, razer.WEIGHT, 16), (64, 16485, 192, razer.WEIGHT, 32), (64, 16485, 128, razer.WEIGHT_F16, 128)])
 def test_number_of_waves(oracle, m, n, k, fmt, block):
-    """16 waves with one group per workgroup and rows long enough; 4 above 32 rows with more workgroups than compute units."""
+    """16 waves with one group per workgroup and rows long enough; fewer where K has fewer steps than waves."""
     _run(oracle, (n,), k, m, fmt, block)
+
+
+@pytest.mark.parametrize("m,k,fmt,block", [(33, 1184, razer.WEIGHT, 16), (64, 1280 + 96, razer.WEIGHT, 32), (64, 1280, razer.WEIGHT_F16, 128), (130, 1152, razer.WEIGHT, 16)])
+def test_four_waves_where_workgroups_outnumber_compute_units(oracle, m, k, fmt, block):
+    """Nine steps of K and more, so that every wave takes a second one; the order of the sum is another than that of the
+    eight waves which a forced shape asks for."""
+    n = 16485
+    print("four waves", m, k, fmt, block, flush=True)
+    a = synth.activation(m, k, seed=4600 + m)
+    a_dev = bf16_bits_to_dev(a)
+    wq, wt = _weights(n, k, 4601 + k, fmt, block)
+    got = []
+    names = launched_kernels(lambda: got.append(razer.razer_linear(wt, a_dev)))
+    groups = [int(x.split("ring_kernel<")[1].split(",")[1]) for x in names if "ring_kernel<16," in x]
+    assert len(groups) == 1 == len(names), names
+    assert -(-n // 16 // groups[0]) * -(-m // 64) > 256                # workgroups
+    razer.razer_tune_force(binding.TUNE_SMALL_BATCH, (2, groups[0], 8))
+    try:
+        eight = dev_to_bf16_bits(razer.razer_linear(wt, a_dev))
+    finally:
+        razer.razer_tune_force(binding.TUNE_SMALL_BATCH, None)
+    got = dev_to_bf16_bits(got[0])
+    cols = np.unique(np.r_[0, n - 1, n - 17, np.random.default_rng(46).choice(n, size=200, replace=False)])
+    y64, _ = oracle.linear((wq[0][cols], wq[1][cols], wq[2]), a_bf16=a)
+    for y in (got, eight):
+        assert max_rel_err(y[:, cols], y64) <= TOL
+    assert (got != eight).any()
 
 
 @pytest.mark.parametrize("m,n,k,block,groups,halves", [(130, 37, 9312, 16, None, 1), (130, 37, 9312, 32, None, 1), (130, 37, 4128, 16, None, 2), (64, 3077, 224, 16, None, 1),
