@@ -1719,17 +1719,25 @@ size_t gemm_grouped_workspace_bytes(int count, const GemvProblem* p, int64_t m, 
 }
 
 // About how long (us) a scale-byte weight call above 64 activation rows takes on the kernels of this file: a start, the
-// K-tiles that a workgroup works through one after the other, and the slices' way through the workspace.  Fitted to 665
-// calls of 65 .. 2048 rows (16 .. 11008 weight rows, 1 .. 3 matrices, K 1056 .. 28672): 90 % of them lie within 0.85 and
-// 1.1 of the estimate.
+// K-tiles that a workgroup works through one after the other (slower the fuller the chip is, and where activation rows
+// start inside a 128-byte line), the slices' way through the workspace, the output, which rows that are no multiple of 8
+// (slices: 4) let a lane store only an element at a time.  Fitted to 863 calls of 65 .. 2048 rows (16 .. 11008 weight
+// rows, 1 .. 3 matrices, K 1024 .. 28672) on which neither kernel takes more than 1.7 times the other's time: 90 % of them
+// lie within 0.93 and 1.08 of the estimate.
 double gemm_estimate_us(int count, const GemvProblem* p, int64_t m, int64_t k)
 {
+    struct Terms {
+        double start, tile, fill, off_line, meet, sums, sums_by_one, out, out_by_one;   // per call; K-tile (3 x); call; million values (4 x)
+    };
     const int64_t kt_all = (k + kBK - 1) / kBK, tm = (m + 255) / 256;
     int64_t rows = 0, t256 = 0, t128 = 0;
+    bool by4 = true, by8 = true;
     for (int i = 0; i < count; ++i) {
         rows += p[i].n;
         t256 += (p[i].n + 255) / 256;
         t128 += (p[i].n + 127) / 128;
+        by4 = by4 && p[i].n % 4 == 0;
+        by8 = by8 && p[i].n % 8 == 0;
     }
     GemmPlan q{0, 1};
     if (count == 1) {
@@ -1740,24 +1748,25 @@ double gemm_estimate_us(int count, const GemvProblem* p, int64_t m, int64_t k)
         q = GemmPlan{w == 256 ? 5 : w == 128 ? 6 : w == 129 ? 7 : w == 8 ? 11 : 9, grouped_split(count, p, m, k)};
     }
     const int64_t per = (kt_all + q.split - 1) / q.split, slices = (kt_all + per - 1) / per;
-    const double sums = slices > 1 ? 1e-6 * (double)(slices * m * rows) : 0.0;      // millions of partial sums
-    const bool wide = q.tile == 3 || q.tile == 5;
-    const int64_t tiles = m <= 128 ? t128 : tm * (wide ? t256 : t128), wgs = tiles * slices;
-    const double rounds = (double)((wgs + kComputeUnits - 1) / kComputeUnits), meet = slices > 1 ? 5.5 : 0.0;
-    if (m <= 128) {
-        const double full = (double)wgs / kComputeUnits;
-        const double t = 7.8 + per * (0.74 + (full < 1.0 ? 0.24 * full : 0.24 + 0.15 * (full - 1.0))) + 2.3 * sums;
-        return k % kBK == 0 ? t : 1.04 * t;                                       // (rows that start inside a 128-byte line)
-    }
+    const int64_t wgs = (m <= 128 ? t128 : tm * (q.tile == 3 || q.tile == 5 ? t256 : t128)) * slices;
+    const double full = (double)wgs / kComputeUnits, values = 1e-6 * (double)(m * rows), sums = slices > 1 ? (double)slices * values : 0.0;
+    const double off_line = k % kBK == 0 ? 0.0 : 1.0;
+    if (m <= 128)
+        return 8.9 + per * (0.68 + (full < 1.0 ? 0.15 * full : 0.6 * full - 0.45) + 0.1 * off_line) + (by4 ? 1.7 : 2.9) * sums;
+    Terms t;
     switch (q.tile) {
-        case 3: return 5.0 + 1.4 * per * rounds + meet + 1.5 * sums;
-        case 4: return 6.0 + 1.08 * per * rounds + meet + 1.5 * sums;
-        case 5: return 5.0 + 1.8 * per * rounds;
-        case 6: return 5.0 + 2.0 * per * (double)((wgs + 2 * kComputeUnits - 1) / (2 * kComputeUnits));
-        case 7: return 2.0 + 1.22 * per;
-        case 10: return 8.3 + 0.93 * per + 2.9 * sums;
-        default: return 12.0 + 0.925 * per * rounds + meet + 1.2 * sums;          // 11: the grouped launch's K-slices
+        case 3: t = Terms{2.0, 1.81, 0.0, 0.0, 0.0, 0.0, 11.5, 1.75, 1.5}; break;
+        case 4: t = Terms{5.7, 0.97, 0.09, 0.03, 5.9, 1.5, 1.7, 0.0, 2.8}; break;
+        case 5: t = Terms{10.9, 0.93, 0.66, 0.03, 0.0, 0.0, 0.0, 1.0, 1.3}; break;
+        case 6: t = Terms{5.4, 0.65, 0.58, 0.05, 0.0, 0.0, 0.0, 0.8, 1.5}; break;
+        case 7: t = Terms{9.5, 0.49, 0.51, 0.09, 0.0, 0.0, 0.0, 0.0, 2.3}; break;
+        case 10: t = Terms{0.0, 0.67, 0.3, 0.0, 18.8, 1.0, 1.6, 0.0, 0.0}; break;
+        default: t = Terms{8.0, 0.86, 0.05, 0.065, 5.0, 1.6, 0.0, 0.0, 2.1}; break;   // 11: the grouped launch's K-slices
     }
+    const int64_t units = q.tile == 6 ? 2 * kComputeUnits : kComputeUnits;
+    const double rounds = (double)((wgs + units - 1) / units);
+    const double us = t.start + per * (t.tile * rounds + t.fill * full + t.off_line * off_line * rounds);
+    return slices > 1 ? us + t.meet + (t.sums + (by4 ? 0.0 : t.sums_by_one)) * sums : us + (t.out + (by8 ? 0.0 : t.out_by_one)) * values;
 }
 
 template <int NW, int S, int KG = 1, int MT = 8, bool GB = false>

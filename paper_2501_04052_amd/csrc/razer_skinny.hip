@@ -555,17 +555,26 @@ static int ring_groups(int64_t groups, int64_t m, bool f16)
 // About how long (us) a scale-byte call above 64 activation rows takes here: per round of workgroups (above 32 rows several
 // share a unit; with less than a full round more their number still counts as rounded up) K times what a group of weight
 // rows and an activation row cost, rows that start inside a 128-byte line nearly twice as much; 16 waves are 10 % slower
-// again from about 18000 elements; and activations that the XCDs fetch each for itself and that leave the L2.  Fitted to
-// 1208 calls: 90 % of them lie within 0.9 and 1.12 of the estimate.
-static double ring_estimate_us(int64_t groups, int64_t k, int64_t m)
+// again from about 18000 elements; activations that the XCDs fetch each for itself and that leave the L2; and the output,
+// which rows that are no multiple of 4 let a lane store only an element at a time.  Fitted to 863 calls on which neither
+// kernel takes more than 1.7 times the other's time: 90 % of them lie within 0.93 and 1.1 of the estimate.
+static double ring_estimate_us(int count, const GemvProblem* p, int64_t k, int64_t m)
 {
+    int64_t rows = 0;
+    bool by4 = true;
+    for (int i = 0; i < count; ++i) {
+        rows += p[i].n;
+        by4 = by4 && p[i].n % 4 == 0;
+    }
+    const int64_t groups = ring_row_groups(count, p);
     const int g = ring_groups(groups, m, false);
     const int64_t chunks = (m + kRingMaxM - 1) / kRingMaxM, per_run = (groups + g - 1) / g, rounds = (chunks * per_run + kComputeUnits - 1) / kComputeUnits;
     double kk = 1e-3 * (double)k;
-    const double fetched = kk * 1e-3 * (double)(m * (per_run < 8 ? per_run : 8));
+    const double fetched = kk * 1e-3 * (double)(m * (per_run < 8 ? per_run : 8)), values = 1e-6 * (double)(m * rows);
     if (k > 18000 && g == 1 && rounds == 1) kk *= 1.1;
-    const double row = k % 64 == 0 ? 0.0052 : 0.0102;
-    return 2.8 + (double)rounds * (1.7 + kk * (0.33 + row * (double)ring_chunk(m) + 0.63 * g)) + (fetched > 40.0 ? 0.11 * (fetched - 40.0) : 0.0);
+    const double row = k % 64 == 0 ? 0.0074 : 0.0131;
+    return 5.1 + (double)rounds * kk * (0.27 + row * (double)ring_chunk(m) + 0.52 * g) + (fetched > 40.0 ? 0.115 * (fetched - 40.0) : 0.0) +
+           (by4 ? 2.2 : 2.5) * values;
 }
 
 static hipError_t launch_ring(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, hipStream_t st)
@@ -629,16 +638,18 @@ static hipError_t launch_ring(SvConfig cfg, int count, const GemvProblem* p, int
 // 5.35 -> 5.15).  57344 x 8192 at 4 rows would take 63 instead of 57 us.
 // Above 64 rows, scale bytes, against the register-decode and the tiled GEMM: whichever of two estimates is the shorter.
 // Where the two meet depends on how well either fills the chip -- K-slices and the width of tiles there, groups per
-// workgroup and rounds of workgroups here -- so that no bound on sizes follows it: over 1137 calls of 65 .. 2048 rows the
-// choice is 0.5 % (geometric mean) behind the faster kernel, limits on units, units x K and K are 2 to 6 % behind it and
-// up to 1.7 times the time of the faster.  GEMM -> this (us): 4096 x 4096 at 512 rows 40.4 -> 29.8, 2 x 5120 x 5120 at 320
-// 88 -> 64, 1139 x 5376 at 1249 55.6 -> 32.8, 1000 x 28672 at 256 67.7 -> 51.1; not taken 100 x 24576 at 128 rows 25.6 -> 41.2,
-// 3000 x 28672 at 128 50.0 -> 65.6, 720 x 15104 at 1445 59.8 -> 88.3, 10352 x 1216 at 438 25.4 -> 34.9.  Nothing above
-// 6400 units (a unit is a group of 16 weight rows times a run of up to 64 activation rows) was measured: the GEMM's.
-// FP16 scales, whose GEMM multiplies every block apart and has one launch per matrix (8.5 million units x K per matrix):
-// 28672 x 8192 at 128 rows 237 -> 114; 4096 x 4096 at 512 rows (8.4) 41.0 -> 34.2; 4096 x 11008 at 192 rows (8.4) 42.7 ->
-// 41.8; 8192 x 8192 at 160 rows (12.6) 52.0 -> 53.7; 2 x 11008 x 4096 at 192 rows (8.5) 103 -> 69; 3 x 4096 x 4096 at 512
-// rows (8.4) 122 -> 90.
+// workgroup and rounds of workgroups here -- so that no bound on sizes follows it: over 1346 calls of 65 .. 2048 rows the
+// choice is 0.23 % (geometric mean) behind the faster kernel and at most 1.17 times its time (over 451 calls that nothing was
+// fitted to 0.17 %, 1.10); limits on units, units x K
+// and K are 1.6 to 8 % behind it and up to 2.9 times.  GEMM -> this (us): 4096 x 4096 at 512 rows 40.4 -> 29.8, 2 x 5120 x
+// 5120 at 320 88 -> 64, 1139 x 5376 at 1249 55.6 -> 32.8, 1000 x 28672 at 256 67.7 -> 51.1, 2865 x 8832 at 380 62.2 -> 43.9,
+// 5539 x 1536 at 1390 (rows that the GEMM stores an element at a time) 83.8 -> 57.6; not taken 100 x 24576 at 128 rows 25.6
+// -> 41.2, 3000 x 28672 at 128 50.0 -> 65.6, 720 x 15104 at 1445 59.8 -> 88.3, 10352 x 1216 at 438 25.4 -> 34.9, 130 x 21696
+// at 1514 60.5 -> 84.7.
+// FP16 scales, whose GEMM multiplies every block apart and has one launch per matrix: 8.5 million units (a group of 16
+// weight rows times a run of up to 64 activation rows) x K per matrix.  28672 x 8192 at 128 rows 237 -> 114; 4096 x 4096 at
+// 512 rows (8.4) 41.0 -> 34.2; 4096 x 11008 at 192 rows (8.4) 42.7 -> 41.8; 8192 x 8192 at 160 rows (12.6) 52.0 -> 53.7;
+// 2 x 11008 x 4096 at 192 rows (8.5) 103 -> 69; 3 x 4096 x 4096 at 512 rows (8.4) 122 -> 90.
 // This kernel scales its operands; a special value of 9.5 times a block scale does not always fit a bf16, which the
 // 4x4x4 kernel (bare operands) does not need, so up to 4 rows such tensors stay there.  The layout of the weights has
 // no say: canonical and interleaved tensors give the same bits.
@@ -655,9 +666,11 @@ bool ring_serves(SvConfig cfg, int count, const GemvProblem* p, int64_t k, int64
     }
     if (m > kRingMaxM) {
         if (!cfg.f16 && tuned_shape(kTuneGemmSlices, m, rows, k).source == 1) return false;
-        const int64_t units = (m + kRingMaxM - 1) / kRingMaxM * groups;
-        if (cfg.f16) return m <= 128 || (units <= 2500 * count && units * k <= (int64_t)8500000 * count);
-        return k <= kRbMaxK && units <= 6400 && ring_estimate_us(groups, k, m) <= gemm_estimate_us(count, p, m, k);
+        if (cfg.f16) {
+            const int64_t units = (m + kRingMaxM - 1) / kRingMaxM * groups;
+            return m <= 128 || (units <= 2500 * count && units * k <= (int64_t)8500000 * count);
+        }
+        return k <= kRbMaxK && ring_estimate_us(count, p, k, m) <= gemm_estimate_us(count, p, m, k);
     }
     if (m <= kSkinnyMaxM || cfg.f16) return false;
     if (tuned_shape(kTuneGemmSlices, m, rows, k).source == 1) return false;

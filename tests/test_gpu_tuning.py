@@ -141,7 +141,8 @@ def test_a_forced_shape_launches_what_its_entry_would(m, family, shape, kernel):
     (128, (100,), 24576, "gemm_rb_kernel"), (65, (300,), 20480, "gemm_rb_kernel"), (128, (3000,), 28672, "gemm_rb_kernel"), (128, (1000,), 8192, "ring_kernel"),
     (1445, (720,), 15104, "gemm_"), (438, (10352,), 1216, "gemm_"), (2015, (220, 24), 28160, "gemm_"), (1454, (326,), 24960, "gemm_"),
     (512, (4096,), 4096, "ring_kernel"), (700, (300,), 4096, "ring_kernel"), (320, (5120, 5120), 5120, "ring_kernel"), (256, (1000,), 28672, "ring_kernel"),
-    (1024, (1536, 1536, 1536), 1536, "ring_kernel"), (2048, (4096,), 4096, "gemm_")])
+    (1024, (1536, 1536, 1536), 1536, "ring_kernel"), (2048, (4096,), 4096, "gemm_"),
+    (380, (2865,), 8832, "ring_kernel"), (1250, (899,), 6720, "ring_kernel"), (1390, (5539,), 1536, "ring_kernel"), (1514, (130,), 21696, "gemm_"), (1163, (5258,), 1088, "gemm_")])
 def test_the_faster_kernel_is_chosen(m, ns, k, kernel):
     """Long rows of few weights are for the GEMM, which cuts K across workgroups; each call here is 5 % or more faster on
     the kernel named, or lies right at the line."""
