@@ -1606,16 +1606,19 @@ static GemmPlan gemm_plan(int64_t m, int64_t n, int64_t k, bool register_decode_
 
 // Few 256 x 128 tiles, K-slices on the other compute units: where the slices are long, the same slices on the
 // register-decode kernel with two K groups per workgroup (tile 10).  Bound as that kernel is, and by the slices' way
-// through the workspace; the second group costs a start and a meeting, which only long slices repay.  Time against the
-// LDS-staged tiles at 8 / 16 / 32 / 40 / 43 / 64 K-tiles per slice: 1664 weight rows at 512 activation rows 1.08 /
-// 1.06 / 1.00 / 1.00 / 0.99 / 0.97, 4096 at 384 1.08 / 1.05 / 1.00 / 1.02 / 0.97 / 0.99, 1664 at 1000 1.07 / 1.03 / 0.98
-// / 0.98 / 0.95 / 0.95 (4096 x 11008 at 1000 rows 120.8 -> 113.2 us).  Not above 1024 rows (640 weight rows at 1500
-// 1.04 .. 1.10 at any length), and only with whole K-tiles: past K this kernel multiplies re-read activations by weights
-// of 0, a NaN where they are infinite (the LDS-staged one loads zeros), and rows that start inside a 128-byte line
-// make its copies ask for every line twice (1.01 .. 1.26 of the time).
-static bool long_slices(const GemmPlan& p, int64_t m, int64_t k)
+// through the workspace; the second group costs a start and a meeting.  Over 600 calls of 129 .. 4096 activation rows and
+// 18 .. 230 K-tiles per slice its time against the LDS-staged tiles is 0.97 in the middle, 0.85 .. 1.15: 0.95 and at most
+// 1.01 with up to 100 workgroups, 0.97 up to 192, above that 0.93 from 100 K-tiles on (at most 1.08; 1390 x 19520 at 1865
+// rows 183 -> 156 us), 0.95 .. 0.97 up to 512 rows from 30 K-tiles on (4096 x 11008 at 512 rows 0.97), else 1.00 with up to
+// 1.15 (896 x 21376 at 1117 rows 76.6 -> 87.9).  Below 16 K-tiles it is the slower one (8: 1.05 .. 1.09).  The choice loses
+// 1 % against the faster of the two, at most 8.  Only with whole K-tiles: past K this kernel multiplies re-read activations
+// by weights of 0, a NaN where they are infinite (the LDS-staged one loads zeros), and rows that start inside a 128-byte
+// line make its copies ask for every line twice (1.01 .. 1.26 of the time).
+static bool long_slices(const GemmPlan& p, int64_t m, int64_t n, int64_t k)
 {
-    return p.tile == 4 && p.split > 1 && k <= kRbMaxK && m <= 1024 && k % kBK == 0 && k >= (int64_t)p.split * 42 * kBK;
+    if (p.tile != 4 || p.split <= 1 || k > kRbMaxK || k % kBK != 0) return false;
+    const int64_t kt_all = k / kBK, per = (kt_all + p.split - 1) / p.split, slices = (kt_all + per - 1) / per;
+    return per >= 18 && ((m + 255) / 256 * ((n + 127) / 128) * slices <= 192 || per >= 100 || (m <= 512 && per >= 30));
 }
 
 size_t gemm_workspace_bytes(int64_t n, int64_t k, int64_t m)
@@ -1646,7 +1649,7 @@ static hipError_t launch_gemm_t(const uint8_t* w_codes, const uint8_t* w_scales,
     // operand of W4A4, which that kernel does not decode)
     GemmPlan p = gemm_plan(m, n, k, !AQ && k <= kRbMaxK);
     if ((m <= kSkinnyMaxM && k <= kSkinnyMaxK) || !workspace) p.split = 1;   // not sized a workspace
-    if (!AQ && long_slices(p, m, k)) p.tile = 10;
+    if (!AQ && long_slices(p, m, n, k)) p.tile = 10;
 #define RAZER_GEMM(BM, BN, WGM, WGN, PP) \
     launch_cfg<BM, BN, WGM, WGN, AQ, PP, GB>(w_codes, w_scales, w_ts, wcfg, n, k, a, a_codes, a_scales, a_ts, acfg, m, y, ld_y, p.split, workspace, st)
     switch (p.tile) {
@@ -1742,7 +1745,7 @@ double gemm_estimate_us(int count, const GemvProblem* p, int64_t m, int64_t k)
     GemmPlan q{0, 1};
     if (count == 1) {
         q = gemm_plan(m, rows, k, true);
-        if (long_slices(q, m, k)) q.tile = 10;
+        if (long_slices(q, m, rows, k)) q.tile = 10;
     } else {
         const int w = grouped_tile_width(count, p, m, k);
         q = GemmPlan{w == 256 ? 5 : w == 128 ? 6 : w == 129 ? 7 : w == 8 ? 11 : 9, grouped_split(count, p, m, k)};
@@ -1760,7 +1763,7 @@ double gemm_estimate_us(int count, const GemvProblem* p, int64_t m, int64_t k)
         case 5: t = Terms{10.9, 0.93, 0.66, 0.03, 0.0, 0.0, 0.0, 1.0, 1.3}; break;
         case 6: t = Terms{5.4, 0.65, 0.58, 0.05, 0.0, 0.0, 0.0, 0.8, 1.5}; break;
         case 7: t = Terms{9.5, 0.49, 0.51, 0.09, 0.0, 0.0, 0.0, 0.0, 2.3}; break;
-        case 10: t = Terms{0.0, 0.67, 0.3, 0.0, 18.8, 1.0, 1.6, 0.0, 0.0}; break;
+        case 10: t = Terms{0.0, 0.78, 0.15, 0.0, 13.9, 1.7, 1.5, 0.0, 0.0}; break;
         default: t = Terms{8.0, 0.86, 0.05, 0.065, 5.0, 1.6, 0.0, 0.0, 2.1}; break;   // 11: the grouped launch's K-slices
     }
     const int64_t units = q.tile == 6 ? 2 * kComputeUnits : kComputeUnits;

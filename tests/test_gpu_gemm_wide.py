@@ -36,12 +36,13 @@ def test_wide_tiles(oracle, m, ns, k, block):
 
 
 @pytest.mark.parametrize("m,n,k,block,kernel", [
-    # 256 x 128 tiles with two K groups: 37 to 43 K-tiles per slice, an odd and an even number of them, the shortest slices that take it
+    # 256 x 128 tiles with two K groups: 42 and 43 K-tiles per slice, the shortest slices that take it with few and with many workgroups
     (257, 260, 21568, 16, "gemm_rb_kernel<8, 2, 2, 8, false>"), (140, 130, 22016, 16, "gemm_rb_kernel<8, 2, 2, 8, false>"),
     (300, 389, 21696, 16, "gemm_rb_kernel<8, 2, 2, 8, false>"), (257, 389, 21760, 32, "gemm_rb_kernel<8, 2, 2, 8, true>"),
-    (300, 261, 21504, 64, "gemm_rb_kernel<8, 2, 2, 8, true>"),
+    (300, 261, 21504, 64, "gemm_rb_kernel<8, 2, 2, 8, true>"), (300, 389, 9152, 16, "gemm_rb_kernel<8, 2, 2, 8, false>"),
+    (512, 1664, 15360, 16, "gemm_rb_kernel<8, 2, 2, 8, false>"),
     # the LDS-staged tiles: shorter slices, K that ends inside a K-tile, one width of tiles as good as the other
-    (300, 261, 21440, 64, "gemm_pp_kernel<256, 128,"), (257, 260, 22048, 16, "gemm_pp_kernel<256, 128,"), (257, 260, 8320, 32, "gemm_pp_kernel<256, 128,"),
+    (512, 1664, 14848, 16, "gemm_pp_kernel<256, 128,"), (600, 1280, 9280, 16, "gemm_pp_kernel<256, 128,"), (257, 260, 22048, 16, "gemm_pp_kernel<256, 128,"), (257, 260, 8320, 32, "gemm_pp_kernel<256, 128,"),
     (140, 130, 8256, 64, "gemm_pp_kernel<256, 128,"), (129, 100, 8192, 16, "gemm_pp_kernel<256, 256,"), (130, 37, 8224, 16, "gemm_pp_kernel<256, 256,"),
     (300, 5, 8288, 16, "gemm_pp_kernel<256, 256,")])
 def test_k_slices_of_few_tiles(oracle, m, n, k, block, kernel):
