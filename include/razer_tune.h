@@ -23,8 +23,10 @@
  *   RAZER_TUNE_SMALL_BATCH  5 <= m where the small-batch kernel serves the call: p[0] = 2, p[1] = groups of 16
  *                           rows per workgroup (1, 2, 3, 4, 6; above 32 rows at most 4, FP16-scale format 3),
  *                           p[2] = waves that share K (8, or 16 with one group and at most 8 rows, 9 .. 16 rows
- *                           of 4096 elements or more, above 32 rows of 10240 or more; 0: the heuristic's number,
- *                           when forced 8; fewer where K has fewer steps of 128 elements).
+ *                           of 4096 elements or more, above 32 rows of 10240 or more, but not where K ends with half
+ *                           a line of activations and the kernel takes whole steps; 0: the heuristic's number, when
+ *                           forced 8; fewer where K has fewer steps of 128 elements; with 16, or with 0 in an entry,
+ *                           4 above 32 rows where the workgroups outnumber the compute units).
  *                           The number of waves is the order of the sum over K.
  *                           p[0] = 0 or 1 (5 <= m <= 32) names a shape of the kernels this one replaced: an entry
  *                           selects only the size razer_workspace_bytes reports, forced it also asks for 8 waves:

@@ -449,7 +449,7 @@ static int64_t ring_wgs(int count, const GemvProblem* p, int64_t m)
 }
 
 template <int NA, int G, bool GB, int SF, bool IL, int W, int H = ring_parts<NA, W>()>
-static hipError_t launch_ring_w(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, bool eight, hipStream_t st)
+static hipError_t launch_ring_w(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, int asked, hipStream_t st)
 {
     RingArgs arg;
     uint32_t groups = 0;
@@ -477,7 +477,7 @@ static hipError_t launch_ring_w(SvConfig cfg, int count, const GemvProblem* p, i
     static_assert(most >= 4, "LDS");
     const int64_t nsteps = (k + 127) / 128;
     const int64_t wgs = ring_wgs<G>(count, p, m);
-    const int use = NA == 16 && wgs > kComputeUnits && !eight ? 4 : most;
+    const int use = NA == 16 && wgs > kComputeUnits && asked != 8 ? 4 : most;
     const int waves = nsteps < use ? (int)nsteps : use;
     auto kern = ring_kernel<NA, G, GB, SF, W, IL, H>;
     constexpr uint32_t lds = (uint32_t)most * ring_wave_bytes<NA, G, H>();
@@ -503,32 +503,44 @@ static bool ring_split_lines(int count, const GemvProblem* p, int64_t k, int64_t
     return m * k > 1200000 || (G == 1 ? rows > 48 && wgs > 192 : rows * k > 250000);
 }
 
-// 8 waves; 16 for one group of rows and at most 16 activation rows: such a launch has at most one workgroup per compute
-// unit and little data under way, so twice the waves pay (4096 x 11008 at 4 rows 11.0 -> 8.8 us, at 8 rows 11.1 -> 9.8, at
-// 16 rows 13.0 -> 12.3, 2048 x 8192 8.7 -> 7.6; at 24 and 32 rows within 2 %, with two groups or more 0-15 % slower, and
-// from 9 rows up rows of 4096 elements are needed: 1000 x 2048 at 9 rows 4.3 -> 4.6); 16 again above 32 rows with one
-// group and rows of 10240 elements and more (4096 x 11008 at 64 rows 25.2 -> 24.4; 4096 x 4096 9.5 -> 10.0).
+// 9 .. 16 activation rows, one group of weight rows: whether the rows are long enough for 16 waves.  Sixteen start and meet
+// later than eight and save steps of the longest wave; eight also take the copies of a full step without selections.
+// Time of 16 waves against 8 at 12 rows, scale bytes: 4096 elements 1.05 with 64 weight rows, 1.02 with 1000 to 4096;
+// 4608 1.05, 1.01; 4736 1.01, 0.97; 6656 1.02, 0.98; 6784 0.98, 0.96; 11008 0.96, 0.92 .. 0.94 (4096 x 11008 13.0 -> 12.3 us).
+// FP16 scales: 4096 1.07, 1.05; 6656 1.05, 1.03; 8192 1.04, 1.01; 8832 with 2000 weight rows and more 0.98 (at 16 rows
+// 1.01); 10496 1.02, 0.99; 11008 0.99, 0.95.  (A step is 128 elements.)
+static bool ring_long_rows(bool f16, int count, const GemvProblem* p, int64_t k, int64_t m)
+{
+    const int64_t steps = (k + 127) / 128, groups = ring_row_groups(count, p);
+    return f16 ? steps > 82 || (steps > 68 && groups > 120 && m <= 12) : steps > 52 || (steps > 36 && groups > 40);
+}
+
+// 8 waves; 16 for one group of rows and at most 8 activation rows, or 16 where the rows are long: such a launch has at most
+// one workgroup per compute unit and little data under way, so twice the waves pay (4096 x 11008 at 4 rows 11.0 -> 8.8 us,
+// at 8 rows 11.1 -> 9.8; at 24 and 32 rows within 2 %, with two groups or more 0-15 % slower); 16 again above 32 rows with
+// one group and rows of 10240 elements and more (4096 x 11008 at 64 rows 25.2 -> 24.4; 4096 x 4096 9.5 -> 10.0).
 // 4 above 32 rows when the workgroups outnumber the compute units: three or four of them then share a unit, each at
 // another point of its steps (2 x 11008 x 4096 at 64 rows 31.4 -> 28.9; with one workgroup per unit 8 stay faster:
-// {q,k,v} 3 x 4096 x 4096 17.0, with 4 waves 18.4).  The number of waves decides the order of the sum over K: eight: a
-// launch shape that asks for 8.
+// {q,k,v} 3 x 4096 x 4096 17.0, with 4 waves 18.4).  The number of waves decides the order of the sum over K: asked: 8 or 16
+// where a launch shape asks for them (16 only where built and, from 9 rows up, with rows of 4096 elements or more).
 template <int NA, int G, bool GB, int SF, bool IL = false>
-static hipError_t launch_ring_t(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, bool eight, hipStream_t st)
+static hipError_t launch_ring_t(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, int asked, hipStream_t st)
 {
     if constexpr (G == 1 && NA == 1) {                            // (up to 4 rows no launch shape is asked for)
-        return launch_ring_w<NA, G, GB, SF, IL, 16>(cfg, count, p, k, a, m, eight, st);
+        return launch_ring_w<NA, G, GB, SF, IL, 16>(cfg, count, p, k, a, m, asked, st);
     } else {
         if constexpr (G == 1 && NA <= 4) {
-            if (!eight && (NA < 4 || (k >= 4096 && !ring_split_lines<NA, G>(count, p, k, m)))) return launch_ring_w<NA, G, GB, SF, IL, 16>(cfg, count, p, k, a, m, eight, st);
+            if (asked != 8 && (NA < 4 || ((asked == 16 ? k >= 4096 : ring_long_rows(SF != 0, count, p, k, m)) && !ring_split_lines<NA, G>(count, p, k, m))))
+                return launch_ring_w<NA, G, GB, SF, IL, 16>(cfg, count, p, k, a, m, asked, st);
         }
         if constexpr (NA == 16 && G <= 2 && !SF) {
             if (ring_split_lines<NA, G>(count, p, k, m))
-                return launch_ring_w<NA, G, GB, SF, IL, kRingWaves, 1>(cfg, count, p, k, a, m, eight, st);
+                return launch_ring_w<NA, G, GB, SF, IL, kRingWaves, 1>(cfg, count, p, k, a, m, asked, st);
         }
         if constexpr (G == 1 && NA == 16) {
-            if (!eight && k >= 10240) return launch_ring_w<NA, G, GB, SF, IL, 16>(cfg, count, p, k, a, m, eight, st);
+            if (asked != 8 && k >= 10240) return launch_ring_w<NA, G, GB, SF, IL, 16>(cfg, count, p, k, a, m, asked, st);
         }
-        return launch_ring_w<NA, G, GB, SF, IL, kRingWaves>(cfg, count, p, k, a, m, eight, st);
+        return launch_ring_w<NA, G, GB, SF, IL, kRingWaves>(cfg, count, p, k, a, m, asked, st);
     }
 }
 
@@ -588,12 +600,12 @@ static hipError_t launch_ring(SvConfig cfg, int count, const GemvProblem* p, int
     if (m > kGemvDirectMaxM) t = tuned_shape(kTuneSmallBatch, m, rows, k);
     const bool shaped = t.source && t.p[0] == 2;
     if (shaped && (t.p[1] == 1 || t.p[1] == 2 || t.p[1] == 3 || (t.p[1] == 4 && !(m > 32 && cfg.f16)) || (t.p[1] == 6 && m <= 32))) g = t.p[1];
-    const bool eight = shaped && t.p[2] ? t.p[2] != 16 : t.source == 1;
+    const int asked = shaped && t.p[2] ? (t.p[2] == 16 ? 16 : 8) : t.source == 1 ? 8 : 0;
 #define RAZER_RING(NA, G)                                                                  \
     do {                                                                                   \
-        if (cfg.f16) return launch_ring_t<NA, G, false, 1>(cfg, count, p, k, a, m, eight, st);    \
-        if (cfg.lb == 4) return launch_ring_t<NA, G, false, 0>(cfg, count, p, k, a, m, eight, st); \
-        return launch_ring_t<NA, G, true, 0>(cfg, count, p, k, a, m, eight, st);                  \
+        if (cfg.f16) return launch_ring_t<NA, G, false, 1>(cfg, count, p, k, a, m, asked, st);    \
+        if (cfg.lb == 4) return launch_ring_t<NA, G, false, 0>(cfg, count, p, k, a, m, asked, st); \
+        return launch_ring_t<NA, G, true, 0>(cfg, count, p, k, a, m, asked, st);                  \
     } while (0)
 #define RAZER_RING_G(NA)                   \
     do {                                   \
@@ -604,11 +616,11 @@ static hipError_t launch_ring(SvConfig cfg, int count, const GemvProblem* p, int
         RAZER_RING(NA, 6);                 \
     } while (0)
     if (m <= 4 && cfg.il) {                                       // the interleaved layout is a form of 2..4 rows
-        if (g == 1) return launch_ring_t<1, 1, false, 0, true>(cfg, count, p, k, a, m, eight, st);
-        if (g == 2) return launch_ring_t<1, 2, false, 0, true>(cfg, count, p, k, a, m, eight, st);
-        if (g == 3) return launch_ring_t<1, 3, false, 0, true>(cfg, count, p, k, a, m, eight, st);
-        if (g == 4) return launch_ring_t<1, 4, false, 0, true>(cfg, count, p, k, a, m, eight, st);
-        return launch_ring_t<1, 6, false, 0, true>(cfg, count, p, k, a, m, eight, st);
+        if (g == 1) return launch_ring_t<1, 1, false, 0, true>(cfg, count, p, k, a, m, asked, st);
+        if (g == 2) return launch_ring_t<1, 2, false, 0, true>(cfg, count, p, k, a, m, asked, st);
+        if (g == 3) return launch_ring_t<1, 3, false, 0, true>(cfg, count, p, k, a, m, asked, st);
+        if (g == 4) return launch_ring_t<1, 4, false, 0, true>(cfg, count, p, k, a, m, asked, st);
+        return launch_ring_t<1, 6, false, 0, true>(cfg, count, p, k, a, m, asked, st);
     }
     if (cfg.il) return hipErrorInvalidValue;
     if (m <= 4) RAZER_RING_G(1);
@@ -618,7 +630,7 @@ static hipError_t launch_ring(SvConfig cfg, int count, const GemvProblem* p, int
     if (g == 1) RAZER_RING(16, 1);
     if (g == 2) RAZER_RING(16, 2);
     if (g == 3) RAZER_RING(16, 3);
-    return cfg.lb == 4 ? launch_ring_t<16, 4, false, 0>(cfg, count, p, k, a, m, eight, st) : launch_ring_t<16, 4, true, 0>(cfg, count, p, k, a, m, eight, st);
+    return cfg.lb == 4 ? launch_ring_t<16, 4, false, 0>(cfg, count, p, k, a, m, asked, st) : launch_ring_t<16, 4, true, 0>(cfg, count, p, k, a, m, asked, st);
 #undef RAZER_RING_G
 #undef RAZER_RING
 }

@@ -70,7 +70,8 @@ def test_runs_of_activation_rows(oracle, m, ns, k, fmt, block):
 
 
 @pytest.mark.parametrize("m,n,k,fmt,block", [(9, 37, 4096 + 96, razer.WEIGHT, 16), (16, 70, 4096, razer.WEIGHT, 64), (16, 20, 4224, razer.WEIGHT_F16, 128),
-                                             (40, 37, 10240 + 96, razer.WEIGHT, 16), (64, 20, 10240, razer.WEIGHT_F16, 128), (33, 16485, 160, razer.WEIGHT, 16), (64, 16485, 192, razer.WEIGHT, 32), (64, 16485, 128, razer.WEIGHT_F16, 128)])
+                                             (40, 37, 10240 + 96, razer.WEIGHT, 16), (64, 20, 10240, razer.WEIGHT_F16, 128), (33, 16485, 160, razer.WEIGHT, 16), (64, 16485, 192, razer.WEIGHT, 32), (64, 16485, 128, razer.WEIGHT_F16, 128),
+                                             (9, 37, 6784 + 64, razer.WEIGHT, 16), (16, 700, 4800, razer.WEIGHT, 64), (16, 20, 10624, razer.WEIGHT_F16, 128)])
 def test_number_of_waves(oracle, m, n, k, fmt, block):
     """16 waves with one group per workgroup and rows long enough; fewer where K has fewer steps than waves."""
     _run(oracle, (n,), k, m, fmt, block)
@@ -105,7 +106,7 @@ def test_four_waves_where_workgroups_outnumber_compute_units(oracle, m, k, fmt, 
 
 @pytest.mark.parametrize("m,n,k,block,groups,halves", [(130, 37, 9312, 16, None, 1), (130, 37, 9312, 32, None, 1), (130, 37, 4128, 16, None, 2), (64, 3077, 224, 16, None, 1),
                                                        (64, 37, 4128, 16, 2, 1), (50, 37, 8224, 32, 2, 1), (64, 37, 3360, 16, 2, 2), (64, 37, 4160, 16, 2, 2),
-                                                       (16, 37, 4128, 16, None, 1), (12, 37, 4128, 32, None, 2)])
+                                                       (16, 37, 6688, 16, None, 1), (12, 37, 6688, 32, None, 2), (12, 37, 4128, 32, None, 1)])
 def test_steps_of_rows_that_start_inside_a_line(oracle, m, n, k, block, groups, halves):
     """K of an odd number of 32-element runs: whole steps where many rows are read, halves elsewhere (the last template
     argument counts the parts)."""
@@ -119,6 +120,16 @@ def test_steps_of_rows_that_start_inside_a_line(oracle, m, n, k, block, groups, 
         razer.razer_tune_force(binding.TUNE_SMALL_BATCH, None)
     assert any("ring_kernel" in x and "false, %d>" % halves in x for x in names), names
     _run(oracle, (n,), k, m, razer.WEIGHT, block, groups)
+
+
+@pytest.mark.parametrize("m,n,k,fmt,waves", [(16, 4096, 4096, razer.WEIGHT, 8), (9, 704, 4608, razer.WEIGHT, 8), (9, 704, 4736, razer.WEIGHT, 16), (12, 300, 6656, razer.WEIGHT, 8),
+                                             (12, 300, 6784, razer.WEIGHT, 16), (16, 300, 10496, razer.WEIGHT_F16, 8), (16, 300, 10624, razer.WEIGHT_F16, 16)])
+def test_sixteen_waves_where_rows_are_long(m, n, k, fmt, waves):
+    """9..16 rows, both sides of the lengths from which 16 waves are faster."""
+    a = bf16_bits_to_dev(synth.activation(m, k, seed=4900))
+    wt = _weights(n, k, 4901, fmt, 16)[1]
+    names = launched_kernels(lambda: razer.razer_linear(wt, a))
+    assert len(names) == 1 and ", %d, false, " % waves in names[0] and "ring_kernel<4, 1," in names[0], names
 
 
 def test_runs_of_activation_rows_keep_to_a_strided_output(oracle):
