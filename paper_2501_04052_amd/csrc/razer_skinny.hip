@@ -3,12 +3,13 @@
 // v_mfma_f32_16x16x32_bf16 it is used in.
 //
 // Mapping (ring_kernel).  A workgroup owns G groups of 16 weight rows, numbered through all matrices of the launch
-// one after another; its 8 (or 16) waves take the 128-k steps of K in turn (wave w: steps w, w + 8, ...).  What a step needs
+// one after another; its W waves (8; 16 or 4 where launch_ring_t and launch_ring_w say so) take the 128-k steps of K in turn
+// (wave w: steps w, w + W, ...).  What a step needs
 // -- G x (1 KiB of codes, 64 scale entries) and the step's activation rows -- is copied global -> LDS by the load
 // unit into memory that only this wave reads, so the K loop has no barrier: the wave waits for its own copies, takes
 // the operands into registers, requests its next step into the same place and multiplies while that one is on its
-// way.  Above 32 rows the activations come in halves of 64 k (one 128-byte line per row), codes and scales still a step
-// at a time and ahead of the step's second half.  Partial sums of the waves meet in LDS after one barrier.  One launch, no workspace.
+// way.  Above 32 rows, and with 16 waves at 9 .. 16, the activations come in halves of 64 k (one 128-byte line per row), codes
+// and scales still a step at a time, the next step's behind this step's second half.  Partial sums of the waves meet in LDS after one barrier.  One launch, no workspace.
 //
 // Why through LDS although nothing is shared: the matrix instruction wants 16 rows in 16 neighbouring lanes, and a
 // load whose neighbouring lanes lie in 16 different rows costs the address unit a cache-line lookup per lane.  Read
@@ -131,9 +132,11 @@ struct RingArgs {
     int chunk, lb;
 };
 
-template <int NA, int G, bool GB, int SF, int W, bool IL, int H>
+// FORM: SF, + 2: whole steps where ring_parts() would take halves
+template <int NA, int G, bool GB, int FORM, int W, bool IL = false>
 __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
 {
+    constexpr int SF = FORM & 1, H = FORM & 2 ? 1 : ring_parts<NA, W>();
     const uint32_t e1 = arg.e[0], e2 = arg.e[1], e3 = arg.e[2], e4 = arg.e[3];
     const float sv0 = arg.sv0, sv1 = arg.sv1;
     const int64_t k = arg.k, m0 = (int64_t)blockIdx.y * arg.chunk, m = arg.m - m0 < arg.chunk ? arg.m - m0 : arg.chunk;
@@ -479,7 +482,7 @@ static hipError_t launch_ring_w(SvConfig cfg, int count, const GemvProblem* p, i
     const int64_t wgs = ring_wgs<G>(count, p, m);
     const int use = NA == 16 && wgs > kComputeUnits && asked != 8 ? 4 : most;
     const int waves = nsteps < use ? (int)nsteps : use;
-    auto kern = ring_kernel<NA, G, GB, SF, W, IL, H>;
+    auto kern = ring_kernel<NA, G, GB, SF + (H == ring_parts<NA, W>() ? 0 : 2), W, IL>;
     constexpr uint32_t lds = (uint32_t)most * ring_wave_bytes<NA, G, H>();
     if constexpr (lds > 64u * 1024u) RAZER_RAISE_LDS_LIMIT(kern, lds);
     launch(kern, dim3((groups + G - 1) / G, (unsigned)((m + arg.chunk - 1) / arg.chunk)), 64 * waves, (size_t)waves * ring_wave_bytes<NA, G, H>(), st, arg);

@@ -108,8 +108,7 @@ def test_four_waves_where_workgroups_outnumber_compute_units(oracle, m, k, fmt, 
                                                        (64, 37, 4128, 16, 2, 1), (50, 37, 8224, 32, 2, 1), (64, 37, 3360, 16, 2, 2), (64, 37, 4160, 16, 2, 2),
                                                        (16, 37, 6688, 16, None, 1), (12, 37, 6688, 32, None, 2), (12, 37, 4128, 32, None, 1)])
 def test_steps_of_rows_that_start_inside_a_line(oracle, m, n, k, block, groups, halves):
-    """K of an odd number of 32-element runs: whole steps where many rows are read, halves elsewhere (the last template
-    argument counts the parts)."""
+    """K of an odd number of 32-element runs: whole steps where many rows are read, halves elsewhere."""
     a = bf16_bits_to_dev(synth.activation(m, k, seed=4800))
     wt = _weights(n, k, 4801, razer.WEIGHT, block)[1]
     if groups:
@@ -118,7 +117,10 @@ def test_steps_of_rows_that_start_inside_a_line(oracle, m, n, k, block, groups, 
         names = launched_kernels(lambda: razer.razer_linear(wt, a))
     finally:
         razer.razer_tune_force(binding.TUNE_SMALL_BATCH, None)
-    assert any("ring_kernel" in x and "false, %d>" % halves in x for x in names), names
+    if m > 16:
+        assert any("ring_kernel<16," in x and ", %d, 8, false>" % (0 if halves == 2 else 2) in x for x in names), names
+    else:                                                             # (16 waves with halves, 8 with whole steps)
+        assert any("ring_kernel<4," in x and ", %d, false>" % (8 * halves) in x for x in names), names
     _run(oracle, (n,), k, m, razer.WEIGHT, block, groups)
 
 
@@ -129,7 +131,7 @@ def test_sixteen_waves_where_rows_are_long(m, n, k, fmt, waves):
     a = bf16_bits_to_dev(synth.activation(m, k, seed=4900))
     wt = _weights(n, k, 4901, fmt, 16)[1]
     names = launched_kernels(lambda: razer.razer_linear(wt, a))
-    assert len(names) == 1 and ", %d, false, " % waves in names[0] and "ring_kernel<4, 1," in names[0], names
+    assert len(names) == 1 and ", %d, false>" % waves in names[0] and "ring_kernel<4, 1," in names[0], names
 
 
 def test_runs_of_activation_rows_keep_to_a_strided_output(oracle):
