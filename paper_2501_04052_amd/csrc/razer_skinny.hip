@@ -550,7 +550,8 @@ static hipError_t launch_ring_t(SvConfig cfg, int count, const GemvProblem* p, i
 // Groups of 16 rows per workgroup.  The busiest of the 256 compute units holds ceil(workgroups / 256) workgroups of G
 // groups each; what a workgroup spends on its activations (m x K, whatever G is) grows with m / G: about 5.5 % of a
 // group's time per activation row.  Six groups leave one workgroup of eight waves per unit, which overlaps less
-// (15 %).  Measured over 1024 x 1024 .. 57344 x 8192 at 4..64 rows this picks the fastest G or one within 3 % of it:
+// (15 %).  Measured over 1024 x 1024 .. 57344 x 8192 at 4..64 rows, with eight waves throughout (above 32 rows four, where
+// workgroups share a unit, came later), this picks the fastest G or one within 3 % of it:
 // 4096 rows 1; 8192 or 5003 rows 2; {q,k,v} 3 x 4096 or 10240 rows 3; 2 x 11008 rows 3, with 32 activation rows 6.
 // More than 32 activation rows take at most 4 groups (the FP16-scale format 3): six do not fit the registers.
 static int ring_groups(int64_t groups, int64_t m, bool f16)

@@ -44,7 +44,8 @@ def _check(oracle, family, shape, m, ns, k, block=16, seed=0):
         assert err <= TOL, (family, shape, err)
 
 
-# groups of 16 rows per workgroup and waves (6 groups: up to 32 rows, else the heuristic; 16 waves: one group, up to 8 rows)
+# groups of 16 rows per workgroup and waves (6 groups: up to 32 rows, else the heuristic; 16 waves: one group, up to 8 rows, 9..16
+# rows of 4096 elements and more, above 32 rows of 10240 and more)
 SMALL_BATCH_SHAPES = [(2, 1, 8), (2, 1, 16), (2, 2, 8), (2, 3, 8), (2, 4, 8), (2, 6, 8), (2, 2)]
 
 
