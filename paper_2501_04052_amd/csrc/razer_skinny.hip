@@ -108,12 +108,12 @@ template <int NA, int W>
 constexpr int ring_parts() { return NA == 16 || (NA == 4 && W == 16) ? 2 : 1; }
 template <int NA, int H>
 constexpr uint32_t ring_act_bytes() { return NA * 1024u / H; }
-template <int NA, int G, int H>
-constexpr uint32_t ring_slot_bytes() { return ring_act_bytes<NA, H>() + G * 1280u; }
-template <int NA, int G, int H>
+template <int NA, int G, int H, bool ST>
+constexpr uint32_t ring_slot_bytes() { return ring_act_bytes<NA, H>() + G * (ST ? 1024u : 1280u); }
+template <int NA, int G, int H, bool ST>
 constexpr uint32_t ring_wave_bytes()
 {
-    const uint32_t slot = ring_slot_bytes<NA, G, H>(), part = G * ((NA + 3) / 4) * 1024u;
+    const uint32_t slot = ring_slot_bytes<NA, G, H, ST>(), part = G * ((NA + 3) / 4) * 1024u;
     return slot > part ? slot : part;
 }
 
@@ -132,11 +132,20 @@ struct RingArgs {
     int chunk, lb;
 };
 
+// Staged scales (ST): the scale entries of a group's 16 rows are one contiguous piece of memory, K bytes with 16-element
+// blocks.  The workgroup copies the pieces of its groups to LDS once, 1 KiB per instruction, ahead of the first step,
+// instead of 8 bytes per row and step: those copies ask for as many lines as the codes' (a third of all the lookups at 8
+// rows), all waves for the same ones, and the load path waits where a line is asked for again that is still on its way.
+// The LDS address of chunk c of 16 bytes is c ^ ((c >> 4) & 15): rows of 256 bytes (K = 4096) would all start in one bank.
+__device__ __forceinline__ uint32_t ring_scale_swizzle(uint32_t byte) { return byte ^ ((byte >> 4) & 0xF0u); }
+__host__ __device__ __forceinline__ uint32_t ring_scale_region(uint32_t scale_ld) { return (16u * scale_ld + 255u) & ~255u; }
+
 // FORM: SF, + 2: whole steps where ring_parts() would take halves
-template <int NA, int G, bool GB, int FORM, int W, bool IL = false>
-__global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
+template <int NA, int G, bool GB, int FORM, int W, bool IL, bool ST>
+__device__ __forceinline__ void ring_body(const RingArgs arg)
 {
     constexpr int SF = FORM & 1, H = FORM & 2 ? 1 : ring_parts<NA, W>();
+    constexpr bool EARLY = SF || ST;                                  // the tensor scales
     const uint32_t e1 = arg.e[0], e2 = arg.e[1], e3 = arg.e[2], e4 = arg.e[3];
     const float sv0 = arg.sv0, sv1 = arg.sv1;
     const int64_t k = arg.k, m0 = (int64_t)blockIdx.y * arg.chunk, m = arg.m - m0 < arg.chunk ? arg.m - m0 : arg.chunk;
@@ -144,9 +153,10 @@ __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
     const uint16_t* a = arg.a + m0 * k;
     constexpr int NB = (NA + 3) / 4, J = 4 / H, AC = NA / H;
     constexpr uint32_t ACT = ring_act_bytes<NA, H>(), AROW = 256u / H;
-    constexpr uint32_t WAVE = ring_wave_bytes<NA, G, H>();
+    constexpr uint32_t WAVE = ring_wave_bytes<NA, G, H, ST>();
+    static_assert(!ST || !IL, "the interleaved layout keeps scales with the codes");
     __shared__ uint4 lut[SF ? 1 : 256];
-    extern __shared__ __align__(16) uint8_t dyn_smem[];               // [waves][WAVE]
+    extern __shared__ __align__(16) uint8_t dyn_smem[];               // [waves][WAVE], ST: [G][ring_scale_region]
     const uint32_t lane = threadIdx.x & 63u, nwaves = blockDim.x >> 6;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t r = lane & 15u, g = lane >> 4;
@@ -160,7 +170,7 @@ __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
     const uint32_t wr = lane >> 2, wp = lane & 3u, wc = wp ^ ((wr >> 2) & 3u);
     const uint8_t* cbase[G];
     const uint8_t* sbase[G];
-    uint32_t crow[G], srow[G];
+    uint32_t crow[G], srow[G], sleft[ST ? G : 1];
 #pragma unroll
     for (int gi = 0; gi < G; ++gi) {
         uint32_t q = blockIdx.x * G + gi;
@@ -178,6 +188,7 @@ __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
         sbase[gi] = (IL ? codes + 1024 : scales) + row0 * (int64_t)scale_ld;
         crow[gi] = dl * code_ld;
         srow[gi] = dl * scale_ld;
+        if constexpr (ST) sleft[gi] = left;
     }
     uint32_t arow[AC], achk[AC];
 #pragma unroll
@@ -203,7 +214,7 @@ __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
 #pragma unroll
             for (int gi = 0; gi < G; ++gi) RAZER_COPY(cbase[gi] + cstep, crow[gi] + wcc * 16u, ring + ACT + gi * 1024, 16);
 #pragma unroll
-            for (int gi = 0; gi < G; ++gi) {
+            for (int gi = 0; gi < (ST ? 0 : G); ++gi) {
                 if constexpr (SF != 0)
                     RAZER_COPY(sbase[gi] + (size_t)step * 2u, srow[gi], ring + ACT + G * 1024 + gi * 256, 2);
                 else if constexpr (GB)
@@ -234,6 +245,10 @@ __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
     const uint32_t swz = (r >> 2) & 3u;
     const uint32_t code_lds0 = ring_lds + ACT + r * 64u + (H == 1 ? (g ^ swz) << 4 : (((g >> 1) ^ swz) << 4) + (g & 1u) * 8u);
     const uint32_t code_lds1 = code_lds0 ^ 32u;
+    // ST: byte of the lane's first scale entry inside its group's piece at step 0
+    const uint32_t scale_row = r * scale_ld + (SF ? 0u : GB ? 0u : H == 1 ? 2u * g : g), scale_k = H == 1 ? 32u * g : 16u * g;
+    const uint32_t region = ST ? ring_scale_region(scale_ld) : 0u, staged = nwaves * WAVE;
+    const uint32_t staged_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)dyn_smem + staged;
     const uint32_t scale_lds = ring_lds + ACT + G * 1024u + (H == 1 || SF ? (4u * r + g) * 4u : (4u * r + (g >> 1)) * 4u + (GB ? 0u : g & 1u));
     // (fewer than 16 staged rows: the lanes of the missing ones repeat staged rows, their product columns are never stored)
     const uint32_t ra = NA < 4 ? r & (4u * NA - 1u) : r;
@@ -247,15 +262,63 @@ __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
 #define RAZER_DS16(dst, addr, imm) asm volatile("ds_read_u16 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(imm))
 
     uint32_t step = wave;                                             // (the host starts at most nsteps waves)
+    if constexpr (ST) {
+        const uint32_t bytes = 16u * scale_ld;
+#pragma unroll
+        for (int gi = 0; gi < G; ++gi) {
+            uint8_t* dst = dyn_smem + staged + gi * region;
+            if (sleft[gi] == 15u) {
+                uint32_t p = wave + (gi & 1) * (nwaves >> 1);         // (the waves share the pieces evenly)
+                for (p = p < nwaves ? p : p - nwaves; p * 1024u < region; p += nwaves) {
+                    const uint32_t at = p * 1024u + lane * 16u, from = ring_scale_swizzle(at);
+                    if (at < region) RAZER_COPY(sbase[gi], from < bytes ? from : bytes - 16u, dst + p * 1024u, 16);
+                }
+            } else {                                                  // the last rows of a matrix: not a byte past them
+                const uint32_t have = (sleft[gi] + 1u) * scale_ld;
+                for (uint32_t i = threadIdx.x; i < have; i += blockDim.x) {
+                    const uint32_t v = sbase[gi][i];
+                    asm volatile("ds_write_b8 %0, %1" ::"v"(staged_lds + gi * region + ring_scale_swizzle(i)), "v"(v) : "memory");
+                }
+            }
+        }
+    }
     issue(step, yes, yes, 0u);
+    // The groups' tensor scales, requested behind the first step (read at the end, their way from memory, 2 us under load, is
+    // the last thing a workgroup waits for).  FP16 scales: 4096 x 4096 at 8 rows 5.11 -> 4.75 us, x 11008 7.6 -> 7.4; staged: 57344 x
+    // 8192 at 8 rows, seven workgroups per unit, 68.9 -> 62.  Not with a step's scale bytes at a time: the wait would stand
+    // ahead of the table's barrier, which costs as much as it gains.
+    float tensor_scales[EARLY ? G : 1];
+    if constexpr (EARLY) {
+#pragma unroll
+        for (int gi = 0; gi < G; ++gi) {
+            uint32_t q = blockIdx.x * G + gi;
+            q = q < e4 ? q : e4 - 1u;
+            const float* ts = arg.ts[0];
+            if (q >= e1) ts = arg.ts[1];
+            if (q >= e2) ts = arg.ts[2];
+            if (q >= e3) ts = arg.ts[3];
+            tensor_scales[gi] = *(const __attribute__((address_space(4))) float*)(uintptr_t)ts;
+        }
+    }
     if (!SF) {
         for (uint32_t sb = threadIdx.x; sb < 256u; sb += blockDim.x) {
             const v4u e = __builtin_bit_cast(v4u, sk_byte_table(sb, sv0, sv1));
             asm volatile("ds_write_b128 %0, %1" ::"v"(lut_lds + sb * 16u), "v"(e) : "memory");
         }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if constexpr (!ST) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        }
+    }
+    if constexpr (ST) {
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
+    }
+    if constexpr (EARLY) {
+#pragma unroll
+        for (int gi = 0; gi < G; ++gi) asm volatile("" : "+s"(tensor_scales[gi]));   // (loaded here, not at its use)
     }
     v4f acc[G][NB];
 #pragma unroll
@@ -270,14 +333,28 @@ __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
 #pragma unroll
         for (int h = 0; h < H; ++h) {
             // what this part reads has landed: in the second half the next step's codes and scales, the newest 2 G
-            // copies, may be under way (copies land in the order of their issue)
-            if (h == 1 && step + nwaves < nsteps) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * G) : "memory");
+            // copies (with staged scales G), may be under way (copies land in the order of their issue)
+            if (h == 1 && step + nwaves < nsteps) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((ST ? 1 : 2) * G) : "memory");
             else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             v4u af[NB][J];
             if (h == 0) {
+                uint32_t s_at[H];
+                if constexpr (ST) {
+#pragma unroll
+                    for (int i = 0; i < H; ++i) {
+                        const uint32_t off = SF ? step * 2u : GB ? (128u * step + 64u * i + scale_k) >> lb : step * 8u + 4u * i;
+                        s_at[i] = staged_lds + ring_scale_swizzle(scale_row + off);
+                    }
+                }
 #pragma unroll
                 for (int gi = 0; gi < G; ++gi) {
-                    if constexpr (H == 1 || SF) RAZER_DS16(sw[gi][0], scale_lds, gi * 256);
+                    if constexpr (ST) {
+                        if constexpr (SF || (H == 1 && !GB)) RAZER_DS16(sw[gi][0], s_at[0] + gi * region, 0);
+                        else {
+                            RAZER_DS8(sw[gi][0], s_at[0] + gi * region, 0);
+                            if constexpr (H == 2) RAZER_DS8(sw[gi][H - 1], s_at[H - 1] + gi * region, 0);
+                        }
+                    } else if constexpr (H == 1 || SF) RAZER_DS16(sw[gi][0], scale_lds, gi * 256);
                     else { RAZER_DS8(sw[gi][0], scale_lds, gi * 256); RAZER_DS8(sw[gi][H - 1], scale_lds, gi * 256 + 8); }
                     if constexpr (H == 1) RAZER_DS128(cw[gi][0], code_lds0, gi * 1024);
                     else { RAZER_DS64(cw[gi][0], code_lds0, gi * 1024); RAZER_DS64(cw[gi][H - 1], code_lds1, gi * 1024); }
@@ -397,7 +474,15 @@ __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
         if (q >= e3) { ts = arg.ts[3]; y = arg.y[3]; n = arg.n[3]; ld_y = arg.ld_y[3]; first = e3; }
         y += m0 * ld_y;
         const int64_t row0 = (int64_t)(q - first) * 16;
-        const float sc = SF ? -*ts : *ts;                                 // (the bare decode carries a negation)
+        float sc;
+        if constexpr (EARLY) {
+            sc = tensor_scales[0];
+#pragma unroll
+            for (int i = 1; i < G; ++i) sc = gi == (uint32_t)i ? tensor_scales[i] : sc;
+        } else {
+            sc = *ts;
+        }
+        sc = SF ? -sc : sc;                                               // (the bare decode carries a negation)
         float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
         for (uint32_t w = 0; w < nwaves; ++w) {
             const float4 p = *reinterpret_cast<const float4*>(dyn_smem + w * WAVE + (u * 64u + lane) * 16u);
@@ -432,6 +517,16 @@ __global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
     }
 }
 
+template <int NA, int G, bool GB, int FORM, int W, bool IL = false>
+__global__ __launch_bounds__(64 * W) void ring_kernel(const RingArgs arg)
+{
+    ring_body<NA, G, GB, FORM, W, IL, false>(arg);
+}
+template <int NA, int G, bool GB, int FORM, int W, bool IL = false>
+__global__ __launch_bounds__(64 * W) void staged_ring_kernel(const RingArgs arg)
+{
+    ring_body<NA, G, GB, FORM, W, IL, true>(arg);
+}
 
 // More than 64 activation rows go in equal runs of at most 64, blockIdx.y counting them.
 static int64_t ring_chunk(int64_t m)
@@ -449,6 +544,27 @@ template <int G>
 static int64_t ring_wgs(int count, const GemvProblem* p, int64_t m)
 {
     return (ring_row_groups(count, p) + G - 1) / G * ((m + kRingMaxM - 1) / kRingMaxM);
+}
+
+// Staged scales or a step's at a time.  Staging takes the scales out of the load path's way, which every workgroup of a unit
+// gains from, and costs a start: no wave begins before all scales and every wave's first step are there.  So it pays with
+// the work of a workgroup (G x steps of 128 elements) and with several workgroups per unit, which start over each other's
+// work.  Time with staged scales against without at 8 / 16 / 64 rows.  Several workgroups per unit: 22016 x 1024 (G x steps =
+// 24) 1.05 / 1.07 / 1.03, x 2048 (48) 0.97 / 0.97 / 1.00, x 4096 0.98 / 0.95 / 0.96, x 6144 0.91 / 0.92 / 0.95, 57344 x 8192 at 8 rows 0.88
+// (68.7 -> 60.6 us); FP16 scales 22016 x 4096 (96) 1.02 / 1.02 / 0.99, 28672 x 4096 (128) 0.98 / 0.99 / 1.00, 57344 x 8192 0.86 / 0.87 / 0.95.
+// One workgroup per unit: 4096 x 4096 (32) 1.11 / 1.10 / 1.04, 12288 x 4096 (96) 1.03 / 1.03 / 1.01, 12288 x 6144 (144) 1.02 / 0.99 / 0.98,
+// 12288 x 8192 (192) 1.00 / 0.97 / 0.98, 8192 x 20480 (320) 0.95 / 0.93 / 0.95, 12288 x 20480 0.85 / 0.83 / 0.99.  Where the regions leave
+// LDS for fewer workgroups than without them: two are as good as three up to 32 rows; one instead of two pays from about
+// 190 (28672 x 4096 at 16 rows 1.07, x 6144 0.98, 22016 x 8192 1.01, 28672 x 8192 0.96); above 32 rows (four waves) behind: 57344 x
+// 8192 1.16.
+template <int NA, int G>
+static bool ring_stages(bool f16, int64_t wgs, int64_t nsteps, size_t plain, size_t staged)
+{
+    const int64_t per_unit = (wgs + kComputeUnits - 1) / kComputeUnits, now = kLdsBytes / plain, then = kLdsBytes / staged, work = G * nsteps;
+    if (then < 1) return false;
+    if (then < now && then < per_unit && (NA > 8 || (then < 2 && work < 190))) return false;
+    if (per_unit > 1) return work >= (f16 ? 120 : 48);
+    return work >= (NA <= 2 ? 190 : 140);
 }
 
 template <int NA, int G, bool GB, int SF, bool IL, int W, int H = ring_parts<NA, W>()>
@@ -475,17 +591,32 @@ static hipError_t launch_ring_w(SvConfig cfg, int count, const GemvProblem* p, i
     arg.a = a;
     arg.lb = cfg.lb;
     // as many of the W waves as their LDS leaves room for
-    constexpr uint32_t fit = (kLdsBytes - kRingTableBytes) / ring_wave_bytes<NA, G, H>();
+    constexpr uint32_t fit = (kLdsBytes - kRingTableBytes) / ring_wave_bytes<NA, G, H, false>();
     constexpr int most = fit < (uint32_t)W ? (int)fit : W;
     static_assert(most >= 4, "LDS");
     const int64_t nsteps = (k + 127) / 128;
     const int64_t wgs = ring_wgs<G>(count, p, m);
     const int use = NA == 16 && wgs > kComputeUnits && asked != 8 ? 4 : most;
     const int waves = nsteps < use ? (int)nsteps : use;
-    auto kern = ring_kernel<NA, G, GB, SF + (H == ring_parts<NA, W>() ? 0 : 2), W, IL>;
-    constexpr uint32_t lds = (uint32_t)most * ring_wave_bytes<NA, G, H>();
+    constexpr int FORM = SF + (H == ring_parts<NA, W>() ? 0 : 2);
+    const dim3 grid((groups + G - 1) / G, (unsigned)((m + arg.chunk - 1) / arg.chunk));
+    const size_t plain = (size_t)waves * ring_wave_bytes<NA, G, H, false>();
+    if constexpr (!IL) {
+        const int64_t scale_ld = SF ? (k >> 7) * 2 : k >> cfg.lb;
+        if (scale_ld <= (int64_t)kLdsBytes / 16) {
+            const size_t staged = (size_t)waves * ring_wave_bytes<NA, G, H, true>() + G * (size_t)ring_scale_region((uint32_t)scale_ld);
+            if (ring_stages<NA, G>(SF != 0, wgs, nsteps, plain + kRingTableBytes, staged + kRingTableBytes)) {
+                auto kern = staged_ring_kernel<NA, G, GB, FORM, W, IL>;
+                RAZER_RAISE_LDS_LIMIT(kern, kLdsBytes - kRingTableBytes);
+                launch(kern, grid, 64 * waves, staged, st, arg);
+                return hipGetLastError();
+            }
+        }
+    }
+    auto kern = ring_kernel<NA, G, GB, FORM, W, IL>;
+    constexpr uint32_t lds = (uint32_t)most * ring_wave_bytes<NA, G, H, false>();
     if constexpr (lds > 64u * 1024u) RAZER_RAISE_LDS_LIMIT(kern, lds);
-    launch(kern, dim3((groups + G - 1) / G, (unsigned)((m + arg.chunk - 1) / arg.chunk)), 64 * waves, (size_t)waves * ring_wave_bytes<NA, G, H>(), st, arg);
+    launch(kern, grid, 64 * waves, plain, st, arg);
     return hipGetLastError();
 }
 

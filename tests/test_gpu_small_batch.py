@@ -160,3 +160,32 @@ def test_infinite_activation_stays_infinite_with_a_ragged_last_step(oracle, m):
     assert torch.equal(got[2][hit], torch.sign(w0[hit]) * float("inf"))
     others = [i for i in range(m) if i != 2]
     assert torch.equal(got[others], plain.float().cpu()[others])
+
+
+@pytest.mark.parametrize("m,ns,k,fmt,block,groups", [
+    # rows of 256, 262, 518 and of 64 .. 4 bytes of scales, the last rows of a matrix, several matrices in one workgroup
+    (8, (68, 33 * 4, 12), 4096, razer.WEIGHT, 16, 6), (5, (100, 7), 4192, razer.WEIGHT, 16, 6), (16, (37,), 8288, razer.WEIGHT, 16, 3), (32, (36, 20), 4096, razer.WEIGHT, 32, 6),
+    (8, (50, 3), 8192 + 64, razer.WEIGHT, 64, 3), (33, (68, 5), 4608, razer.WEIGHT, 128, 4), (64, (37, 40), 6176, razer.WEIGHT, 16, 4), (50, (70,), 6144, razer.WEIGHT, 32, 4),
+    (16, (36, 20), 4096, razer.WEIGHT_F16, 128, 6), (64, (52,), 8320, razer.WEIGHT_F16, 128, 3), (12, (21,), 24576, razer.WEIGHT, 16, 1), (4, (37, 20), 10272, razer.WEIGHT, 16, 3),
+    # several workgroups per unit
+    (8, (16485,), 2080, razer.WEIGHT, 16, None), (40, (16485,), 2048, razer.WEIGHT, 64, None), (16, (16485,), 5248, razer.WEIGHT_F16, 128, None),
+    (380, (2865,), 8832, razer.WEIGHT, 16, None)])
+def test_scales_staged_by_the_workgroup(oracle, m, ns, k, fmt, block, groups):
+    ws = [_weights(n, k, 5000 + i + n, fmt, block) for i, n in enumerate(ns)]
+    a = synth.activation(m, k, seed=5100 + m)
+    a_dev = bf16_bits_to_dev(a)
+    print("staged scales", m, ns, k, fmt, block, groups, flush=True)
+    got = []
+    if groups and m > 4:
+        razer.razer_tune_force(binding.TUNE_SMALL_BATCH, (2, groups))
+    try:
+        names = launched_kernels(lambda: got.extend([razer.razer_linear(ws[0][1], a_dev)] if len(ns) == 1 else razer.razer_linear_grouped([w[1] for w in ws], a_dev)))
+    finally:
+        razer.razer_tune_force(binding.TUNE_SMALL_BATCH, None)
+    if m > 4:
+        assert names and all("staged_ring_kernel<" in x for x in names), names
+    for (wq, _), y in zip(ws, got):
+        n = len(wq[0])
+        cols = np.arange(n) if n < 300 else np.unique(np.r_[0:20, n - 37:n, np.random.default_rng(47).choice(n, size=200, replace=False)])
+        y64, _ = oracle.linear((wq[0][cols], wq[1][cols], wq[2]), a_bf16=a)
+        assert max_rel_err(dev_to_bf16_bits(y)[:, cols], y64) <= TOL
