@@ -263,22 +263,19 @@ __device__ __forceinline__ void ring_body(const RingArgs arg)
 
     uint32_t step = wave;                                             // (the host starts at most nsteps waves)
     if constexpr (ST) {
-        const uint32_t bytes = 16u * scale_ld;
 #pragma unroll
         for (int gi = 0; gi < G; ++gi) {
             uint8_t* dst = dyn_smem + staged + gi * region;
-            if (sleft[gi] == 15u) {
-                uint32_t p = wave + (gi & 1) * (nwaves >> 1);         // (the waves share the pieces evenly)
-                for (p = p < nwaves ? p : p - nwaves; p * 1024u < region; p += nwaves) {
-                    const uint32_t at = p * 1024u + lane * 16u, from = ring_scale_swizzle(at);
-                    if (at < region) RAZER_COPY(sbase[gi], from < bytes ? from : bytes - 16u, dst + p * 1024u, 16);
-                }
-            } else {                                                  // the last rows of a matrix: not a byte past them
-                const uint32_t have = (sleft[gi] + 1u) * scale_ld;
-                for (uint32_t i = threadIdx.x; i < have; i += blockDim.x) {
-                    const uint32_t v = sbase[gi][i];
-                    asm volatile("ds_write_b8 %0, %1" ::"v"(staged_lds + gi * region + ring_scale_swizzle(i)), "v"(v) : "memory");
-                }
+            const uint32_t have = (sleft[gi] + 1u) * scale_ld;        // the last rows of a matrix: not a byte past them
+            uint32_t p = wave + (gi & 1) * (nwaves >> 1);             // (the waves share the pieces evenly)
+            for (p = p < nwaves ? p : p - nwaves; p * 1024u < region; p += nwaves) {
+                const uint32_t at = p * 1024u + lane * 16u, from = ring_scale_swizzle(at);
+                if (at < region && from + 16u <= have) RAZER_COPY(sbase[gi], from, dst + p * 1024u, 16);
+            }
+            const uint32_t i = (have & ~15u) + threadIdx.x;
+            if (i < have) {
+                const uint32_t v = sbase[gi][i];
+                asm volatile("ds_write_b8 %0, %1" ::"v"(staged_lds + gi * region + ring_scale_swizzle(i)), "v"(v) : "memory");
             }
         }
     }
@@ -556,7 +553,8 @@ static int64_t ring_wgs(int count, const GemvProblem* p, int64_t m)
 // 12288 x 8192 (192) 1.00 / 0.97 / 0.98, 8192 x 20480 (320) 0.95 / 0.93 / 0.95, 12288 x 20480 0.85 / 0.83 / 0.99.  Where the regions leave
 // LDS for fewer workgroups than without them: two are as good as three up to 32 rows; one instead of two pays from about
 // 190 (28672 x 4096 at 16 rows 1.07, x 6144 0.98, 22016 x 8192 1.01, 28672 x 8192 0.96); above 32 rows (four waves) behind: 57344 x
-// 8192 1.16.
+// 8192 1.16.  Runs of more than 64 rows gain nothing (3 x 5120 x 3840 at 571 rows 1.01, 2 x 5120 x 5120 at 320 1.00) and lose where
+// outputs are stored an element at a time (3 x 5098 x 3808 at 571 1.05): launch_ring_w leaves them out.
 template <int NA, int G>
 static bool ring_stages(bool f16, int64_t wgs, int64_t nsteps, size_t plain, size_t staged)
 {
@@ -605,7 +603,7 @@ static hipError_t launch_ring_w(SvConfig cfg, int count, const GemvProblem* p, i
         const int64_t scale_ld = SF ? (k >> 7) * 2 : k >> cfg.lb;
         if (scale_ld <= (int64_t)kLdsBytes / 16) {
             const size_t staged = (size_t)waves * ring_wave_bytes<NA, G, H, true>() + G * (size_t)ring_scale_region((uint32_t)scale_ld);
-            if (ring_stages<NA, G>(SF != 0, wgs, nsteps, plain + kRingTableBytes, staged + kRingTableBytes)) {
+            if (m <= kRingMaxM && ring_stages<NA, G>(SF != 0, wgs, nsteps, plain + kRingTableBytes, staged + kRingTableBytes)) {
                 auto kern = staged_ring_kernel<NA, G, GB, FORM, W, IL>;
                 RAZER_RAISE_LDS_LIMIT(kern, kLdsBytes - kRingTableBytes);
                 launch(kern, grid, 64 * waves, staged, st, arg);
