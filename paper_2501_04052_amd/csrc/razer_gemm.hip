@@ -20,8 +20,9 @@
 //                    problems above 128 rows, the fused W4A4 kernel, the FP16-scale format
 //   gemm_rb_kernel   W4A16, 16-element blocks: weights decoded in registers by the wave that uses them,
 //                    global -> LDS copies by the load unit; 256-row activation tiles (gemm_wide_kernel: 64
-//                    instead of 32 weight rows per wave) when there are many output tiles, 64- / 128-row tiles for 33..128 activation rows; KG = 2 halves
-//                    K inside the workgroup when there is about one tile per compute unit; the grouped
+//                    instead of 32 weight rows per wave, gemm_halves_kernel the same with K halved inside the workgroup) when
+//                    there are many output tiles, 64- / 128-row tiles for 33..128 activation rows; KG = 2 halves
+//                    K inside the workgroup when there is about one tile per compute unit and K is short; the grouped
 //                    form runs up to four matrices (fused q/k/v, gate/up) as one launch
 // Problems with too few tiles split K over workgroups (fp32 slices in the caller's workspace).
 #include <type_traits>
@@ -1111,30 +1112,53 @@ __global__ __launch_bounds__(64 * NW, (rb_waves_per_simd<NW, KG, MT>())) void ge
 // slice together, a code pair's six operations in a row), 88 us in this one; with every compute unit busy it is 1.8 us
 // per K-tile.  Against 32 rows per wave: 4096 x 11008 x 4096 379 -> 338 us, 4096 x 8192 x 28672 1768 -> 1613 us.  K is at
 // least 2048 (wide_tiles).
-template <bool GB>
+//
+// KG = 2: a 256 x 128 tile, the four waves as two K groups of two, each with its own activation stages (two, LDS is full)
+// and half of the K-tiles; the partial sums meet in LDS at the end.  The same instructions per wave, but twice the
+// activation copies per MFMA, which a stage for one K-tile ahead has to hide: a tile's copies go out from its stage's
+// barrier on, 12 of 20 in the rest of that step and 8 in the next K-tile's first, and have to land by that K-tile's
+// barrier.  All 20 at once behind the barrier are slower (2048 x 4096 x 11008 204 -> 234 us: the workgroups of an XCD ask
+// together), with all operands in the last-level cache it takes 177.  So the lines are prefetched
+// into the L2 and the tiles ordered for it (below, xcd_order).
+// Against gemm_rb_kernel<8, 2, 2, 8>, which has 32 weight rows per wave and two waves per SIMD: 2048 x 4096 x {4096, 11008}
+// 74.1 -> 71.5, 198 -> 181 us, 512 x 12288 x 4096 63.1 -> 61.6, 1900 x 4000 x 5120 88.5 -> 87.0; the same bits.
+template <bool GB, int KG = 1>
 __device__ __forceinline__ void gemm_wide_body(
     const uint8_t* __restrict__ w_codes, const uint8_t* __restrict__ w_scales, const float* __restrict__ w_ts,
     float sv0, float sv1, int64_t n, int64_t k, const uint16_t* __restrict__ a, int64_t m,
-    uint16_t* __restrict__ y, int64_t ld_y, int tile_m, int tile_n, int lb)
+    uint16_t* __restrict__ y, int64_t ld_y, int tile_m, int tile_n, int lb, float* __restrict__ partial = nullptr,
+    int kslice = 0, int kt_per_slice = 0x7FFFFFFF)
 {
-    constexpr int NW = 4, S = 3, MT = 8, NR = 2;        // waves, stages, 32-row activation groups, 32-row weight blocks per wave
-    constexpr int NT = 64 * NW, BM = 32 * MT, BN = 32 * NW * NR;
-    constexpr int NU_A = BM * 8 / NT;                   // 1-KiB activation copies per wave and K-tile
+    constexpr int NW = 4, S = KG == 1 ? 3 : 2, MT = 8, NR = 2;   // waves, stages, 32-row activation groups, 32-row weight blocks per wave
+    constexpr int NWN = NW / KG;                        // waves side by side along N; KG groups of them split K
+    constexpr int NT = 64 * NW, BM = 32 * MT, BN = 32 * NWN * NR;
+    constexpr int NU_A = BM * 8 / (64 * NWN);           // 1-KiB activation copies per wave and K-tile
     constexpr int L = NU_A + 2 * NR;                    // copy instructions per wave and K-tile
     constexpr int A_STAGE = BM * 128, B_CODES = NW * NR * 1024, B_STAGE = NW * NR * 1280;
 
     extern __shared__ __align__(16) uint8_t smem[];
-    uint8_t* As = smem;                                 // S stages x 256 rows x 128 B
-    uint8_t* Bs = smem + S * A_STAGE;                   // S stages x NW NR x (1 KiB of codes + 256 B of scale entries)
-    uint2* wlut = reinterpret_cast<uint2*>(smem + S * (A_STAGE + B_STAGE));
+    uint8_t* As = smem;                                 // KG x S stages x 256 rows x 128 B
+    uint8_t* Bs = smem + KG * S * A_STAGE;              // S stages x NW NR x (1 KiB of codes + 256 B of scale entries)
+    uint2* wlut = reinterpret_cast<uint2*>(smem + S * (KG * A_STAGE + B_STAGE));
 
     // the wave index is uniform: as a scalar it keeps the LDS destinations of the copies (M0) and the
     // base addresses below on the scalar unit
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kg = wave / NWN, wn = wave % NWN;         // K group, position along N
     const int r = lane & 31, h = lane >> 5;
     const int64_t m0 = (int64_t)tile_m * BM, n0 = (int64_t)tile_n * BN;
     const int KT = (int)((k + kBK - 1) / kBK);
-    const int last = KT - 1;                            // (at least 31: the first two K-tiles are full ones)
+    // This wave's K-tiles kbase .. kend - 1: all of them or, with two groups, its half of this workgroup's slice (where
+    // their number is odd the second group has one less).  At least 8, so the first ones are full.
+    int kbase = 0, kend = KT, kmeet = 0;
+    if constexpr (KG == 2) {
+        const int kt0 = kslice * kt_per_slice, kt1 = KT - kt0 < kt_per_slice ? KT : kt0 + kt_per_slice;
+        const int half = (kt1 - kt0 + 1) / 2;
+        kbase = kt0 + kg * half;
+        kmeet = kbase + half;                           // both groups pass half barriers
+        kend = kmeet < kt1 ? kmeet : kt1;
+    }
+    const int last = kend - 1;
     const int64_t scale_ld = GB ? (k >> lb) : (k / 16);
     const uint32_t s_lane = GB ? ((32u * h) >> lb) : 2u * h;          // this lane's byte inside a K-tile's scale bytes
     // this lane's weight row of each block as a uniform base (first row of the block, advanced per K-tile on the
@@ -1145,7 +1169,7 @@ __device__ __forceinline__ void gemm_wide_body(
     uint32_t c_off[NR], s_off[NR];
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
-        const int64_t f = n0 + 32 * (NR * wave + i), wrow_first = f < n ? f : n - 1;
+        const int64_t f = n0 + 32 * (NR * wn + i), wrow_first = f < n ? f : n - 1;
         const int64_t wrow = f + r < n ? f + r : n - 1;
         cfirst[i] = w_codes + wrow_first * (k / 2);
         sfirst[i] = w_scales + wrow_first * scale_ld;
@@ -1153,19 +1177,17 @@ __device__ __forceinline__ void gemm_wide_body(
         s_off[i] = (uint32_t)(wrow - wrow_first) * (uint32_t)scale_ld + s_lane;
     }
 
-    // Activation copy i of this wave fills LDS rows 8 (wave NU_A + i) .. + 7 of a stage: lane l writes
+    // Activation copy i of this wave fills LDS rows 8 (wn NU_A + i) .. + 7 of a stage: lane l writes
     // physical chunk l % 8 of row 8 (..) + l / 8, which must hold logical chunk (l % 8) ^ swizzle(row).
     // Rows past M re-read the last row; byte offsets from the tile's first row fit 32 bits.
     const uint8_t* abase = reinterpret_cast<const uint8_t*>(a + m0 * k);
     const uint32_t rows_here = (uint32_t)((m - m0 < BM) ? m - m0 : BM);
     const uint32_t row_bytes = (uint32_t)k * 2u;
     uint32_t a_src[NU_A];                               // byte offset of (row, k = 0) + 16 * logical chunk
-    uint32_t a_chunk[NU_A];
 #pragma unroll
     for (int i = 0; i < NU_A; ++i) {
-        const uint32_t row = 8u * (wave * NU_A + i) + (lane >> 3);
+        const uint32_t row = 8u * (wn * NU_A + i) + (lane >> 3);
         const uint32_t c = (lane & 7u) ^ ((row >> 1) & 7u);
-        a_chunk[i] = c;
         a_src[i] = (row < rows_here ? row : rows_here - 1) * row_bytes + c * 16u;
     }
     v16f acc[NR][MT];
@@ -1176,7 +1198,7 @@ __device__ __forceinline__ void gemm_wide_body(
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
-    const uint32_t a_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)As;
+    const uint32_t a_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)As + kg * S * A_STAGE;
     const uint32_t lut_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)wlut;
     // this lane's own codes / scale bytes inside a B stage
     const uint32_t bc_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)Bs + wave * NR * 1024 + lane * 16;
@@ -1196,7 +1218,7 @@ __device__ __forceinline__ void gemm_wide_body(
     uint2 le0[NR], le1[NR];
     auto flip_and_mask = [&](int kt, int i, const v4u& c, uint32_t& sc) {
         // past K: code 0, scale byte 0 -> weight 0
-        const uint32_t msk = (kt < KT && (int64_t)kt * kBK + 32 * h < k) ? 0xFFFFFFFFu : 0u;
+        const uint32_t msk = (kt < kend && (int64_t)kt * kBK + 32 * h < k) ? 0xFFFFFFFFu : 0u;
         xw[i][0] = (c.x & msk) ^ kRemapXor;
         xw[i][1] = (c.y & msk) ^ kRemapXor;
         xw[i][2] = (c.z & msk) ^ kRemapXor;
@@ -1224,10 +1246,25 @@ __device__ __forceinline__ void gemm_wide_body(
         }
     };
     // copy instruction c (0 .. NU_A - 1: activations, then codes and scale entries) of K-tile kt into stage st
+    // Two K groups, prefetch into the L2: the workgroups of an XCD that share this row of tiles (consecutive tile_n, at
+    // least 16 of them) ask for 16 of the 256 activation lines of K-tile kt + 4 each, 4 bytes of a line, into LDS that
+    // nobody reads.  A K-tile's own copies then come from the L2: they have only 0.6 of a K-tile's time, and the slowest
+    // line of the tile, from HBM, was what every workgroup of the row stood at the barrier for (2048 x 4096 x 11008: 197
+    // -> 186 us; three tiles ahead 187, eight 187; x 4096 72.6, 72.4).
+    constexpr int PF = KG == 2 ? 1 : 0;
+    uint32_t pf_src = 0;
+    if constexpr (PF != 0) {
+        const uint32_t row = ((uint32_t)tile_n * 16u + (lane & 15u)) & 255u;
+        pf_src = (row < rows_here ? row : rows_here - 1) * row_bytes;
+    }
+    auto prefetch = [&](int kt) {
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(abase + (size_t)(kt < last ? kt : last) * (kBK * 2) + pf_src),
+                                         (__attribute__((address_space(3))) void*)(smem + S * (KG * A_STAGE + B_STAGE) + 256 * sizeof(uint2) + wave * 256), 4, 0, 0);
+    };
     auto issue_one = [&](int kt, int st, int c) {
         if (c < NU_A) {
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(abase + (size_t)kt * (kBK * 2) + a_src[c]),
-                                             (__attribute__((address_space(3))) void*)(As + st * A_STAGE + (wave * NU_A + c) * 1024), 16, 0, 0);
+                                             (__attribute__((address_space(3))) void*)(As + (kg * S + st) * A_STAGE + (wn * NU_A + c) * 1024), 16, 0, 0);
         } else if (c < NU_A + NR) {
             const int i = c - NU_A;
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(cfirst[i] + (size_t)kt * 32 + c_off[i]),
@@ -1248,19 +1285,31 @@ __device__ __forceinline__ void gemm_wide_body(
     };
     // Once only copies of a ragged last tile are left: its second 32 elements do not exist, the lanes that would fetch
     // them fetch the first ones of the same row again (their weights are masked).
-    auto ragged_offsets = [&]() {
-        if ((k & (kBK - 1)) == 0) return;
+    // (the lane number is counted again, here and at the end: no register is free to keep it through the loop)
+    auto lane_again = []() { return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); };
+    auto ragged_acts = [&](int from, int to) {
+        const uint32_t l = lane_again();
 #pragma unroll
-        for (int i = 0; i < NU_A; ++i) a_src[i] -= a_chunk[i] >= 4u ? 64u : 0u;
+        for (int i = from; i < to; ++i) a_src[i] -= (((l & 7u) ^ (4u * (uint32_t)(wn * NU_A + i) + (l >> 4))) & 4u) << 4;
+    };
+    auto ragged_weights = [&]() {
+        const uint32_t hl = lane_again() >> 5;
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
-            c_off[i] -= 16u * h;
-            s_off[i] -= s_lane;
+            c_off[i] -= 16u * hl;
+            s_off[i] -= GB ? (32u * hl) >> lb : 2u * hl;
         }
     };
+    const int ragged = (k & (kBK - 1)) != 0 && kend == KT ? last : -1;
     auto compute = [&](int kt, int st, int st_next, int st_copy) {
-        const int kc = kt + 2 < last ? kt + 2 : last;
-        if (kt + 2 == last) ragged_offsets();
+        const int kc = kt + 2 < last ? kt + 2 : last, kc1 = kt + 1 < last ? kt + 1 : last, kc3 = kt + 3 < last ? kt + 3 : last;
+        if constexpr (KG == 1) {
+            if (kt + 2 == ragged) { ragged_acts(0, NU_A); ragged_weights(); }
+        } else {
+            if (kt + 1 == ragged) ragged_acts(NU_A / 2, NU_A);
+            if (kt + 2 == ragged) ragged_acts(0, NU_A / 2);
+            if (kt + 3 == ragged) ragged_weights();
+        }
         uint32_t wq[2][NR][4];
 #pragma unroll
         for (int i = 0; i < NR; ++i)
@@ -1278,7 +1327,7 @@ __device__ __forceinline__ void gemm_wide_body(
 #pragma unroll
             for (int i = 0; i < NR; ++i) wf[i] = __builtin_bit_cast(v8bf, make_uint4(wq[cb][i][0], wq[cb][i][1], wq[cb][i][2], wq[cb][i][3]));
             const uint32_t an = aoff[(j + 1) & 3] + (j < 3 ? st : st_next) * A_STAGE;
-            if (j == 2) {
+            if (KG == 1 && j == 2) {
                 // this wave's copies of tile kt + 1 have landed (those of tile kt + 2 are in flight)
                 asm volatile("s_waitcnt vmcnt(%0)" ::"n"(L) : "memory");
                 __builtin_amdgcn_sched_barrier(0);
@@ -1326,7 +1375,8 @@ __device__ __forceinline__ void gemm_wide_body(
                 } else if (q == 1) {
                     // every fragment of tile kt is read, and every wave here has seen its copies of tile kt + 1 land: past
                     // the barrier that tile is complete and tile kt's stage is free
-                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                    if constexpr (KG == 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(PF) : "memory");   // (copies land in order; the newest is the prefetch)
+                    else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                     __builtin_amdgcn_s_barrier();
                     asm volatile("" ::: "memory");
                     RAZER_LDS_READ128(af[nb][0], an, 4096 * 0);
@@ -1348,15 +1398,32 @@ __device__ __forceinline__ void gemm_wide_body(
                     part(2 * u);
                     mfma1(1, mi, wf[1], af[cb][mi]);
                     part(2 * u + 1);
-                    if (j < 2) {
-                        issue_one(kc, st_copy, 8 * j + mi);
+                    if (PF && j == 1 && mi == 0) {
+                        prefetch(kt + 4);
                         __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if constexpr (KG == 1) {
+                        if (j < 2) {
+                            issue_one(kc, st_copy, 8 * j + mi);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    } else {
+                        if (j == 0) {
+                            issue_one(kc1, st_next, NU_A / 2 + mi);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                        if (j == 3 && q > 0) {
+                            const int c = 2 * (mi - 2);
+                            if (c < 2 * NR) { issue_one(kc3, st_next, NU_A + c); issue_one(kc3, st_next, NU_A + c + 1); }
+                            else { issue_one(kc, st, c - 2 * NR); issue_one(kc, st, c - 2 * NR + 1); }
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
                     }
                     if (j == 2 && mi == 3) {
 #pragma unroll
                         for (int i = 0; i < NR; ++i) {
                             asm volatile("" : "+v"(cn[i]), "+v"(sn[i]));
-                            const uint32_t msk = (kt + 1 < KT && (int64_t)(kt + 1) * kBK + 32 * h < k) ? 0xFFFFFFFFu : 0u;
+                            const uint32_t msk = (kt + 1 < kend && (int64_t)(kt + 1) * kBK + 32 * h < k) ? 0xFFFFFFFFu : 0u;
                             if (GB) sn[i] = (sn[i] & 255u) * 0x101u;
                             sn[i] &= msk;
                             x0n[i] = (cn[i].x & msk) ^ kRemapXor;
@@ -1382,10 +1449,19 @@ __device__ __forceinline__ void gemm_wide_body(
         }
     };
 
-    issue(0, 0);
+    issue(kbase, 0);
+    if constexpr (KG == 2) {
+#pragma unroll
+        for (int c = NU_A; c < L; ++c) issue_one(kbase + 1, 1, c);
+    }
     fill_scaled_lut<0>(wlut, sv0, sv1, tid, NT);
     __syncthreads();                                    // the first tile has landed, LUT ready
-    issue(1, 1);
+    if constexpr (KG == 1) {
+        issue(1, 1);
+    } else {
+#pragma unroll
+        for (int c = 0; c < NU_A / 2; ++c) issue_one(kbase + 1, 1, c);
+    }
     {
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
@@ -1395,7 +1471,7 @@ __device__ __forceinline__ void gemm_wide_body(
             RAZER_LDS_READ32(s0, bs_lds, 256 * i);
             RAZER_LDS_WAIT(0, c0);
             RAZER_LDS_WAIT(0, s0);
-            flip_and_mask(0, i, c0, s0);
+            flip_and_mask(kbase, i, c0, s0);
             RAZER_LDS_READ64(le0[i], lut_lds + (s0 & 255u) * 8u);
             RAZER_LDS_READ64(le1[i], lut_lds + ((s0 >> 8) & 255u) * 8u);
             RAZER_LDS_WAIT(0, le0[i]);
@@ -1408,12 +1484,18 @@ __device__ __forceinline__ void gemm_wide_body(
 #pragma unroll
         for (int mi = 0; mi < MT; ++mi) RAZER_LDS_READ128(af[0][mi], aoff[0], 4096 * mi);
     }
-    int st = 0;                                         // stage of tile kt; tile kt + 3 follows it into the same stage
-    for (int kt = 0; kt < KT; ++kt) {
+    if constexpr (KG == 2) {                            // (the first tile's codes and scales have been read)
+#pragma unroll
+        for (int c = NU_A; c < L; ++c) issue_one(kbase + 2, 0, c);
+    }
+    int st = 0;                                         // stage of tile kt; tile kt + S follows it into the same stage
+    for (int kt = kbase; kt < kend; ++kt) {
         const int st_next = st == S - 1 ? 0 : st + 1;
         compute(kt, st, st_next, st == 0 ? S - 1 : st - 1);
         st = st_next;
     }
+    // a group with one K-tile less meets the other at its last barrier
+    if (KG == 2 && kend < kmeet) __builtin_amdgcn_s_barrier();
     // copies and fragment reads requested for tiles past the end: let them finish before the registers
     // and the stages they target are used for anything else
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
@@ -1421,24 +1503,112 @@ __device__ __forceinline__ void gemm_wide_body(
 #undef RAZER_LDS_READ64
 #undef RAZER_LDS_READ32
 #undef RAZER_LDS_WAIT
-    // (the lane number is counted again: no register is free to keep it through the loop)
-    store_tile<MT, NR, false>(acc, w_ts, nullptr, m0, n0 + 32 * NR * wave, m, n, y, ld_y,
-                              (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)));
+    const int lane2 = (int)lane_again();
+    if constexpr (KG == 1) {
+        store_tile<MT, NR, false>(acc, w_ts, nullptr, m0, n0 + 32 * NR * wave, m, n, y, ld_y, lane2);
+    } else {
+        // The two K groups hold partial sums of the same 256 x 64 outputs.  Past the barrier the activation stages are
+        // free: each wave hands the half that its partner will finish -- 32 KiB per wave, [block][group][4 registers][lane]
+        // -- and finishes the other half.
+        __syncthreads();
+        float4* mine = reinterpret_cast<float4*>(As + wave * 32768) + lane2;
+        const float4* theirs = reinterpret_cast<const float4*>(As + (wave ^ NWN) * 32768) + lane2;
+        auto meet = [&](auto second) {
+            constexpr int keep0 = decltype(second)::value ? MT / 2 : 0, give0 = MT / 2 - keep0;
+#pragma unroll
+            for (int i = 0; i < NR; ++i)
+#pragma unroll
+                for (int j = 0; j < MT / 2; ++j) {
+                    v16f& g = acc[i][give0 + j];
+                    asm volatile("" : "+a"(g));         // (not copied out of the accumulation registers before it is its turn)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) mine[((i * (MT / 2) + j) * 4 + q) * 64] = make_float4(g[4 * q], g[4 * q + 1], g[4 * q + 2], g[4 * q + 3]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < NR; ++i)
+#pragma unroll
+                for (int j = 0; j < MT / 2; ++j) {
+                    asm volatile("" : "+a"(acc[i][keep0 + j]));
+                    v16f sum[1][1] = {{acc[i][keep0 + j]}};
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const float4 t = theirs[((i * (MT / 2) + j) * 4 + q) * 64];
+                        sum[0][0][4 * q] += t.x;
+                        sum[0][0][4 * q + 1] += t.y;
+                        sum[0][0][4 * q + 2] += t.z;
+                        sum[0][0][4 * q + 3] += t.w;
+                    }
+                    const int64_t mm = m0 + 32 * (keep0 + j), nn = n0 + 32 * (NR * wn + i);
+                    if (partial) store_tile_partial<1, 1>(sum, mm, nn, m, n, partial + (int64_t)kslice * m * n, lane2);
+                    else store_tile<1, 1, false>(sum, w_ts, nullptr, mm, nn, m, n, y, ld_y, lane2);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+        };
+        if (kg == 0) meet(std::false_type{});
+        else meet(std::true_type{});
+    }
 }
 
 constexpr size_t kWideLds = 3 * (256 * 128 + 8 * 1280) + 256 * sizeof(uint2);
+constexpr size_t kHalvesLds = 2 * (2 * 256 * 128 + 8 * 1280) + 256 * sizeof(uint2) + 4 * 256;
+constexpr size_t kMixedLds = kWideLds > kHalvesLds ? kWideLds : kHalvesLds;
 
+// Which of `count` tiles workgroup b computes.  Workgroups go to the eight XCDs in turn; each XCD gets consecutive tiles,
+// in the order of pairs of tile rows, column by column: the 32 tiles it works on at a time are two rows (activations) by
+// 16 columns (weights), which its L2 fetches less for than one row by 32 (2048 x 4096 x 11008 204 -> 197 us, 512 x 22016 x
+// 4096 99.4 -> 97.4; four rows by eight columns are as good).
+__device__ __forceinline__ uint32_t xcd_order(uint32_t b, uint32_t count)
+{
+    const uint32_t x = b & 7u, rest = count & 7u;
+    return x * (count >> 3) + (x < rest ? x : rest) + (b >> 3);
+}
+__device__ __forceinline__ void pair_tile(uint32_t tile, int tiles_m, int tiles_n, int& tile_m, int& tile_n)
+{
+    const uint32_t per = 2u * (uint32_t)tiles_n, pair = tile / per, in = tile - pair * per, two = 2u * pair + 1u < (uint32_t)tiles_m ? 1u : 0u;
+    tile_n = (int)(in >> two);
+    tile_m = (int)(2u * pair + (in & two));
+}
+
+// The grid's first `whole` workgroups compute a 256 x 256 tile each, the others half a tile, 256 x 128 with two K groups (the
+// tiles of a last round that is at most half full, launch_wide).
 template <bool GB>
 __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(
     const uint8_t* __restrict__ w_codes, const uint8_t* __restrict__ w_scales, const float* __restrict__ w_ts,
     float sv0, float sv1, int64_t n, int64_t k, const uint16_t* __restrict__ a, int64_t m,
-    uint16_t* __restrict__ y, int64_t ld_y, int tiles_m, int lb)
+    uint16_t* __restrict__ y, int64_t ld_y, int tiles_m, int tiles_n, int whole, int lb)
 {
-    gemm_wide_body<GB>(w_codes, w_scales, w_ts, sv0, sv1, n, k, a, m, y, ld_y, (int)(blockIdx.x % tiles_m),
-                       (int)(blockIdx.x / tiles_m), lb);
+    int tile_m, tile_n;
+    if ((int)blockIdx.x < whole) {
+        pair_tile(xcd_order(blockIdx.x, whole), tiles_m, tiles_n, tile_m, tile_n);
+        gemm_wide_body<GB>(w_codes, w_scales, w_ts, sv0, sv1, n, k, a, m, y, ld_y, tile_m, tile_n, lb);
+    } else {
+        const uint32_t h = xcd_order(blockIdx.x - whole, gridDim.x - whole);
+        pair_tile(whole + (h >> 1), tiles_m, tiles_n, tile_m, tile_n);
+        gemm_wide_body<GB, 2>(w_codes, w_scales, w_ts, sv0, sv1, n, k, a, m, y, ld_y, tile_m, 2 * tile_n + (int)(h & 1u), lb);
+    }
+}
+// 256 x 128 tiles with two K groups throughout; grid and slices as gemm_rb_kernel.
+template <bool GB>
+__global__ __launch_bounds__(256, 1) void gemm_halves_kernel(
+    const uint8_t* __restrict__ w_codes, const uint8_t* __restrict__ w_scales, const float* __restrict__ w_ts,
+    float sv0, float sv1, int64_t n, int64_t k, const uint16_t* __restrict__ a, int64_t m,
+    uint16_t* __restrict__ y, int64_t ld_y, int tiles_m, int tiles_n, float* __restrict__ partial, int kt_per_slice, int lb)
+{
+    int tile_m, tile_n;
+    pair_tile(xcd_order(blockIdx.x, gridDim.x), tiles_m, tiles_n, tile_m, tile_n);
+    gemm_wide_body<GB, 2>(w_codes, w_scales, w_ts, sv0, sv1, n, k, a, m, y, ld_y, tile_m, tile_n, lb, partial, (int)blockIdx.y, kt_per_slice);
 }
 
-// The grouped form, as gemm_rb_grouped_kernel.
+// The grouped forms, as gemm_rb_grouped_kernel (t1..t3: first tile of matrices 1..3, tiles_n: all of them).
+#define RAZER_WIDE_PICK(tile)                                                                                            \
+    const uint8_t* codes = c0; const uint8_t* scales = s0; const float* ts = f0; uint16_t* y = y0;                      \
+    int64_t n = n0, ld = l0;                                                                                             \
+    int first = 0;                                                                                                       \
+    if (tile >= t1) { codes = c1; scales = s1; ts = f1; y = y1; n = n1; ld = l1; first = t1; }                          \
+    if (tile >= t2) { codes = c2; scales = s2; ts = f2; y = y2; n = n2; ld = l2; first = t2; }                          \
+    if (tile >= t3) { codes = c3; scales = s3; ts = f3; y = y3; n = n3; ld = l3; first = t3; }
 template <bool GB>
 __global__ __launch_bounds__(256, 1) void gemm_wide_grouped_kernel(
     const uint8_t* c0, const uint8_t* c1, const uint8_t* c2, const uint8_t* c3,
@@ -1448,22 +1618,49 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_grouped_kernel(
     int64_t n0, int64_t n1, int64_t n2, int64_t n3,
     int64_t l0, int64_t l1, int64_t l2, int64_t l3,
     int t1, int t2, int t3,
-    float sv0, float sv1, int64_t k, const uint16_t* __restrict__ a, int64_t m, int tiles_m, int lb)
+    float sv0, float sv1, int64_t k, const uint16_t* __restrict__ a, int64_t m, int tiles_m, int tiles_n, int whole, int lb)
 {
-    const int tile_m = (int)(blockIdx.x % tiles_m), t = (int)(blockIdx.x / tiles_m);
-    const uint8_t* codes = c0; const uint8_t* scales = s0; const float* ts = f0; uint16_t* y = y0;
-    int64_t n = n0, ld = l0;
-    int first = 0;
-    if (t >= t1) { codes = c1; scales = s1; ts = f1; y = y1; n = n1; ld = l1; first = t1; }
-    if (t >= t2) { codes = c2; scales = s2; ts = f2; y = y2; n = n2; ld = l2; first = t2; }
-    if (t >= t3) { codes = c3; scales = s3; ts = f3; y = y3; n = n3; ld = l3; first = t3; }
-    gemm_wide_body<GB>(codes, scales, ts, sv0, sv1, n, k, a, m, y, ld, tile_m, t - first, lb);
+    int tile_m, t;
+    if ((int)blockIdx.x < whole) {
+        pair_tile(xcd_order(blockIdx.x, whole), tiles_m, tiles_n, tile_m, t);
+        RAZER_WIDE_PICK(t)
+        gemm_wide_body<GB>(codes, scales, ts, sv0, sv1, n, k, a, m, y, ld, tile_m, t - first, lb);
+    } else {
+        const uint32_t h = xcd_order(blockIdx.x - whole, gridDim.x - whole);
+        pair_tile(whole + (h >> 1), tiles_m, tiles_n, tile_m, t);
+        RAZER_WIDE_PICK(t)
+        gemm_wide_body<GB, 2>(codes, scales, ts, sv0, sv1, n, k, a, m, y, ld, tile_m, 2 * (t - first) + (int)(h & 1u), lb);
+    }
 }
+template <bool GB>
+__global__ __launch_bounds__(256, 1) void gemm_halves_grouped_kernel(
+    const uint8_t* c0, const uint8_t* c1, const uint8_t* c2, const uint8_t* c3,
+    const uint8_t* s0, const uint8_t* s1, const uint8_t* s2, const uint8_t* s3,
+    const float* f0, const float* f1, const float* f2, const float* f3,
+    uint16_t* y0, uint16_t* y1, uint16_t* y2, uint16_t* y3,
+    int64_t n0, int64_t n1, int64_t n2, int64_t n3,
+    int64_t l0, int64_t l1, int64_t l2, int64_t l3,
+    int t1, int t2, int t3,
+    float sv0, float sv1, int64_t k, const uint16_t* __restrict__ a, int64_t m, int tiles_m, int tiles_n, int lb)
+{
+    int tile_m, t;
+    pair_tile(xcd_order(blockIdx.x, gridDim.x), tiles_m, tiles_n, tile_m, t);
+    RAZER_WIDE_PICK(t)
+    gemm_wide_body<GB, 2>(codes, scales, ts, sv0, sv1, n, k, a, m, y, ld, tile_m, t - first, lb);
+}
+#undef RAZER_WIDE_PICK
 
+// Of the tiles of a launch of 256 x 256 tiles, those computed whole: all but a last round of at most half the compute units,
+// whose tiles are cut in two.
+static int64_t whole_tiles(int64_t t256)
+{
+    const int64_t last = t256 % kComputeUnits;
+    return last <= kComputeUnits / 2 ? t256 - last : t256;
+}
 template <bool GB>
 static hipError_t launch_wide(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, hipStream_t st)
 {
-    if (k < 2048) return hipErrorInvalidValue;          // (wide_tiles never asks for it)
+    if (k < 2048) return hipErrorInvalidValue;          // (never asked for)
     const int tiles_m = (int)((m + 255) / 256);
     GemvProblem q[4];
     int t[5] = {0, 0, 0, 0, 0};
@@ -1471,19 +1668,54 @@ static hipError_t launch_wide(SvConfig cfg, int count, const GemvProblem* p, int
         q[i] = p[i < count ? i : count - 1];
         t[i + 1] = t[i] + (i < count ? (int)((q[i].n + 255) / 256) : 0);
     }
-    const dim3 grid((unsigned)(tiles_m * t[4]));
+    const int64_t tiles = (int64_t)tiles_m * t[4], whole = whole_tiles(tiles);
+    const dim3 grid((unsigned)(whole + 2 * (tiles - whole)));
     if (count == 1) {
         auto kern = gemm_wide_kernel<GB>;
-        RAZER_RAISE_LDS_LIMIT(kern, kWideLds);
-        launch(kern, grid, dim3(256), kWideLds, st, q[0].codes, q[0].scales, q[0].ts, cfg.sv0, cfg.sv1, q[0].n, k, a, m, q[0].y, q[0].ld_y, tiles_m, cfg.lb);
+        RAZER_RAISE_LDS_LIMIT(kern, kMixedLds);
+        launch(kern, grid, dim3(256), kMixedLds, st, q[0].codes, q[0].scales, q[0].ts, cfg.sv0, cfg.sv1, q[0].n, k, a, m, q[0].y, q[0].ld_y, tiles_m, t[4], (int)whole, cfg.lb);
     } else {
         auto kern = gemm_wide_grouped_kernel<GB>;
-        RAZER_RAISE_LDS_LIMIT(kern, kWideLds);
-        launch(kern, grid, dim3(256), kWideLds, st, q[0].codes, q[1].codes, q[2].codes, q[3].codes, q[0].scales, q[1].scales, q[2].scales, q[3].scales, q[0].ts,
+        RAZER_RAISE_LDS_LIMIT(kern, kMixedLds);
+        launch(kern, grid, dim3(256), kMixedLds, st, q[0].codes, q[1].codes, q[2].codes, q[3].codes, q[0].scales, q[1].scales, q[2].scales, q[3].scales, q[0].ts,
             q[1].ts, q[2].ts, q[3].ts, q[0].y, q[1].y, q[2].y, q[3].y, q[0].n, q[1].n, q[2].n, q[3].n, q[0].ld_y,
-            q[1].ld_y, q[2].ld_y, q[3].ld_y, t[1], t[2], t[3], cfg.sv0, cfg.sv1, k, a, m, tiles_m, cfg.lb);
+            q[1].ld_y, q[2].ld_y, q[3].ld_y, t[1], t[2], t[3], cfg.sv0, cfg.sv1, k, a, m, tiles_m, t[4], (int)whole, cfg.lb);
     }
     return hipGetLastError();
+}
+
+// split > 1 (one matrix, a workspace of slices * m * n floats): K in slices of whole K-tiles, summed by launch_slice_reduce.
+template <bool GB>
+static hipError_t launch_halves(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, hipStream_t st,
+                                int split = 1, float* workspace = nullptr)
+{
+    if (!workspace || count > 1) split = 1;
+    const int kt_all = (int)((k + kBK - 1) / kBK), kt_per = (kt_all + split - 1) / split;
+    const int slices = (kt_all + kt_per - 1) / kt_per;
+    if (kt_all - (slices - 1) * kt_per < 8) return hipErrorInvalidValue;   // four K-tiles per group, for the copies ahead of the loop (never asked for)
+    const int tiles_m = (int)((m + 255) / 256);
+    GemvProblem q[4];
+    int t[5] = {0, 0, 0, 0, 0};
+    for (int i = 0; i < 4; ++i) {
+        q[i] = p[i < count ? i : count - 1];
+        t[i + 1] = t[i] + (i < count ? (int)((q[i].n + 127) / 128) : 0);
+    }
+    const dim3 grid((unsigned)(tiles_m * t[4]), (unsigned)slices);
+    if (count == 1) {
+        auto kern = gemm_halves_kernel<GB>;
+        RAZER_RAISE_LDS_LIMIT(kern, kHalvesLds);
+        launch(kern, grid, dim3(256), kHalvesLds, st, q[0].codes, q[0].scales, q[0].ts, cfg.sv0, cfg.sv1, q[0].n, k, a, m, q[0].y, q[0].ld_y, tiles_m, t[4],
+            slices > 1 ? workspace : nullptr, slices > 1 ? kt_per : 0x7FFFFFFF, cfg.lb);
+    } else {
+        auto kern = gemm_halves_grouped_kernel<GB>;
+        RAZER_RAISE_LDS_LIMIT(kern, kHalvesLds);
+        launch(kern, grid, dim3(256), kHalvesLds, st, q[0].codes, q[1].codes, q[2].codes, q[3].codes, q[0].scales, q[1].scales, q[2].scales, q[3].scales, q[0].ts,
+            q[1].ts, q[2].ts, q[3].ts, q[0].y, q[1].y, q[2].y, q[3].y, q[0].n, q[1].n, q[2].n, q[3].n, q[0].ld_y,
+            q[1].ld_y, q[2].ld_y, q[3].ld_y, t[1], t[2], t[3], cfg.sv0, cfg.sv1, k, a, m, tiles_m, t[4], cfg.lb);
+    }
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || slices == 1) return e;
+    return launch_slice_reduce(workspace, q[0].ts, nullptr, m, q[0].n, slices, q[0].y, q[0].ld_y, st);
 }
 
 // split > 1 (workspace of slices * m * n floats): K in slices of whole K-tiles, summed by
@@ -1540,7 +1772,7 @@ static hipError_t launch_cfg(const uint8_t* w_codes, const uint8_t* w_scales, co
 // the workgroup, 8 / 9 = register-decode kernel with 64x128 / 128x128 tiles and K-slices (33..64 /
 // 65..128 activation rows: measured 1.3-2.1x faster than tiles 1 / 2 on 4096^2, 11008 x 4096 and
 // 4096 x 11008), 10 = tile 7's kernel with the K-slices of tile 4, which launch_gemm_t puts in its place
-// where they are long.  A K-tile costs about 1 us of latency however small the tile, so
+// where they are long; 12 / 13 = tiles 7 / 10 with 64 weight rows per wave (gemm_halves_kernel).  A K-tile costs about 1 us of latency however small the tile, so
 // when the output tiles cannot occupy the 256 compute units K is split until they do (at most 8 ways,
 // at least 8 K-tiles per slice); the slices meet in the workspace.
 struct GemmPlan {
@@ -1561,17 +1793,22 @@ static int rb_split(int64_t tiles, int64_t kt_all, int64_t m = 0, int64_t rows =
     return split >= 2 ? (int)split : 1;
 }
 // 256-row activation tiles: whether the register-decode kernel with 64 weight rows per wave (256 x 256 tiles, one
-// workgroup per compute unit) beats the one with 32 (256 x 128 tiles, two workgroups).  Per K-tile a full round takes
-// 1.8 against 2.0 us, a 128-wide round that is at most half full only 1.4; a 256-wide tile costs about 3 us more to
-// start and to store.  So: one round of 256-wide tiles where the 128-wide ones need more than one workgroup per unit
-// (2 x 11008 x 4096 at 512 rows 120 -> 101 us, {q,k,v} 3 x 4096 at 1024 rows 128 -> 107), else wherever the last
-// 128-wide round is more than half full or the rounds are many (2 x 11008 at 2048 rows 380 -> 348 us, 8192 x 28672 at
-// 4096 rows 1768 -> 1613; but 2 x 11008 at 1024 rows 202 -> 213, not taken).
+// workgroup per compute unit, a last round of at most 128 as halves of 256 x 128) beats the one with 32 (256 x 128 tiles, two
+// workgroups).  Rounds in units of a 256-wide one, 1.8 us per K-tile: one of halves 0.6 (1.1 us), a full 128-wide round 1.11
+// (2.0), one that is at most half full 0.78 (1.4).  128-wide -> wide with halves (us): {q,k,v} 3 x 4096 x 4096 at 2048 rows 203 ->
+// 190, 2 x 11008 x 4096 at 1024 194 -> 177, 13824 x 5120 at 1500 236 -> 216, 9216 x 3072 at 2048 143 -> 133, 17000 x 2048 at 1024
+// 97.9 -> 95.0; whole tiles only: 2 x 11008 x 4096 at 512 rows 120 -> 101, at 2048 380 -> 348.
+static double wide_rounds(int64_t t256)
+{
+    const int64_t last = t256 % kComputeUnits;
+    return (double)(t256 / kComputeUnits) + (last == 0 ? 0.0 : last <= kComputeUnits / 2 ? 0.6 : 1.0);
+}
 static bool wide_tiles(int64_t t256, int64_t t128, int64_t k)
 {
-    if (k < 2048 || t128 <= 256 || t256 <= 128) return false;
+    if (k < 2048 || t128 <= 256 || t256 <= kComputeUnits / 2) return false;
+    if (t128 < 512) return true;                        // (one round of whole tiles; else K-slices)
     const int64_t last = t128 % 512;
-    return t256 <= 256 || last == 0 || last > 256 || t128 >= 1536;
+    return wide_rounds(t256) <= 1.11 * (double)(t128 / 512) + (last == 0 ? 0.0 : last <= 256 ? 0.78 : 1.11);
 }
 static GemmPlan gemm_plan(int64_t m, int64_t n, int64_t k, bool register_decode_ok)
 {
@@ -1593,7 +1830,8 @@ static GemmPlan gemm_plan(int64_t m, int64_t n, int64_t k, bool register_decode_
         // one round of 256x128 tiles (one workgroup per compute unit): the register-decode kernel with
         // two K groups of four waves keeps two waves on every SIMD (measured 9-10 % over the LDS-staged
         // kernel on 2048 x 4096 x {4096, 11008}; slower than it when the tiles need a second round)
-        if (register_decode_ok && t128 >= 192 && t128 <= 256 && k >= 16 * kBK) return GemmPlan{7, 1};
+        // (with 64 weight rows per wave where K is long enough)
+        if (register_decode_ok && t128 >= 192 && t128 <= 256 && k >= 16 * kBK) return GemmPlan{k >= 2048 ? 12 : 7, 1};
         // else the weight-tile width that wastes fewer compute units in the last round of workgroups
         auto eff = [](int64_t t) { return (double)t / (double)(((t + 255) / 256) * 256); };
         if (eff(t256) >= eff(t128)) { p.tile = 3; tiles = t256; }
@@ -1622,6 +1860,15 @@ static bool long_slices(const GemmPlan& p, int64_t m, int64_t n, int64_t k)
     if (p.tile != 4 || p.split <= 1 || k > kRbMaxK || k % kBK != 0) return false;
     const int64_t kt_all = k / kBK, per = (kt_all + p.split - 1) / p.split, slices = (kt_all + per - 1) / per;
     return per >= 18 && ((m + 255) / 256 * ((n + 127) / 128) * slices <= 192 || per >= 100 || (m <= 512 && per >= 30));
+}
+// Which of the two kernels with two K groups takes long slices: with 64 weight rows per wave where the chip is full and the
+// slices outlast the longer start (us, 32 -> 64): 4096 x 11008 at 512 rows (256 workgroups, 43 K-tiles) 70.9 -> 66.0, 5120 x
+// 13824 (240, 72) 100.9 -> 91.7, 1390 x 19520 at 1390 (198, 102) 137 -> 128; 1664 x 15360 at 512 (208, 30) 49.2 -> 48.6, 520 x 21568 at 257
+// (80, 43) 34.9, 34.9.  The last slice holds eight K-tiles or more.
+static int slices_tile(const GemmPlan& p, int64_t m, int64_t n, int64_t k)
+{
+    const int64_t kt_all = k / kBK, per = (kt_all + p.split - 1) / p.split, slices = (kt_all + per - 1) / per;
+    return per >= 40 && (m + 255) / 256 * ((n + 127) / 128) * slices > 192 && kt_all - (slices - 1) * per >= 8 ? 13 : 10;
 }
 
 size_t gemm_workspace_bytes(int64_t n, int64_t k, int64_t m)
@@ -1652,7 +1899,7 @@ static hipError_t launch_gemm_t(const uint8_t* w_codes, const uint8_t* w_scales,
     // operand of W4A4, which that kernel does not decode)
     GemmPlan p = gemm_plan(m, n, k, !AQ && k <= kRbMaxK);
     if ((m <= kSkinnyMaxM && k <= kSkinnyMaxK) || !workspace) p.split = 1;   // not sized a workspace
-    if (!AQ && long_slices(p, m, n, k)) p.tile = 10;
+    if (!AQ && long_slices(p, m, n, k)) p.tile = slices_tile(p, m, n, k);
 #define RAZER_GEMM(BM, BN, WGM, WGN, PP) \
     launch_cfg<BM, BN, WGM, WGN, AQ, PP, GB>(w_codes, w_scales, w_ts, wcfg, n, k, a, a_codes, a_scales, a_ts, acfg, m, y, ld_y, p.split, workspace, st)
     switch (p.tile) {
@@ -1668,10 +1915,9 @@ static hipError_t launch_gemm_t(const uint8_t* w_codes, const uint8_t* w_scales,
         if (p.tile == 10) return launch_rb<8, 2, 2, 8, GB>(w_codes, w_scales, w_ts, wcfg, n, k, a, m, y, ld_y, st, p.split, workspace);
         if (p.tile == 8) return launch_rb<4, 2, 1, 2, GB>(w_codes, w_scales, w_ts, wcfg, n, k, a, m, y, ld_y, st, p.split, workspace);
         if (p.tile == 9) return launch_rb<4, 2, 1, 4, GB>(w_codes, w_scales, w_ts, wcfg, n, k, a, m, y, ld_y, st, p.split, workspace);
-        if (p.tile == 5) {
-            const GemvProblem one{w_codes, w_scales, w_ts, n, y, ld_y};
-            return launch_wide<GB>(wcfg, 1, &one, k, a, m, st);
-        }
+        const GemvProblem one{w_codes, w_scales, w_ts, n, y, ld_y};
+        if (p.tile == 5) return launch_wide<GB>(wcfg, 1, &one, k, a, m, st);
+        if (p.tile == 12 || p.tile == 13) return launch_halves<GB>(wcfg, 1, &one, k, a, m, st, p.split, workspace);
         if (p.tile == 7) return launch_rb<8, 2, 2, 8, GB>(w_codes, w_scales, w_ts, wcfg, n, k, a, m, y, ld_y, st);
         return launch_rb<4, 2, 1, 8, GB>(w_codes, w_scales, w_ts, wcfg, n, k, a, m, y, ld_y, st);
     }
@@ -1748,10 +1994,10 @@ double gemm_estimate_us(int count, const GemvProblem* p, int64_t m, int64_t k)
     GemmPlan q{0, 1};
     if (count == 1) {
         q = gemm_plan(m, rows, k, true);
-        if (long_slices(q, m, rows, k)) q.tile = 10;
+        if (long_slices(q, m, rows, k)) q.tile = slices_tile(q, m, rows, k);
     } else {
         const int w = grouped_tile_width(count, p, m, k);
-        q = GemmPlan{w == 256 ? 5 : w == 128 ? 6 : w == 129 ? 7 : w == 8 ? 11 : 9, grouped_split(count, p, m, k)};
+        q = GemmPlan{w == 256 ? 5 : w == 128 ? 6 : w == 129 ? (k >= 2048 ? 12 : 7) : w == 8 ? 11 : 9, grouped_split(count, p, m, k)};
     }
     const int64_t per = (kt_all + q.split - 1) / q.split, slices = (kt_all + per - 1) / per;
     const int64_t wgs = (m <= 128 ? t128 : tm * (q.tile == 3 || q.tile == 5 ? t256 : t128)) * slices;
@@ -1767,10 +2013,12 @@ double gemm_estimate_us(int count, const GemvProblem* p, int64_t m, int64_t k)
         case 6: t = Terms{5.4, 0.65, 0.58, 0.05, 0.0, 0.0, 0.0, 0.8, 1.5}; break;
         case 7: t = Terms{9.5, 0.49, 0.51, 0.09, 0.0, 0.0, 0.0, 0.0, 2.3}; break;
         case 10: t = Terms{0.0, 0.78, 0.15, 0.0, 13.9, 1.7, 1.5, 0.0, 0.0}; break;
+        case 12: t = Terms{6.3, 0.53, 0.49, 0.09, 0.0, 0.0, 0.0, 0.0, 2.3}; break;
+        case 13: t = Terms{0.0, 0.70, 0.15, 0.0, 13.9, 1.7, 1.5, 0.0, 0.0}; break;
         default: t = Terms{8.0, 0.86, 0.05, 0.065, 5.0, 1.6, 0.0, 0.0, 2.1}; break;   // 11: the grouped launch's K-slices
     }
     const int64_t units = q.tile == 6 ? 2 * kComputeUnits : kComputeUnits;
-    const double rounds = (double)((wgs + units - 1) / units);
+    const double rounds = q.tile == 5 ? wide_rounds(t256 * tm) : (double)((wgs + units - 1) / units);
     const double us = t.start + per * (t.tile * rounds + t.fill * full + t.off_line * off_line * rounds);
     return slices > 1 ? us + t.meet + (t.sums + (by4 ? 0.0 : t.sums_by_one)) * sums : us + (t.out + (by8 ? 0.0 : t.out_by_one)) * values;
 }
@@ -1809,7 +2057,7 @@ static hipError_t launch_gemm_grouped_t(SvConfig cfg, int count, const GemvProbl
     const int w = grouped_tile_width(count, p, m, k);
     if (w == 256) return launch_wide<GB>(cfg, count, p, k, a, m, st);
     if (w == 128) return launch_rb_grouped<4, 2, 1, 8, GB>(cfg, count, p, k, a, m, st);
-    if (w == 129) return launch_rb_grouped<8, 2, 2, 8, GB>(cfg, count, p, k, a, m, st);
+    if (w == 129) return k >= 2048 ? launch_halves<GB>(cfg, count, p, k, a, m, st) : launch_rb_grouped<8, 2, 2, 8, GB>(cfg, count, p, k, a, m, st);
     if (w == 2 || w == 4 || w == 8) {
         const int split = grouped_split(count, p, m, k);
         if (split > 1 && !workspace) return hipErrorInvalidValue;

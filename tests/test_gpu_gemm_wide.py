@@ -91,3 +91,48 @@ def test_infinite_activation_stays_infinite(oracle, m, n, k, column, kernel):
     assert bool((got[2][hit] == torch.sign(wc[hit]) * float("inf")).all())
     others = [i for i in range(m) if i != 2]
     assert bool((got[others] == plain[others]).all())
+
+
+@pytest.mark.parametrize("m,ns,k,block,kernel", [
+    # one round of 256 x 128 tiles with two K groups: even and odd numbers of K-tiles, a last one of 32 elements, three rows of tiles
+    (300, (12300,), 2048, 16, "gemm_halves_kernel<false>"), (257, (12300,), 2112, 16, "gemm_halves_kernel<false>"), (300, (12164,), 2080, 32, "gemm_halves_kernel<true>"),
+    (520, (8200,), 2176, 64, "gemm_halves_kernel<true>"), (300, (6200, 36, 6000), 2112, 16, "gemm_halves_grouped_kernel<false>"),
+    (300, (6200, 6100), 2176, 128, "gemm_halves_grouped_kernel<true>"),
+    # whole 256 x 256 tiles and a last round of half tiles, the last half of a matrix past its rows
+    (300, (32800,), 2048, 16, "gemm_wide_kernel<false>"), (513, (22100,), 2080, 16, "gemm_wide_kernel<false>"), (300, (20000, 13000), 2112, 16, "gemm_wide_grouped_kernel<false>"),
+    (513, (9000, 40, 13100), 2080, 32, "gemm_wide_grouped_kernel<true>"),
+    # long K-slices, the last one shorter, odd numbers of K-tiles in a slice
+    (512, (4096,), 11008, 16, "gemm_halves_kernel<false>"), (400, (4100,), 11072, 16, "gemm_halves_kernel<false>"), (300, (5003,), 13888, 32, "gemm_halves_kernel<true>")])
+def test_half_tiles(oracle, m, ns, k, block, kernel):
+    """... and an infinite activation stays infinite and in its row."""
+    rng = np.random.default_rng(m + sum(ns) + k)
+    a = synth.activation(m, k, seed=9300 + m)
+    rows = np.unique(np.r_[0, 2, rng.choice(m, size=10, replace=False), 255, 256, m - 1])
+    ws = []
+    for n in ns:
+        wq = (rng.integers(0, 256, size=(n, k // 2), dtype=np.uint8), rng.integers(0, 256, size=(n, k // block), dtype=np.uint8), np.float32(2.0 ** -9))
+        ws.append((wq, razer.RazerTensor.from_host(*wq, razer.WEIGHT, (5.0, 8.0))))
+    print("half tiles", m, ns, k, block, flush=True)
+    a_dev = bf16_bits_to_dev(a)
+    call = lambda: [razer.razer_linear(ws[0][1], a_dev)] if len(ns) == 1 else razer.razer_linear_grouped([w[1] for w in ws], a_dev)  # noqa: E731
+    plain, got = [], []
+    column = (k // 64 - 1) * 64 - 7                              # (in the last whole K-tile but one or before it)
+    razer.razer_tune_force(binding.TUNE_GEMM_SLICES, (1,))       # (keeps the call off the small-batch kernel)
+    try:
+        names = launched_kernels(lambda: plain.extend(call()))
+        a_dev[2, column] = float("inf")
+        got = call()
+    finally:
+        razer.razer_tune_force(binding.TUNE_GEMM_SLICES, None)
+    assert any(kernel in x for x in names) and all(kernel in x or "slice_reduce" in x for x in names), names
+    for (wq, _), y, z in zip(ws, plain, got):
+        n = len(wq[0])
+        cols = np.arange(n) if n < 300 else np.unique(np.r_[0:40, 120:136, 250:262, n - 40:n, rng.choice(n, size=60, replace=False)])
+        y64, _ = oracle.linear((wq[0][cols], wq[1][cols], wq[2]), a_bf16=a[rows])
+        assert max_rel_err(dev_to_bf16_bits(y)[rows][:, cols], y64) <= TOL
+        z, y = z.float().cpu(), y.float().cpu()
+        wc = torch.from_numpy(oracle.dequant(oracle.WEIGHT, wq[0][cols], wq[1][cols], wq[2])["f32"])[:, column].float()
+        hit = torch.from_numpy(cols)[wc != 0]
+        assert bool((z[2][hit] == torch.sign(wc[wc != 0]) * float("inf")).all())
+        others = [i for i in range(m) if i != 2]
+        assert bool((z[others] == y[others]).all())
