@@ -94,7 +94,9 @@ __device__ __forceinline__ void store_tile(const v16f (&acc)[TN][TM], const floa
                                            int64_t wm0, int64_t wn0, int64_t m, int64_t n, uint16_t* y,
                                            int64_t ld_y, int lane)
 {
-    const float scale = AQ ? (*w_ts) * (*a_ts) : -(*w_ts);
+    // (scalar loads: the offset register of a vector load may be set up ahead of a wait that the caller placed by hand)
+    typedef const __attribute__((address_space(4))) float* Uniform;
+    const float scale = AQ ? *(Uniform)(uintptr_t)w_ts * *(Uniform)(uintptr_t)a_ts : -*(Uniform)(uintptr_t)w_ts;
     const int hi = lane >> 5;
 #pragma unroll
     for (int i = 0; i < TN; ++i)
@@ -1286,7 +1288,7 @@ __device__ __forceinline__ void gemm_wide_body(
     // Once only copies of a ragged last tile are left: its second 32 elements do not exist, the lanes that would fetch
     // them fetch the first ones of the same row again (their weights are masked).
     // (the lane number is counted again, here and at the end: no register is free to keep it through the loop)
-    auto lane_again = []() { return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); };
+    auto lane_again = [](uint32_t all = ~0u) { return __builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0u)); };
     auto ragged_acts = [&](int from, int to) {
         const uint32_t l = lane_again();
 #pragma unroll
@@ -1503,7 +1505,9 @@ __device__ __forceinline__ void gemm_wide_body(
 #undef RAZER_LDS_READ64
 #undef RAZER_LDS_READ32
 #undef RAZER_LDS_WAIT
-    const int lane2 = (int)lane_again();
+    uint32_t all = ~0u;
+    asm volatile("" : "+s"(all));                       // (not counted ahead of the wait, into a register of a read in flight)
+    const int lane2 = (int)lane_again(all);
     if constexpr (KG == 1) {
         store_tile<MT, NR, false>(acc, w_ts, nullptr, m0, n0 + 32 * NR * wave, m, n, y, ld_y, lane2);
     } else {
