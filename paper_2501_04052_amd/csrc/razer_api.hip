@@ -314,7 +314,7 @@ razer_status razer_linear(const razer_tensor* w, const void* a_bf16, const razer
     } else if (!a_q && m > kGemvDirectMaxM && m <= kSkinnyMaxM && k <= kSkinnyMaxK) {
         const size_t need = skinny_workspace_bytes(n, k, m);
         if (need > 0 && (!workspace || workspace_bytes < need || !aligned16(workspace))) return RAZER_ERR_WORKSPACE;
-        e = launch_skinny(wsv, 1, &one, k, (const uint16_t*)a_bf16, m, st);
+        e = launch_skinny(wsv, 1, &one, k, (const uint16_t*)a_bf16, m, st, need > 0 ? (float*)workspace : nullptr, need);
     } else if (!a_q && m <= kGemvDirectMaxM) {
         e = launch_gemv(wsv, w->codes, w->scales, w->tensor_scale, n, k, (const uint16_t*)a_bf16, m,
                         (uint16_t*)y_bf16, ld_y, st);
@@ -322,7 +322,7 @@ razer_status razer_linear(const razer_tensor* w, const void* a_bf16, const razer
         const size_t need = gemm_workspace_bytes(n, k, m);
         if (need > 0 && (!workspace || workspace_bytes < need || !aligned16(workspace))) return RAZER_ERR_WORKSPACE;
         if (!a_q && ring_serves(wsv, 1, &one, k, m))
-            e = launch_skinny(wsv, 1, &one, k, (const uint16_t*)a_bf16, m, st);
+            e = launch_skinny(wsv, 1, &one, k, (const uint16_t*)a_bf16, m, st, need > 0 ? (float*)workspace : nullptr, need);
         else
             e = launch_gemm(wsv, w->codes, w->scales, w->tensor_scale, n, k, (const uint16_t*)a_bf16, asv,
                             a_q ? a_q->codes : nullptr, a_q ? a_q->scales : nullptr,

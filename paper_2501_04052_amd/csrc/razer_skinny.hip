@@ -130,6 +130,8 @@ struct RingArgs {
     int64_t k, m;
     const uint16_t* a;
     int chunk, lb;
+    float* partial;                                                   // K-slices: [slice][m][n] sums, steps per slice
+    uint32_t slice_steps;
 };
 
 // Staged scales (ST): the scale entries of a group's 16 rows are one contiguous piece of memory, K bytes with 16-element
@@ -141,7 +143,7 @@ __device__ __forceinline__ uint32_t ring_scale_swizzle(uint32_t byte) { return b
 __host__ __device__ __forceinline__ uint32_t ring_scale_region(uint32_t scale_ld) { return (16u * scale_ld + 255u) & ~255u; }
 
 // FORM: SF, + 2: whole steps where ring_parts() would take halves
-template <int NA, int G, bool GB, int FORM, int W, bool IL, bool ST>
+template <int NA, int G, bool GB, int FORM, int W, bool IL, bool ST, bool KS = false>
 __device__ __forceinline__ void ring_body(const RingArgs arg)
 {
     constexpr int SF = FORM & 1, H = FORM & 2 ? 1 : ring_parts<NA, W>();
@@ -164,7 +166,8 @@ __device__ __forceinline__ void ring_body(const RingArgs arg)
     static_assert(!IL || (!GB && !SF), "interleaved layout: 16-element blocks, scale bytes");
     const uint32_t code_ld = IL ? (uint32_t)il_row_bytes(k) : (uint32_t)(k >> 1);
     const uint32_t scale_ld = IL ? code_ld : SF ? (uint32_t)(k >> 7) * 2u : (uint32_t)(k >> (GB ? lb : 4));
-    const uint32_t nsteps = (kk32 + 127u) >> 7;
+    const uint32_t all_steps = (kk32 + 127u) >> 7, step0 = KS ? blockIdx.z * arg.slice_steps : 0u;
+    const uint32_t nsteps = KS && step0 + arg.slice_steps < all_steps ? step0 + arg.slice_steps : all_steps;   // (behind the last one)
 
     // copy lanes: codes and scale bits -- row lane / 4, 16-byte chunk / 32-element run; activations -- row 4 i + lane / 16
     const uint32_t wr = lane >> 2, wp = lane & 3u, wc = wp ^ ((wr >> 2) & 3u);
@@ -261,7 +264,7 @@ __device__ __forceinline__ void ring_body(const RingArgs arg)
 #define RAZER_DS8(dst, addr, imm) asm volatile("ds_read_u8 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(imm))
 #define RAZER_DS16(dst, addr, imm) asm volatile("ds_read_u16 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(imm))
 
-    uint32_t step = wave;                                             // (the host starts at most nsteps waves)
+    uint32_t step = step0 + wave;                                     // (the host starts no more waves than there are steps)
     if constexpr (ST) {
 #pragma unroll
         for (int gi = 0; gi < G; ++gi) {
@@ -471,8 +474,9 @@ __device__ __forceinline__ void ring_body(const RingArgs arg)
         if (q >= e3) { ts = arg.ts[3]; y = arg.y[3]; n = arg.n[3]; ld_y = arg.ld_y[3]; first = e3; }
         y += m0 * ld_y;
         const int64_t row0 = (int64_t)(q - first) * 16;
-        float sc;
-        if constexpr (EARLY) {
+        float sc = 1.0f;
+        if constexpr (KS) {
+        } else if constexpr (EARLY) {
             sc = tensor_scales[0];
 #pragma unroll
             for (int i = 1; i < G; ++i) sc = gi == (uint32_t)i ? tensor_scales[i] : sc;
@@ -486,7 +490,20 @@ __device__ __forceinline__ void ring_body(const RingArgs arg)
             t.x += p.x; t.y += p.y; t.z += p.z; t.w += p.w;
         }
         const float v[4] = {t.x, t.y, t.z, t.w};
-        if constexpr (SF != 0) {
+        if constexpr (KS) {
+            // (negated: slice_reduce_kernel undoes the negation of the other kernels' decode)
+            const int64_t gn = row0 + 4 * g, gm = 16 * b + r;
+            if (gm < m && gn < n) {
+                float* dst = arg.partial + ((int64_t)blockIdx.z * m + gm) * n + gn;
+                if ((n & 3) == 0) {
+                    *reinterpret_cast<float4*>(dst) = make_float4(-t.x, -t.y, -t.z, -t.w);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (gn + i < n) dst[i] = -v[i];
+                }
+            }
+        } else if constexpr (SF != 0) {
             // swapped operands: weight row 16 q + l % 16, activation rows 16 b + 4 (l / 16) + 0..3
             const int64_t wn = row0 + r;
             if (wn < n) {
@@ -524,6 +541,12 @@ __global__ __launch_bounds__(64 * W) void staged_ring_kernel(const RingArgs arg)
 {
     ring_body<NA, G, GB, FORM, W, IL, true>(arg);
 }
+// blockIdx.z: a slice of K; its sums go to the workspace.
+template <int NA, int G, bool GB, int FORM, int W, bool IL = false>
+__global__ __launch_bounds__(64 * W) void sliced_ring_kernel(const RingArgs arg)
+{
+    ring_body<NA, G, GB, FORM, W, IL, false, true>(arg);
+}
 
 // More than 64 activation rows go in equal runs of at most 64, blockIdx.y counting them.
 static int64_t ring_chunk(int64_t m)
@@ -550,7 +573,8 @@ static int64_t ring_wgs(int count, const GemvProblem* p, int64_t m)
 // 24) 1.05 / 1.07 / 1.03, x 2048 (48) 0.97 / 0.97 / 1.00, x 4096 0.98 / 0.95 / 0.96, x 6144 0.91 / 0.92 / 0.95, 57344 x 8192 at 8 rows 0.88
 // (68.7 -> 60.6 us); FP16 scales 22016 x 4096 (96) 1.02 / 1.02 / 0.99, 28672 x 4096 (128) 0.98 / 0.99 / 1.00, 57344 x 8192 0.86 / 0.87 / 0.95.
 // One workgroup per unit: 4096 x 4096 (32) 1.11 / 1.10 / 1.04, 12288 x 4096 (96) 1.03 / 1.03 / 1.01, 12288 x 6144 (144) 1.02 / 0.99 / 0.98,
-// 12288 x 8192 (192) 1.00 / 0.97 / 0.98, 8192 x 20480 (320) 0.95 / 0.93 / 0.95, 12288 x 20480 0.85 / 0.83 / 0.99.  Where the regions leave
+// 12288 x 8192 (192) 1.00 / 0.97 / 0.98, 12288 x 20480 0.85 / 0.83 / 0.99; with one or two groups later: 8192 x 12288 (192) 1.01 / 0.99 /
+// 0.97, 5120 x 13824 (216) at 24 rows 1.08, 8192 x 20480 (320) 0.95 / 0.93 / 0.95, x 28672 at 8 rows 0.95.  Where the regions leave
 // LDS for fewer workgroups than without them: two are as good as three up to 32 rows; one instead of two pays from about
 // 190 (28672 x 4096 at 16 rows 1.07, x 6144 0.98, 22016 x 8192 1.01, 28672 x 8192 0.96); above 32 rows (four waves) behind: 57344 x
 // 8192 1.16.  Runs of more than 64 rows gain nothing (3 x 5120 x 3840 at 571 rows 1.01, 2 x 5120 x 5120 at 320 1.00) and lose where
@@ -562,7 +586,7 @@ static bool ring_stages(bool f16, int64_t wgs, int64_t nsteps, size_t plain, siz
     if (then < 1) return false;
     if (then < now && then < per_unit && (NA > 8 || (then < 2 && work < 190))) return false;
     if (per_unit > 1) return work >= (f16 ? 120 : 48);
-    return work >= (NA <= 2 ? 190 : 140);
+    return work >= (G <= 2 ? 300 : NA <= 2 ? 190 : 140);
 }
 
 template <int NA, int G, bool GB, int SF, bool IL, int W, int H = ring_parts<NA, W>()>
@@ -722,7 +746,64 @@ static double ring_estimate_us(int count, const GemvProblem* p, int64_t k, int64
            (by4 ? 2.2 : 2.5) * values;
 }
 
-static hipError_t launch_ring(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, hipStream_t st)
+template <int NA, int G, bool GB>
+static hipError_t launch_ring_slices(SvConfig cfg, const GemvProblem& p, int64_t k, const uint16_t* a, int64_t m, int slices, float* workspace, hipStream_t st)
+{
+    constexpr int W = kRingWaves, H = ring_parts<NA, W>();
+    const uint32_t groups = (uint32_t)((p.n + 15) / 16), steps = (uint32_t)((k + 127) / 128), per = (steps + slices - 1) / slices;
+    RingArgs arg;
+    for (int i = 0; i < 4; ++i) {
+        arg.codes[i] = p.codes; arg.scales[i] = p.scales; arg.ts[i] = p.ts; arg.y[i] = p.y; arg.n[i] = p.n; arg.ld_y[i] = p.ld_y; arg.e[i] = groups;
+    }
+    arg.sv0 = cfg.sv0; arg.sv1 = cfg.sv1; arg.k = k; arg.m = m; arg.chunk = (int)m; arg.a = a; arg.lb = cfg.lb;
+    arg.partial = workspace;
+    arg.slice_steps = per;
+    constexpr uint32_t lds = W * ring_wave_bytes<NA, G, H, false>();
+    static_assert(lds + kRingTableBytes <= kLdsBytes, "LDS");
+    auto kern = sliced_ring_kernel<NA, G, GB, 0, W>;
+    RAZER_RAISE_LDS_LIMIT(kern, lds);
+    launch(kern, dim3((groups + G - 1) / G, 1, (unsigned)slices), 64 * W, lds, st, arg);
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : launch_slice_reduce(workspace, p.ts, nullptr, m, p.n, slices, p.y, p.ld_y, st);
+}
+// K-slices of one matrix of 17 .. 64 rows (0: none) and the groups of weight rows per workgroup with them.  Where the weight rows
+// are few, a workgroup of one group (16 rows) reads all the activations for them, 64 x 11008 x 2 B = 1.4 MB at what a unit's
+// load path takes, 50 bytes a clock; slices of K let it own two or four groups and read half or a quarter.  They cost the
+// sums' way through the workspace and a second launch, 3.5 us (four groups 5.6).  Times as ring_estimate_us has them (16 waves, rows of 10240
+// elements and more: 10 % more).  us, without -> with: 4096 x 11008 at 64
+// rows 21.4 -> 18.3, at 40 18.6 -> 17.0, 2048 x 8192 14.8 -> 11.8, 13.2 -> 11.3, 1024 x 8192 14.6 -> 10.8, 1000 x 11008 at 40 17.7 -> 11.9,
+// 5120 x 13824 (four groups) 27.1 -> 22.5; not taken: 4096 x 5120 at 64 rows 12.0, 12.1, 2048 x 4096 9.2, 10.2, 4096 x 8192 at 40 13.7, 14.2.
+// Up to 32 rows (whole steps, half the activations) only slices of a quarter and less of long rows: 2048 x 12288 at 32 rows 13.0 ->
+// 11.1, 1000 x 11008 at 20 11.5 -> 10.1; not taken 2048 x 8192 at 32 9.6, 10.2, 4096 x 16384 16.9, 17.5.
+static double ring_sum_us(int64_t k, int64_t m, int64_t rounds, int g)
+{
+    const double row = k % 64 == 0 ? 0.0074 : 0.0131;
+    return 1e-3 * (double)(k * rounds) * (0.27 + row * (double)m + 0.52 * g);
+}
+static int ring_slices(int64_t n, int64_t k, int64_t m, int g, size_t workspace_bytes, int& groups_each)
+{
+    const int64_t steps = (k + 127) / 128, groups = (n + 15) / 16, wgs = (groups + g - 1) / g;
+    const double whole = (5.1 + ring_sum_us(k, m, (wgs + kComputeUnits - 1) / kComputeUnits, g)) * (g == 1 && k >= 10240 ? 1.1 : 1.0);
+    int best = 0;
+    double us = 0.98 * whole;
+    for (int sg = 2; sg <= (m > 32 ? 4 : 2); sg += 2) {
+        int64_t s = kComputeUnits / ((groups + sg - 1) / sg);
+        for (s = s < 8 ? s : 8; s >= 2; --s) {                        // every slice has a step for each wave
+            const int64_t per = (steps + s - 1) / s;
+            if (per >= kRingWaves && steps - (s - 1) * per >= kRingWaves && (size_t)(s * m * n) * sizeof(float) <= workspace_bytes) break;
+        }
+        if (s < 2) continue;
+        if (m <= 32) {
+            if (s >= 4 && k >= 10240) { best = (int)s; groups_each = sg; }
+            continue;
+        }
+        const double sliced = (sg == 2 ? 8.6 : 10.7) + ring_sum_us(k, m, 1, sg) / (double)s;
+        if (sliced < us) { us = sliced; best = (int)s; groups_each = sg; }
+    }
+    return best;
+}
+
+static hipError_t launch_ring(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, float* workspace, size_t workspace_bytes, hipStream_t st)
 {
     int g = ring_groups(ring_row_groups(count, p), m, cfg.f16 != 0);
     int64_t rows = 0;
@@ -734,6 +815,16 @@ static hipError_t launch_ring(SvConfig cfg, int count, const GemvProblem* p, int
     const bool shaped = t.source && t.p[0] == 2;
     if (shaped && (t.p[1] == 1 || t.p[1] == 2 || t.p[1] == 3 || (t.p[1] == 4 && !(m > 32 && cfg.f16)) || (t.p[1] == 6 && m <= 32))) g = t.p[1];
     const int asked = shaped && t.p[2] ? (t.p[2] == 16 ? 16 : 8) : t.source == 1 ? 8 : 0;
+    if (count == 1 && !cfg.f16 && !cfg.il && m > 16 && m <= kRingMaxM && !t.source && workspace) {
+        int sg = 0;
+        const int slices = ring_slices(p[0].n, k, m, g, workspace_bytes, sg);
+#define RAZER_RING_SLICES(NA, G)                                                                                         \
+    (cfg.lb == 4 ? launch_ring_slices<NA, G, false>(cfg, p[0], k, a, m, slices, workspace, st)                          \
+                 : launch_ring_slices<NA, G, true>(cfg, p[0], k, a, m, slices, workspace, st))
+        if (slices && m <= 32) return RAZER_RING_SLICES(8, 2);
+        if (slices) return sg == 4 ? RAZER_RING_SLICES(16, 4) : RAZER_RING_SLICES(16, 2);
+#undef RAZER_RING_SLICES
+    }
 #define RAZER_RING(NA, G)                                                                  \
     do {                                                                                   \
         if (cfg.f16) return launch_ring_t<NA, G, false, 1>(cfg, count, p, k, a, m, asked, st);    \
@@ -861,12 +952,13 @@ size_t skinny_grouped_workspace_bytes(int count, const GemvProblem* p, int64_t k
     return ws_bytes(rows, k, m, count);
 }
 
-hipError_t launch_skinny(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, hipStream_t st)
+hipError_t launch_skinny(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, hipStream_t st,
+                         float* workspace, size_t workspace_bytes)
 {
     if (count < 1 || count > 4 || m < 2 || k <= 0 || k > kSkinnyMaxK) return hipErrorInvalidValue;
     for (int i = 0; i < count; ++i)
         if (p[i].n <= 0) return hipErrorInvalidValue;
-    return launch_ring(cfg, count, p, k, a, m, st);
+    return launch_ring(cfg, count, p, k, a, m, workspace, workspace_bytes, st);
 }
 
 

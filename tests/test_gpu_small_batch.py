@@ -166,7 +166,7 @@ def test_infinite_activation_stays_infinite_with_a_ragged_last_step(oracle, m):
     # rows of 256, 262, 518 and of 64 .. 4 bytes of scales, the last rows of a matrix, several matrices in one workgroup
     (8, (68, 33 * 4, 12), 4096, razer.WEIGHT, 16, 6), (5, (100, 7), 4192, razer.WEIGHT, 16, 6), (16, (37,), 8288, razer.WEIGHT, 16, 3), (32, (36, 20), 4096, razer.WEIGHT, 32, 6),
     (8, (50, 3), 8192 + 64, razer.WEIGHT, 64, 3), (33, (68, 5), 4608, razer.WEIGHT, 128, 4), (64, (37, 40), 6176, razer.WEIGHT, 16, 4), (50, (70,), 6144, razer.WEIGHT, 32, 4),
-    (16, (36, 20), 4096, razer.WEIGHT_F16, 128, 6), (64, (52,), 8320, razer.WEIGHT_F16, 128, 3), (12, (21,), 24576, razer.WEIGHT, 16, 1), (4, (37, 20), 10272, razer.WEIGHT, 16, 3),
+    (16, (36, 20), 4096, razer.WEIGHT_F16, 128, 6), (64, (52,), 8320, razer.WEIGHT_F16, 128, 3), (12, (21,), 38528, razer.WEIGHT, 16, 1), (4, (37, 20), 10272, razer.WEIGHT, 16, 3),
     # several workgroups per unit
     (8, (16485,), 2080, razer.WEIGHT, 16, None), (40, (16485,), 2048, razer.WEIGHT, 64, None), (16, (16485,), 5248, razer.WEIGHT_F16, 128, None)])
 def test_scales_staged_by_the_workgroup(oracle, m, ns, k, fmt, block, groups):
@@ -188,3 +188,27 @@ def test_scales_staged_by_the_workgroup(oracle, m, ns, k, fmt, block, groups):
         cols = np.arange(n) if n < 300 else np.unique(np.r_[0:20, n - 37:n, np.random.default_rng(47).choice(n, size=200, replace=False)])
         y64, _ = oracle.linear((wq[0][cols], wq[1][cols], wq[2]), a_bf16=a)
         assert max_rel_err(dev_to_bf16_bits(y)[:, cols], y64) <= TOL
+
+
+@pytest.mark.parametrize("m,n,k,block,groups", [
+    # ragged rows, steps and last slices; outputs that are no multiple of 4; two and four groups per workgroup
+    (64, 37, 8192 + 96, 16, 2), (33, 100, 8192, 32, 2), (40, 1000, 11008, 16, 2), (64, 129, 9216 + 64, 64, 2), (64, 4096, 11008, 16, 2), (64, 5120, 13824, 16, 4),
+    (56, 5121, 13824, 32, 4), (20, 37, 10240 + 32, 16, 2), (32, 520, 12288, 128, 2), (17, 16, 14336, 16, 2)])
+def test_k_slices(oracle, m, n, k, block, groups):
+    """Few weight rows with long K: slices of K, their sums in the workspace; one infinite activation stays in its row."""
+    print("k slices", m, n, k, block, flush=True)
+    wq, wt = _weights(n, k, 5200 + n, razer.WEIGHT, block)
+    a = synth.activation(m, k, seed=5300 + m)
+    a_dev = bf16_bits_to_dev(a)
+    got = []
+    names = launched_kernels(lambda: got.append(razer.razer_linear(wt, a_dev)))
+    assert any("sliced_ring_kernel<%d, %d," % (16 if m > 32 else 8, groups) in x for x in names) and any("slice_reduce" in x for x in names) and len(names) == 2, names
+    cols = np.arange(n) if n < 300 else np.unique(np.r_[0:20, n - 37:n, np.random.default_rng(48).choice(n, size=200, replace=False)])
+    y64, _ = oracle.linear((wq[0][cols], wq[1][cols], wq[2]), a_bf16=a)
+    assert max_rel_err(dev_to_bf16_bits(got[0])[:, cols], y64) <= TOL
+    a_dev[2, k - 3] = float("inf")
+    z = razer.razer_linear(wt, a_dev).float().cpu()
+    wc = torch.from_numpy(oracle.dequant(oracle.WEIGHT, wq[0][cols], wq[1][cols], wq[2])["f32"])[:, k - 3].float()
+    assert bool((z[2][torch.from_numpy(cols)[wc != 0]] == torch.sign(wc[wc != 0]) * float("inf")).all())
+    others = [i for i in range(m) if i != 2]
+    assert torch.equal(z[others], got[0].float().cpu()[others])
