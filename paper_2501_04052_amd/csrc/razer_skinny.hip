@@ -130,6 +130,7 @@ struct RingArgs {
     int64_t k, m;
     const uint16_t* a;
     int chunk, lb;
+    uint32_t waves;                                                   // of a workgroup (a field: the hidden argument lies in a line of its own)
     float* partial;                                                   // K-slices: [slice][m][n] sums, steps per slice
     uint32_t slice_steps;
 };
@@ -148,6 +149,9 @@ __device__ __forceinline__ void ring_body(const RingArgs arg)
 {
     constexpr int SF = FORM & 1, H = FORM & 2 ? 1 : ring_parts<NA, W>();
     constexpr bool EARLY = SF || ST;                                  // the tensor scales
+    // All arguments in one wait (those of line 0x40 .. 0x7f, used at the end, into the scalar cache): the compiler loads them where
+    // they are first used, one cold line after the other ahead of the first copy
+    asm volatile("" ::"s"(arg.codes[0]), "s"(arg.ts[0]), "s"(arg.n[0]), "s"(arg.e[0]), "s"(arg.k), "s"(arg.m), "s"(arg.a), "s"(arg.chunk), "s"(arg.lb), "s"(arg.waves));
     const uint32_t e1 = arg.e[0], e2 = arg.e[1], e3 = arg.e[2], e4 = arg.e[3];
     const float sv0 = arg.sv0, sv1 = arg.sv1;
     const int64_t k = arg.k, m0 = (int64_t)blockIdx.y * arg.chunk, m = arg.m - m0 < arg.chunk ? arg.m - m0 : arg.chunk;
@@ -159,7 +163,7 @@ __device__ __forceinline__ void ring_body(const RingArgs arg)
     static_assert(!ST || !IL, "the interleaved layout keeps scales with the codes");
     __shared__ uint4 lut[SF ? 1 : 256];
     extern __shared__ __align__(16) uint8_t dyn_smem[];               // [waves][WAVE], ST: [G][ring_scale_region]
-    const uint32_t lane = threadIdx.x & 63u, nwaves = blockDim.x >> 6;
+    const uint32_t lane = threadIdx.x & 63u, nwaves = arg.waves;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t r = lane & 15u, g = lane >> 4;
     const uint32_t kk32 = (uint32_t)k;
@@ -301,7 +305,7 @@ __device__ __forceinline__ void ring_body(const RingArgs arg)
         }
     }
     if (!SF) {
-        for (uint32_t sb = threadIdx.x; sb < 256u; sb += blockDim.x) {
+        for (uint32_t sb = threadIdx.x; sb < 256u; sb += 64u * nwaves) {
             const v4u e = __builtin_bit_cast(v4u, sk_byte_table(sb, sv0, sv1));
             asm volatile("ds_write_b128 %0, %1" ::"v"(lut_lds + sb * 16u), "v"(e) : "memory");
         }
@@ -612,6 +616,9 @@ static hipError_t launch_ring_w(SvConfig cfg, int count, const GemvProblem* p, i
     arg.chunk = (int)ring_chunk(m);
     arg.a = a;
     arg.lb = cfg.lb;
+    arg.waves = 0;
+    arg.partial = nullptr;
+    arg.slice_steps = 0;
     // as many of the W waves as their LDS leaves room for
     constexpr uint32_t fit = (kLdsBytes - kRingTableBytes) / ring_wave_bytes<NA, G, H, false>();
     constexpr int most = fit < (uint32_t)W ? (int)fit : W;
@@ -620,6 +627,7 @@ static hipError_t launch_ring_w(SvConfig cfg, int count, const GemvProblem* p, i
     const int64_t wgs = ring_wgs<G>(count, p, m);
     const int use = NA == 16 && wgs > kComputeUnits && asked != 8 ? 4 : most;
     const int waves = nsteps < use ? (int)nsteps : use;
+    arg.waves = (uint32_t)waves;
     constexpr int FORM = SF + (H == ring_parts<NA, W>() ? 0 : 2);
     const dim3 grid((groups + G - 1) / G, (unsigned)((m + arg.chunk - 1) / arg.chunk));
     const size_t plain = (size_t)waves * ring_wave_bytes<NA, G, H, false>();
@@ -756,6 +764,7 @@ static hipError_t launch_ring_slices(SvConfig cfg, const GemvProblem& p, int64_t
         arg.codes[i] = p.codes; arg.scales[i] = p.scales; arg.ts[i] = p.ts; arg.y[i] = p.y; arg.n[i] = p.n; arg.ld_y[i] = p.ld_y; arg.e[i] = groups;
     }
     arg.sv0 = cfg.sv0; arg.sv1 = cfg.sv1; arg.k = k; arg.m = m; arg.chunk = (int)m; arg.a = a; arg.lb = cfg.lb;
+    arg.waves = W;
     arg.partial = workspace;
     arg.slice_steps = per;
     constexpr uint32_t lds = W * ring_wave_bytes<NA, G, H, false>();
