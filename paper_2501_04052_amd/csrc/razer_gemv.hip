@@ -594,6 +594,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void gemv_quad_kernel(const uint8_t
                                                                    int64_t n, int64_t k, const uint16_t* __restrict__ a,
                                                                    int64_t m, uint16_t* __restrict__ y, int64_t ld_y, int lb)
 {
+    asm volatile("" ::"s"((uint32_t)blockDim.x), "s"(codes), "s"(n), "s"(k), "s"(a), "s"(m), "s"(y), "s"(lb));   // (as below)
     gemv_quad_body<C, G, D, P, MS, PS, IL, FMT>(codes, scales, w_ts, sv0, sv1, n, k, a, m, y, ld_y,
                                                 (int64_t)blockIdx.x * (P * 4 * G), lb);
 }
@@ -609,6 +610,10 @@ __global__ __launch_bounds__(64 * kMaxWaves) void gemv_quad_grouped_kernel(
     unsigned g1, unsigned g2, unsigned g3,
     float sv0, float sv1, int64_t k, const uint16_t* __restrict__ a, int64_t m, int lb)
 {
+    // All arguments in one wait: the compiler loads the last ones and the hidden workgroup size, a cache line of its own that
+    // is cold in every launch, only after a wait for the first (2 x 11008 x 4096 at 2 rows 13.12 -> 13.01 us, at 4 14.51 -> 14.42; the
+    // M = 1 kernels, whose size lies in a line they need anyway, gain nothing)
+    asm volatile("" ::"s"((uint32_t)blockDim.x), "s"(c0), "s"(t0), "s"(n0), "s"(g1), "s"(k), "s"(a), "s"(m), "s"(lb));
     const unsigned b = blockIdx.x;
     const uint8_t* codes = c0; const uint8_t* scales = s0; const float* ts = t0; uint16_t* y = y0;
     int64_t n = n0, ld = l0;
