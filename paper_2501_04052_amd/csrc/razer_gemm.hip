@@ -674,7 +674,7 @@ __global__ __launch_bounds__(512) void gemm_pp_kernel(
 // the barrier at the end of the iteration instead, all waves of a workgroup started every K-tile
 // with an empty LDS queue at the same moment (2-4 % slower).
 //
-// KG = 2 (for problems with about one 256 x 128 tile per compute unit): eight waves as two K groups of
+// KG = 2 (about one 256 x 128 tile per compute unit and K below 2048, K-slices that are short or leave units idle): eight waves as two K groups of
 // four; group g runs the same loop over its half of the K-tiles with its own activation stages, both
 // groups meet at the same barriers, and at the end the two partial sums of every output meet through
 // LDS -- each wave finishes half of the 256 rows.  The sum of the two halves is rounded once more than

@@ -9,7 +9,8 @@
 // unit into memory that only this wave reads, so the K loop has no barrier: the wave waits for its own copies, takes
 // the operands into registers, requests its next step into the same place and multiplies while that one is on its
 // way.  Above 32 rows, and with 16 waves at 9 .. 16, the activations come in halves of 64 k (one 128-byte line per row), codes
-// and scales still a step at a time, the next step's behind this step's second half.  Partial sums of the waves meet in LDS after one barrier.  One launch, no workspace.
+// and scales still a step at a time, the next step's behind this step's second half.  Partial sums of the waves meet in LDS after one barrier.  One launch, no
+// workspace (but for the K-slices of sliced_ring_kernel).
 //
 // Why through LDS although nothing is shared: the matrix instruction wants 16 rows in 16 neighbouring lanes, and a
 // load whose neighbouring lanes lie in 16 different rows costs the address unit a cache-line lookup per lane.  Read
