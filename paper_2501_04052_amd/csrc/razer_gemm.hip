@@ -1286,7 +1286,7 @@ __device__ __forceinline__ void gemm_wide_body(
         for (int c = 0; c < L; ++c) issue_one(kt, st, c);
     };
     // Once only copies of a ragged last tile are left: its second 32 elements do not exist, the lanes that would fetch
-    // them fetch the first ones of the same row again (their weights are masked).
+    // them fetch the first ones of the same row again (their weights are masked, the activations cleared: clear_past_k).
     // (the lane number is counted again, here and at the end: no register is free to keep it through the loop)
     auto lane_again = [](uint32_t all = ~0u) { return __builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0u)); };
     auto ragged_acts = [&](int from, int to) {
@@ -1302,15 +1302,28 @@ __device__ __forceinline__ void gemm_wide_body(
             s_off[i] -= GB ? (32u * hl) >> lb : 2u * hl;
         }
     };
-    const int ragged = (k & (kBK - 1)) != 0 && kend == KT ? last : -1;
-    auto compute = [&](int kt, int st, int st_next, int st_copy) {
+    // The second half of a ragged tile's activation rows, in the rows whose copies are this wave's: weights of 0 would
+    // make a NaN of an infinity there.
+    auto clear_past_k = [&](int st) {
+        const uint32_t l = lane_again();
+        const uint32_t at = a_lds + st * A_STAGE + (8u * (uint32_t)(wn * NU_A) + l) * 128u + ((l & 8u) ? 0u : 64u);   // (chunks 4 .. 7 ^ swizzle(row))
+        const uint64_t zero = 0;
+#pragma unroll
+        for (int i = 0; i < 8 * NU_A; i += 64)
+#pragma unroll
+            for (int c = 0; c < 64; c += 8) asm volatile("ds_write_b64 %0, %1 offset:%2" ::"v"(at), "v"(zero), "n"(i * 128 + c) : "memory");
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    };
+    // ragged: one of the last four K-tiles where the last one has 32 elements (a loop of their own: the comparisons take 1 % in every K-tile)
+    auto compute = [&](auto ragged, int kt, int st, int st_next, int st_copy) {
+        constexpr bool RG = decltype(ragged)::value;
         const int kc = kt + 2 < last ? kt + 2 : last, kc1 = kt + 1 < last ? kt + 1 : last, kc3 = kt + 3 < last ? kt + 3 : last;
-        if constexpr (KG == 1) {
-            if (kt + 2 == ragged) { ragged_acts(0, NU_A); ragged_weights(); }
-        } else {
-            if (kt + 1 == ragged) ragged_acts(NU_A / 2, NU_A);
-            if (kt + 2 == ragged) ragged_acts(0, NU_A / 2);
-            if (kt + 3 == ragged) ragged_weights();
+        if constexpr (RG && KG == 1) {
+            if (kt + 2 == last) { ragged_acts(0, NU_A); ragged_weights(); }
+        } else if constexpr (RG) {
+            if (kt + 1 == last) ragged_acts(NU_A / 2, NU_A);
+            if (kt + 2 == last) ragged_acts(0, NU_A / 2);
+            if (kt + 3 == last) ragged_weights();
         }
         uint32_t wq[2][NR][4];
 #pragma unroll
@@ -1379,6 +1392,9 @@ __device__ __forceinline__ void gemm_wide_body(
                     // the barrier that tile is complete and tile kt's stage is free
                     if constexpr (KG == 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(PF) : "memory");   // (copies land in order; the newest is the prefetch)
                     else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                    if constexpr (RG) {
+                        if (kt + 1 == last) clear_past_k(st_next);
+                    }
                     __builtin_amdgcn_s_barrier();
                     asm volatile("" ::: "memory");
                     RAZER_LDS_READ128(af[nb][0], an, 4096 * 0);
@@ -1491,11 +1507,18 @@ __device__ __forceinline__ void gemm_wide_body(
         for (int c = NU_A; c < L; ++c) issue_one(kbase + 2, 0, c);
     }
     int st = 0;                                         // stage of tile kt; tile kt + S follows it into the same stage
-    for (int kt = kbase; kt < kend; ++kt) {
-        const int st_next = st == S - 1 ? 0 : st + 1;
-        compute(kt, st, st_next, st == 0 ? S - 1 : st - 1);
-        st = st_next;
-    }
+    int kt = kbase;
+    auto loop = [&](auto ragged, int stop) {
+        for (; kt < stop; ++kt) {
+            const int st_next = st == S - 1 ? 0 : st + 1;
+            compute(ragged, kt, st, st_next, st == 0 ? S - 1 : st - 1);
+            st = st_next;
+        }
+    };
+    // (from the start of a line of the instruction cache: elsewhere 2 x 11008 x 4096 at 512 rows takes up to 1 % longer)
+    asm volatile(".p2align 6");
+    loop(std::false_type{}, (k & (kBK - 1)) != 0 && kend == KT ? last - 3 : kend);
+    loop(std::true_type{}, kend);
     // a group with one K-tile less meets the other at its last barrier
     if (KG == 2 && kend < kmeet) __builtin_amdgcn_s_barrier();
     // copies and fragment reads requested for tiles past the end: let them finish before the registers

@@ -136,3 +136,39 @@ def test_half_tiles(oracle, m, ns, k, block, kernel):
         assert bool((z[2][hit] == torch.sign(wc[wc != 0]) * float("inf")).all())
         others = [i for i in range(m) if i != 2]
         assert bool((z[others] == y[others]).all())
+
+
+@pytest.mark.parametrize("m,ns,k,block,kernel", [
+    # half tiles (16 and 17 K-tiles per group, the second group's last one ragged), whole ones, a launch of both
+    (300, (12300,), 2080, 16, "gemm_halves_kernel<false>"), (257, (12164,), 2144, 32, "gemm_halves_kernel<true>"), (300, (6200, 36, 6000), 2080, 16, "gemm_halves_grouped_kernel<false>"),
+    (257, (16640,), 2080, 16, "gemm_wide_kernel<false>"), (513, (22100,), 2080, 32, "gemm_wide_kernel<true>"), (300, (20000, 13000), 2144, 16, "gemm_wide_grouped_kernel<false>")])
+def test_infinities_in_rows_that_end_inside_a_k_tile(oracle, m, ns, k, block, kernel):
+    """The last K-tile has 32 elements, and what stands in the place of the others may not be anything that a weight of 0
+    makes a NaN of: a row with one infinity, at either end of the row or of a K-tile, is infinite wherever that weight is not 0."""
+    rng = np.random.default_rng(m + sum(ns) + k)
+    a = torch.from_numpy(synth.bf16_bits_to_f32(synth.activation(m, k, seed=9400 + m))).to(torch.bfloat16).cuda()
+    end = k // 64 * 64
+    columns = {row: c for row, c in zip((0, 3, 6, 9, 12, 15, m - 5, m - 3, m - 1), (0, 7, 31, 32, 63, end - 1, end, k - 8, k - 1)) if 0 <= c < k}
+    print("infinities", m, ns, k, block, flush=True)
+    ws = [(rng.integers(0, 256, size=(n, k // 2), dtype=np.uint8), rng.integers(0, 256, size=(n, k // block), dtype=np.uint8), np.float32(2.0 ** -9)) for n in ns]
+    wts = [razer.RazerTensor.from_host(*wq, razer.WEIGHT, (5.0, 8.0)) for wq in ws]
+    call = lambda: [razer.razer_linear(wts[0], a)] if len(ns) == 1 else razer.razer_linear_grouped(wts, a)  # noqa: E731
+    got = []
+    razer.razer_tune_force(binding.TUNE_GEMM_SLICES, (1,))       # (keeps the call off the small-batch kernel)
+    try:
+        plain = call()
+        for row, column in columns.items():
+            a[row, column] = float("inf") if row % 2 else -float("inf")
+        names = launched_kernels(lambda: got.extend(call()))
+    finally:
+        razer.razer_tune_force(binding.TUNE_GEMM_SLICES, None)
+    assert any(kernel in x for x in names), names
+    others = [i for i in range(m) if i not in columns]
+    for wq, y, z in zip(ws, plain, got):
+        sample = np.arange(len(wq[0])) if len(wq[0]) < 300 else np.unique(np.r_[0:40, 120:136, len(wq[0]) - 140:len(wq[0]), rng.choice(len(wq[0]), size=60, replace=False)])
+        w = torch.from_numpy(oracle.dequant(oracle.WEIGHT, wq[0][sample], wq[1][sample], wq[2])["f32"])
+        y, z = y.float().cpu()[:, sample], z.float().cpu()[:, sample]
+        for row, column in columns.items():
+            hit = w[:, column] != 0
+            assert torch.equal(z[row][hit], torch.sign(w[hit, column]) * (float("inf") if row % 2 else -float("inf"))), (row, column)
+        assert torch.equal(z[others], y[others])
