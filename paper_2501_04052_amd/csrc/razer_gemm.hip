@@ -756,6 +756,7 @@ __device__ __forceinline__ void gemm_rb_body(
         a_chunk[i] = c;
         a_src[i] = (row < rows_here ? row : rows_here - 1) * row_bytes + c * 16u;
     }
+    const uint32_t a_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)As + kg * S * A_STAGE;
     // all copies of K-tile kt into stage st (kt already clamped to the last tile by the caller)
     auto issue = [&](int kt, int st) {
         if ((int64_t)(kt + 1) * kBK <= k) {             // a full K-tile (uniform): scalar base + constant lane offsets
@@ -778,13 +779,21 @@ __device__ __forceinline__ void gemm_rb_body(
                     (__attribute__((address_space(3))) void*)(Bs + st * B_STAGE + B_CODES + wave * 256), 2, 0, 0);
             return;
         }
+        uint32_t clear = lane * 16;
+        uint64_t zero;
+        asm volatile("v_mov_b64 %1, 0" : "+v"(clear), "=v"(zero));                      // (not kept through the loop)
+        clear += a_lds + st * A_STAGE + wn * NU_A * 1024;
 #pragma unroll
         for (int i = 0; i < NU_A; ++i) {
             const uint32_t kk = (uint32_t)kt * kBK + a_chunk[i] * 8u;
-            const uint32_t off = kk < (uint32_t)k ? a_src[i] + (uint32_t)kt * (kBK * 2u) : a_src[i] - a_chunk[i] * 16u;
-            __builtin_amdgcn_global_load_lds(
-                (const __attribute__((address_space(1))) void*)(abase + off),           // past K: any finite data
-                (__attribute__((address_space(3))) void*)(As + (kg * S + st) * A_STAGE + (wn * NU_A + i) * 1024), 16, 0, 0);
+            if (kk < (uint32_t)k) {
+                const uint32_t off = a_src[i] + (uint32_t)kt * (kBK * 2u);
+                __builtin_amdgcn_global_load_lds(
+                    (const __attribute__((address_space(1))) void*)(abase + off),
+                    (__attribute__((address_space(3))) void*)(As + (kg * S + st) * A_STAGE + (wn * NU_A + i) * 1024), 16, 0, 0);
+            } else {                                                                    // past K: 0, an infinity would meet a weight of 0
+                asm volatile("ds_write_b64 %0, %1 offset:%2\n\tds_write_b64 %0, %1 offset:%3" ::"v"(clear), "v"(zero), "n"(i * 1024), "n"(i * 1024 + 8) : "memory");
+            }
         }
         const int kc = ((int64_t)kt * kBK + 32 * h < k) ? kt : 0;                       // past K: masked where used
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(crow + 32 * kc),
@@ -806,7 +815,6 @@ __device__ __forceinline__ void gemm_rb_body(
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[0][j][v] = 0.0f;
 
-    const uint32_t a_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)As + kg * S * A_STAGE;
     const uint32_t lut_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)wlut;
     // this lane's own codes / scale bytes inside a B stage
     const uint32_t bc_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)Bs + wave * 1024 + lane * 16;
@@ -992,7 +1000,7 @@ __device__ __forceinline__ void gemm_rb_body(
         st = st_next;
     }
     // a group with one K-tile less meets the other at its last barrier (a tile of zero weights in its place would make a
-    // NaN of an infinity in the activations it re-reads)
+    // NaN of an infinity in its activations)
     if (KG == 2 && kstop < kbase + KTH) __builtin_amdgcn_s_barrier();
     // copies and fragment reads requested for tiles past the end: let them finish before the registers
     // and the stages they target are used for anything else (the fragments are named after the wait: to the
@@ -1879,9 +1887,8 @@ static GemmPlan gemm_plan(int64_t m, int64_t n, int64_t k, bool register_decode_
 // 1.01 with up to 100 workgroups, 0.97 up to 192, above that 0.93 from 100 K-tiles on (at most 1.08; 1390 x 19520 at 1865
 // rows 183 -> 156 us), 0.95 .. 0.97 up to 512 rows from 30 K-tiles on (4096 x 11008 at 512 rows 0.97), else 1.00 with up to
 // 1.15 (896 x 21376 at 1117 rows 76.6 -> 87.9).  Below 16 K-tiles it is the slower one (8: 1.05 .. 1.09).  The choice loses
-// 1 % against the faster of the two, at most 8.  Only with whole K-tiles: past K this kernel multiplies re-read activations
-// by weights of 0, a NaN where they are infinite (the LDS-staged one loads zeros), and rows that start inside a 128-byte
-// line make its copies ask for every line twice (1.01 .. 1.26 of the time).
+// 1 % against the faster of the two, at most 8.  Only with whole K-tiles: rows that start inside a 128-byte line make this
+// kernel's copies ask for every line twice (1.01 .. 1.26 of the time).
 static bool long_slices(const GemmPlan& p, int64_t m, int64_t n, int64_t k)
 {
     if (p.tile != 4 || p.split <= 1 || k > kRbMaxK || k % kBK != 0) return false;

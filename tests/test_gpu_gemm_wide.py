@@ -141,7 +141,12 @@ def test_half_tiles(oracle, m, ns, k, block, kernel):
 @pytest.mark.parametrize("m,ns,k,block,kernel", [
     # half tiles (16 and 17 K-tiles per group, the second group's last one ragged), whole ones, a launch of both
     (300, (12300,), 2080, 16, "gemm_halves_kernel<false>"), (257, (12164,), 2144, 32, "gemm_halves_kernel<true>"), (300, (6200, 36, 6000), 2080, 16, "gemm_halves_grouped_kernel<false>"),
-    (257, (16640,), 2080, 16, "gemm_wide_kernel<false>"), (513, (22100,), 2080, 32, "gemm_wide_kernel<true>"), (300, (20000, 13000), 2144, 16, "gemm_wide_grouped_kernel<false>")])
+    (257, (16640,), 2080, 16, "gemm_wide_kernel<false>"), (513, (22100,), 2080, 32, "gemm_wide_kernel<true>"), (300, (20000, 13000), 2144, 16, "gemm_wide_grouped_kernel<false>"),
+    # 32 weight rows per wave: 64, 128 and 256 activation rows per tile, two K groups, with and without K-slices, grouped
+    (64, (300,), 2080, 16, "gemm_rb_kernel<4, 2, 1, 2, false>"), (40, (300,), 96, 32, "gemm_rb_kernel<4, 2, 1, 2, true>"), (33, (130,), 32, 16, "gemm_rb_kernel<4, 2, 1, 2, false>"),
+    (128, (300,), 8224, 16, "gemm_rb_kernel<4, 2, 1, 4, false>"), (100, (300, 40), 2144, 32, "gemm_rb_grouped_kernel<4, 2, 1, 4, true>"),
+    (2040, (8200,), 1056, 16, "gemm_rb_kernel<4, 2, 1, 8, false>"), (300, (300, 40), 2080, 16, "gemm_rb_grouped_kernel<4, 2, 1, 8, false>"),
+    (2000, (4090,), 1056, 16, "gemm_rb_kernel<8, 2, 2, 8, false>"), (2000, (4090,), 1120, 32, "gemm_rb_kernel<8, 2, 2, 8, true>"), (2000, (2040, 2044), 1056, 16, "gemm_rb_grouped_kernel<8, 2, 2, 8, false>")])
 def test_infinities_in_rows_that_end_inside_a_k_tile(oracle, m, ns, k, block, kernel):
     """The last K-tile has 32 elements, and what stands in the place of the others may not be anything that a weight of 0
     makes a NaN of: a row with one infinity, at either end of the row or of a K-tile, is infinite wherever that weight is not 0."""
