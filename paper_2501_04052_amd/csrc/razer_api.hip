@@ -312,9 +312,9 @@ razer_status razer_linear(const razer_tensor* w, const void* a_bf16, const razer
                                 nullptr, nullptr, m, (uint16_t*)y_bf16, ld_y, need > 0 ? (float*)workspace : nullptr, st);
         }
     } else if (!a_q && m > kGemvDirectMaxM && m <= kSkinnyMaxM && k <= kSkinnyMaxK) {
-        const size_t need = skinny_workspace_bytes(n, k, m);
+        const size_t need = skinny_workspace_bytes(n, k, m);             // (checked, not written to)
         if (need > 0 && (!workspace || workspace_bytes < need || !aligned16(workspace))) return RAZER_ERR_WORKSPACE;
-        e = launch_skinny(wsv, 1, &one, k, (const uint16_t*)a_bf16, m, st, need > 0 ? (float*)workspace : nullptr, need);
+        e = launch_skinny(wsv, 1, &one, k, (const uint16_t*)a_bf16, m, st);
     } else if (!a_q && m <= kGemvDirectMaxM) {
         e = launch_gemv(wsv, w->codes, w->scales, w->tensor_scale, n, k, (const uint16_t*)a_bf16, m,
                         (uint16_t*)y_bf16, ld_y, st);

@@ -113,9 +113,9 @@ hipError_t launch_gemm(SvConfig wcfg, const uint8_t* w_codes, const uint8_t* w_s
                        float* workspace, hipStream_t st);
 
 // m >= 2: decode-once MFMA kernel (runs of up to kRingMaxM activation rows), one launch for up to 4 matrices sharing K,
-// the activation rows, the format, the block size and the special values (every n > 0, 0 < k <= kSkinnyMaxK).  No
-// workspace.
-// (17 .. 64 rows of one matrix with a workspace: long rows of few weights go in K-slices, whose sums meet there.)
+// the activation rows, the format, the block size and the special values (every n > 0, 0 < k <= kSkinnyMaxK).  Needs no
+// workspace; with one, 33 .. 64 scale-byte rows of one matrix go in K-slices where K is long and the weight rows are few, and
+// the slices' sums meet there.
 hipError_t launch_skinny(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, hipStream_t st,
                          float* workspace = nullptr, size_t workspace_bytes = 0);
 // 2..4 rows, 33..64 of the scale-byte format, and above 64: whether that kernel is faster than the 4x4x4 GEMV / the

@@ -755,10 +755,10 @@ static double ring_estimate_us(int count, const GemvProblem* p, int64_t k, int64
            (by4 ? 2.2 : 2.5) * values;
 }
 
-template <int NA, int G, bool GB>
+template <int G, bool GB>
 static hipError_t launch_ring_slices(SvConfig cfg, const GemvProblem& p, int64_t k, const uint16_t* a, int64_t m, int slices, float* workspace, hipStream_t st)
 {
-    constexpr int W = kRingWaves, H = ring_parts<NA, W>();
+    constexpr int NA = 16, W = kRingWaves, H = ring_parts<NA, W>();
     const uint32_t groups = (uint32_t)((p.n + 15) / 16), steps = (uint32_t)((k + 127) / 128), per = (steps + slices - 1) / slices;
     RingArgs arg;
     for (int i = 0; i < 4; ++i) {
@@ -776,15 +776,14 @@ static hipError_t launch_ring_slices(SvConfig cfg, const GemvProblem& p, int64_t
     const hipError_t e = hipGetLastError();
     return e != hipSuccess ? e : launch_slice_reduce(workspace, p.ts, nullptr, m, p.n, slices, p.y, p.ld_y, st);
 }
-// K-slices of one matrix of 17 .. 64 rows (0: none) and the groups of weight rows per workgroup with them.  Where the weight rows
+// K-slices of one matrix of 33 .. 64 rows (0: none) and the groups of weight rows per workgroup with them.  Where the weight rows
 // are few, a workgroup of one group (16 rows) reads all the activations for them, 64 x 11008 x 2 B = 1.4 MB at what a unit's
 // load path takes, 50 bytes a clock; slices of K let it own two or four groups and read half or a quarter.  They cost the
 // sums' way through the workspace and a second launch, 3.5 us (four groups 5.6).  Times as ring_estimate_us has them (16 waves, rows of 10240
 // elements and more: 10 % more).  us, without -> with: 4096 x 11008 at 64
 // rows 21.4 -> 18.3, at 40 18.6 -> 17.0, 2048 x 8192 14.8 -> 11.8, 13.2 -> 11.3, 1024 x 8192 14.6 -> 10.8, 1000 x 11008 at 40 17.7 -> 11.9,
 // 5120 x 13824 (four groups) 27.1 -> 22.5; not taken: 4096 x 5120 at 64 rows 12.0, 12.1, 2048 x 4096 9.2, 10.2, 4096 x 8192 at 40 13.7, 14.2.
-// Up to 32 rows (whole steps, half the activations) only slices of a quarter and less of long rows: 2048 x 12288 at 32 rows 13.0 ->
-// 11.1, 1000 x 11008 at 20 11.5 -> 10.1; not taken 2048 x 8192 at 32 9.6, 10.2, 4096 x 16384 16.9, 17.5.
+// Not up to 32 rows, where callers have the promise that nothing is written to the workspace.
 static double ring_sum_us(int64_t k, int64_t m, int64_t rounds, int g)
 {
     const double row = k % 64 == 0 ? 0.0074 : 0.0131;
@@ -796,17 +795,13 @@ static int ring_slices(int64_t n, int64_t k, int64_t m, int g, size_t workspace_
     const double whole = (5.1 + ring_sum_us(k, m, (wgs + kComputeUnits - 1) / kComputeUnits, g)) * (g == 1 && k >= 10240 ? 1.1 : 1.0);
     int best = 0;
     double us = 0.98 * whole;
-    for (int sg = 2; sg <= (m > 32 ? 4 : 2); sg += 2) {
+    for (int sg = 2; sg <= 4; sg += 2) {
         int64_t s = kComputeUnits / ((groups + sg - 1) / sg);
         for (s = s < 8 ? s : 8; s >= 2; --s) {                        // every slice has a step for each wave
             const int64_t per = (steps + s - 1) / s;
             if (per >= kRingWaves && steps - (s - 1) * per >= kRingWaves && (size_t)(s * m * n) * sizeof(float) <= workspace_bytes) break;
         }
         if (s < 2) continue;
-        if (m <= 32) {
-            if (s >= 4 && k >= 10240) { best = (int)s; groups_each = sg; }
-            continue;
-        }
         const double sliced = (sg == 2 ? 8.6 : 10.7) + ring_sum_us(k, m, 1, sg) / (double)s;
         if (sliced < us) { us = sliced; best = (int)s; groups_each = sg; }
     }
@@ -825,14 +820,13 @@ static hipError_t launch_ring(SvConfig cfg, int count, const GemvProblem* p, int
     const bool shaped = t.source && t.p[0] == 2;
     if (shaped && (t.p[1] == 1 || t.p[1] == 2 || t.p[1] == 3 || (t.p[1] == 4 && !(m > 32 && cfg.f16)) || (t.p[1] == 6 && m <= 32))) g = t.p[1];
     const int asked = shaped && t.p[2] ? (t.p[2] == 16 ? 16 : 8) : t.source == 1 ? 8 : 0;
-    if (count == 1 && !cfg.f16 && !cfg.il && m > 16 && m <= kRingMaxM && !t.source && workspace) {
+    if (count == 1 && !cfg.f16 && !cfg.il && m > kSkinnyMaxM && m <= kRingMaxM && !t.source && workspace) {
         int sg = 0;
         const int slices = ring_slices(p[0].n, k, m, g, workspace_bytes, sg);
-#define RAZER_RING_SLICES(NA, G)                                                                                         \
-    (cfg.lb == 4 ? launch_ring_slices<NA, G, false>(cfg, p[0], k, a, m, slices, workspace, st)                          \
-                 : launch_ring_slices<NA, G, true>(cfg, p[0], k, a, m, slices, workspace, st))
-        if (slices && m <= 32) return RAZER_RING_SLICES(8, 2);
-        if (slices) return sg == 4 ? RAZER_RING_SLICES(16, 4) : RAZER_RING_SLICES(16, 2);
+#define RAZER_RING_SLICES(G)                                                                                             \
+    (cfg.lb == 4 ? launch_ring_slices<G, false>(cfg, p[0], k, a, m, slices, workspace, st)                              \
+                 : launch_ring_slices<G, true>(cfg, p[0], k, a, m, slices, workspace, st))
+        if (slices) return sg == 4 ? RAZER_RING_SLICES(4) : RAZER_RING_SLICES(2);
 #undef RAZER_RING_SLICES
     }
 #define RAZER_RING(NA, G)                                                                  \
@@ -923,7 +917,7 @@ bool ring_serves(SvConfig cfg, int count, const GemvProblem* p, int64_t k, int64
     return ring_groups(groups, m, false) > 1 || m * k <= 600000 || (groups > 160 && k <= (groups > 208 ? 14336 : 12288));
 }
 
-// What razer_workspace_bytes reports for 5..32 activation rows.  The kernel above needs none; callers size and pass
+// What razer_workspace_bytes reports for 5..32 activation rows.  The kernel above writes nothing there; callers size and pass
 // what these functions have always asked for, and a smaller workspace is refused as before, so the rule stays: the
 // K-slices of 512 or 1024 elements ([slices][m][rows] fp32) unless the launch shape on record keeps K inside the
 // workgroup.

@@ -193,7 +193,7 @@ def test_scales_staged_by_the_workgroup(oracle, m, ns, k, fmt, block, groups):
 @pytest.mark.parametrize("m,n,k,block,groups", [
     # ragged rows, steps and last slices; outputs that are no multiple of 4; two and four groups per workgroup
     (64, 37, 8192 + 96, 16, 2), (33, 100, 8192, 32, 2), (40, 1000, 11008, 16, 2), (64, 129, 9216 + 64, 64, 2), (64, 4096, 11008, 16, 2), (64, 5120, 13824, 16, 4),
-    (56, 5121, 13824, 32, 4), (20, 37, 10240 + 32, 16, 2), (32, 520, 12288, 128, 2), (17, 16, 14336, 16, 2)])
+    (56, 5121, 13824, 32, 4)])
 def test_k_slices(oracle, m, n, k, block, groups):
     """Few weight rows with long K: slices of K, their sums in the workspace; one infinite activation stays in its row."""
     print("k slices", m, n, k, block, flush=True)
@@ -202,7 +202,7 @@ def test_k_slices(oracle, m, n, k, block, groups):
     a_dev = bf16_bits_to_dev(a)
     got = []
     names = launched_kernels(lambda: got.append(razer.razer_linear(wt, a_dev)))
-    assert any("sliced_ring_kernel<%d, %d," % (16 if m > 32 else 8, groups) in x for x in names) and any("slice_reduce" in x for x in names) and len(names) == 2, names
+    assert any("sliced_ring_kernel<16, %d," % groups in x for x in names) and any("slice_reduce" in x for x in names) and len(names) == 2, names
     cols = np.arange(n) if n < 300 else np.unique(np.r_[0:20, n - 37:n, np.random.default_rng(48).choice(n, size=200, replace=False)])
     y64, _ = oracle.linear((wq[0][cols], wq[1][cols], wq[2]), a_bf16=a)
     assert max_rel_err(dev_to_bf16_bits(got[0])[:, cols], y64) <= TOL
@@ -212,3 +212,16 @@ def test_k_slices(oracle, m, n, k, block, groups):
     assert bool((z[2][torch.from_numpy(cols)[wc != 0]] == torch.sign(wc[wc != 0]) * float("inf")).all())
     others = [i for i in range(m) if i != 2]
     assert torch.equal(z[others], got[0].float().cpu()[others])
+
+
+@pytest.mark.parametrize("m,n,k,block", [(32, 2048, 12288, 16), (17, 16, 14336, 16), (20, 1000, 11008, 16), (24, 520, 12288, 128), (16, 300, 16384, 16), (5, 4096, 4096, 16)])
+def test_the_workspace_is_not_written_up_to_32_rows(m, n, k, block):
+    """It is asked for and checked, but calls that overlap may share it and its bytes are the caller's."""
+    print("workspace", m, n, k, block, flush=True)
+    _, wt = _weights(n, k, 5400 + n, razer.WEIGHT, block)
+    a_dev = bf16_bits_to_dev(synth.activation(m, k, seed=5500 + m))
+    ws = torch.full((max(razer.razer_workspace_bytes(binding.OP_LINEAR, n, k, m), 16),), 0xA5, dtype=torch.uint8, device="cuda")
+    razer.razer_linear(wt, a_dev, workspace=ws)
+    out = torch.empty((m, n), dtype=torch.bfloat16, device="cuda")
+    razer.prepare_linear(wt, a_dev, out, workspace=ws)()
+    assert bool((ws == 0xA5).all())
