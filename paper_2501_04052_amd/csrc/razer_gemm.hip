@@ -1606,22 +1606,24 @@ __device__ __forceinline__ void pair_tile(uint32_t tile, int tiles_m, int tiles_
     tile_m = (int)(2u * pair + (in & two));
 }
 
-// The grid's first `whole` workgroups compute a 256 x 256 tile each, the others half a tile, 256 x 128 with two K groups (the
-// tiles of a last round that is at most half full, launch_wide).
+// The workgroups of the first `whole_n` columns of tiles compute a 256 x 256 tile each, those of the others half a tile, 256 x
+// 128 with two K groups (the tiles of a last round that is at most half full, launch_wide).  Whole columns, so that what an
+// activation row gives does not depend on its place: the two kinds of tile add up K in different orders.
 template <bool GB>
 __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(
     const uint8_t* __restrict__ w_codes, const uint8_t* __restrict__ w_scales, const float* __restrict__ w_ts,
     float sv0, float sv1, int64_t n, int64_t k, const uint16_t* __restrict__ a, int64_t m,
-    uint16_t* __restrict__ y, int64_t ld_y, int tiles_m, int tiles_n, int whole, int lb)
+    uint16_t* __restrict__ y, int64_t ld_y, int tiles_m, int tiles_n, int whole_n, int lb)
 {
     int tile_m, tile_n;
-    if ((int)blockIdx.x < whole) {
-        pair_tile(xcd_order(blockIdx.x, whole), tiles_m, tiles_n, tile_m, tile_n);
+    const uint32_t whole = (uint32_t)tiles_m * (uint32_t)whole_n;
+    if (blockIdx.x < whole) {
+        pair_tile(xcd_order(blockIdx.x, whole), tiles_m, whole_n, tile_m, tile_n);
         gemm_wide_body<GB>(w_codes, w_scales, w_ts, sv0, sv1, n, k, a, m, y, ld_y, tile_m, tile_n, lb);
     } else {
         const uint32_t h = xcd_order(blockIdx.x - whole, gridDim.x - whole);
-        pair_tile(whole + (h >> 1), tiles_m, tiles_n, tile_m, tile_n);
-        gemm_wide_body<GB, 2>(w_codes, w_scales, w_ts, sv0, sv1, n, k, a, m, y, ld_y, tile_m, 2 * tile_n + (int)(h & 1u), lb);
+        pair_tile(h >> 1, tiles_m, tiles_n - whole_n, tile_m, tile_n);
+        gemm_wide_body<GB, 2>(w_codes, w_scales, w_ts, sv0, sv1, n, k, a, m, y, ld_y, tile_m, 2 * (whole_n + tile_n) + (int)(h & 1u), lb);
     }
 }
 // 256 x 128 tiles with two K groups throughout; grid and slices as gemm_rb_kernel.
@@ -1653,16 +1655,18 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_grouped_kernel(
     int64_t n0, int64_t n1, int64_t n2, int64_t n3,
     int64_t l0, int64_t l1, int64_t l2, int64_t l3,
     int t1, int t2, int t3,
-    float sv0, float sv1, int64_t k, const uint16_t* __restrict__ a, int64_t m, int tiles_m, int tiles_n, int whole, int lb)
+    float sv0, float sv1, int64_t k, const uint16_t* __restrict__ a, int64_t m, int tiles_m, int tiles_n, int whole_n, int lb)
 {
     int tile_m, t;
-    if ((int)blockIdx.x < whole) {
-        pair_tile(xcd_order(blockIdx.x, whole), tiles_m, tiles_n, tile_m, t);
+    const uint32_t whole = (uint32_t)tiles_m * (uint32_t)whole_n;
+    if (blockIdx.x < whole) {
+        pair_tile(xcd_order(blockIdx.x, whole), tiles_m, whole_n, tile_m, t);
         RAZER_WIDE_PICK(t)
         gemm_wide_body<GB>(codes, scales, ts, sv0, sv1, n, k, a, m, y, ld, tile_m, t - first, lb);
     } else {
         const uint32_t h = xcd_order(blockIdx.x - whole, gridDim.x - whole);
-        pair_tile(whole + (h >> 1), tiles_m, tiles_n, tile_m, t);
+        pair_tile(h >> 1, tiles_m, tiles_n - whole_n, tile_m, t);
+        t += whole_n;
         RAZER_WIDE_PICK(t)
         gemm_wide_body<GB, 2>(codes, scales, ts, sv0, sv1, n, k, a, m, y, ld, tile_m, 2 * (t - first) + (int)(h & 1u), lb);
     }
@@ -1685,12 +1689,15 @@ __global__ __launch_bounds__(256, 1) void gemm_halves_grouped_kernel(
 }
 #undef RAZER_WIDE_PICK
 
-// Of the tiles of a launch of 256 x 256 tiles, those computed whole: all but a last round of at most half the compute units,
-// whose tiles are cut in two.
-static int64_t whole_tiles(int64_t t256)
+// Of the columns of a launch of 256 x 256 tiles, those computed whole: all but the fewest that hold a last round of at most
+// half the compute units, whose tiles are cut in two.  Tiles of the round before that go with them leave as many units free,
+// which take two halves each (0.6 of a whole tile's time) by the end of the last round.  Each XCD gets every eighth workgroup and has
+// to do with its own 32 units: where its halves are more than that nothing is cut (2900 x 8192 x 4096, 132 tiles in 11 columns,
+// 4 of them of the round before: 247 us, 199 on the 128-wide tiles).
+static int64_t whole_columns(int64_t tiles_m, int64_t tiles_n)
 {
-    const int64_t last = t256 % kComputeUnits;
-    return last <= kComputeUnits / 2 ? t256 - last : t256;
+    const int64_t last = tiles_m * tiles_n % kComputeUnits, columns = (last + tiles_m - 1) / tiles_m, cut = columns * tiles_m;
+    return (2 * cut + 7) / 8 <= kComputeUnits / 8 + (cut - last) / 8 ? tiles_n - columns : tiles_n;
 }
 template <bool GB>
 static hipError_t launch_wide(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, hipStream_t st)
@@ -1703,18 +1710,18 @@ static hipError_t launch_wide(SvConfig cfg, int count, const GemvProblem* p, int
         q[i] = p[i < count ? i : count - 1];
         t[i + 1] = t[i] + (i < count ? (int)((q[i].n + 255) / 256) : 0);
     }
-    const int64_t tiles = (int64_t)tiles_m * t[4], whole = whole_tiles(tiles);
-    const dim3 grid((unsigned)(whole + 2 * (tiles - whole)));
+    const int64_t whole_n = whole_columns(tiles_m, t[4]);
+    const dim3 grid((unsigned)(tiles_m * (2 * t[4] - whole_n)));
     if (count == 1) {
         auto kern = gemm_wide_kernel<GB>;
         RAZER_RAISE_LDS_LIMIT(kern, kMixedLds);
-        launch(kern, grid, dim3(256), kMixedLds, st, q[0].codes, q[0].scales, q[0].ts, cfg.sv0, cfg.sv1, q[0].n, k, a, m, q[0].y, q[0].ld_y, tiles_m, t[4], (int)whole, cfg.lb);
+        launch(kern, grid, dim3(256), kMixedLds, st, q[0].codes, q[0].scales, q[0].ts, cfg.sv0, cfg.sv1, q[0].n, k, a, m, q[0].y, q[0].ld_y, tiles_m, t[4], (int)whole_n, cfg.lb);
     } else {
         auto kern = gemm_wide_grouped_kernel<GB>;
         RAZER_RAISE_LDS_LIMIT(kern, kMixedLds);
         launch(kern, grid, dim3(256), kMixedLds, st, q[0].codes, q[1].codes, q[2].codes, q[3].codes, q[0].scales, q[1].scales, q[2].scales, q[3].scales, q[0].ts,
             q[1].ts, q[2].ts, q[3].ts, q[0].y, q[1].y, q[2].y, q[3].y, q[0].n, q[1].n, q[2].n, q[3].n, q[0].ld_y,
-            q[1].ld_y, q[2].ld_y, q[3].ld_y, t[1], t[2], t[3], cfg.sv0, cfg.sv1, k, a, m, tiles_m, t[4], (int)whole, cfg.lb);
+            q[1].ld_y, q[2].ld_y, q[3].ld_y, t[1], t[2], t[3], cfg.sv0, cfg.sv1, k, a, m, tiles_m, t[4], (int)whole_n, cfg.lb);
     }
     return hipGetLastError();
 }
@@ -1833,17 +1840,17 @@ static int rb_split(int64_t tiles, int64_t kt_all, int64_t m = 0, int64_t rows =
 // (2.0), one that is at most half full 0.78 (1.4).  128-wide -> wide with halves (us): {q,k,v} 3 x 4096 x 4096 at 2048 rows 203 ->
 // 190, 2 x 11008 x 4096 at 1024 194 -> 177, 13824 x 5120 at 1500 236 -> 216, 9216 x 3072 at 2048 143 -> 133, 17000 x 2048 at 1024
 // 97.9 -> 95.0; whole tiles only: 2 x 11008 x 4096 at 512 rows 120 -> 101, at 2048 380 -> 348.
-static double wide_rounds(int64_t t256)
+static double wide_rounds(int64_t tiles_m, int64_t t256)
 {
-    const int64_t last = t256 % kComputeUnits;
-    return (double)(t256 / kComputeUnits) + (last == 0 ? 0.0 : last <= kComputeUnits / 2 ? 0.6 : 1.0);
+    const int64_t last = t256 % kComputeUnits, tiles_n = t256 / tiles_m;
+    return (double)(t256 / kComputeUnits) + (last == 0 ? 0.0 : whole_columns(tiles_m, tiles_n) < tiles_n ? 0.6 : 1.0);
 }
-static bool wide_tiles(int64_t t256, int64_t t128, int64_t k)
+static bool wide_tiles(int64_t tiles_m, int64_t t256, int64_t t128, int64_t k)
 {
     if (k < 2048 || t128 <= 256 || t256 <= kComputeUnits / 2) return false;
     if (t128 < 512) return true;                        // (one round of whole tiles; else K-slices)
     const int64_t last = t128 % 512;
-    return wide_rounds(t256) <= 1.11 * (double)(t128 / 512) + (last == 0 ? 0.0 : last <= 256 ? 0.78 : 1.11);
+    return wide_rounds(tiles_m, t256) <= 1.11 * (double)(t128 / 512) + (last == 0 ? 0.0 : last <= 256 ? 0.78 : 1.11);
 }
 static GemmPlan gemm_plan(int64_t m, int64_t n, int64_t k, bool register_decode_ok)
 {
@@ -1858,7 +1865,7 @@ static GemmPlan gemm_plan(int64_t m, int64_t n, int64_t k, bool register_decode_
         // 256-row activation tiles so every weight is decoded once per 256 rows
         const int64_t tm = (m + 255) / 256;
         const int64_t t256 = tm * ((n + 255) / 256), t128 = tm * ((n + 127) / 128);
-        if (register_decode_ok && wide_tiles(t256, t128, k)) return GemmPlan{5, 1};
+        if (register_decode_ok && wide_tiles(tm, t256, t128, k)) return GemmPlan{5, 1};
         // enough tiles for two resident waves per SIMD: the kernel that decodes weights in registers
         // (measured 5-28 % faster than the LDS-staged one on the 7B projection shapes from M = 2048)
         if (register_decode_ok && t128 >= 512) return GemmPlan{6, 1};
@@ -1975,7 +1982,7 @@ static int grouped_tile_width(int count, const GemvProblem* p, int64_t m, int64_
         t256 += tm * ((p[i].n + 255) / 256);
         t128 += tm * ((p[i].n + 127) / 128);
     }
-    if (wide_tiles(t256, t128, k)) return 256;
+    if (wide_tiles(tm, t256, t128, k)) return 256;
     if (t128 >= 512) return 128;
     if (t128 >= 192 && t128 <= 256 && k >= 16 * kBK) return 129;
     return 8;                                           // fewer tiles, or between one and two rounds: K-slices
@@ -2052,7 +2059,7 @@ double gemm_estimate_us(int count, const GemvProblem* p, int64_t m, int64_t k)
         default: t = Terms{8.0, 0.86, 0.05, 0.065, 5.0, 1.6, 0.0, 0.0, 2.1}; break;   // 11: the grouped launch's K-slices
     }
     const int64_t units = q.tile == 6 ? 2 * kComputeUnits : kComputeUnits;
-    const double rounds = q.tile == 5 ? wide_rounds(t256 * tm) : (double)((wgs + units - 1) / units);
+    const double rounds = q.tile == 5 ? wide_rounds(tm, t256 * tm) : (double)((wgs + units - 1) / units);
     const double us = t.start + per * (t.tile * rounds + t.fill * full + t.off_line * off_line * rounds);
     return slices > 1 ? us + t.meet + (t.sums + (by4 ? 0.0 : t.sums_by_one)) * sums : us + (t.out + (by8 ? 0.0 : t.out_by_one)) * values;
 }
