@@ -440,8 +440,12 @@ razer_status razer_linear_grouped(const razer_tensor* const* w, int32_t count, c
         case GEMV: e = launch_gemv_grouped(sv0, count, p, k, (const uint16_t*)a_bf16, m, st); break;
         case SKINNY: e = launch_skinny(sv0, count, p, k, (const uint16_t*)a_bf16, m, st); break;
         case GEMM:
-            if (ring_serves(sv0, count, p, k, m)) e = launch_skinny(sv0, count, p, k, (const uint16_t*)a_bf16, m, st);
-            else e = launch_gemm_grouped(sv0, count, p, k, (const uint16_t*)a_bf16, m, (float*)workspace, st);
+            if (ring_serves(sv0, count, p, k, m)) {
+                // a group of one matrix is the single call: K-slices under the same conditions
+                const size_t need = count == 1 && workspace && aligned16(workspace) ? gemm_workspace_bytes(p[0].n, k, m) : 0;
+                const bool room = need > 0 && workspace_bytes >= need;
+                e = launch_skinny(sv0, count, p, k, (const uint16_t*)a_bf16, m, st, room ? (float*)workspace : nullptr, need);
+            } else e = launch_gemm_grouped(sv0, count, p, k, (const uint16_t*)a_bf16, m, (float*)workspace, st);
             break;
         case SEQUENCE:
             for (int i = 0; i < count; ++i) {

@@ -225,3 +225,16 @@ def test_the_workspace_is_not_written_up_to_32_rows(m, n, k, block):
     out = torch.empty((m, n), dtype=torch.bfloat16, device="cuda")
     razer.prepare_linear(wt, a_dev, out, workspace=ws)()
     assert bool((ws == 0xA5).all())
+
+
+@pytest.mark.parametrize("m,n,k,block", [(64, 4096, 11008, 16), (40, 1000, 11008, 32), (64, 5120, 13824, 16), (33, 100, 8192, 16), (32, 2048, 12288, 16), (17, 16, 14336, 16), (64, 4096, 4096, 16),
+                                         (64, 1000, 16384, 16), (100, 2048, 4096, 16)])
+def test_a_group_of_one_matrix_is_the_single_call(m, n, k, block):
+    """Up to 128 rows the same kernels, launched alike: the same bits."""
+    print("group of one", m, n, k, block, flush=True)
+    _, wt = _weights(n, k, 5600 + n, razer.WEIGHT, block)
+    a_dev = bf16_bits_to_dev(synth.activation(m, k, seed=5700 + m))
+    one, group = [], []
+    single = launched_kernels(lambda: one.append(razer.razer_linear(wt, a_dev)))
+    grouped = launched_kernels(lambda: group.extend(razer.razer_linear_grouped([wt], a_dev)))
+    assert torch.equal(one[0], group[0]), (single, grouped)
