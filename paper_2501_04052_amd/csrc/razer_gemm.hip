@@ -1159,7 +1159,8 @@ __device__ __forceinline__ void gemm_wide_body(
     const int64_t m0 = (int64_t)tile_m * BM, n0 = (int64_t)tile_n * BN;
     const int KT = (int)((k + kBK - 1) / kBK);
     // This wave's K-tiles kbase .. kend - 1: all of them or, with two groups, its half of this workgroup's slice (where
-    // their number is odd the second group has one less).  At least 8, so the first ones are full.
+    // their number is odd the second group has one less).  At least four: the copies ahead of the loop are of the first
+    // three, which are full, and a ragged last one is met by the last four.
     int kbase = 0, kend = KT, kmeet = 0;
     if constexpr (KG == 2) {
         const int kt0 = kslice * kt_per_slice, kt1 = KT - kt0 < kt_per_slice ? KT : kt0 + kt_per_slice;
@@ -1702,7 +1703,7 @@ static int64_t whole_columns(int64_t tiles_m, int64_t tiles_n)
 template <bool GB>
 static hipError_t launch_wide(SvConfig cfg, int count, const GemvProblem* p, int64_t k, const uint16_t* a, int64_t m, hipStream_t st)
 {
-    if (k < 2048) return hipErrorInvalidValue;          // (never asked for)
+    if (k < 2048) return hipErrorInvalidValue;          // four K-tiles per group and more (never asked for)
     const int tiles_m = (int)((m + 255) / 256);
     GemvProblem q[4];
     int t[5] = {0, 0, 0, 0, 0};
@@ -1734,7 +1735,7 @@ static hipError_t launch_halves(SvConfig cfg, int count, const GemvProblem* p, i
     if (!workspace || count > 1) split = 1;
     const int kt_all = (int)((k + kBK - 1) / kBK), kt_per = (kt_all + split - 1) / split;
     const int slices = (kt_all + kt_per - 1) / kt_per;
-    if (kt_all - (slices - 1) * kt_per < 8) return hipErrorInvalidValue;   // four K-tiles per group, for the copies ahead of the loop (never asked for)
+    if (kt_all - (slices - 1) * kt_per < 8) return hipErrorInvalidValue;   // four K-tiles per group (never asked for)
     const int tiles_m = (int)((m + 255) / 256);
     GemvProblem q[4];
     int t[5] = {0, 0, 0, 0, 0};
@@ -1905,11 +1906,11 @@ static bool long_slices(const GemmPlan& p, int64_t m, int64_t n, int64_t k)
 // Which of the two kernels with two K groups takes long slices: with 64 weight rows per wave where the chip is full and the
 // slices outlast the longer start (us, 32 -> 64): 4096 x 11008 at 512 rows (256 workgroups, 43 K-tiles) 70.9 -> 66.0, 5120 x
 // 13824 (240, 72) 100.9 -> 91.7, 1390 x 19520 at 1390 (198, 102) 137 -> 128; 1664 x 15360 at 512 (208, 30) 49.2 -> 48.6, 520 x 21568 at 257
-// (80, 43) 34.9, 34.9.  The last slice holds eight K-tiles or more.
+// (80, 43) 34.9, 34.9.
 static int slices_tile(const GemmPlan& p, int64_t m, int64_t n, int64_t k)
 {
     const int64_t kt_all = k / kBK, per = (kt_all + p.split - 1) / p.split, slices = (kt_all + per - 1) / per;
-    return per >= 40 && (m + 255) / 256 * ((n + 127) / 128) * slices > 192 && kt_all - (slices - 1) * per >= 8 ? 13 : 10;
+    return per >= 40 && (m + 255) / 256 * ((n + 127) / 128) * slices > 192 ? 13 : 10;
 }
 
 size_t gemm_workspace_bytes(int64_t n, int64_t k, int64_t m)
