@@ -110,40 +110,56 @@ def test_registers_of_lds_reads_are_left_alone_until_their_wait():
 
 def _copies_before_counted_wait(lines):
     """What stands between a full wait for copies and the next counted one, in the order of issue: a = 16-byte copy, s =
-    scale copy (1 or 2 bytes), | = branch."""
-    seq, found = "", []
+    scale copy (1 or 2 bytes), p = 4-byte copy (a prefetch), | = branch.  A full wait with no copy between it and the counted
+    one is the one in its place when nothing follows."""
+    seq, before, found = "", "", []
     for line in lines:
         op = line.split(";")[0].strip()
         if op.startswith("global_load_lds"):
-            seq += "a" if op.startswith("global_load_lds_dwordx4") else "s"
+            seq += {"x4": "a", "rd": "p"}.get(op.split()[0][-2:], "s")
         elif op.startswith(("s_cbranch", "s_branch")):
             seq += "" if seq.endswith("|") else "|"
         elif op.startswith("s_waitcnt") and "vmcnt" in op:
             n = int(re.search(r"vmcnt\((\d+)\)", op).group(1))
             if n:
-                found.append((n, seq))
-            elif not seq.strip("|").endswith("s") or not seq.strip("|"):      # (the wait in place of the counted one when nothing follows)
-                seq = ""
+                found.append((n, seq if seq.strip("|") else before))
+            else:
+                before, seq = (seq if seq.strip("|") else before), ""
     return found
 
 
 def test_small_batch_kernel_counts_the_copies_it_may_leave():
-    """With activations in halves the wait ahead of the second half leaves the newest 2 G copies in flight.  Copies land in
-    the order of their issue, so these must be the next step's G codes and G scales and every activation copy must stand
-    before them."""
-    kernels = 0
-    for m in re.finditer(r"^(_ZN5razer11ring_kernelILi(\d+)ELi(\d)ELb[01]ELi[01]ELi(\d+)ELb[01]EE\S*):[^\n]*\n(.*?)^\.Lfunc_end", _asm("razer_skinny.hip"), re.S | re.M):
-        na, g, waves = int(m.group(2)), int(m.group(3)), int(m.group(4))
+    """With activations in halves the wait ahead of the second half leaves the newest 2 G copies in flight (G where the
+    workgroup staged the scales).  Copies land in the order of their issue, so these must be the next step's G codes and G
+    scales and every activation copy must stand before them."""
+    kernels = {"": 0, "staged_": 0, "sliced_": 0}
+    for m in re.finditer(r"^(_ZN5razer\d\d(|staged_|sliced_)ring_kernelILi(\d+)ELi(\d)ELb[01]ELi[01]ELi(\d+)ELb[01]EE\S*):[^\n]*\n(.*?)^\.Lfunc_end", _asm("razer_skinny.hip"), re.S | re.M):
+        kind, na, g, waves = m.group(2), int(m.group(3)), int(m.group(4)), int(m.group(5))
         if not (na == 16 or (na == 4 and waves == 16)):              # (whole steps)
             continue
-        kernels += 1
-        assert _copies_before_counted_wait(m.group(5).split("\n")) == [(2 * g, "a" * (na // 2) + "|" + "a" * g + "s" * g + "|")], m.group(1)
-    assert kernels >= 17
+        kernels[kind] += 1
+        left = "a" * g + ("" if kind == "staged_" else "s" * g)
+        assert _copies_before_counted_wait(m.group(6).split("\n")) == [(len(left), "a" * (na // 2) + "|" + left + "|")], m.group(1)
+    assert kernels == {"": 17, "staged_": 17, "sliced_": 4}
     # the check itself: an activation copy behind the codes
     copy, scale, wait = "global_load_lds_dwordx4 v1, s[0:1]", "global_load_lds_ushort v1, s[0:1]", "s_waitcnt vmcnt(2)"
     full = ["s_waitcnt vmcnt(0)", copy, copy, "s_cbranch_scc1 .L1", copy, scale, ".L1:", "s_cbranch_scc1 .L2", "s_waitcnt vmcnt(0)", "s_cbranch_scc1 .L3", wait]
     assert _copies_before_counted_wait(full) == [(2, "aa|as|")]
     assert _copies_before_counted_wait(full[:2] + full[3:5] + [copy] + full[5:]) == [(2, "a|aas|")]
+
+
+def test_wide_gemm_counts_the_copies_it_may_leave():
+    """64 weight rows per wave.  The wait for K-tile kt + 1 leaves the newest 12 copies in flight, which must be those of tile
+    kt + 2 (eight of activations, two of codes, two of scales); with two K groups the newest one, which must be the
+    prefetch.  Each loop has one such wait: whole K-tiles, and the last ones of a row that ends inside a K-tile."""
+    kernels = 0
+    for m in re.finditer(r"^(_ZN5razer\d\dgemm_(halves|wide)\S*):[^\n]*\n(.*?)^\.Lfunc_end", _asm("razer_gemm.hip"), re.S | re.M):
+        kernels += 1
+        found = _copies_before_counted_wait(m.group(3).split("\n"))
+        assert [n for n, _ in found] == [1, 1] + [12, 12] * (m.group(2) == "wide"), (m.group(1), found)
+        for n, seq in found:
+            assert re.search(r"a{8}p$" if n == 1 else r"a{10}ss$", seq), (m.group(1), n, seq)
+    assert kernels == 8
 
 
 def test_no_scratch_no_dispatch_packet():
