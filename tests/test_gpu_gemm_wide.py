@@ -116,7 +116,7 @@ def test_half_tiles(oracle, m, ns, k, block, kernel):
     a_dev = bf16_bits_to_dev(a)
     call = lambda: [razer.razer_linear(ws[0][1], a_dev)] if len(ns) == 1 else razer.razer_linear_grouped([w[1] for w in ws], a_dev)  # noqa: E731
     plain, got = [], []
-    column = (k // 64 - 1) * 64 - 7                              # (in the last whole K-tile but one or before it)
+    column = k - 7                                               # (in the last K-tile, whole or not)
     razer.razer_tune_force(binding.TUNE_GEMM_SLICES, (1,))       # (keeps the call off the small-batch kernel)
     try:
         names = launched_kernels(lambda: plain.extend(call()))
@@ -197,3 +197,36 @@ def test_equal_rows_of_a_call_have_equal_results(m, ns, k, kernel):
     assert any(kernel in x for x in names), names
     for y in got:
         assert torch.equal(y, y[:1].expand_as(y))
+
+
+@pytest.mark.parametrize("m,n,k,kernel", [(300, 12300, 2080, "gemm_halves_kernel"), (513, 22100, 2048, "gemm_wide_kernel"), (512, 4100, 11008, "gemm_halves_kernel"), (300, 32803, 2048, "gemm_wide_kernel")])
+def test_half_tiles_into_any_output(oracle, m, n, k, kernel):
+    """Rows of the output further apart than N, one that starts 2 bytes behind a 16-byte boundary, the entry without a
+    workspace argument, activations in their own format: the same sums."""
+    rng = np.random.default_rng(m + n + k)
+    wq = (rng.integers(0, 256, size=(n, k // 2), dtype=np.uint8), rng.integers(0, 256, size=(n, k // 16), dtype=np.uint8), np.float32(2.0 ** -9))
+    w = razer.RazerTensor.from_host(*wq, razer.WEIGHT, (5.0, 8.0))
+    a_dev = bf16_bits_to_dev(synth.activation(m, k, seed=9600 + m))
+    print("half tiles, outputs", m, n, k, flush=True)
+    razer.razer_tune_force(binding.TUNE_GEMM_SLICES, (1,))       # (keeps the call off the small-batch kernel)
+    try:
+        want = razer.razer_linear(w, a_dev)
+        ld = (n + 11) // 8 * 8
+        for ld_y, offset in ((ld, 0), (ld + 3, 0), (ld, 1), (ld + 4, 4)):
+            buf = torch.full((m * ld_y + 8,), 7.0, dtype=torch.bfloat16, device="cuda")
+            out = torch.as_strided(buf, (m, n), (ld_y, 1), offset)
+            names = launched_kernels(lambda: razer.razer_linear(w, a_dev, out=out))
+            assert any(kernel in x for x in names), names
+            assert torch.equal(out, want), (ld_y, offset)
+            out.fill_(7.0)
+            assert bool((buf == 7.0).all()), (ld_y, offset)              # (nothing beside the outputs)
+        out = torch.empty_like(want)
+        assert torch.equal(razer.razer_linear_static(w, a_dev, out), want)
+        aq = razer.razer_quantize(a_dev, razer.ACT, (5.0,))
+        names = launched_kernels(lambda: razer.razer_linear(w, aq, out=out))
+    finally:
+        razer.razer_tune_force(binding.TUNE_GEMM_SLICES, None)
+    assert any(kernel in x for x in names), names
+    rows, cols = np.unique(np.r_[0, rng.choice(m, size=6, replace=False), 255, 256, m - 1]), np.unique(np.r_[0:40, 120:136, n - 140:n, rng.choice(n, size=60, replace=False)])
+    y64, _ = oracle.linear((wq[0][cols], wq[1][cols], wq[2]), a_q=(aq.codes.cpu().numpy()[rows], aq.scales.cpu().numpy()[rows], np.float32(aq.tensor_scale.item())))
+    assert max_rel_err(dev_to_bf16_bits(out)[rows][:, cols], y64) <= TOL

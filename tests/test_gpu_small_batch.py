@@ -166,7 +166,10 @@ def test_infinite_activation_stays_infinite_with_a_ragged_last_step(oracle, m):
     # rows of 256, 262, 518 and of 64 .. 4 bytes of scales, the last rows of a matrix, several matrices in one workgroup
     (8, (68, 33 * 4, 12), 4096, razer.WEIGHT, 16, 6), (5, (100, 7), 4192, razer.WEIGHT, 16, 6), (16, (37,), 8288, razer.WEIGHT, 16, 3), (32, (36, 20), 4096, razer.WEIGHT, 32, 6),
     (8, (50, 3), 8192 + 64, razer.WEIGHT, 64, 3), (33, (68, 5), 4608, razer.WEIGHT, 128, 4), (64, (37, 40), 6176, razer.WEIGHT, 16, 4), (50, (70,), 6144, razer.WEIGHT, 32, 4),
-    (16, (36, 20), 4096, razer.WEIGHT_F16, 128, 6), (64, (52,), 8320, razer.WEIGHT_F16, 128, 3), (12, (21,), 38528, razer.WEIGHT, 16, 1), (4, (37, 20), 10272, razer.WEIGHT, 16, 3),
+    (16, (36, 20), 4096, razer.WEIGHT_F16, 128, 6), (64, (52,), 8320, razer.WEIGHT_F16, 128, 3), (12, (21,), 38528, razer.WEIGHT, 16, 1),
+    # up to 4 rows: two, three and four groups, one with 16 waves; 16 waves with whole steps and with halves
+    (4, (4200,), 20512, razer.WEIGHT, 16, None), (3, (5000, 3300, 20), 8224, razer.WEIGHT, 16, None), (4, (13000,), 6208, razer.WEIGHT, 64, None), (3, (4200,), 20480, razer.WEIGHT_F16, 128, None),
+    (4, (37,), 38432, razer.WEIGHT, 32, None), (8, (21,), 38432, razer.WEIGHT, 16, None), (12, (21,), 38464, razer.WEIGHT, 16, None), (16, (37,), 38528, razer.WEIGHT_F16, 128, None),
     # several workgroups per unit
     (8, (16485,), 2080, razer.WEIGHT, 16, None), (40, (16485,), 2048, razer.WEIGHT, 64, None), (16, (16485,), 5248, razer.WEIGHT_F16, 128, None)])
 def test_scales_staged_by_the_workgroup(oracle, m, ns, k, fmt, block, groups):
@@ -175,14 +178,15 @@ def test_scales_staged_by_the_workgroup(oracle, m, ns, k, fmt, block, groups):
     a_dev = bf16_bits_to_dev(a)
     print("staged scales", m, ns, k, fmt, block, groups, flush=True)
     got = []
-    if groups and m > 4:
+    if groups:
         razer.razer_tune_force(binding.TUNE_SMALL_BATCH, (2, groups))
     try:
         names = launched_kernels(lambda: got.extend([razer.razer_linear(ws[0][1], a_dev)] if len(ns) == 1 else razer.razer_linear_grouped([w[1] for w in ws], a_dev)))
     finally:
         razer.razer_tune_force(binding.TUNE_SMALL_BATCH, None)
-    if m > 4:
-        assert names and all("staged_ring_kernel<" in x for x in names), names
+    assert names and all("staged_ring_kernel<" in x for x in names), names
+    if k > 38400 and not groups:
+        assert all(x.split("<")[1].split(",")[4].strip() == "16" for x in names), names      # (waves)
     for (wq, _), y in zip(ws, got):
         n = len(wq[0])
         cols = np.arange(n) if n < 300 else np.unique(np.r_[0:20, n - 37:n, np.random.default_rng(47).choice(n, size=200, replace=False)])
@@ -238,3 +242,29 @@ def test_a_group_of_one_matrix_is_the_single_call(m, n, k, block):
     single = launched_kernels(lambda: one.append(razer.razer_linear(wt, a_dev)))
     grouped = launched_kernels(lambda: group.extend(razer.razer_linear_grouped([wt], a_dev)))
     assert torch.equal(one[0], group[0]), (single, grouped)
+
+
+@pytest.mark.parametrize("m,n,k", [(40, 1000, 11008), (64, 5120, 13824), (33, 1003, 11008)])
+def test_k_slices_into_any_output(oracle, m, n, k):
+    """Rows of the output further apart than N, one that starts 2 bytes behind an 8-byte boundary, the entry without a
+    workspace argument, activations in their own format: the same sums."""
+    print("k slices, outputs", m, n, k, flush=True)
+    wq, wt = _weights(n, k, 5800 + n, razer.WEIGHT, 16)
+    a_dev = bf16_bits_to_dev(synth.activation(m, k, seed=5900 + m))
+    want = razer.razer_linear(wt, a_dev)
+    ld = (n + 11) // 8 * 8
+    for ld_y, offset in ((ld, 0), (ld + 3, 0), (ld, 1), (ld + 1, 3)):
+        buf = torch.full((m * ld_y + 8,), 7.0, dtype=torch.bfloat16, device="cuda")
+        out = torch.as_strided(buf, (m, n), (ld_y, 1), offset)
+        names = launched_kernels(lambda: razer.razer_linear(wt, a_dev, out=out))
+        assert any("sliced_ring_kernel<" in x for x in names), names
+        assert torch.equal(out, want), (ld_y, offset)
+        out.fill_(7.0)
+        assert bool((buf == 7.0).all()), (ld_y, offset)                  # (nothing beside the outputs)
+    out = torch.empty_like(want)
+    assert torch.equal(razer.razer_linear_static(wt, a_dev, out), want)
+    aq = razer.razer_quantize(a_dev, razer.ACT, (5.0,))
+    names = launched_kernels(lambda: razer.razer_linear(wt, aq, out=out))
+    assert any("sliced_ring_kernel<" in x for x in names), names
+    y64, _ = oracle.linear(wq, a_q=tuple(x.cpu().numpy() for x in (aq.codes, aq.scales)) + (np.float32(aq.tensor_scale.item()),))
+    assert max_rel_err(dev_to_bf16_bits(out), y64) <= TOL
