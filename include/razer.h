@@ -160,13 +160,17 @@ razer_status razer_dequant(const razer_tensor *t, void *out, int32_t dtype, int6
  * is non-NULL.  Products are accumulated in fp32 (bf16 matrix cores for large
  * m, wavefront dot products for m <= 4, a decode-once MFMA kernel in between), scaled by the
  * tensor scale(s) and rounded to bf16:  y_bf16 device [m][ld_y], ld_y >= N.
- * The first call on a device that reaches one of the large-tile matrix-core kernels raises that kernel's
+ * The order of the sum over K depends on the sizes and formats and on the output's column, not on an
+ * activation row's place: equal rows of one call give equal results (K up to 2^24).
+ * The first call on a device that reaches one of the kernels with more than 64 KiB of LDS (the decode-once
+ * MFMA kernel, from m = 2 on, and the large-tile matrix-core kernels) raises that kernel's
  * dynamic-LDS limit (hipFuncSetAttribute, once per kernel and device, race-free): a caller that captures
  * a stream into a HIP graph makes one ordinary call of each shape first.
  * workspace: device, 16-byte aligned, >= razer_workspace_bytes(RAZER_OP_LINEAR, N, K, m) bytes
  * (non-zero for W4A16 with 5 <= m <= 32, whose kernel no longer writes to it, and for m > 32 with too few
  * output tiles to occupy the GPU, where K may be split over workgroups and the slices meet in fp32 -- ask
- * razer_workspace_bytes; else may be NULL); too small -> RAZER_ERR_WORKSPACE. */
+ * razer_workspace_bytes; else may be NULL); too small -> RAZER_ERR_WORKSPACE.  Calls that overlap in time need
+ * workspaces of their own from 33 rows on, and with a_q at any m. */
 razer_status razer_linear(const razer_tensor *w, const void *a_bf16, const razer_tensor *a_q,
                           int64_t m, void *y_bf16, int64_t ld_y,
                           void *workspace, size_t workspace_bytes, void *hip_stream);

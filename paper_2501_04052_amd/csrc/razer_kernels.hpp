@@ -78,7 +78,7 @@ constexpr uint32_t kLdsBytes = 160u * 1024u;   // per compute unit
 constexpr int64_t kSkinnyMaxK = (int64_t)1 << 24;
 constexpr int64_t kRbMaxK = (int64_t)1 << 22;
 
-// Workspace reported for 5 <= m <= kSkinnyMaxM (the kernel itself needs none; razer_skinny.hip).
+// Workspace reported for 5 <= m <= kSkinnyMaxM (the kernel writes nothing there; razer_skinny.hip).
 size_t skinny_workspace_bytes(int64_t n, int64_t k, int64_t m);
 // y = bf16(scale * sum of the K-slices' fp32 partial sums [slices][m][n], in slice order); scale = -ts_w,
 // or ts_w * ts_a when a_ts is given.

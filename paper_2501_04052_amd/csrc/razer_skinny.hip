@@ -715,7 +715,8 @@ static hipError_t launch_ring_t(SvConfig cfg, int count, const GemvProblem* p, i
 // (15 %).  Measured over 1024 x 1024 .. 57344 x 8192 at 4..64 rows, with eight waves throughout (above 32 rows four, where
 // workgroups share a unit, came later), this picks the fastest G or one within 3 % of it:
 // 4096 rows 1; 8192 or 5003 rows 2; {q,k,v} 3 x 4096 or 10240 rows 3; 2 x 11008 rows 3, with 32 activation rows 6.
-// More than 32 activation rows take at most 4 groups (the FP16-scale format 3): six do not fit the registers.
+// More than 32 activation rows take at most 4 groups (the FP16-scale format 3): with whole steps six did not fit the registers,
+// and their sums take 24 KiB of LDS per wave; with halves they have not been tried.
 static int ring_groups(int64_t groups, int64_t m, bool f16)
 {
     int best = 1;
@@ -734,8 +735,10 @@ static int ring_groups(int64_t groups, int64_t m, bool f16)
 // share a unit; with less than a full round more their number still counts as rounded up) K times what a group of weight
 // rows and an activation row cost, rows that start inside a 128-byte line nearly twice as much; 16 waves are 10 % slower
 // again from about 18000 elements; activations that the XCDs fetch each for itself and that leave the L2; and the output,
-// which rows that are no multiple of 4 let a lane store only an element at a time.  Fitted to 863 calls on which neither
-// kernel takes more than 1.7 times the other's time: 90 % of them lie within 0.93 and 1.1 of the estimate.
+// which rows that are no multiple of 4 let a lane store only an element at a time.  Fitted to 863 calls before short launches
+// got 3 to 6 % faster.  As the kernels are now, on 212 other calls on which neither kernel takes more than 1.7 times the
+// other's time, the middle is 1.00 of the estimate and 90 % lie within 0.78 and 1.13; those far below it are long rows of
+// few weights (114 x 104 x 8480 13.2 us, estimate 18.2), those above it many runs of few weights (1994 x 2 x 72 x 8256 30.5, 25.3).
 static double ring_estimate_us(int count, const GemvProblem* p, int64_t k, int64_t m)
 {
     int64_t rows = 0;
@@ -865,23 +868,24 @@ static hipError_t launch_ring(SvConfig cfg, int count, const GemvProblem* p, int
 
 // Where this kernel takes over from its neighbours (unless a tuner or test forces one of their launch shapes).
 // 33..64 activation rows, scale-byte format, against the K-sliced register-decode GEMM: except where one group per
-// workgroup makes every workgroup read more activations than it gains: one group and m x K above 600 thousand, where the
-// GEMM's K-slices fill the units that few rows leave idle (1500 x 12288 at 64 rows 21.4 -> 21.9 us, 1000 x 16384 22.4 ->
-// 25.3).  From 161 groups on the length of K decides, whatever the number of rows (time of this kernel / the GEMM's): 2600
-// weight rows at 64 activation rows 0.91 with 11264 elements, 0.95 with 12288, 1.04 with 14336, at 37 rows 1.15 with 20480;
-// 3200 at 64 rows 0.87, 0.91, 1.01; 3600 and 4096 at 56 rows 0.90 with 12288, 0.97 with 14336, 1.02 with 16384 and at 37
-// rows 1.05 with 20480.  With more groups 13-50 % faster.
+// workgroup makes every workgroup read more activations than it gains: one group and m x K above 600 thousand; from 161
+// groups on the length of K decides, whatever the number of rows.  The lines were drawn for whole K (1500 x 12288 at 64 rows
+// 21.4 us on the GEMM, 21.9 here; 2600 weight rows at 64 rows 0.95 of the GEMM's time with 12288 elements, 1.04 with 14336;
+// 3200 0.91, 1.01; 4096 at 56 rows 0.90, 0.97 and with 16384 1.02) and still hold for groups of matrices.  With the K-slices of
+// one matrix (ring_slices), which this rule does not ask, they lie too low: 1500 x 12288 at 64 rows 20.8 on the GEMM, 12.4
+// here, 1000 x 16384 21.8, 12.6, 2600 x 14336 25.0, 17.1, 4096 x 16384 at 56 rows 33.0, 22.5.
 // 2..4 activation rows, against the 4x4x4 kernel of razer_gemv.hip, whose waves cross all of K in one or two passes:
-// long rows and not too many of them (1024 groups) -- at 4 rows 8192 x 28672 38.0 -> 30.4 us, {q,k,v} 10240 x 8192
-// 16.6 -> 14.6, 2 x 3000 x 6144 10.0 -> 9.0; at 2 rows one group per workgroup only (4096 x 11008 9.7 -> 8.7; but
-// 10240 x 8192 14.5 -> 15.8) -- and 4 rows with one group per workgroup from 2048 elements up (4096 x 4096
-// 5.35 -> 5.15).  57344 x 8192 at 4 rows would take 63 instead of 57 us.
+// long rows and not too many of them (1024 groups) -- at 4 rows 8192 x 28672 38.4 -> 31.0 us, {q,k,v} 10240 x 8192
+// 16.5 -> 14.5, 2 x 3000 x 6144 9.8 -> 8.2; at 2 rows one group per workgroup only (4096 x 11008 9.4 -> 7.8; but
+// 10240 x 8192 13.9 -> 14.4) -- and 4 rows with one group per workgroup from 2048 elements up (4096 x 4096
+// 5.30 -> 4.97).  Beyond the lines, as both kernels are now: 57344 x 8192 at 4 rows 58.0, here 56.9; 2 x 11008 x 4096 at 3 and
+// 4 rows 14.0, 14.6 and 14.5, 14.7; but 3 x 4096 x 4096 9.0, 8.7 and 9.7, 8.7, which is not taken yet.
 // Above 64 rows, scale bytes, against the register-decode and the tiled GEMM: whichever of two estimates is the shorter.
 // Where the two meet depends on how well either fills the chip -- K-slices and the width of tiles there, groups per
-// workgroup and rounds of workgroups here -- so that no bound on sizes follows it: over 1346 calls of 65 .. 2048 rows the
-// choice is 0.23 % (geometric mean) behind the faster kernel and at most 1.17 times its time (over 451 calls that nothing was
-// fitted to 0.17 %, 1.10); limits on units, units x K
-// and K are 1.6 to 8 % behind it and up to 2.9 times.  GEMM -> this (us): 4096 x 4096 at 512 rows 40.4 -> 29.8, 2 x 5120 x
+// workgroup and rounds of workgroups here -- so that no bound on sizes follows it: over 420 calls of 65 .. 2048 rows that
+// nothing was fitted to the choice is 0.43 % (geometric mean) behind the faster kernel and at most 1.26 times its time (108 x
+// 2 x 36 x 8480 16.5 us, 13.1 here); limits on units, units x K
+// and K were 1.6 to 8 % behind it and up to 2.9 times.  GEMM -> this (us): 4096 x 4096 at 512 rows 40.4 -> 29.8, 2 x 5120 x
 // 5120 at 320 88 -> 64, 1139 x 5376 at 1249 55.6 -> 32.8, 1000 x 28672 at 256 67.7 -> 51.1, 2865 x 8832 at 380 62.2 -> 43.9,
 // 5539 x 1536 at 1390 (rows that the GEMM stores an element at a time) 83.8 -> 57.6; not taken 100 x 24576 at 128 rows 25.6
 // -> 41.2, 3000 x 28672 at 128 50.0 -> 65.6, 720 x 15104 at 1445 59.8 -> 88.3, 10352 x 1216 at 438 25.4 -> 34.9, 130 x 21696
